@@ -21,6 +21,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "sd.h"
+
 #ifdef __cplusplus
 extern "C" {
 #endif
@@ -63,6 +65,22 @@ int sdden_eval(sdden* den, int32_t R, const float* X, const int32_t* krow, float
  * own conversion pass; the other denoisers ignore it.  Rows with krow < 0 need no valid image. */
 int sdden_eval_mirror(sdden* den, int32_t R, const float* X, const uint16_t* Xbf16,
                       const int32_t* krow, float* out, void* stream);
+
+/* The while-loop of the sampler for each chain in one launch, where the denoiser is cheap enough to be evaluated inside
+ * the kernel that owns the chain (gmm with at most 64 components): windows back to back until step T, each
+ * what (sdden_eval, sd_draft, sdden_eval, sd_verify, sd_advance) computes under the context's draft mode, carry rule,
+ * temperature and seed.  Chains do not interact, so none waits for another's window; a window's positions are predicted
+ * in order and only up to its first rejection.
+ * in : y [B,d], n [B], chain_id [B]; draft_den: the draft network (EXPLICIT mode: the independent draft model), else
+ *      ignored; D_frozen [B,d]: the carried prediction (FROZEN_REUSED), else ignored                         (dev)
+ * out: out [*, d], row index = chain_id; B_active: dev int32, set to 0; counters: dev int64[5] or NULL, accumulated as in
+ *      sd_advance (windows: those of the chain that needed most).
+ * SD_ERR_UNSUPPORTED, with nothing enqueued, when this denoiser (or draft_den) has no such form, is being timed
+ * (sdden_profile) or runs under a device-resident count: the caller then makes the separate calls.  Calls on one context
+ * must be ordered, as for sd_langevin_window. */
+int sdden_run(sdden* den, sdden* draft_den, sd_ctx* ctx, int32_t B, const float* y, const int32_t* n,
+              const int64_t* chain_id, const float* D_frozen, float* out, int32_t* B_active, int64_t* counters,
+              void* stream);
 
 /* Optional device-resident row limit: when `count` (dev int32) is set, only rows
  * r < min(R, *count * rows_per_chain) are evaluated, which lets a fixed launch sequence follow

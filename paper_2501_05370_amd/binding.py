@@ -25,6 +25,7 @@ SD_MAX_WINDOW = 64
 SD_STATIC_MAX_CHAINS = 65536
 SD_CARRY_DRAFT = 0
 SD_CARRY_LAST_ACCEPTED = 1
+SD_ERR_UNSUPPORTED = -5
 
 
 class SDError(RuntimeError):
@@ -79,6 +80,7 @@ _SIGNATURES = {
                                                                                POINTER(c_void_p)]),
     "sdden_reserve": (c_int, [c_void_p, c_int32]),
     "sdden_eval": (c_int, [c_void_p, c_int32, c_void_p, c_void_p, c_void_p, c_void_p]),
+    "sdden_run": (c_int, [c_void_p, c_void_p, c_void_p, c_int32] + [c_void_p] * 8),
     "sdden_set_active_count": (c_int, [c_void_p, c_void_p, c_int32]),
     "sdden_profile": (c_int, [c_void_p, c_int32]),
     "sdden_profile_min_rows": (c_int, [c_void_p, c_int32]),
@@ -365,6 +367,17 @@ class Denoiser:
                 raise SDError(f"{nm}: need a contiguous {dt} CUDA tensor")
         self._check(self._lib.sdden_eval_mirror(self._h, R, X.data_ptr(), Xbf16.data_ptr(), krow.data_ptr(),
                                                 out.data_ptr(), _stream()), "sdden_eval_mirror")
+
+    def sdden_run(self, ctx: Context, B, y, n, chain_id, out, B_active, counters=None, D_frozen=None, draft_den=None) -> bool:
+        """False when the chains of this denoiser have to be run window by window (nothing was enqueued then)."""
+        rc = self._lib.sdden_run(self._h, draft_den._h if draft_den is not None else None, ctx._h, B, _dev(y, torch.float32, "y"),
+                                 _dev(n, torch.int32, "n"), _dev(chain_id, torch.int64, "chain_id"),
+                                 _dev(D_frozen, torch.float32, "D_frozen", True), _dev(out, torch.float32, "out"),
+                                 _dev(B_active, torch.int32, "B_active"), _dev(counters, torch.int64, "counters", True), _stream())
+        if rc == SD_ERR_UNSUPPORTED:
+            return False
+        self._check(rc, "sdden_run")
+        return True
 
     def sdden_reserve(self, Rmax: int):
         self._check(self._lib.sdden_reserve(self._h, Rmax), "sdden_reserve")

@@ -68,6 +68,24 @@ __device__ __forceinline__ double pair_sum_rows(double v) {
   return a + b;
 }
 
+// max of v and (v of lane ^ MASK), the same way.
+template <int MASK>
+__device__ __forceinline__ double pair_max_rows(double v) {
+  static_assert(MASK == 16 || MASK == 32, "row-swap masks");
+  const long long bits = __double_as_longlong(v);
+  const unsigned lo = static_cast<unsigned>(bits), hi = static_cast<unsigned>(bits >> 32);
+  uint2v rl, rh;
+  if constexpr (MASK == 16) {
+    rl = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    rh = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+  } else {
+    rl = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    rh = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+  }
+  return fmax(__longlong_as_double((static_cast<long long>(rh[0]) << 32) | rl[0]),
+              __longlong_as_double((static_cast<long long>(rh[1]) << 32) | rl[1]));
+}
+
 // Halving step of a transposed reduction at distance MASK: a lane whose bit MASK is clear keeps `lower`, a
 // lane whose bit is set keeps `upper`, and each adds its partner's copy of the value it keeps.  For the two
 // row-swap masks one swap per 32-bit half delivers exactly that with no select; for 4 the two shifted moves

@@ -1,21 +1,19 @@
 // Posterior mean of a diagonal-covariance Gaussian mixture under the forward noising
 // x_t = sqrt(ab) x0 + sqrt(1-ab) eps -- the analytic stand-in for the target network
 // (paper Sec. 3.1 treats the drift as a black box; the low-dimensional mixture study of the
-// experiments has this shape).  Also the generic entry points of sdden.h.
+// experiments has this shape) -- and whole chains on it in one launch (sdden_run).  Also the generic
+// entry points of sdden.h.
 //
-//   r_m(x)  = softmax_m( log w_m + log N(x; sqrt(ab) mu_m, diag(ab s_m^2 + 1-ab)) )
-//   D(x,k)  = sum_m r_m(x) ( mu_m + sqrt(ab) s_m^2 / v_m * (x - sqrt(ab) mu_m) )
-//
-// One wavefront per row.  Phase 1: a lane owns a component and walks the coordinates (no
-// cross-lane reduction for the logits).  Phase 2: a lane owns a coordinate and walks the
-// components.  All arithmetic in fp64: the rows are few and small, and the responsibilities are
-// exponentials of sums of d terms.  Reciprocal variances use the fp32 hardware reciprocal refined by
-// two Newton steps in fp64 (relative error ~1e-14) instead of full fp64 divisions.
+// Up to 64 components: one wavefront per row, gmm_rows.h.  More components: the general kernel below.
+// All arithmetic in fp64: the rows are few and small, and the responsibilities are
+// exponentials of sums of d terms.
+#include <algorithm>
 #include <cmath>
 #include <new>
 #include <vector>
 
-#include "sd_lanes.h"
+#include "gmm_rows.h"
+#include "sd_rng.h"
 #include "sdden_internal.h"
 
 namespace sdi {
@@ -24,110 +22,109 @@ std::string g_den_create_error;
 
 namespace {
 
-constexpr int kRowsPerBlock = 4;
+using sdgmm::reciprocal;
 
-constexpr int kRegNI = 32;   // coordinates per lane of the register-resident kernel
+constexpr int kRowsPerBlock = 4;
 
 struct GmmArgs {
   const float* X;
   const int32_t* krow;
   float* out;
-  const float *mu, *sd;      // [M,d]  component means and stds
+  sdgmm::Model g;
+  const float *mu, *sd;      // [M,d]  component means and stds        (general kernel only)
   const float *muT, *sdT;    // [d,M]  the same, transposed
-  const float2* lane_tab;    // [kRegNI,64] (mean, std) in the lane order of the register kernel, or null
-  const double* cst;         // [T,M]  log w_m - 1/2 sum_i log v_mi(k)
-  int Mp;                    // M rounded up to a power of two (<= 64), lanes per coordinate slice
   const float* ab;           // [T+1]
   const int32_t* active;
   int rows_per_chain;
-  int R, d, M, T;
+  int R;
 };
 
-// 1/v for v in [~1e-3, ~1e3]: the hardware fp32 reciprocal (1 ulp; the correctly rounded one is a
-// ten-instruction sequence), then y <- y (2 - v y) twice.
-__device__ __forceinline__ double reciprocal(double v) {
-  double y = static_cast<double>(__builtin_amdgcn_rcpf(static_cast<float>(v)));
-  y = y * fma(-v, y, 2.0);
-  y = y * fma(-v, y, 2.0);
-  return y;
-}
-
-// One Newton step: relative error < 4e-14 (the start is within 2e-7), far inside the 1e-5 of the parity contract.
-__device__ __forceinline__ double reciprocal_one_step(double v) {
-  const double y = static_cast<double>(__builtin_amdgcn_rcpf(static_cast<float>(v)));
-  return y * fma(-v, y, 2.0);
-}
-
-__global__ __launch_bounds__(64 * kRowsPerBlock) void gmm_posterior_mean_kernel(GmmArgs p) {
+// One wavefront per row (gmm_rows.h), tables from the vector caches: a launch lives too short to pay for a copy in LDS.
+// Bound by fp64 issue: 6.5 vector instructions per (component, coordinate) pair of the logit phase, about 11 per
+// coordinate and live component.  32768 rows of 64 coordinates and 32 components: 66 us (80 with the component means of
+// every row kept in registers and exchanged); 2000 rows of 200 and 48: 33 us (88 with a kernel that had no registers for it).
+template <int E, int C>
+__global__ __launch_bounds__(64 * kRowsPerBlock) void gmm_rows_kernel(GmmArgs p) {
   extern __shared__ double smem[];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  double* rs = smem + static_cast<size_t>(wave) * (p.M + p.d);   // [M] responsibilities
-  double* xs = rs + p.M;                                          // [d] the row
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int r = blockIdx.x * kRowsPerBlock + wave;
   const int Ract = sdi::active_rows(p.active, p.rows_per_chain, p.R);
   const int k = r < Ract ? p.krow[r] : -1;
   // masked row (k < 0) or a step the chain does not have; the whole wavefront leaves together, no barriers used
-  if (static_cast<unsigned>(k) >= static_cast<unsigned>(p.T)) return;
+  if (static_cast<unsigned>(k) >= static_cast<unsigned>(p.g.T)) return;
+  const float* row = p.X + static_cast<int64_t>(r) * p.g.d;
+  const double2 st = p.g.steps[k];
+  const double base = sdgmm::lane_constant(p.g, k, lane);
+  float x[C][E], y[C][E];
+#pragma unroll
+  for (int c = 0; c < C; ++c)
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int i = E * (lane + 64 * c) + e;
+      x[c][e] = i < p.g.d ? row[i] : 0.f;
+    }
+  sdgmm::posterior_mean<E, C, false>(p.g, nullptr, smem + static_cast<size_t>(wave) * (p.g.nslots << (6 - p.g.lm)), x, st.x, st.y, base,
+                                     lane, y);
+  float* o = p.out + static_cast<int64_t>(r) * p.g.d;
+#pragma unroll
+  for (int c = 0; c < C; ++c)
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int i = E * (lane + 64 * c) + e;
+      if (i < p.g.d) o[i] = y[c][e];
+    }
+}
+
+// More than 64 components.  Phase 1: a lane owns components lane, lane + 64, .. and walks the coordinates (no
+// cross-lane reduction for the logits).  Phase 2: a lane owns a coordinate and walks the components.
+__global__ __launch_bounds__(64 * kRowsPerBlock) void gmm_many_components_kernel(GmmArgs p) {
+  extern __shared__ double smem[];
+  const int M = p.g.M, d = p.g.d;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  double* rs = smem + static_cast<size_t>(wave) * (M + d);       // [M] responsibilities
+  double* xs = rs + M;                                           // [d] the row
+  const int r = blockIdx.x * kRowsPerBlock + wave;
+  const int Ract = sdi::active_rows(p.active, p.rows_per_chain, p.R);
+  const int k = r < Ract ? p.krow[r] : -1;
+  if (static_cast<unsigned>(k) >= static_cast<unsigned>(p.g.T)) return;
   const double ab = p.ab[k];
   const double sab = sqrt(ab), om = 1.0 - ab;
-  const float* x = p.X + static_cast<int64_t>(r) * p.d;
-  for (int i = lane; i < p.d; i += 64) xs[i] = x[i];
-  __builtin_amdgcn_wave_barrier();
-  __threadfence_block();
+  const float* x = p.X + static_cast<int64_t>(r) * d;
+  for (int i = lane; i < d; i += 64) xs[i] = x[i];
+  sdgmm::wave_lds_fence();
 
   double mx = -INFINITY;
-  if (p.Mp < 64) {
-    // fewer than 64 components: 64/Mp lanes share a component and split the coordinates
-    const int m = lane % p.Mp, part = lane / p.Mp, parts = 64 / p.Mp;
+  for (int m = lane; m < M; m += 64) {
     double q = 0.0;
-    if (m < p.M) {
-      for (int i = part; i < p.d; i += parts) {
-        const double diff = xs[i] - sab * p.muT[static_cast<int64_t>(i) * p.M + m];
-        const double sd = p.sdT[static_cast<int64_t>(i) * p.M + m];
-        const double iv = reciprocal(ab * sd * sd + om);
-        q = fma(diff * diff, iv, q);
-      }
+    for (int i = 0; i < d; ++i) {
+      const double diff = xs[i] - sab * p.muT[static_cast<int64_t>(i) * M + m];
+      const double sd = p.sdT[static_cast<int64_t>(i) * M + m];
+      const double iv = reciprocal(ab * sd * sd + om);
+      q = fma(diff * diff, iv, q);
     }
-    for (int s = p.Mp; s < 64; s <<= 1) q += __shfl_xor(q, s, 64);
-    if (m < p.M && part == 0) {
-      const double logit = p.cst[static_cast<int64_t>(k) * p.M + m] - 0.5 * q;
-      rs[m] = logit;
-      mx = logit;
-    }
-  } else {
-    for (int m = lane; m < p.M; m += 64) {
-      double q = 0.0;
-      for (int i = 0; i < p.d; ++i) {
-        const double diff = xs[i] - sab * p.muT[static_cast<int64_t>(i) * p.M + m];
-        const double sd = p.sdT[static_cast<int64_t>(i) * p.M + m];
-        const double iv = reciprocal(ab * sd * sd + om);
-        q = fma(diff * diff, iv, q);
-      }
-      const double logit = p.cst[static_cast<int64_t>(k) * p.M + m] - 0.5 * q;
-      rs[m] = logit;
-      mx = fmax(mx, logit);
-    }
+    const double logit = p.g.cst[static_cast<int64_t>(k) * M + m] - 0.5 * q;
+    rs[m] = logit;
+    mx = fmax(mx, logit);
   }
   for (int s = 32; s >= 1; s >>= 1) mx = fmax(mx, __shfl_xor(mx, s, 64));
   double sum = 0.0;
-  for (int m = lane; m < p.M; m += 64) {
+  for (int m = lane; m < M; m += 64) {
     const double e = exp(rs[m] - mx);
     rs[m] = e;
     sum += e;
   }
   for (int s = 32; s >= 1; s >>= 1) sum += __shfl_xor(sum, s, 64);
   const double inv = 1.0 / sum;
-  __builtin_amdgcn_wave_barrier();
-  __threadfence_block();
+  sdgmm::wave_lds_fence();
 
-  float* o = p.out + static_cast<int64_t>(r) * p.d;
-  for (int i = lane; i < p.d; i += 64) {
+  float* o = p.out + static_cast<int64_t>(r) * d;
+  for (int i = lane; i < d; i += 64) {
     const double xi = xs[i];
     double acc = 0.0;
-    for (int m = 0; m < p.M; ++m) {
+    for (int m = 0; m < M; ++m) {
       if (rs[m] < 1e-25) continue;          // the same for every lane; such a component moves nothing
-      const double mu = p.mu[static_cast<int64_t>(m) * p.d + i];
-      const double sd = p.sd[static_cast<int64_t>(m) * p.d + i];
+      const double mu = p.mu[static_cast<int64_t>(m) * d + i];
+      const double sd = p.sd[static_cast<int64_t>(m) * d + i];
       const double s2 = sd * sd;
       const double iv = reciprocal(ab * s2 + om);
       acc += rs[m] * (mu + sab * s2 * iv * (xi - sab * mu));
@@ -136,146 +133,393 @@ __global__ __launch_bounds__(64 * kRowsPerBlock) void gmm_posterior_mean_kernel(
   }
 }
 
-// Small mixtures (MP = M rounded up to a power of two <= 32, d <= (64 / MP) * NI): a lane computes the
-// per-component posterior mean of its (component, coordinate) pairs in the same pass as the quadratic
-// form and keeps it in registers, so the reciprocal variance and x - sqrt(ab) mu are computed once
-// instead of once per phase.
-// Lane = part + PARTS * m (component m, PARTS = 64 / MP lanes per component); the lane owns coordinates
-// i = part + PARTS * j, j < NI.  Phase 1 sums its quadratic form and finishes it across the parts; the
-// softmax runs across the component lanes; phase 2 scales the kept means by r_m and a halving exchange over
-// the component lanes leaves each lane with the finished sums of NI / MP coordinates, which it writes.
-// The component index sits in the high lane bits so that the two largest levels of the exchange (half
-// and a quarter of the list) are row swaps, one instruction per 32-bit word with no select.
-// No LDS, no barrier.
-__device__ __forceinline__ double lane_xor_f64(double v, int mask) {   // mask: one bit, constant after unrolling
-  switch (mask) {
-    case 1: return sdlane::lane_xor<1>(v);
-    case 2: return sdlane::lane_xor<2>(v);
-    case 4: return sdlane::lane_xor<4>(v);
-    case 8: return sdlane::lane_xor<8>(v);
-    case 16: return sdlane::lane_xor<16>(v);
-    default: return sdlane::lane_xor<32>(v);
+// ---------------------------------------------------------------------------------------------
+// Every chain of a batch from its step to T in one launch: one wavefront owns a chain and walks its windows, each of
+// which computes what (window-start prediction, draft, batched prediction, verify, advance) computes for it.  Chains
+// do not interact, so nothing needs the launches, the compaction and the readback between two windows; and because
+// the walk of a window is serial it stops at the first rejection, so a chain costs exactly one target evaluation per
+// step it takes (plus the carried one of the efficient frozen drafter) instead of K per window.
+// Values: drafts, predictions and states are rounded to fp32 exactly where the separate calls store them; log-ratios
+// are fp64 sums of the same terms.
+// Measured against windows of separate calls: 4096 chains, d = 64, 32 components, 200 steps 1.05 ms against 4.76; 64 chains,
+// d = 2, 8 components, 100 steps 0.16 ms against 1.81; 300 chains, d = 75, 12 components, a draft model, 60 steps 0.25 ms
+// against 8.1.  The first is bound by fp64 issue (560 vector instructions per step and chain, the vector units 82 % busy),
+// the others by the latency of one wavefront's step (1.5 us): hence no branch per exchange level, no load and no
+// generator pass per step.
+// ---------------------------------------------------------------------------------------------
+struct RunArgs {
+  sdgmm::Model t, q;         // target; draft model of the independent drafter
+  const float *y, *Dfz;      // start states; carried predictions (efficient frozen drafter)
+  const int32_t* n;
+  const int64_t* id;
+  float* out;
+  const float *a, *c, *sigma;
+  int B, K, T;
+  int reused, carry_last;    // efficient frozen drafter and its second carry rule
+  uint64_t seed;
+  double inv_tau;
+  unsigned long long* counters;   // optional: sum adv, chain-windows, rejections, windows, sum Kt
+  int32_t* longest;               // windows of the chain that needed most (zero on entry)
+};
+
+// Standard normals of this lane's coordinates E * (lane + 64 c) + e of the vector keyed (seed, id, k).
+// d <= 128 (E < 4): a step needs ceil(d / 4) <= 32 blocks of the generator, so one pass of the 64 lanes draws the noise
+// of several steps, a block each, and parks it in wavefront-private LDS; a chain takes its steps in order.  (Drawing
+// per step, lanes that share a block would each repeat its ten rounds.)
+struct NoiseBatch {
+  int base, steps, shift;    // first step held, steps held at a time (64 >> shift), log2 of the blocks a step takes
+  __device__ __forceinline__ void init(int d) {
+    shift = 0;
+    while ((4 << shift) < d) ++shift;
+    steps = 64 >> shift;
+    base = -64;
   }
-}
+};
 
-__device__ __forceinline__ double halving_add_f64(double lower, double upper, int mask) {
-  switch (mask) {
-    case 1: return sdlane::halving_add<1>(lower, upper);
-    case 2: return sdlane::halving_add<2>(lower, upper);
-    case 4: return sdlane::halving_add<4>(lower, upper);
-    case 8: return sdlane::halving_add<8>(lower, upper);
-    case 16: return sdlane::halving_add<16>(lower, upper);
-    default: return sdlane::halving_add<32>(lower, upper);
-  }
-}
-
-template <int MP, int NI>
-__global__ __launch_bounds__(64 * kRowsPerBlock) void gmm_posterior_mean_reg_kernel(GmmArgs p) {
-  static_assert(NI % MP == 0 && MP <= 32 && (MP & (MP - 1)) == 0, "component lanes must divide the coordinate list");
-  constexpr int PARTS = 64 / MP;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int r = blockIdx.x * kRowsPerBlock + wave;
-  const int Ract = sdi::active_rows(p.active, p.rows_per_chain, p.R);
-  const int k = r < Ract ? p.krow[r] : -1;
-  // masked row (k < 0) or a step the chain does not have; the whole wavefront leaves together
-  if (static_cast<unsigned>(k) >= static_cast<unsigned>(p.T)) return;
-  const double ab = p.ab[k];
-  const double sab = sqrt(ab), om = 1.0 - ab;
-  const int part = lane % PARTS, m = lane / PARTS;
-  const bool live = m < p.M;
-  const float* x = p.X + static_cast<int64_t>(r) * p.d;
-
-  double v[NI];                             // posterior mean of component m at the owned coordinates
-  double q = 0.0;
+template <int E, int C>
+__device__ __forceinline__ void lane_normals(NoiseBatch& nb, float* zs, uint64_t seed, int64_t id, int k, int lane, float (&z)[C][E]) {
+  if constexpr (E == 4) {
 #pragma unroll
-  for (int j = 0; j < NI; ++j) {
-    const int i = part + PARTS * j;
-    v[j] = 0.0;
-    if (live && i < p.d) {
-      const float2 ms = p.lane_tab[j * 64 + lane];           // one coalesced 512-byte read per wavefront
-      const double mu = ms.x, sd = ms.y;
-      const double s2 = sd * sd;
-      const double iv = reciprocal_one_step(fma(ab, s2, om));
-      const double df = fma(-sab, mu, static_cast<double>(x[i]));
-      q = fma(df * df, iv, q);
-      v[j] = fma(sab * s2 * iv, df, mu);
+    for (int c = 0; c < C; ++c)
+      sdrng::normal4(seed, id, static_cast<uint32_t>(k), sdrng::kStreamNoise, static_cast<uint32_t>(lane + 64 * c), z[c]);
+  } else {
+    static_assert(C == 1, "one group of coordinates per lane");
+    if (k - nb.base >= nb.steps) {
+      nb.base = k;
+      float w[4];
+      sdrng::normal4(seed, id, static_cast<uint32_t>(k + (lane >> nb.shift)), sdrng::kStreamNoise,
+                     static_cast<uint32_t>(lane & ((1 << nb.shift) - 1)), w);
+      sdgmm::wave_lds_fence();
+      *reinterpret_cast<float4*>(zs + 4 * lane) = make_float4(w[0], w[1], w[2], w[3]);
+      sdgmm::wave_lds_fence();
+    }
+    const int at = ((k - nb.base) << (nb.shift + 2)) + E * lane;       // a step's noise: 4 << shift consecutive floats
+    if constexpr (E == 2) {
+      const float2 v = *reinterpret_cast<const float2*>(zs + (at & 255));
+      z[0][0] = v.x; z[0][1] = v.y;
+    } else {
+      z[0][0] = zs[at & 255];              // lanes past d read another coordinate's noise, which is not used
     }
   }
-#pragma unroll
-  for (int s = 1; s < PARTS; s <<= 1) q += lane_xor_f64(q, s);
-  const double logit = live ? p.cst[static_cast<int64_t>(k) * p.M + m] - 0.5 * q : -INFINITY;
-  double mx = logit;
-#pragma unroll
-  for (int s = PARTS; s < 64; s <<= 1) mx = fmax(mx, lane_xor_f64(mx, s));
-  const double e = live ? exp(logit - mx) : 0.0;
-  double sum = e;
-#pragma unroll
-  for (int s = PARTS; s < 64; s <<= 1) sum += lane_xor_f64(sum, s);
-  const double rm = e / sum;
-#pragma unroll
-  for (int j = 0; j < NI; ++j) v[j] *= rm;
-  // halving exchange over the component lanes: at component distance s a lane keeps the upper half of its
-  // list if bit s of its component is set (else the lower half) and adds the partner's sums for that half
-  int n = NI;
-#pragma unroll
-  for (int s = MP / 2; s >= 1; s >>= 1) {
-    n >>= 1;
-#pragma unroll
-    for (int j = 0; j < NI / 2; ++j)
-      if (j < n) v[j] = halving_add_f64(v[j], v[j + n], s * PARTS);
-  }
-  constexpr int C = NI / MP;                // finished coordinates per lane: j = m * C + jj
-  float* o = p.out + static_cast<int64_t>(r) * p.d;
-#pragma unroll
-  for (int jj = 0; jj < C; ++jj) {
-    const int i = part + PARTS * (m * C + jj);
-    if (i < p.d) o[i] = static_cast<float>(v[jj]);
+}
+
+template <bool LDS>
+__device__ __forceinline__ void stage_table(const sdgmm::Model& g, double2* tab) {
+  if (!LDS) return;
+#pragma unroll 4
+  for (int s = threadIdx.x; s < g.nslots * 64; s += blockDim.x) {
+    const float2 v = g.lane_tab[s];
+    tab[(s >> 6) * sdgmm::kTabStride + (s & 63)] = make_double2(v.x, static_cast<double>(v.y) * v.y);
   }
 }
 
-template <int MP, int NI>
-void launch_reg(const GmmArgs& p, unsigned grid, hipStream_t st) {
-  hipLaunchKernelGGL((gmm_posterior_mean_reg_kernel<MP, NI>), dim3(grid), dim3(64 * kRowsPerBlock), 0, st, p);
+// What a step needs from the per-step tables, 64 steps at a time in the lanes of a wavefront: a chain's evaluations come
+// in the order of the steps whatever its windows do, so a step is served by readlane instead of by loads whose latency
+// a lone wavefront could not hide.
+struct StepBatch {
+  int base;                  // first step held; -64 before the first refill
+  float a, c, s;
+  double inv_s2, log_u;      // 1 / sigma^2; log of the uniform that tests the state the step produces
+  double2 t, q;              // (ab, sqrt(ab)) of the target's and the draft model's tables
+  __device__ __forceinline__ void refill(const RunArgs& p, bool indep, int k, int64_t id, int lane) {
+    base = k;
+    const int kk = min(k + lane, p.T - 1);
+    a = p.a[kk]; c = p.c[kk]; s = p.sigma[kk];
+    const double sg = s;
+    inv_s2 = 1.0 / (sg * sg);
+    log_u = sdrng::log_uniform(p.seed, id, static_cast<uint32_t>(k + lane + 1));
+    t = p.t.steps[kk];
+    if (indep) q = p.q.steps[kk];
+  }
+};
+
+__device__ __forceinline__ float readlane_f32(float v, int src_lane) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), src_lane));
+}
+
+template <int E, int C, bool LDS, bool INDEP>
+__global__ __launch_bounds__(256) void gmm_run_kernel(RunArgs p) {
+  extern __shared__ __align__(16) unsigned char run_smem[];
+  __shared__ unsigned long long sh_cnt[4];
+  __shared__ int sh_longest;
+  double2* tab_t = reinterpret_cast<double2*>(run_smem);
+  double2* tab_q = tab_t + (LDS ? p.t.nslots * sdgmm::kTabStride : 0);
+  double* xs0 = reinterpret_cast<double*>(tab_q + (LDS && INDEP ? p.q.nslots * sdgmm::kTabStride : 0));
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  int npad = p.t.nslots << (6 - p.t.lm);
+  if (INDEP) npad = max(npad, p.q.nslots << (6 - p.q.lm));
+  npad = (npad + 1) & ~1;                  // 16-byte pieces
+  double* xs = xs0 + static_cast<size_t>(wave) * npad;
+  float* zs = reinterpret_cast<float*>(xs0 + static_cast<size_t>(blockDim.x >> 6) * npad) + 256 * wave;   // E < 4 only
+  stage_table<LDS>(p.t, tab_t);
+  if (INDEP) stage_table<LDS>(p.q, tab_q);
+  if (threadIdx.x < 4) sh_cnt[threadIdx.x] = 0;
+  if (threadIdx.x == 0) sh_longest = 0;
+  __syncthreads();
+
+  const int b = blockIdx.x * static_cast<int>(blockDim.x >> 6) + wave;
+  if (b < p.B) {                           // uniform over the wavefront
+    const int d = p.t.d;
+    const int64_t id = p.id[b];
+    int n = __builtin_amdgcn_readfirstlane(p.n[b]);
+    const int n_start = n;
+    float y[C][E], d0[C][E];
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const int i = E * (lane + 64 * c) + e;
+        y[c][e] = i < d ? p.y[static_cast<int64_t>(b) * d + i] : 0.f;
+        d0[c][e] = !INDEP && p.reused && i < d ? p.Dfz[static_cast<int64_t>(b) * d + i] : 0.f;
+      }
+    int windows = 0, rejections = 0;
+    long long kt_sum = 0;
+    StepBatch sb;
+    sb.base = -64;
+    NoiseBatch nb;
+    nb.init(d);
+    // component constants of the next step to be evaluated, requested one step ahead
+    double next_t = sdgmm::lane_constant(p.t, min(n, p.T - 1), lane), next_q = 0.0;
+    if (INDEP) next_q = sdgmm::lane_constant(p.q, min(n, p.T - 1), lane);
+
+    while (n < p.T) {                      // every window advances the chain by at least one step
+      const int Kt = min(p.K, p.T - n);
+      const bool frozen = !INDEP && !p.reused;
+      float dr[C][E], dq[C][E];
+      int adv = Kt;
+      bool rejected = false;
+      for (int j = 0; j < Kt; ++j) {
+        const int k = n + j;
+        if (k - sb.base >= 64) sb.refill(p, INDEP, k, id, lane);
+        const int at = k - sb.base;
+        const float a = readlane_f32(sb.a, at), cf = readlane_f32(sb.c, at), s = readlane_f32(sb.s, at);
+        const double ab = sdgmm::readlane_f64(sb.t.x, at), sab = sdgmm::readlane_f64(sb.t.y, at);
+        const double base_t = next_t, base_q = next_q;
+        next_t = sdgmm::lane_constant(p.t, min(k + 1, p.T - 1), lane);
+        if (INDEP) next_q = sdgmm::lane_constant(p.q, min(k + 1, p.T - 1), lane);
+        float z[C][E], mp[C][E];
+        lane_normals<E, C>(nb, zs, p.seed, id, k + 1, lane, z);
+        // The step's one target evaluation, at the state it starts from: the frozen prediction of the window (first
+        // position of the frozen drafter), else what the draft is tested against.
+        sdgmm::posterior_mean<E, C, LDS>(p.t, tab_t, xs, y, ab, sab, base_t, lane, dq);
+        if (frozen && j == 0) {
+#pragma unroll
+          for (int c = 0; c < C; ++c)
+#pragma unroll
+            for (int e = 0; e < E; ++e) d0[c][e] = dq[c][e];
+        }
+        if (INDEP)                         // the draft model's prediction
+          sdgmm::posterior_mean<E, C, LDS>(p.q, tab_q, xs, y, sdgmm::readlane_f64(sb.q.x, at), sdgmm::readlane_f64(sb.q.y, at),
+                                           base_q, lane, mp);
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+#pragma unroll
+          for (int e = 0; e < E; ++e) {
+            if (INDEP) {
+              mp[c][e] = fmaf(a, y[c][e], cf * mp[c][e]);
+              dr[c][e] = fmaf(s, z[c][e], mp[c][e]);
+            } else {
+              dr[c][e] = fmaf(a, y[c][e], fmaf(cf, d0[c][e], s * z[c][e]));
+            }
+            if (E * (lane + 64 * c) + e >= d) dr[c][e] = 0.f;
+          }
+        // frozen drafter, first position: draft and target mean are the same, accepted without a test
+        if (!frozen || j > 0) {
+          double s1 = 0.0, s2 = 0.0;
+#pragma unroll
+          for (int c = 0; c < C; ++c)
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+              if (E * (lane + 64 * c) + e >= d) continue;
+              double w, dl;                // as in verify_kernel: sigma Z, and (sigma / c) Delta or sigma Delta
+              if (INDEP) {
+                w = static_cast<double>(dr[c][e]) - static_cast<double>(mp[c][e]);
+                dl = static_cast<double>(mp[c][e]) - (static_cast<double>(a) * y[c][e] + static_cast<double>(cf) * dq[c][e]);
+              } else {
+                w = static_cast<double>(dr[c][e]) - static_cast<double>(a) * y[c][e] - static_cast<double>(cf) * d0[c][e];
+                dl = static_cast<double>(d0[c][e]) - static_cast<double>(dq[c][e]);
+              }
+              s1 = fma(w, dl, s1);
+              s2 = fma(dl, dl, s2);
+            }
+          // both sums in one butterfly: the lower half of the wavefront carries s1, the upper half s2
+          double t = sdlane::halving_add<32>(s1, s2);
+          if (d > 16 * E) t = sdlane::pair_sum_rows<16>(t);            // lanes past d hold 0
+          if (d > 8 * E) t += sdlane::lane_xor<8>(t);
+          t += sdlane::lane_xor<4>(t);
+          t += sdlane::lane_xor<2>(t);
+          t += sdlane::lane_xor<1>(t);
+          const double lu = sdgmm::readlane_f64(sb.log_u, at), inv_s2 = sdgmm::readlane_f64(sb.inv_s2, at);
+          const double cc = INDEP ? 1.0 : static_cast<double>(cf);
+          const double S1 = sdgmm::readlane_f64(t, 0) * cc * inv_s2, S2 = sdgmm::readlane_f64(t, 32) * cc * cc * inv_s2;
+          const double lr = (-S1 - 0.5 * S2) * p.inv_tau;
+          if (!(S2 == 0.0 || (lr == lr && lu <= fmin(0.0, lr)))) {       // uniform; a log-ratio that is not a number rejects
+            const double two_coef = 2.0 * (S2 > 0.0 ? S1 / S2 : 0.0);
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+#pragma unroll
+              for (int e = 0; e < E; ++e) {
+                if (INDEP) {
+                  const double mq = static_cast<double>(a) * y[c][e] + static_cast<double>(cf) * dq[c][e];
+                  const double mpd = mp[c][e];
+                  y[c][e] = static_cast<float>(mq + (static_cast<double>(dr[c][e]) - mpd) - two_coef * (mpd - mq));
+                } else {
+                  const double f = static_cast<double>(cf) * (1.0 + two_coef);
+                  y[c][e] = static_cast<float>(static_cast<double>(dr[c][e]) -
+                                               f * (static_cast<double>(d0[c][e]) - static_cast<double>(dq[c][e])));
+                }
+                if (E * (lane + 64 * c) + e >= d) y[c][e] = 0.f;
+              }
+            adv = j + 1;
+            rejected = true;
+            break;
+          }
+        }
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+#pragma unroll
+          for (int e = 0; e < E; ++e) y[c][e] = dr[c][e];
+      }
+      n += adv;
+      windows += 1;
+      rejections += rejected ? 1 : 0;
+      kt_sum += Kt;
+      if (!INDEP && p.reused && n < p.T) {
+        // the next window's frozen prediction: at the draft state of the step advanced to, or (second rule, after a
+        // rejection) the one already at hand for the last state kept
+        if (rejected && p.carry_last) {
+#pragma unroll
+          for (int c = 0; c < C; ++c)
+#pragma unroll
+            for (int e = 0; e < E; ++e) d0[c][e] = dq[c][e];
+        } else {
+          if (n - sb.base >= 64) sb.refill(p, INDEP, n, id, lane);
+          const int at = n - sb.base;
+          sdgmm::posterior_mean<E, C, LDS>(p.t, tab_t, xs, dr, sdgmm::readlane_f64(sb.t.x, at), sdgmm::readlane_f64(sb.t.y, at),
+                                           next_t, lane, d0);     // next_t: step n's, requested when step n - 1 was taken
+        }
+      }
+    }
+    float* o = p.out + id * d;
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const int i = E * (lane + 64 * c) + e;
+        if (i < d && windows > 0) o[i] = y[c][e];
+      }
+    if (lane == 0) {
+      atomicAdd(&sh_cnt[0], static_cast<unsigned long long>(n - n_start));
+      atomicAdd(&sh_cnt[1], static_cast<unsigned long long>(windows));
+      atomicAdd(&sh_cnt[2], static_cast<unsigned long long>(rejections));
+      atomicAdd(&sh_cnt[3], static_cast<unsigned long long>(kt_sum));
+      atomicMax(&sh_longest, windows);
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    if (p.counters) {
+      if (sh_cnt[0]) atomicAdd(p.counters + 0, sh_cnt[0]);
+      if (sh_cnt[1]) atomicAdd(p.counters + 1, sh_cnt[1]);
+      if (sh_cnt[2]) atomicAdd(p.counters + 2, sh_cnt[2]);
+      if (sh_cnt[3]) atomicAdd(p.counters + 4, sh_cnt[3]);
+    }
+    if (sh_longest) atomicMax(p.longest, sh_longest);
+  }
+}
+
+__global__ void run_begin_kernel(int32_t* longest) { *longest = 0; }
+
+// A batch stepped window by window makes as many windows as its longest chain.
+__global__ void run_end_kernel(const int32_t* longest, unsigned long long* counters, int32_t* B_active) {
+  if (counters) counters[3] += static_cast<unsigned long long>(*longest);
+  *B_active = 0;
 }
 
 struct GmmDenoiser final : sdden {
-  int M = 0, Mp = 1;          // Mp: M rounded up to a power of two, at most 64
-  float* dev_f = nullptr;     // mu, sd, muT, sdT, ab, then the lane-ordered table when the register kernel applies
-  const float2* lane_tab = nullptr;
-  double* dev_cst = nullptr;
+  sdgmm::Model g{};
+  float* dev_f = nullptr;     // fp32 tables: row table and lane table, or (more than 64 components) mu, sd, muT, sdT, ab
+  double* dev_d = nullptr;    // cst [T,M], then (ab, sqrt(ab)) [T]
+  bool lanes = false;         // at most 64 components: gmm_rows.h
+  const float *mu = nullptr, *sd = nullptr, *muT = nullptr, *sdT = nullptr, *ab = nullptr;
   ~GmmDenoiser() override {
     if (dev_f) (void)hipFree(dev_f);
-    if (dev_cst) (void)hipFree(dev_cst);
+    if (dev_d) (void)hipFree(dev_d);
   }
   int eval(int R, const float* X, const int32_t* krow, float* out, hipStream_t st) override {
     GmmArgs p;
-    const size_t md = static_cast<size_t>(M) * d;
-    p.X = X; p.krow = krow; p.out = out;
-    p.mu = dev_f; p.sd = dev_f + md; p.muT = dev_f + 2 * md; p.sdT = dev_f + 3 * md; p.ab = dev_f + 4 * md;
-    p.Mp = Mp;
-    p.lane_tab = lane_tab;
-    p.cst = dev_cst; p.active = active; p.rows_per_chain = rows_per_chain;
-    p.R = R; p.d = d; p.M = M; p.T = T;
-    const size_t shmem = sizeof(double) * kRowsPerBlock * static_cast<size_t>(M + d);
-    const unsigned grid = static_cast<unsigned>((R + kRowsPerBlock - 1) / kRowsPerBlock);
+    p.X = X; p.krow = krow; p.out = out; p.g = g;
+    p.mu = mu; p.sd = sd; p.muT = muT; p.sdT = sdT; p.ab = ab;
+    p.active = active; p.rows_per_chain = rows_per_chain; p.R = R;
+    const dim3 grid(static_cast<unsigned>((R + kRowsPerBlock - 1) / kRowsPerBlock)), block(64 * kRowsPerBlock);
     prof.mark(1, st);
-    if (lane_tab) {
-      switch (p.Mp) {
-        case 32: launch_reg<32, kRegNI>(p, grid, st); break;
-        case 16: launch_reg<16, kRegNI>(p, grid, st); break;
-        case 8: launch_reg<8, kRegNI>(p, grid, st); break;
-        case 4: launch_reg<4, kRegNI>(p, grid, st); break;
-        case 2: launch_reg<2, kRegNI>(p, grid, st); break;
-        default: launch_reg<1, kRegNI>(p, grid, st); break;
-      }
+    if (lanes) {
+      const size_t shmem = sizeof(double) * kRowsPerBlock * (static_cast<size_t>(g.nslots) << (6 - g.lm));
+      if (d <= 64) hipLaunchKernelGGL((gmm_rows_kernel<1, 1>), grid, block, shmem, st, p);
+      else if (d <= 128) hipLaunchKernelGGL((gmm_rows_kernel<2, 1>), grid, block, shmem, st, p);
+      else if (d <= 256) hipLaunchKernelGGL((gmm_rows_kernel<4, 1>), grid, block, shmem, st, p);
+      else if (d <= 512) hipLaunchKernelGGL((gmm_rows_kernel<4, 2>), grid, block, shmem, st, p);
+      else if (d <= 1024) hipLaunchKernelGGL((gmm_rows_kernel<4, 4>), grid, block, shmem, st, p);
+      else hipLaunchKernelGGL((gmm_rows_kernel<4, 8>), grid, block, shmem, st, p);
     } else {
-      hipLaunchKernelGGL(gmm_posterior_mean_kernel, dim3(grid), dim3(64 * kRowsPerBlock), shmem, st, p);
+      const size_t shmem = sizeof(double) * kRowsPerBlock * static_cast<size_t>(g.M + d);
+      hipLaunchKernelGGL(gmm_many_components_kernel, grid, block, shmem, st, p);
     }
     prof.mark(1, st);
     SD_HIP_TRY(err, hipGetLastError());
     return SD_OK;
   }
+  int run(sdden* draft, sd_ctx* ctx, int B, const float* y, const int32_t* n, const int64_t* chain_id, const float* D_frozen,
+          float* out, int32_t* B_active, int64_t* counters, hipStream_t st) override;
 };
+
+template <int E, int C, bool LDS>
+void launch_run(const RunArgs& p, bool indep, unsigned grid, unsigned block, size_t shmem, hipStream_t st) {
+  if (indep) hipLaunchKernelGGL((gmm_run_kernel<E, C, LDS, true>), dim3(grid), dim3(block), shmem, st, p);
+  else hipLaunchKernelGGL((gmm_run_kernel<E, C, LDS, false>), dim3(grid), dim3(block), shmem, st, p);
+}
+
+int GmmDenoiser::run(sdden* draft, sd_ctx* ctx, int B, const float* y, const int32_t* n, const int64_t* chain_id,
+                     const float* D_frozen, float* out, int32_t* B_active, int64_t* counters, hipStream_t st) {
+  const bool indep = ctx->mode == SD_DRAFT_EXPLICIT;
+  GmmDenoiser* q = indep ? dynamic_cast<GmmDenoiser*>(draft) : nullptr;
+  // what needs the separate calls: more than 64 components, kernels timed one by one, a batch size kept on the device
+  if (!lanes || prof.which || active || ctx->active || (indep && (!q || !q->lanes || q->prof.which || q->active)))
+    return sdi::fail(err, SD_ERR_UNSUPPORTED, "sdden_run: this denoiser's chains run window by window");
+  RunArgs p{};
+  p.t = g;
+  if (q) p.q = q->g;
+  p.y = y; p.n = n; p.id = chain_id; p.Dfz = D_frozen; p.out = out;
+  p.a = ctx->dev_a; p.c = ctx->dev_c; p.sigma = ctx->dev_sigma;
+  p.B = B; p.K = ctx->K; p.T = ctx->T; p.seed = ctx->seed; p.inv_tau = 1.0 / ctx->tau;
+  p.reused = ctx->mode == SD_DRAFT_FROZEN_REUSED;
+  p.carry_last = ctx->carry_rule == SD_CARRY_LAST_ACCEPTED;
+  p.counters = reinterpret_cast<unsigned long long*>(counters);
+  p.longest = ctx->dev_queue + 1;
+  // Few chains: a workgroup each, spread over the CUs.  From 1024 on four share a workgroup and its table.
+  const int waves = B >= 2048 ? 4 : (B >= 1024 ? 2 : 1);
+  const unsigned grid = static_cast<unsigned>((B + waves - 1) / waves), block = 64u * waves;
+  size_t npad = static_cast<size_t>(g.nslots) << (6 - g.lm), slots = g.nslots;
+  if (q) {
+    npad = std::max(npad, static_cast<size_t>(q->g.nslots) << (6 - q->g.lm));
+    slots += q->g.nslots;
+  }
+  npad = (npad + 1) / 2 * 2;
+  // The tables go to LDS as fp64 (no conversion and no square per pair) while four workgroups still fit a CU.
+  const size_t table = sizeof(double2) * sdgmm::kTabStride * slots, xs = (sizeof(double) * npad + (d <= 128 ? 1024 : 0)) * waves;
+  const bool lds = d <= 256 && table <= 36 * 1024;
+  const size_t shmem = xs + (lds ? table : 0);
+  hipLaunchKernelGGL(run_begin_kernel, dim3(1), dim3(1), 0, st, p.longest);
+  if (d <= 64) lds ? launch_run<1, 1, true>(p, indep, grid, block, shmem, st) : launch_run<1, 1, false>(p, indep, grid, block, shmem, st);
+  else if (d <= 128) lds ? launch_run<2, 1, true>(p, indep, grid, block, shmem, st) : launch_run<2, 1, false>(p, indep, grid, block, shmem, st);
+  else if (d <= 256) lds ? launch_run<4, 1, true>(p, indep, grid, block, shmem, st) : launch_run<4, 1, false>(p, indep, grid, block, shmem, st);
+  else if (d <= 512) launch_run<4, 2, false>(p, indep, grid, block, shmem, st);
+  else if (d <= 1024) launch_run<4, 4, false>(p, indep, grid, block, shmem, st);
+  else launch_run<4, 8, false>(p, indep, grid, block, shmem, st);
+  hipLaunchKernelGGL(run_end_kernel, dim3(1), dim3(1), 0, st, p.longest, p.counters, B_active);
+  SD_HIP_TRY(err, hipGetLastError());
+  return SD_OK;
+}
 
 }  // namespace
 
@@ -289,59 +533,76 @@ int sdden_gmm_create(int32_t M, int32_t d, const float* means, const float* stds
   if (static_cast<size_t>(M + d) * sizeof(double) * kRowsPerBlock > 60000)
     return sdi::fail(E, SD_ERR_UNSUPPORTED, "sdden_gmm_create: M+d=%d too large for the LDS staging", M + d);
   const size_t md = static_cast<size_t>(M) * d;
-  std::vector<float> h(4 * md + T + 1);
-  std::vector<double> cst(static_cast<size_t>(T) * M);
-  for (int m = 0; m < M; ++m)
-    for (int i = 0; i < d; ++i) {
-      const float mu = means[m * static_cast<size_t>(d) + i], s = stds[m * static_cast<size_t>(d) + i];
-      if (!(s > 0.f)) return sdi::fail(E, SD_ERR_ARG, "sdden_gmm_create: stds must be > 0");
-      h[m * static_cast<size_t>(d) + i] = mu;
-      h[md + m * static_cast<size_t>(d) + i] = s;
-      h[2 * md + i * static_cast<size_t>(M) + m] = mu;
-      h[3 * md + i * static_cast<size_t>(M) + m] = s;
+  for (size_t i = 0; i < md; ++i)
+    if (!(stds[i] > 0.f)) return sdi::fail(E, SD_ERR_ARG, "sdden_gmm_create: stds must be > 0");
+  const bool lanes = M <= sdgmm::kMaxLaneComponents;
+  int lm = 0;                                                // lanes per component: 64 / (M rounded up to a power of two)
+  while (lm < 6 && (1 << lm) < M) ++lm;
+  const int parts = 64 >> lm;
+  int nslots = (d + parts - 1) / parts;
+  if (nslots > 2) nslots = (nslots + 3) / 4 * 4;             // whole groups of four pairs
+  std::vector<float> h;
+  std::vector<double> dbl(static_cast<size_t>(T) * M + 1 + 2 * static_cast<size_t>(T));
+  const size_t step_off = (static_cast<size_t>(T) * M + 1) / 2 * 2;       // 16-byte aligned
+  if (lanes) {
+    h.resize(2 * md + 128 * static_cast<size_t>(nslots));
+    for (size_t i = 0; i < md; ++i) {
+      h[2 * i] = means[i];
+      h[2 * i + 1] = stds[i];
     }
-  for (int k = 0; k <= T; ++k) h[4 * md + k] = alpha_bar_state[k];
-  int Mp = 1;
-  while (Mp < M && Mp < 64) Mp <<= 1;
-  size_t lane_off = 0;
-  if (Mp <= 32 && d <= (64 / Mp) * kRegNI) {
-    // (mean, std) of the pair that lane part + PARTS * m reads at its j-th coordinate i = part + PARTS * j;
-    // slots without a pair hold (0, 1) and are never used
-    const int parts = 64 / Mp;
-    lane_off = (h.size() + 1) / 2 * 2;                       // 8-byte aligned
-    h.resize(lane_off + 2 * static_cast<size_t>(kRegNI) * 64);
-    for (int j = 0; j < kRegNI; ++j)
+    for (int j = 0; j < nslots; ++j)
       for (int lane = 0; lane < 64; ++lane) {
-        const int part = lane % parts, m = lane / parts, i = part + parts * j;
+        const int m = lane >> (6 - lm), i = (lane & (parts - 1)) + parts * j;
         const bool has = m < M && i < d;
-        h[lane_off + 2 * (static_cast<size_t>(j) * 64 + lane)] = has ? means[m * static_cast<size_t>(d) + i] : 0.f;
-        h[lane_off + 2 * (static_cast<size_t>(j) * 64 + lane) + 1] = has ? stds[m * static_cast<size_t>(d) + i] : 1.f;
+        float* slot = h.data() + 2 * md + 2 * (static_cast<size_t>(j) * 64 + lane);
+        slot[0] = has ? means[m * static_cast<size_t>(d) + i] : 0.f;
+        slot[1] = has ? stds[m * static_cast<size_t>(d) + i] : 1.f;
       }
+  } else {
+    h.resize(4 * md + T + 1);
+    for (int m = 0; m < M; ++m)
+      for (int i = 0; i < d; ++i) {
+        const float mu = means[m * static_cast<size_t>(d) + i], s = stds[m * static_cast<size_t>(d) + i];
+        h[m * static_cast<size_t>(d) + i] = mu;
+        h[md + m * static_cast<size_t>(d) + i] = s;
+        h[2 * md + i * static_cast<size_t>(M) + m] = mu;
+        h[3 * md + i * static_cast<size_t>(M) + m] = s;
+      }
+    for (int k = 0; k <= T; ++k) h[4 * md + k] = alpha_bar_state[k];
   }
   for (int k = 0; k < T; ++k) {
     const double ab = alpha_bar_state[k];
     for (int m = 0; m < M; ++m) {
       double ld = 0.0;
       for (int i = 0; i < d; ++i) {
-        const double sd = h[md + m * static_cast<size_t>(d) + i];
+        const double sd = stds[m * static_cast<size_t>(d) + i];
         ld += std::log(ab * sd * sd + (1.0 - ab));
       }
-      cst[static_cast<size_t>(k) * M + m] = static_cast<double>(logw[m]) - 0.5 * ld;
+      dbl[static_cast<size_t>(k) * M + m] = static_cast<double>(logw[m]) - 0.5 * ld;
     }
+    dbl[step_off + 2 * k] = ab;
+    dbl[step_off + 2 * k + 1] = std::sqrt(ab);
   }
   GmmDenoiser* g = new (std::nothrow) GmmDenoiser;
   if (!g) return sdi::fail(E, SD_ERR_ARG, "sdden_gmm_create: out of host memory");
-  g->d = d; g->T = T; g->M = M;
+  g->d = d; g->T = T; g->lanes = lanes;
   hipError_t e = hipMalloc(&g->dev_f, h.size() * sizeof(float));
-  if (e == hipSuccess) e = hipMalloc(&g->dev_cst, cst.size() * sizeof(double));
+  if (e == hipSuccess) e = hipMalloc(&g->dev_d, dbl.size() * sizeof(double));
   if (e == hipSuccess) e = hipMemcpy(g->dev_f, h.data(), h.size() * sizeof(float), hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemcpy(g->dev_cst, cst.data(), cst.size() * sizeof(double), hipMemcpyHostToDevice);
+  if (e == hipSuccess) e = hipMemcpy(g->dev_d, dbl.data(), dbl.size() * sizeof(double), hipMemcpyHostToDevice);
   if (e != hipSuccess) {
     delete g;
     return sdi::fail(E, SD_ERR_HIP, "sdden_gmm_create: %s", hipGetErrorString(e));
   }
-  g->Mp = Mp;
-  if (lane_off) g->lane_tab = reinterpret_cast<const float2*>(g->dev_f + lane_off);
+  g->g.M = M; g->g.d = d; g->g.T = T; g->g.lm = lm; g->g.nslots = nslots;
+  g->g.cst = g->dev_d;
+  g->g.steps = reinterpret_cast<const double2*>(g->dev_d + step_off);
+  if (lanes) {
+    g->g.row_tab = reinterpret_cast<const float2*>(g->dev_f);
+    g->g.lane_tab = reinterpret_cast<const float2*>(g->dev_f + 2 * md);
+  } else {
+    g->mu = g->dev_f; g->sd = g->dev_f + md; g->muT = g->dev_f + 2 * md; g->sdT = g->dev_f + 3 * md; g->ab = g->dev_f + 4 * md;
+  }
   *out = g;
   return SD_OK;
 }
@@ -352,6 +613,17 @@ int sdden_eval(sdden* den, int32_t R, const float* X, const int32_t* krow, float
   if (R == 0) return SD_OK;
   den->prof.cur_rows = R;
   return den->eval(R, X, krow, out, static_cast<hipStream_t>(stream));
+}
+
+int sdden_run(sdden* den, sdden* draft_den, sd_ctx* ctx, int32_t B, const float* y, const int32_t* n, const int64_t* chain_id,
+              const float* D_frozen, float* out, int32_t* B_active, int64_t* counters, void* stream) {
+  if (!den || !ctx) return SD_ERR_ARG;
+  if (B <= 0 || !y || !n || !chain_id || !out || !B_active || (ctx->mode == SD_DRAFT_EXPLICIT && !draft_den) ||
+      (ctx->mode == SD_DRAFT_FROZEN_REUSED && !D_frozen))
+    return sdi::fail(den->err, SD_ERR_ARG, "sdden_run: bad argument");
+  if (den->d != ctx->d || den->T < ctx->T || (ctx->mode == SD_DRAFT_EXPLICIT && (draft_den->d != ctx->d || draft_den->T < ctx->T)))
+    return sdi::fail(den->err, SD_ERR_ARG, "sdden_run: denoiser and context describe chains of different sizes");
+  return den->run(draft_den, ctx, B, y, n, chain_id, D_frozen, out, B_active, counters, static_cast<hipStream_t>(stream));
 }
 
 int sdden_eval_mirror(sdden* den, int32_t R, const float* X, const uint16_t* Xbf16, const int32_t* krow, float* out,

@@ -40,6 +40,13 @@ struct sdden {
     (void)Xbf16;
     return eval(R, X, krow, out, st);
   }
+  // Every chain from its step to T in one launch, where the denoiser has such a form (sdden_run).
+  virtual int run(sdden* draft, sd_ctx* ctx, int B, const float* y, const int32_t* n, const int64_t* chain_id,
+                  const float* D_frozen, float* out, int32_t* B_active, int64_t* counters, hipStream_t st) {
+    (void)draft; (void)ctx; (void)B; (void)y; (void)n; (void)chain_id; (void)D_frozen; (void)out; (void)B_active;
+    (void)counters; (void)st;
+    return SD_ERR_UNSUPPORTED;
+  }
   int d = 0, T = 0;
   sdden_profiler prof;
   const int32_t* active = nullptr;   // optional device-side chain count

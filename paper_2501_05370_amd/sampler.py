@@ -111,6 +111,8 @@ class _SamplerBase:
         tens of microseconds of kernels, launch cost is what is left.  Results do not depend on
         either option (noise is keyed by chain id and step, never by the launch)."""
         B = self.start(chain_ids, reset_counters)
+        if B > 0 and isinstance(self.timer, _NoTimer) and self._run_chains(B):
+            return self.buf.out, self.buf.counters.tolist()
         if windows_per_sync <= 1 and not graph:
             while B > 0:
                 self.window(B)
@@ -137,6 +139,11 @@ class _SamplerBase:
         finally:
             self._set_active(None)
         return b.out, b.counters.tolist()
+
+    def _run_chains(self, B: int) -> bool:
+        """All windows of the started chains in one launch, where the library has such a form for this sampler's denoiser:
+        same noise, same decisions, no launches or readback between windows.  False: nothing was done."""
+        return False
 
     def _bound(self, B: int) -> int:
         """Launch bound for B remaining chains: B rounded up to 1/8 steps of the capacity, so that a
@@ -175,6 +182,10 @@ class DiffusionSampler(_SamplerBase):
         # a network with bf16 inputs gets the drafts as bf16 straight from the draft kernel
         self.mirror = (torch.zeros(B, ctx.K, ctx.d, dtype=torch.int16, device="cuda")
                        if getattr(den, "wants_bf16", False) else None)
+
+    def _run_chains(self, B: int) -> bool:
+        b = self.buf
+        return self.den.sdden_run(self.ctx, B, b.y, b.n, b.chain_id, b.out, b.B_active, b.counters)
 
     def window(self, B: int, diagnostics=None):
         """One pass of the while-loop body for the first B chains of the buffers."""
@@ -217,6 +228,10 @@ class IndependentDrafterSampler(_SamplerBase):
         b.kcur = [torch.full((B,), -1, dtype=torch.int32, device="cuda") for _ in range(2)]
         ctx.sd_set_draft_mode(SD_DRAFT_EXPLICIT)
         ctx.sd_set_start_prediction(b.D0)
+
+    def _run_chains(self, B: int) -> bool:
+        b = self.buf
+        return self.den.sdden_run(self.ctx, B, b.y, b.n, b.chain_id, b.out, b.B_active, b.counters, draft_den=self.draft_den)
 
     def window(self, B: int, diagnostics=None):
         b, ctx, d, K, t = self.buf, self.ctx, self.ctx.d, self.ctx.K, self.timer
@@ -271,6 +286,10 @@ class EfficientFrozenSampler(_SamplerBase):
         b = self.buf
         self.den.sdden_eval(B, b.y, b.n, b.Dfz)                 # initialisation: D(y_0, 0)
         return B
+
+    def _run_chains(self, B: int) -> bool:
+        b = self.buf
+        return self.den.sdden_run(self.ctx, B, b.y, b.n, b.chain_id, b.out, b.B_active, b.counters, D_frozen=b.Dfz)
 
     def window(self, B: int, diagnostics=None):
         b, ctx, d, K, t = self.buf, self.ctx, self.ctx.d, self.ctx.K, self.timer
