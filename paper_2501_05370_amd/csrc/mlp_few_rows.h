@@ -1,0 +1,238 @@
+// The MLP denoiser's three products for calls of few rows (one image-sized chain, a handful of requests, the window
+// start of a batch):  C[M,N] = A[M,K] * Bt[N,K]^T with the epilogues of mlp_gemm.h.
+//
+// What bounds such a call is reading the weights once, and the tiles of mlp_gemm.h cannot: an output of 16 rows is
+// 32 tiles of 64 x 128 at N = 4096, so 32 of 256 CUs pull the whole matrix, each through one chain of dependent
+// slices.  Here a tile is 16 * MT rows x 16 * NT columns, so 16 columns already give every CU one at N = 4096, and a
+// ring in LDS keeps RING - 1 stages of S steps of 32 k on their way per workgroup (56 KiB for one row tile).
+//
+// Every output is summed over k in one chain, 32 at a time and in order, as the tiles of mlp_gemm.h do, so a
+// prediction has the same bits whatever kernel and however many rows a call has.  Splitting k over the wavefronts of a
+// workgroup measured 44 us against 51 for one row and 61 against 77 for 64 (the three products at d = 12288,
+// H = 4096), but moves every prediction by 3e-4 (a hidden activation that rounds to the other bf16 moves all that
+// follow), and with it the drafts that are made from it.
+//
+// Layout.  Both operands are stored in fragment order: 16 rows x 32 k are one block of 1 KiB in which lane (l16, lq)
+// of the wavefront finds its 16 bytes (row l16, k = 8 lq .. 8 lq + 7) at 16 * lane, and the blocks of 16 rows follow
+// each other along k.  A direct load into LDS is then eight whole cache lines and a fragment read is conflict free
+// with no permutation; out of row-major operands a block is 16 half lines one row stride apart, which for these widths
+// (multiples of 512 bytes) meet on few cache channels (16 rows, split k: 57.6 us row-major, 40.3 in fragment order).
+// The weights' copy in this order is made when the denoiser is created; pack_rows_kernel writes the call's rows, and
+// each product's epilogue writes the next one's operand.
+//
+// Measured, the three products with pack_rows_kernel against the LDS tiles without their compaction and conversion:
+//   d = 12288, H = 4096    1 row 51 / 161 us   32 rows 54 / 169   64 rows 72 / 170   200 rows 136 / 158
+//   d = 3072, H = 1024     1 row 17 / 39 us    32 rows 17 / 46    64 rows 20 / 46    200 rows 25 / 48
+// 237 MB of weights in 47 us are 5 TB/s; from 64 rows on it is the operands' path out of L2 that counts.
+#pragma once
+#include "mlp_gemm.h"
+#include "sdden_internal.h"
+
+namespace mlpfew {
+
+using mlpgemm::bf16x8;
+using mlpgemm::u32x4;
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kPackThreads = 256;
+constexpr int kMaxRows = 1024;    // rows of a call: pack_rows_kernel ranks them four per thread
+
+// Element offset of (row, k .. k + 7), k a multiple of 8, in fragment order.
+__host__ __device__ __forceinline__ size_t frag_offset(int row, int k, int K) {
+  return (static_cast<size_t>(row >> 4) * (K >> 5) + (k >> 5)) * 512 + (((k & 31) >> 3) * 16 + (row & 15)) * 8;
+}
+
+// W[N,K] row-major -> fragment order; one 16-byte chunk per thread.
+__global__ __launch_bounds__(256) void pack_weights_kernel(const uint16_t* __restrict__ W, uint16_t* __restrict__ F, int N, int K) {
+  const int64_t g = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  const int chunks = K / 8;
+  if (g >= static_cast<int64_t>(N) * chunks) return;
+  const int n = static_cast<int>(g / chunks), k = static_cast<int>(g % chunks) * 8;
+  *reinterpret_cast<u32x4*>(F + frag_offset(n, k, K)) = *reinterpret_cast<const u32x4*>(W + static_cast<size_t>(n) * K + k);
+}
+
+// The rows r < active rows with 0 <= krow[r] < T, in increasing order, as dense rows of F in fragment order: from the
+// bf16 image when the caller has one, else X rounded to bf16.  Every workgroup ranks all (at most kMaxRows) rows itself
+// -- one load per 256 rows -- and moves its 16 dense rows x `kchunk` columns; the first column of workgroups leaves
+// rowidx and the count for the products.  One launch in place of a compaction and a conversion.
+__global__ __launch_bounds__(kPackThreads) void pack_rows_kernel(const float* __restrict__ X, const uint16_t* __restrict__ Xb,
+                                                                 const int32_t* __restrict__ krow, const int32_t* active,
+                                                                 int rows_per_chain, int R, int T, int K, int kchunk,
+                                                                 uint16_t* __restrict__ F, int32_t* __restrict__ rowidx,
+                                                                 int32_t* __restrict__ count) {
+  constexpr int NW = kPackThreads / 64, NC = kMaxRows / kPackThreads;
+  __shared__ int tot[NC][NW];
+  __shared__ int src_row[16];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int Ract = sdi::active_rows(active, rows_per_chain, R);
+  unsigned long long m[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    const int r = c * kPackThreads + t;
+    const bool keep = r < Ract && static_cast<unsigned>(krow[r < R ? r : 0]) < static_cast<unsigned>(T);
+    m[c] = __ballot(keep);
+    if (lane == 0) tot[c][wave] = __popcll(m[c]);
+  }
+  if (t < 16) src_row[t] = -1;
+  __syncthreads();
+  const int first = blockIdx.y * 16;
+  int base = 0;
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      if (w == wave && ((m[c] >> lane) & 1ull)) {
+        const int pos = base + __popcll(m[c] & ((1ull << lane) - 1ull));
+        if (pos >= first && pos < first + 16) src_row[pos - first] = c * kPackThreads + t;
+      }
+      base += tot[c][w];
+    }
+  __syncthreads();
+  if (blockIdx.x == 0) {
+    if (t < 16 && src_row[t] >= 0) rowidx[first + t] = src_row[t];
+    if (blockIdx.y == 0 && t == 0) *count = base;
+  }
+  if (first >= base) return;
+  const int k0 = blockIdx.x * kchunk, k1 = k0 + kchunk < K ? k0 + kchunk : K;
+  // 16 lanes share a k chunk of 8 and take one row each: stores of 256 contiguous bytes
+  const int row = t & 15, src = src_row[row];
+  if (src < 0) return;
+  for (int k = k0 + 8 * (t >> 4); k < k1; k += 8 * (kPackThreads / 16)) {
+    u32x4 o;
+    if (Xb) {
+      o = *reinterpret_cast<const u32x4*>(Xb + static_cast<size_t>(src) * K + k);
+    } else {
+      const float* s = X + static_cast<size_t>(src) * K + k;
+      const f32x4 lo = *reinterpret_cast<const f32x4*>(s), hi = *reinterpret_cast<const f32x4*>(s + 4);
+      bf16x8 b;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        b[e] = static_cast<__bf16>(lo[e]);
+        b[4 + e] = static_cast<__bf16>(hi[e]);
+      }
+      o = __builtin_bit_cast(u32x4, b);
+    }
+    *reinterpret_cast<u32x4*>(F + frag_offset(first + row, k, K)) = o;
+  }
+}
+
+struct Args {
+  const uint16_t* A;        // [rows rounded up to a whole tile, K] bf16, fragment order
+  const uint16_t* W;        // [N, K] bf16, fragment order
+  int N, K;
+  const int32_t* count;     // device: M
+  const int32_t* rowidx;    // dense row -> source row
+  const int32_t* krow;      // source row -> chain step
+  const float* bias;        // EPI 1: per-step table [T, N]; EPI 2, 3: [N]
+  uint16_t* outb;           // EPI 1, 2: bf16 [M, N], fragment order (N is the next product's K)
+  float* outf;              // EPI 3: fp32 [*, N] at source rows
+};
+
+// waits until at most N of this wavefront's vector-memory loads are outstanding (they complete in order)
+template <int N>
+__device__ __forceinline__ void wait_loads() {
+  static_assert(N >= 0 && N < 64, "vmcnt is six bits");
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+template <int OPS, int LEFT>
+__device__ __forceinline__ void wait_stages(int left) {      // at most `left` (<= LEFT) stages outstanding
+  if constexpr (LEFT == 0) wait_loads<0>();
+  else {
+    if (left >= LEFT) wait_loads<LEFT * OPS>();
+    else wait_stages<OPS, LEFT - 1>(left);
+  }
+}
+
+// EPI as in mlp_gemm.h.  Grid: (N / (16 NT), tiles of 16 MT rows), MT wavefronts; wavefront i owns rows 16 i .. 16 i + 15
+// of the tile.  A stage of the ring is S steps of 32 k: per step MT blocks of A, then NT of W.  Rows >= M of the last
+// tile are computed on whatever is there and never stored.
+template <int EPI, int MT, int NT, int S, int RING>
+__global__ __launch_bounds__(64 * MT) void kernel(Args p) {
+  constexpr int kStep = (MT + NT) * 1024, kStage = S * kStep;
+  constexpr int WLOADS = S * NT / MT, OPS = S + WLOADS;      // loads per wavefront and stage: its rows' A, a share of W
+  static_assert(S * NT % MT == 0 && RING >= 2 && RING * kStage <= 160 * 1024 && (RING - 1) * OPS < 64, "ring");
+  __shared__ __align__(1024) unsigned char ring[RING * kStage];
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int row0 = blockIdx.y * 16 * MT, col0 = blockIdx.x * 16 * NT;
+  const int M = *p.count;
+  if (blockIdx.y > 0 && row0 >= M) return;           // the first tile need not wait for the count
+
+  const int steps = p.K / 32, nk = steps / S;        // steps: blocks of 1 KiB per 16 rows
+  const unsigned char* asrc = reinterpret_cast<const unsigned char*>(p.A) + static_cast<size_t>(row0 / 16 + wave) * steps * 1024 + 16 * lane;
+  const unsigned char* wsrc = reinterpret_cast<const unsigned char*>(p.W) + static_cast<size_t>(col0 / 16) * steps * 1024 + 16 * lane;
+  typedef __attribute__((address_space(3))) void* lds_ptr;
+  typedef const __attribute__((address_space(1))) void* gbl_ptr;
+  auto fetch = [&](int slot, int kt) {
+#pragma unroll
+    for (int u = 0; u < S; ++u)
+      __builtin_amdgcn_global_load_lds((gbl_ptr)(asrc + static_cast<size_t>(kt * S + u) * 1024),
+                                       (lds_ptr)(ring + slot * kStage + u * kStep + wave * 1024), 16, 0, 0);
+#pragma unroll
+    for (int u = 0; u < WLOADS; ++u) {
+      const int b = u * MT + wave, step = b / NT, j = b % NT;          // the stage's W blocks, dealt to the wavefronts
+      __builtin_amdgcn_global_load_lds((gbl_ptr)(wsrc + (static_cast<size_t>(j) * steps + kt * S + step) * 1024),
+                                       (lds_ptr)(ring + slot * kStage + step * kStep + (MT + j) * 1024), 16, 0, 0);
+    }
+  };
+
+  f32x4 acc[NT];
+#pragma unroll
+  for (int j = 0; j < NT; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int k = 0; k < RING - 1; ++k)
+    if (k < nk) fetch(k, k);
+  int slot = 0, free_slot = RING - 1;
+  for (int kt = 0; kt < nk; ++kt) {
+    // stage kt has landed once only the younger ones are outstanding; past the barrier every wavefront has read stage
+    // kt - 1, whose slot takes stage kt + RING - 1
+    wait_stages<OPS, RING - 2>(nk - 1 - kt);
+    if (MT > 1) mlpgemm::barrier_keep_loads();
+    if (kt + RING - 1 < nk) fetch(free_slot, kt + RING - 1);
+    const unsigned char* base = ring + slot * kStage + 16 * lane;
+    u32x4 a[S], w[S][NT];
+#pragma unroll
+    for (int u = 0; u < S; ++u) {
+      a[u] = *reinterpret_cast<const u32x4*>(base + u * kStep + wave * 1024);
+#pragma unroll
+      for (int j = 0; j < NT; ++j) w[u][j] = *reinterpret_cast<const u32x4*>(base + u * kStep + (MT + j) * 1024);
+    }
+    __builtin_amdgcn_sched_barrier(0);               // every read is on its way before the first product waits for one
+    // the weights are the first operand: a lane then holds 4 consecutive output columns of one row
+#pragma unroll
+    for (int u = 0; u < S; ++u)
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[u][j]), __builtin_bit_cast(bf16x8, a[u]),
+                                                         acc[j], 0, 0, 0);
+    free_slot = slot;
+    slot = slot + 1 == RING ? 0 : slot + 1;
+  }
+
+  // lane (l16, lq): columns col0 + 16 j + 4 lq .. + 3 of row row0 + 16 wave + l16
+  const int gm = row0 + 16 * wave + (lane & 15);
+  if (gm >= M) return;
+  const int src = EPI == 2 ? 0 : p.rowidx[gm];
+  const float* b = EPI == 1 ? p.bias + static_cast<size_t>(p.krow[src]) * p.N : p.bias;
+#pragma unroll
+  for (int j = 0; j < NT; ++j) {
+    const int gn = col0 + 16 * j + 4 * (lane >> 4);
+    const f32x4 c = acc[j] + *reinterpret_cast<const f32x4*>(b + gn);
+    if (EPI == 3) {
+      *reinterpret_cast<f32x4*>(p.outf + static_cast<size_t>(src) * p.N + gn) = c;
+    } else {
+      uint2 o;
+      o.x = mlpgemm::to_bf16_bits(mlpgemm::silu(c[0])) | (static_cast<uint32_t>(mlpgemm::to_bf16_bits(mlpgemm::silu(c[1]))) << 16);
+      o.y = mlpgemm::to_bf16_bits(mlpgemm::silu(c[2])) | (static_cast<uint32_t>(mlpgemm::to_bf16_bits(mlpgemm::silu(c[3]))) << 16);
+      *reinterpret_cast<uint2*>(p.outb + frag_offset(gm, gn & ~7, p.N) + (gn & 4)) = o;
+    }
+  }
+}
+
+template <int EPI, int MT, int NT, int S, int RING>
+hipError_t launch(const Args& a, int R, hipStream_t st) {
+  hipLaunchKernelGGL((kernel<EPI, MT, NT, S, RING>), dim3(a.N / (16 * NT), (R + 16 * MT - 1) / (16 * MT)), dim3(64 * MT), 0, st, a);
+  return hipGetLastError();
+}
+
+}  // namespace mlpfew

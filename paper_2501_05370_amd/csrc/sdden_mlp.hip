@@ -10,6 +10,8 @@
 //   gemm<1>           H1 = silu(Xb W1x + tb[krow])        tb[k] = b1 + emb(k) W1t, folded at create
 //   gemm<2>           H2 = silu(H1 W2 + b2)
 //   gemm<3>           out[rowidx[m]] = H2 W3 + b3          (fp32, scattered back to the source rows)
+// Calls of few rows take the kernels of mlp_few_rows.h instead (one launch for the first two steps, three products
+// bound by the weights' bytes).
 //
 // The GEMM kernel (direct global->LDS loads, XOR-swizzled LDS rows, 32x32x16 bf16 MFMA tiles,
 // XCD-aware tile order) is in mlp_gemm.h.
@@ -20,6 +22,7 @@
 #include <new>
 #include <vector>
 
+#include "mlp_few_rows.h"
 #include "mlp_gemm.h"
 #include "mlp_gemm_pp.h"
 #include "sdden_internal.h"
@@ -103,9 +106,39 @@ int launch_gemm(const mlpgemm::Args& a, int R, hipStream_t st, std::string& err,
   return SD_OK;
 }
 
+// Which calls take mlp_few_rows.h.  Its workgroups pull the weights once per 64 rows (out of L2 after the first), so its
+// time grows with that product where the LDS tiles of launch_gemm stay flat until they fill the chip.  Measured for
+// the three products, few rows against LDS tiles without their compaction and conversion, in us:
+//   d = 12288, H = 4096 (117 M weights)   100 rows 92 / 171   300 rows 158 / 186   500 rows 211 / 224
+//   d = 3072, H = 1024 (7.3 M)            100 rows 23 / 47    500 rows 34 / 49
+//   d = 1024, H = 512 (1.3 M)             100 rows 14 / 28    500 rows 19 / 28
+// The line lies between the 5 and the 8 tiles of the first size; kMaxRows is what pack_rows_kernel ranks.
+bool few_rows(int R, int d, int H) {
+  const int64_t weights = static_cast<int64_t>(H) * (2 * static_cast<int64_t>(d) + H);
+  return R <= mlpfew::kMaxRows && ((R + 63) / 64) * weights <= 800000000;
+}
+
+// Tile of mlp_few_rows.h: rows in steps of 16 up to one tile of 64, and the narrowest of 16, 32 or 64 columns whose
+// workgroups fit the 256 CUs at once: a workgroup of 16 columns takes most of a CU's LDS (10 us at K = 4096), one of 32
+// too (13 us), two of 64 share a CU (20 us alone, 16 per 256 of them).  100 rows, K = 4096, in us at 16 / 32 / 64
+// columns: N = 4096 (512 / 256 / 128 workgroups) 19 / 14 / 19; N = 12288 (1536 / 768 / 384) 53 / 40 / 27.
+template <int EPI>
+int launch_few(const mlpfew::Args& a, int R, hipStream_t st, std::string& err) {
+  const int row_tiles = (R + 63) / 64;
+  hipError_t e;
+  if (R <= 16) e = mlpfew::launch<EPI, 1, 1, 8, 4>(a, R, st);
+  else if (R <= 32) e = mlpfew::launch<EPI, 2, 1, 8, 5>(a, R, st);
+  else if (a.N / 16 * row_tiles <= 256) e = mlpfew::launch<EPI, 4, 1, 8, 4>(a, R, st);
+  else if (a.N / 32 * row_tiles <= 256) e = mlpfew::launch<EPI, 4, 2, 4, 6>(a, R, st);
+  else e = mlpfew::launch<EPI, 4, 4, 2, 4>(a, R, st);
+  if (e != hipSuccess) return sdi::fail(err, SD_ERR_HIP, "mlp few-row product launch: %s", hipGetErrorString(e));
+  return SD_OK;
+}
+
 struct MlpDenoiser final : sdden {
   int H = 0, E = 0;
   uint16_t *W1t = nullptr, *W2t = nullptr, *W3t = nullptr;    // [H,d], [H,H], [d,H] bf16
+  uint16_t *F1 = nullptr, *F2 = nullptr, *F3 = nullptr;       // the same in the fragment order of mlp_few_rows.h
   float *tb = nullptr, *b2 = nullptr, *b3 = nullptr;          // [T,H], [H], [d]
   int32_t *rowidx = nullptr, *count = nullptr;
   uint16_t *Xb = nullptr, *H1 = nullptr, *H2 = nullptr;
@@ -113,8 +146,8 @@ struct MlpDenoiser final : sdden {
   int gemm_variant = 0;          // 0: kernel_pp; measurement only: 1 = kernel_hs, 2..5 = kernel_pp with pieces left out
 
   ~MlpDenoiser() override {
-    for (void* q : {static_cast<void*>(W1t), static_cast<void*>(W2t), static_cast<void*>(W3t), static_cast<void*>(tb),
-                    static_cast<void*>(b2), static_cast<void*>(b3), static_cast<void*>(rowidx), static_cast<void*>(count),
+    for (void* q : {static_cast<void*>(W1t), static_cast<void*>(W2t), static_cast<void*>(W3t), static_cast<void*>(F1),
+                    static_cast<void*>(F2), static_cast<void*>(F3), static_cast<void*>(tb), static_cast<void*>(b2), static_cast<void*>(b3), static_cast<void*>(rowidx), static_cast<void*>(count),
                     static_cast<void*>(Xb), static_cast<void*>(H1), static_cast<void*>(H2)})
       if (q) (void)hipFree(q);
   }
@@ -153,6 +186,7 @@ struct MlpDenoiser final : sdden {
       return sdi::fail(err, SD_ERR_ARG, "sdden_eval(mlp): X and out must be 16-byte aligned");
     if (Xbf16 && !sdi::aligned16(Xbf16))
       return sdi::fail(err, SD_ERR_ARG, "sdden_eval_mirror(mlp): Xbf16 must be 16-byte aligned");
+    if (few_rows(R, d, H)) return eval_few(R, X, Xbf16, krow, out, st);
     hipLaunchKernelGGL(sdrows::compact_rows_kernel, dim3(sdrows::compact_rows_grid(R)), dim3(sdrows::kScan), 0, st, krow, rowidx, count,
                        active, rows_per_chain, R, T);
     mlpgemm::Args a;
@@ -183,6 +217,32 @@ struct MlpDenoiser final : sdden {
     a.A = H2; a.Bt = W3t; a.N = d; a.Kdim = H; a.bias = b3; a.outb = nullptr; a.outf = out;
     prof.mark(3, st);
     rc = launch_gemm<3>(a, R, st, err, gemm_variant);
+    prof.mark(3, st);
+    if (rc) return rc;
+    SD_HIP_TRY(err, hipGetLastError());
+    return SD_OK;
+  }
+
+  // few_rows(R, d, H): Xb, H1 and H2 hold the rows in fragment order.
+  int eval_few(int R, const float* X, const uint16_t* Xbf16, const int32_t* krow, float* out, hipStream_t st) {
+    const int kchunk = 512;                        // 32 KiB of fp32 states per workgroup
+    hipLaunchKernelGGL(mlpfew::pack_rows_kernel, dim3((d + kchunk - 1) / kchunk, (R + 15) / 16), dim3(mlpfew::kPackThreads), 0, st, X,
+                       Xbf16, krow, active, rows_per_chain, R, T, d, kchunk, Xb, rowidx, count);
+    mlpfew::Args a;
+    a.count = count; a.rowidx = rowidx; a.krow = krow;
+    a.A = Xb; a.W = F1; a.N = H; a.K = d; a.bias = tb; a.outb = H1; a.outf = nullptr;
+    prof.mark(1, st);
+    int rc = launch_few<1>(a, R, st, err);
+    prof.mark(1, st);
+    if (rc) return rc;
+    a.A = H1; a.W = F2; a.N = H; a.K = H; a.bias = b2; a.outb = H2;
+    prof.mark(2, st);
+    rc = launch_few<2>(a, R, st, err);
+    prof.mark(2, st);
+    if (rc) return rc;
+    a.A = H2; a.W = F3; a.N = d; a.K = H; a.bias = b3; a.outb = nullptr; a.outf = out;
+    prof.mark(3, st);
+    rc = launch_few<3>(a, R, st, err);
     prof.mark(3, st);
     if (rc) return rc;
     SD_HIP_TRY(err, hipGetLastError());
@@ -250,6 +310,18 @@ extern "C" int sdden_mlp_create(int32_t d, int32_t H, int32_t E, const uint16_t*
   up(&m->W1t, w1t.data(), w1t.size() * 2);
   up(&m->W2t, w2t.data(), w2t.size() * 2);
   up(&m->W3t, w3t.data(), w3t.size() * 2);
+  auto repack = [&](uint16_t** dst, const uint16_t* W, int N, int K) {
+    if (e != hipSuccess) return;
+    e = hipMalloc(reinterpret_cast<void**>(dst), 2 * static_cast<size_t>(N) * K);
+    if (e != hipSuccess) return;
+    const int64_t chunks = static_cast<int64_t>(N) * (K / 8);
+    hipLaunchKernelGGL(mlpfew::pack_weights_kernel, dim3(static_cast<unsigned>((chunks + 255) / 256)), dim3(256), 0, nullptr, W, *dst, N, K);
+    e = hipGetLastError();
+  };
+  repack(&m->F1, m->W1t, H, d);
+  repack(&m->F2, m->W2t, H, H);
+  repack(&m->F3, m->W3t, d, H);
+  if (e == hipSuccess) e = hipStreamSynchronize(nullptr);   // callers' streams need not wait for the null stream
   up(&m->tb, tb.data(), tb.size() * 4);
   up(&m->b2, b2, static_cast<size_t>(H) * 4);
   up(&m->b3, b3, static_cast<size_t>(d) * 4);

@@ -1,0 +1,58 @@
+"""The MLP denoiser's kernels for calls of few rows: row counts at the edges of their tiles (16, 32, 64 rows) and of their
+range (1024), widths at the edges of the column rule, masked rows and a device-side chain count, against the oracle.
+
+Tolerance 2e-2 of the row's scale, as for the other MLP tests: bf16 weights and activations, fp32 sums.  Against the
+kernels for many rows the results are the same bits: every kernel sums over k in the same order."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from oracle.denoisers import MLPDenoiser
+
+from _gpu import as_f32_f64, dev, f32, host, rel_err
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d,H", [(256, 256), (3072, 512), (768, 1280)])
+def test_row_counts_at_tile_edges(d, H):
+    from paper_2501_05370_amd.binding import Denoiser
+    rng = np.random.default_rng(7)
+    T = 25
+    p = W.random_mlp(rng, d, H, 16)
+    ref = MLPDenoiser(p)
+    g = Denoiser.sdden_mlp_create(p, T, 1025)
+    x = as_f32_f64(rng.standard_normal((1025, d)))
+    k = rng.integers(-2, T + 2, size=1025).astype(np.int32)
+    k[[0, 15, 16, 31, 32, 63, 64, 1023, 1024]] = [3, -1, T, 0, T - 1, 5, -1, 2, 7]
+    live = (k >= 0) & (k < T)
+    want = np.zeros((1025, d))
+    want[live] = ref(x[live], k[live])
+    xg, kg = f32(x), dev(k, torch.int32)
+    whole = torch.full((1025, d), 777.0, dtype=torch.float32, device="cuda")
+    g.sdden_eval(1025, xg, kg, whole)                                # the tiles for many rows
+    for R in (1, 15, 16, 17, 32, 33, 64, 65, 257, 1023, 1024, 1025):
+        out = torch.full((R, d), 777.0, dtype=torch.float32, device="cuda")
+        g.sdden_eval(R, xg[:R], kg[:R], out)
+        got = host(out)
+        assert rel_err(got[live[:R]], want[:R][live[:R]]) < 2e-2, R
+        assert torch.equal(out, whole[:R]), R                        # a prediction does not depend on the call's size
+        img = xg[:R].to(torch.bfloat16).view(torch.int16).contiguous()
+        img[~dev(live[:R], torch.bool)] = 0x7fc0                     # masked rows carry NaN in the image
+        out2 = torch.full((R, d), 777.0, dtype=torch.float32, device="cuda")
+        g.sdden_eval_mirror(R, xg[:R], img, kg[:R], out2)
+        assert torch.equal(out2, out), R
+    # 7 of 20 chains of 5 rows present; every row masked
+    R = 100
+    out = torch.full((R, d), 777.0, dtype=torch.float32, device="cuda")
+    cnt = torch.tensor([7], dtype=torch.int32, device="cuda")
+    g.sdden_set_active_count(cnt, 5)
+    g.sdden_eval(R, xg[:R], kg[:R], out)
+    g.sdden_set_active_count(None, 1)
+    got, present = host(out), live[:R] & (np.arange(R) < 35)
+    assert rel_err(got[present], want[:R][present]) < 2e-2
+    assert np.all(got[~present] == 777.0)
+    out.fill_(777.0)
+    g.sdden_eval(R, xg[:R], torch.full((R,), -1, dtype=torch.int32, device="cuda"), out)
+    assert bool((out == 777.0).all())
