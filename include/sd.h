@@ -254,6 +254,16 @@ int sd_langevin_window_phi4(sd_ctx* ctx, int32_t B, const float* x, const int32_
 int sd_langevin_run(sd_ctx* ctx, int32_t B, const float* x, const int32_t* n, const int64_t* chain_id,
                     const float* means, const float* logw, float comp_std, int32_t M, float gamma,
                     int32_t max_windows, float* x_out, int32_t* n_out, int64_t* counters, void* stream);
+/* The loop of sd_langevin_window and sd_advance to its end, for every chain in one launch, where a chain has a workgroup to
+ * itself (1024 < d <= 4096): same bits, chains that reach T leave their state in out[chain_id].
+ * in : as sd_langevin_run
+ * out: out [*, d], row index = chain_id; B_active: dev int32, set to 0; counters: dev int64[5] or NULL, accumulated as in
+ *      sd_advance (windows: those of the chain that needed most).
+ * SD_ERR_UNSUPPORTED, with nothing enqueued, for other d, more than 16 components or under a device-resident count: the
+ * caller then loops over windows.  Ordering of calls on one context as for sd_langevin_window. */
+int sd_langevin_chains(sd_ctx* ctx, int32_t B, const float* x, const int32_t* n, const int64_t* chain_id,
+                       const float* means, const float* logw, float comp_std, int32_t M, float gamma,
+                       float* out, int32_t* B_active, int64_t* counters, void* stream);
 int sd_langevin_run_phi4(sd_ctx* ctx, int32_t B, const float* x, const int32_t* n,
                          const int64_t* chain_id, int32_t L, float beta, float gamma, int32_t max_windows,
                          float* x_out, int32_t* n_out, int64_t* counters, void* stream);

@@ -63,6 +63,8 @@ _SIGNATURES = {
                                    c_float, c_int32, c_float] + [c_void_p] * 6),
     "sd_langevin_window_phi4": (c_int, [c_void_p, c_int32, c_void_p, c_void_p, c_void_p, c_int32, c_float, c_float]
                                 + [c_void_p] * 6),
+    "sd_langevin_chains": (c_int, [c_void_p, c_int32, c_void_p, c_void_p, c_void_p, c_void_p, c_void_p,
+                                   c_float, c_int32, c_float, c_void_p, c_void_p, c_void_p, c_void_p]),
     "sd_langevin_run": (c_int, [c_void_p, c_int32, c_void_p, c_void_p, c_void_p, c_void_p, c_void_p,
                                 c_float, c_int32, c_float, c_int32] + [c_void_p] * 4),
     "sd_langevin_run_phi4": (c_int, [c_void_p, c_int32, c_void_p, c_void_p, c_void_p, c_int32, c_float, c_float,
@@ -292,6 +294,18 @@ class Context:
             _dev(logw, torch.float32, "logw"), comp_std, M, gamma, max_windows,
             _dev(x_out, torch.float32, "x_out"), _dev(n_out, torch.int32, "n_out"),
             _dev(counters, torch.int64, "counters", True), _stream()), "sd_langevin_run")
+
+    def sd_langevin_chains(self, B, x, n, chain_id, means, logw, comp_std, M, gamma, out, B_active, counters=None) -> bool:
+        """False when the chains have to be run window by window (nothing was enqueued then)."""
+        rc = self._lib.sd_langevin_chains(
+            self._h, B, _dev(x, torch.float32, "x"), _dev(n, torch.int32, "n"),
+            _dev(chain_id, torch.int64, "chain_id"), _dev(means, torch.float32, "means"),
+            _dev(logw, torch.float32, "logw"), comp_std, M, gamma, _dev(out, torch.float32, "out"),
+            _dev(B_active, torch.int32, "B_active"), _dev(counters, torch.int64, "counters", True), _stream())
+        if rc == SD_ERR_UNSUPPORTED:
+            return False
+        self._check(rc, "sd_langevin_chains")
+        return True
 
     def sd_langevin_run_phi4(self, B, x, n, chain_id, L, beta, gamma, max_windows, x_out, n_out, counters=None):
         self._check(self._lib.sd_langevin_run_phi4(

@@ -8,13 +8,11 @@
 //   reject:  x_out = y~_{j-1} - gamma grad E(y~_{j-1}) + sqrt(2 gamma) (z - 2 (z.Delta/|Delta|^2) Delta)
 // with E(x) = -log sum_m w_m N(x; mu_m, s^2 I), grad E = (x - sum_m r_m(x) mu_m) / s^2.
 //
-// Three kernels.  For d <= 1024 a WAVEFRONT owns a chain (langevin_window_wave_kernel, further down); for
-// larger d a workgroup does (langevin_window_kernel, next): a thread owns CPT groups of four consecutive
-// coordinates (= one Philox block each), keeps the window state, the frozen gradient and its slice of
-// the mixture means in registers, and walks the window positions in order; because the whole chain
-// lives in one workgroup the walk simply stops at the first rejection, so no work is spent on drafts
-// that would be discarded.  Per position: 16 logit partial sums and the two dot products are reduced
-// over the workgroup in fp64.  The phi^4 lattice energy has kernels of its own at the end of the file.
+// Three kernels.  For d <= 1024 a WAVEFRONT owns a chain (langevin_window_wave_kernel), for larger d a workgroup does
+// (langevin_window_kernel).  State, frozen gradient and Delta stay in registers, and because the whole chain lives in
+// one place the walk simply stops at the first rejection: no work is spent on drafts that would be discarded.  The 16
+// logits and the two dot products of a position are summed in fp64.  The phi^4 lattice energy has kernels of its own at
+// the end of the file.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -25,8 +23,7 @@
 
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int kWaves = kThreads / 64;
+constexpr int kMaxGroups = 1024;           // groups of four coordinates a chain may have
 
 struct LangevinArgs {
   const float* x;
@@ -39,7 +36,8 @@ struct LangevinArgs {
   uint8_t* rej;
   float *logratio, *logu;
   const int32_t* active;
-  int32_t* queue;       // chain dispenser of the wavefront kernel: the next chain to hand out (zeroed ahead of the launch)
+  int32_t* queue;       // [0]: the wavefront kernel's next chain to hand out; [1]: windows of the longest chain of a run to T
+                        // (each zeroed ahead of the launch that uses it)
   int max_windows;      // 1: one window per chain (sd_langevin_window); > 1: windows back to back (sd_langevin_run)
   int32_t* n_out;       // run mode: the step each chain reached
   unsigned long long* counters;   // run mode, optional: sum adv, chain-windows, rejections, launches, sum Kt
@@ -62,171 +60,6 @@ __device__ __forceinline__ double dpp_xor(double v, int mask) {
   }
 }
 
-// CPT: float4 groups per thread; MMAX: compile-time bound on the number of components.
-template <int CPT, int MMAX>
-__global__ __launch_bounds__(kThreads) void langevin_window_kernel(LangevinArgs p) {
-  __shared__ double sh_part[kWaves][MMAX + 2];
-  __shared__ double sh_r[MMAX];
-
-  const int b = blockIdx.x;
-  const int Bact = p.active ? min(p.B, max(0, *p.active)) : p.B;
-  if (b >= Bact) return;                       // uniform over the workgroup
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int n = p.n[b];
-  const int Kt = max(0, min(p.K, p.T - n));
-  const int64_t id = p.id[b];
-  const int d = p.d, M = p.M;
-  const double gamma = p.gamma, inv_s2 = p.inv_s2;
-  const double sq2g = sqrt(2.0 * gamma), sqg2 = sqrt(0.5 * gamma);
-
-  // ---- my coordinates, my slice of the means
-  bool own[CPT][4];
-  double cur[CPT][4];          // y~_{j-1}: the state the target gradient is evaluated at
-  float mu[CPT][MMAX][4];
-#pragma unroll
-  for (int c = 0; c < CPT; ++c) {
-    const int i0 = 4 * (t + kThreads * c);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      own[c][e] = i0 + e < d;
-      cur[c][e] = own[c][e] ? static_cast<double>(p.x[static_cast<int64_t>(b) * d + i0 + e]) : 0.0;
-#pragma unroll
-      for (int m = 0; m < MMAX; ++m)
-        mu[c][m][e] = (own[c][e] && m < M) ? p.means[static_cast<int64_t>(m) * d + i0 + e] : 0.f;
-    }
-  }
-
-  // grad E at `cur` for my coordinates.  Uniform control flow: called by every thread.
-  auto gradient = [&](double g[CPT][4]) {
-    double q[MMAX];
-#pragma unroll
-    for (int m = 0; m < MMAX; ++m) {
-      double acc = 0.0;
-#pragma unroll
-      for (int c = 0; c < CPT; ++c)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const double df = cur[c][e] - static_cast<double>(mu[c][m][e]);
-          acc = fma(df, df, acc);              // unowned coordinates contribute 0 - 0
-        }
-      q[m] = wave_sum(acc);
-    }
-    __syncthreads();                           // previous readers of sh_part / sh_r are done
-    if (lane == 0) {
-#pragma unroll
-      for (int m = 0; m < MMAX; ++m) sh_part[wave][m] = q[m];
-    }
-    __syncthreads();
-    if (t < 64) {                              // first wavefront: softmax over the components
-      double logit = -INFINITY;
-      if (t < M) {
-        double tot = 0.0;
-#pragma unroll
-        for (int w = 0; w < kWaves; ++w) tot += sh_part[w][t];
-        logit = static_cast<double>(p.logw[t]) - 0.5 * tot * inv_s2;
-      }
-      double mx = logit;
-#pragma unroll
-      for (int s = 32; s >= 1; s >>= 1) mx = fmax(mx, dpp_xor(mx, s));
-      const double ex = t < M ? exp(logit - mx) : 0.0;
-      const double sum = wave_sum(ex);
-      if (t < M) sh_r[t] = ex / sum;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int c = 0; c < CPT; ++c)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        double bar = 0.0;
-#pragma unroll
-        for (int m = 0; m < MMAX; ++m)
-          if (m < M) bar = fma(sh_r[m], static_cast<double>(mu[c][m][e]), bar);
-        g[c][e] = (cur[c][e] - bar) * inv_s2;
-      }
-  };
-
-  double g0[CPT][4];
-  gradient(g0);
-
-  int jr = -1;
-  double coef = 0.0;
-  double gj[CPT][4];
-  float z[CPT][4];
-  double dl[CPT][4];
-  for (int j = 0; j < Kt; ++j) {               // tests state n+j+1; Kt is uniform over the workgroup
-    const uint32_t k1 = static_cast<uint32_t>(n + j + 1);
-#pragma unroll
-    for (int c = 0; c < CPT; ++c)
-      sdrng::normal4(p.seed, id, k1, sdrng::kStreamNoise, static_cast<uint32_t>(t + kThreads * c), z[c]);
-    double lr = 0.0, lu = 0.0;
-    bool reject = false;
-    if (j > 0) {                               // position 1: the target gradient IS g0, Delta = 0
-      gradient(gj);
-      double a1 = 0.0, a2 = 0.0;
-#pragma unroll
-      for (int c = 0; c < CPT; ++c)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          dl[c][e] = own[c][e] ? sqg2 * (gj[c][e] - g0[c][e]) : 0.0;
-          a1 = fma(static_cast<double>(z[c][e]), dl[c][e], a1);
-          a2 = fma(dl[c][e], dl[c][e], a2);
-        }
-      a1 = wave_sum(a1);
-      a2 = wave_sum(a2);
-      __syncthreads();
-      if (lane == 0) { sh_part[wave][MMAX] = a1; sh_part[wave][MMAX + 1] = a2; }
-      __syncthreads();
-      double S1 = 0.0, S2 = 0.0;
-#pragma unroll
-      for (int w = 0; w < kWaves; ++w) { S1 += sh_part[w][MMAX]; S2 += sh_part[w][MMAX + 1]; }
-      lr = (-S1 - 0.5 * S2) * p.inv_tau;
-      lu = sdrng::log_uniform(p.seed, id, k1);
-      reject = !(S2 == 0.0 || (lr == lr && lu <= fmin(0.0, lr)));   // a log-ratio that is not a number rejects
-      coef = S2 > 0.0 ? S1 / S2 : 0.0;
-    } else {
-      lu = sdrng::log_uniform(p.seed, id, k1);
-    }
-    if (t == 0) {
-      if (p.logratio) p.logratio[static_cast<int64_t>(b) * p.K + j] = static_cast<float>(lr);
-      if (p.logu) p.logu[static_cast<int64_t>(b) * p.K + j] = static_cast<float>(lu);
-    }
-    if (reject) {                              // every thread holds the same totals: uniform branch
-      jr = j;
-#pragma unroll
-      for (int c = 0; c < CPT; ++c)
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (own[c][e])
-            cur[c][e] = cur[c][e] - gamma * gj[c][e] +
-                        sq2g * (static_cast<double>(z[c][e]) - 2.0 * coef * dl[c][e]);
-      break;
-    }
-#pragma unroll
-    for (int c = 0; c < CPT; ++c)
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (own[c][e])                         // unowned slots stay 0 so they never reach a sum
-          cur[c][e] = cur[c][e] - gamma * g0[c][e] + sq2g * static_cast<double>(z[c][e]);
-  }
-
-  if (t == 0) {
-    p.adv[b] = jr >= 0 ? jr + 1 : Kt;
-    if (p.rej) p.rej[b] = jr >= 0 ? 1 : 0;
-    const int jdone = jr >= 0 ? jr + 1 : Kt;   // positions not reached report 0
-    for (int j = jdone; j < p.K; ++j) {
-      if (p.logratio) p.logratio[static_cast<int64_t>(b) * p.K + j] = 0.f;
-      if (p.logu) p.logu[static_cast<int64_t>(b) * p.K + j] = 0.f;
-    }
-  }
-#pragma unroll
-  for (int c = 0; c < CPT; ++c) {
-    const int i0 = 4 * (t + kThreads * c);
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (own[c][e]) p.x_out[static_cast<int64_t>(b) * d + i0 + e] = static_cast<float>(cur[c][e]);
-  }
-}
-
 // ---------------------------------------------------------------------------------------------
 // One WAVEFRONT per chain (d <= 1024 * CPT/4): no workgroup barrier on the walk at all.
 // A lane owns CPT groups of four coordinates; the mixture means sit in LDS as fp64, once per workgroup
@@ -241,12 +74,9 @@ __global__ __launch_bounds__(kThreads) void langevin_window_kernel(LangevinArgs 
 constexpr int kWaveChains = 8;             // chains (wavefronts) per workgroup: one workgroup fills a CU at 2 per SIMD
 constexpr int kWaveM = 16;                 // components handled by the transposed reduction
 
-
-// in: 16 per-lane partial sums; out: total of value ((lane >> 2) & 15), on every lane
-__device__ __forceinline__ double reduce16_transposed(double (&a)[16], int lane) {
-  (void)lane;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) a[i] = sdlane::halving_add<32>(a[i], a[i + 8]);
+// the steps of reduce16_transposed after the first
+template <int N>
+__device__ __forceinline__ double reduce8_transposed(double (&a)[N]) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) a[i] = sdlane::halving_add<16>(a[i], a[i + 4]);
 #pragma unroll
@@ -257,11 +87,216 @@ __device__ __forceinline__ double reduce16_transposed(double (&a)[16], int lane)
   return a[0];
 }
 
+// in: 16 per-lane partial sums; out: total of value ((lane >> 2) & 15), on every lane
+__device__ __forceinline__ double reduce16_transposed(double (&a)[16], int lane) {
+  (void)lane;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) a[i] = sdlane::halving_add<32>(a[i], a[i + 8]);
+  return reduce8_transposed(a);
+}
+
 __device__ __forceinline__ double readlane_f64(double v, int src_lane) {
   const long long bits = __double_as_longlong(v);
   const int lo = __builtin_amdgcn_readlane(static_cast<int>(bits), src_lane);
   const int hi = __builtin_amdgcn_readlane(static_cast<int>(bits >> 32), src_lane);
   return __longlong_as_double((static_cast<long long>(hi) << 32) | static_cast<unsigned int>(lo));
+}
+
+// d > 1024: a workgroup per chain, a thread per group of four coordinates (= one Philox block), up to 1024 threads.
+// What bounds it is one chain's walk, a serial chain of gradients: every chain has its own CU (and at 1024 threads
+// the whole of it), so what counts is the time from one gradient to the next.  Hence one group per thread -- its
+// slice of the 16 means is 64 registers; with four groups per thread of a 256-thread workgroup it was 256 and lived
+// in scratch memory -- and two workgroup barriers per position instead of five: every wavefront adds the partial sums
+// of all and runs the softmax itself, the responsibilities never leave scalar registers, and the partial sums
+// alternate between two buffers.  The position's noise is drawn while the partial sums settle, the window's uniforms
+// once, one position per lane.  200 chains, K = 8, in us a window (before: 256 threads x up to 4 groups): d = 1100 33 (55),
+// d = 2500 44 (458), d = 4000 69 (441).
+// MAXT: bound on the workgroup's threads (512, 768 or 1024: 256, 168 or 128 registers per thread).
+// RUN: the chain's windows follow each other inside the kernel, what sd_advance does to the chain between two of them
+// included (the state passes through fp32, so the bits are those of separate calls).  60 steps of those chains: 0.26,
+// 0.34 and 0.59 ms, against 0.86, 1.19 and 1.85 with a launch, a compaction and its share of a readback per window.
+template <int MAXT, bool RUN>
+__global__ __launch_bounds__(MAXT) void langevin_window_kernel(LangevinArgs p) {
+  constexpr int MC = 16, NWMAX = MAXT / 64;
+  __shared__ double sh_part[2][NWMAX][MC];
+  __shared__ double2 sh_s[NWMAX];
+
+  const int b = blockIdx.x;
+  const int Bact = p.active ? min(p.B, max(0, *p.active)) : p.B;
+  if (b >= Bact) return;                       // uniform over the workgroup
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  int n = p.n[b];
+  int Kt = max(0, min(p.K, p.T - n));
+  const int64_t id = p.id[b];
+  const int d = p.d, M = p.M;
+  const double gamma = p.gamma, inv_s2 = p.inv_s2;
+  const double sq2g = sqrt(2.0 * gamma), sqg2 = sqrt(0.5 * gamma);
+  const int my_m = lane >> 2;                  // component whose totals this lane holds after a reduction
+  const double my_logw = my_m < M ? static_cast<double>(p.logw[my_m]) : 0.0;
+
+  // the sums over wavefronts run over all NWMAX slots, unrolled: the slots of wavefronts the launch does not have hold 0
+  for (int q = t; q < 2 * NWMAX * MC; q += blockDim.x) (&sh_part[0][0][0])[q] = 0.0;
+  if (t < NWMAX) sh_s[t] = make_double2(0.0, 0.0);
+  __syncthreads();
+
+  // ---- my coordinates, my slice of the means (0 beyond M and d)
+  bool own[4];
+  double cur[4];                               // y~_{j-1}: the state the target gradient is evaluated at
+  float mu[MC][4];
+  const int i0 = 4 * t;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    own[e] = i0 + e < d;
+    cur[e] = own[e] ? static_cast<double>(p.x[static_cast<int64_t>(b) * d + i0 + e]) : 0.0;
+#pragma unroll
+    for (int m = 0; m < MC; ++m) mu[m][e] = (own[e] && m < M) ? p.means[static_cast<int64_t>(m) * d + i0 + e] : 0.f;
+  }
+
+  // grad E at `cur` for my coordinates, in two parts so that the caller can put work between them.  Uniform control
+  // flow: called by every thread.  A buffer is written again two gradients later, past the barrier of the next one.
+  int buf = 0;
+  auto gradient_begin = [&]() {
+    auto dist2 = [&](int m) {
+      double q = 0.0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        asm volatile("" : "+v"(mu[m][e]));     // keeps the compiler from holding 64 converted copies across the walk
+        const double df = cur[e] - static_cast<double>(mu[m][e]);
+        q = fma(df, df, q);                    // unowned coordinates contribute 0 - 0
+      }
+      return q;
+    };
+    double q[MC / 2];                          // the first halving step as the sums come, to keep half of them
+#pragma unroll
+    for (int m = 0; m < MC / 2; ++m) {
+      const double lower = dist2(m), upper = dist2(m + MC / 2);
+      q[m] = sdlane::halving_add<32>(lower, upper);
+    }
+    const double tot = reduce8_transposed(q);
+    if ((lane & 3) == 0) sh_part[buf][wave][my_m] = tot;
+  };
+  auto gradient_end = [&](double g[4]) {
+    __syncthreads();
+    double tot = 0.0;
+#pragma unroll
+    for (int w = 0; w < NWMAX; ++w) tot += sh_part[buf][w][my_m];
+    buf ^= 1;
+    const double logit = my_m < M ? my_logw - 0.5 * tot * inv_s2 : -INFINITY;
+    double mx = logit;
+#pragma unroll
+    for (int s = 4; s <= 32; s <<= 1) mx = fmax(mx, dpp_xor(mx, s));
+    const double ex = my_m < M ? exp(logit - mx) : 0.0;
+    double sum = ex;
+#pragma unroll
+    for (int s = 4; s <= 32; s <<= 1) sum += dpp_xor(sum, s);
+    const double r_mine = ex / sum;
+    double bar[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int m = 0; m < MC; ++m) {
+      const double r = readlane_f64(r_mine, 4 * m);        // uniform: lives in scalar registers
+      if (r < 1e-25) continue;                 // moves nothing by more than 1e-25 |mu| (see the wavefront kernel)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        asm volatile("" : "+v"(mu[m][e]));
+        bar[e] = fma(r, static_cast<double>(mu[m][e]), bar[e]);
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) g[e] = (cur[e] - bar[e]) * inv_s2;
+  };
+
+  int jr = -1;
+  unsigned long long acc_adv = 0, acc_win = 0, acc_rej = 0, acc_kt = 0;
+  do {                                         // the windows (RUN), each of which advances the chain; Kt is uniform
+  if (RUN && Kt == 0) break;                   // a chain handed over at step T: no window
+  double g0[4];
+  gradient_begin();
+  // log u of the window's positions: lane j of every wavefront draws position j + 1 (the window has at most 64)
+  const double lu_mine = lane < Kt ? sdrng::log_uniform(p.seed, id, static_cast<uint32_t>(n + lane + 1)) : 0.0;
+  gradient_end(g0);
+
+  jr = -1;
+  double coef = 0.0;
+  double gj[4], dl[4];
+  float z[4];
+  for (int j = 0; j < Kt; ++j) {               // tests state n+j+1; Kt is uniform over the workgroup
+    if (j > 0) gradient_begin();               // position 1: the target gradient IS g0, Delta = 0
+    sdrng::normal4(p.seed, id, static_cast<uint32_t>(n + j + 1), sdrng::kStreamNoise, static_cast<uint32_t>(t), z);
+    const double lu = readlane_f64(lu_mine, j);
+    double lr = 0.0;
+    bool reject = false;
+    if (j > 0) {
+      gradient_end(gj);
+      double a1 = 0.0, a2 = 0.0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        dl[e] = own[e] ? sqg2 * (gj[e] - g0[e]) : 0.0;
+        a1 = fma(static_cast<double>(z[e]), dl[e], a1);
+        a2 = fma(dl[e], dl[e], a2);
+      }
+      a1 = wave_sum(a1);
+      a2 = wave_sum(a2);
+      if (lane == 0) sh_s[wave] = make_double2(a1, a2);    // last read ahead of this position's first barrier
+      __syncthreads();
+      double S1 = 0.0, S2 = 0.0;
+#pragma unroll
+      for (int w = 0; w < NWMAX; ++w) { S1 += sh_s[w].x; S2 += sh_s[w].y; }
+      lr = (-S1 - 0.5 * S2) * p.inv_tau;
+      reject = !(S2 == 0.0 || (lr == lr && lu <= fmin(0.0, lr)));   // a log-ratio that is not a number rejects
+      coef = S2 > 0.0 ? S1 / S2 : 0.0;
+    }
+    if (t == 0) {
+      if (p.logratio) p.logratio[static_cast<int64_t>(b) * p.K + j] = static_cast<float>(lr);
+      if (p.logu) p.logu[static_cast<int64_t>(b) * p.K + j] = static_cast<float>(lu);
+    }
+    if (reject) {                              // every thread holds the same totals: uniform branch
+      jr = j;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (own[e]) cur[e] = cur[e] - gamma * gj[e] + sq2g * (static_cast<double>(z[e]) - 2.0 * coef * dl[e]);
+      break;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (own[e])                              // unowned slots stay 0 so they never reach a sum
+        cur[e] = cur[e] - gamma * g0[e] + sq2g * static_cast<double>(z[e]);
+  }
+
+  if (RUN) {
+    const int jdone = jr >= 0 ? jr + 1 : Kt;
+    n += jdone;
+    acc_adv += jdone; acc_win += 1; acc_rej += jr >= 0 ? 1 : 0; acc_kt += Kt;
+    Kt = max(0, min(p.K, p.T - n));
+#pragma unroll
+    for (int e = 0; e < 4; ++e) cur[e] = static_cast<double>(static_cast<float>(cur[e]));
+  }
+  } while (RUN && Kt > 0);
+
+  if (RUN) {
+    if (t == 0 && acc_win) {
+      if (p.counters) {
+        atomicAdd(&p.counters[0], acc_adv);
+        atomicAdd(&p.counters[1], acc_win);
+        atomicAdd(&p.counters[2], acc_rej);
+        atomicAdd(&p.counters[4], acc_kt);
+      }
+      atomicMax(&p.queue[1], static_cast<int32_t>(acc_win));
+    }
+    if (acc_win == 0) return;
+  } else if (t == 0) {
+    p.adv[b] = jr >= 0 ? jr + 1 : Kt;
+    if (p.rej) p.rej[b] = jr >= 0 ? 1 : 0;
+    const int jdone = jr >= 0 ? jr + 1 : Kt;   // positions not reached report 0
+    for (int j = jdone; j < p.K; ++j) {
+      if (p.logratio) p.logratio[static_cast<int64_t>(b) * p.K + j] = 0.f;
+      if (p.logu) p.logu[static_cast<int64_t>(b) * p.K + j] = 0.f;
+    }
+  }
+  const int64_t row = RUN ? id : b;            // sd_advance leaves a finished chain's state at its id
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    if (own[e]) p.x_out[row * d + i0 + e] = static_cast<float>(cur[e]);
 }
 
 // WHOLE: d is a multiple of 4, so a group of four coordinates is inside d or outside it as a whole (one mask
@@ -511,7 +546,22 @@ __global__ __launch_bounds__(64 * kWaveChains, 2) void langevin_window_wave_kern
 // The chain dispenser starts every launch at zero: a one-thread kernel ahead of the launch (a kernel, not a
 // memset, so that the sequence can be captured in a HIP graph), never a rewind at the end of the previous one --
 // a launch that does not run to its end must not leave the next call without chains.
-__global__ void reset_dispenser_kernel(int32_t* queue) { queue[0] = 0; }
+__global__ void reset_queue_kernel(int32_t* queue, int slot) { queue[slot] = 0; }
+
+// run to T: a batch stepped window by window makes as many windows as its longest chain, and ends with none active
+__global__ void chains_end_kernel(const int32_t* longest, unsigned long long* counters, int32_t* B_active) {
+  if (counters) counters[3] += static_cast<unsigned long long>(*longest);
+  *B_active = 0;
+}
+
+// The workgroup-per-chain kernel at the thread count of the row length.
+template <bool RUN>
+void launch_wide(const LangevinArgs& p, int groups, hipStream_t st) {
+  const dim3 grid(static_cast<unsigned>(p.B)), block(static_cast<unsigned>((groups + 63) / 64 * 64));
+  if (block.x <= 512) hipLaunchKernelGGL((langevin_window_kernel<512, RUN>), grid, block, 0, st, p);
+  else if (block.x <= 768) hipLaunchKernelGGL((langevin_window_kernel<768, RUN>), grid, block, 0, st, p);
+  else hipLaunchKernelGGL((langevin_window_kernel<1024, RUN>), grid, block, 0, st, p);
+}
 
 // run mode: one launch counts as one entry of the `windows` counter
 __global__ void bump_launches_kernel(unsigned long long* counters) { counters[3] += 1; }
@@ -529,7 +579,7 @@ hipError_t launch_wave(const LangevinArgs& p, int dpad, int resident, hipStream_
   const size_t shmem = sizeof(double) * kWaveM * static_cast<size_t>(256 * CPT);
   const int groups = (p.B + kWaveChains - 1) / kWaveChains;
   const unsigned grid = static_cast<unsigned>(groups < resident ? groups : resident);
-  hipLaunchKernelGGL(reset_dispenser_kernel, dim3(1), dim3(1), 0, st, p.queue);
+  hipLaunchKernelGGL(reset_queue_kernel, dim3(1), dim3(1), 0, st, p.queue, 0);
   hipLaunchKernelGGL((langevin_window_wave_kernel<CPT, WHOLE, RUN>), dim3(grid), dim3(64 * kWaveChains), shmem, st, p, dpad);
   return hipGetLastError();
 }
@@ -885,10 +935,9 @@ int langevin_launch(const char* who, sd_ctx* ctx, int32_t B, const float* x, con
   if (M > 16)
     return sdi::fail(ctx->err, SD_ERR_UNSUPPORTED, "%s: at most 16 mixture components (M=%d)", who, M);
   const int groups = (ctx->d + 3) / 4;
-  const int cpt = (groups + kThreads - 1) / kThreads;
-  if (cpt > 4)
+  if (groups > kMaxGroups)
     return sdi::fail(ctx->err, SD_ERR_UNSUPPORTED, "%s: d=%d exceeds the register-resident limit of %d", who,
-                     ctx->d, 4 * 4 * kThreads);
+                     ctx->d, 4 * kMaxGroups);
   LangevinArgs p;
   p.x = x; p.n = n; p.id = chain_id; p.means = means; p.logw = logw; p.x_out = x_out; p.adv = adv;
   p.rej = rejected; p.logratio = logratio; p.logu = logu; p.active = ctx->active; p.queue = ctx->dev_queue;
@@ -925,12 +974,7 @@ int langevin_launch(const char* who, sd_ctx* ctx, int32_t B, const float* x, con
   }
   if (max_windows > 1)
     return sdi::fail(ctx->err, SD_ERR_UNSUPPORTED, "%s: d=%d is above the 1024 the back-to-back form serves", who, ctx->d);
-  const dim3 grid(static_cast<unsigned>(B)), block(kThreads);
-  switch (cpt) {
-    case 1: hipLaunchKernelGGL((langevin_window_kernel<1, 16>), grid, block, 0, st, p); break;
-    case 2: hipLaunchKernelGGL((langevin_window_kernel<2, 16>), grid, block, 0, st, p); break;
-    default: hipLaunchKernelGGL((langevin_window_kernel<4, 16>), grid, block, 0, st, p); break;
-  }
+  launch_wide<false>(p, groups, st);
   SD_HIP_TRY(ctx->err, hipGetLastError());
   return SD_OK;
 }
@@ -960,6 +1004,31 @@ extern "C" int sd_langevin_run(sd_ctx* ctx, int32_t B, const float* x, const int
   if (B == 0) return SD_OK;
   return langevin_launch("sd_langevin_run", ctx, B, x, n, chain_id, means, logw, comp_std, M, gamma, x_out, nullptr,
                          nullptr, nullptr, nullptr, max_windows, n_out, counters, stream);
+}
+
+extern "C" int sd_langevin_chains(sd_ctx* ctx, int32_t B, const float* x, const int32_t* n, const int64_t* chain_id,
+                                  const float* means, const float* logw, float comp_std, int32_t M, float gamma,
+                                  float* out, int32_t* B_active, int64_t* counters, void* stream) {
+  if (!ctx) return SD_ERR_ARG;
+  if (B < 0 || M <= 0 || !(comp_std > 0.f) || !(gamma > 0.f) ||
+      (B > 0 && (!x || !n || !chain_id || !means || !logw || !out || !B_active)))
+    return sdi::fail(ctx->err, SD_ERR_ARG, "sd_langevin_chains: bad argument");
+  const int groups = (ctx->d + 3) / 4;
+  if (M > 16 || ctx->d <= 1024 || groups > kMaxGroups || ctx->active)
+    return sdi::fail(ctx->err, SD_ERR_UNSUPPORTED, "sd_langevin_chains: 1024 < d <= %d, at most 16 components, no device-side count",
+                     4 * kMaxGroups);
+  if (B == 0) return SD_OK;
+  LangevinArgs p{};
+  p.x = x; p.n = n; p.id = chain_id; p.means = means; p.logw = logw; p.x_out = out; p.queue = ctx->dev_queue;
+  p.B = B; p.d = ctx->d; p.K = ctx->K; p.T = ctx->T; p.M = M; p.seed = ctx->seed;
+  p.gamma = gamma; p.inv_s2 = 1.0 / (static_cast<double>(comp_std) * comp_std); p.inv_tau = 1.0 / ctx->tau;
+  p.counters = reinterpret_cast<unsigned long long*>(counters);
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  hipLaunchKernelGGL(reset_queue_kernel, dim3(1), dim3(1), 0, st, p.queue, 1);
+  launch_wide<true>(p, groups, st);
+  hipLaunchKernelGGL(chains_end_kernel, dim3(1), dim3(1), 0, st, p.queue + 1, p.counters, B_active);
+  SD_HIP_TRY(ctx->err, hipGetLastError());
+  return SD_OK;
 }
 
 extern "C" int sd_langevin_window_phi4(sd_ctx* ctx, int32_t B, const float* x, const int32_t* n,

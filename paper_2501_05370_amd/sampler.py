@@ -316,6 +316,11 @@ class LangevinSampler(_SamplerBase):
         self.comp_std, self.gamma, self.M = comp_std, gamma, means.shape[0]
         self._setup(ctx, B, out_rows, False)
 
+    def _run_chains(self, B: int) -> bool:
+        b = self.buf
+        return self.ctx.sd_langevin_chains(B, b.y, b.n, b.chain_id, self.means, self.logw, self.comp_std, self.M,
+                                           self.gamma, b.out, b.B_active, b.counters)
+
     def window(self, B: int, logratio=None, logu=None):
         b = self.buf
         with self.timer.stage("langevin_window", B):
