@@ -6,7 +6,7 @@
  * plain definition; each maps rows X [R,d] with a per-row chain step krow [R] to out [R,d]:
  *
  *   gmm      E[x0 | x_t] of a diagonal-covariance Gaussian mixture (Bayes' rule over components)
- *   lowrank  E[x0 | x_t] of N(mu, U U^T + s2 I): two skinny fp32 MFMA GEMMs in the eigenbasis of
+ *   lowrank  E[x0 | x_t] of N(mu, U U^T + s2 I): two skinny fp32 GEMMs in the eigenbasis of
  *            U U^T with a per-row diagonal gain in between
  *   mlp      3-layer SiLU MLP on [x ; sinusoidal(k)], bf16 weights, fp32 accumulation (bf16 MFMA)
  *

@@ -1,38 +1,41 @@
-// fp32 x fp32 -> fp32 GEMM on the gfx950 matrix cores for the two skinny products of the low-rank
-// Gaussian denoiser:  C[M,N] = A[M,K] * Bt[N,K]^T, both operands K-contiguous, rows of A optionally
-// gathered through an index.
+// The two skinny products of the low-rank Gaussian denoiser, fp32 in and out, on the bf16 matrix instructions:
+// C[M,N] = A[M,K] * Bt[N,K]^T with every fp32 operand as the sum of three bf16 pieces.
 //
-// Same skeleton as the bf16 MLP GEMM: BM x BN x 32 workgroup tile, WM x WN wavefronts of 32x32
-// v_mfma_f32_32x32x2f32 accumulators, K-slices of 32 floats (128 B per row) loaded from global memory
-// straight into LDS (a wavefront load fills 8 rows, lane l landing at byte 16*l, the lane fetching
-// chunk (l%8) ^ ((row >> 1) & 7) of its row so that fragment reads are bank-conflict free on the 64-bank
-// LDS: see the bf16 GEMM), an NS-stage LDS
-// ring with a workgroup barrier that leaves loads in flight.
-// Fragments: a lane reads one 16-byte chunk = 4 consecutive k of its row and feeds 4 MFMAs; the two
-// lane halves of an MFMA (k index 0 / 1 of the instruction) read chunks 2m / 2m+1, i.e. MFMA e of
-// step m contracts k = 8m+e and k = 8m+4+e.  Both operands use the same pairing, so the sum over the
-// slice is the plain dot product.
-// An MFMA of this shape runs 64 cycles for 4096 flop, so LDS and global traffic are far from
-// binding; what matters is that every SIMD always has a wavefront with MFMAs to issue.  The first
-// product (N = rank, long K) has few output tiles: its K range is split over gridDim.y and the
-// partial sums go to separate slabs that a second small kernel adds in a fixed order (no atomics:
-// results do not depend on scheduling).
-// The Bt fragment is the FIRST MFMA operand: the accumulator tile is then C^T, a lane owns one row m of C and,
-// per 32x32 tile, four runs of 4 consecutive columns, so everything the epilogues move (partial slabs, the X
-// tile, the output) goes as 16-byte accesses, 16 per thread instead of 64 four-byte ones.  The second product
-// has K = rank: its K loop is as short as its prologue and epilogue, and those are what its speed hangs on.
+// Why split.  The fp32 MFMA runs at a sixteenth of the bf16 rate and was what both products hung on (0.65 of its
+// 157 TFLOP/s).  24 bits of mantissa are three pieces of 8, x = x0 + x1 + x2 exactly (truncation) or to 2^-25 (rounding);
+// the six products of order 2^0, 2^-8 and 2^-16 keep everything above 2^-24 of a term, go through v_mfma_f32_16x16x32_bf16
+// with fp32 accumulation, small ones first, and cost 6/16 of the fp32 instruction's time.  Error against fp64 sums
+// (N(0.3, 1) times N(0, 1/K), relative 2-norm, the same K ranges): K = 256 2.3e-7 (fp32 MFMA 2.9e-7), K = 768 4.2e-7
+// (5.0e-7), K = 3072 8.6e-7 (9.8e-7): fewer roundings per term, so slightly closer than the fp32 instruction.
+// Truncation cannot overflow; an infinite or NaN input makes its own row NaN (as inf * q of both signs did).
+//
+// Layout.  16 rows x 32 k of a split operand are one block: three pieces of 1 KiB in which lane (l16, lq) of a wavefront
+// finds its 16 bytes (row l16, k = 8 lq .. 8 lq + 7) at 16 * lane; the blocks of 16 rows follow each other along k.  A
+// direct load into LDS is then eight whole cache lines and a fragment read is conflict free.  The weights are kept so
+// from the denoiser's creation, the second product's A is written so by reduce_gain_kernel; the first product's A are
+// gathered fp32 rows (8 rows of 128 B per load, chunk c of a row at c ^ ((row >> 1) & 7): conflict free on 64 banks),
+// split in registers.
+//
+// Order of sums.  An output is one chain of MFMAs over its K range, the same whatever the tile, and the ranges of the
+// first product (fixed per denoiser) go to slabs that reduce_gain_kernel adds in order: a prediction has the same bits
+// however many rows a call has, and tiles can be chosen by size alone.
 #pragma once
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
 
+#include "sdden_internal.h"
+
 namespace lrgemm {
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int BK = 32;
+constexpr int kBlockBytes = 3072;      // 16 rows x 32 k, three pieces
+constexpr int kRowTile = 128;          // split operands are allocated for whole tiles of the largest height
+constexpr int kRankRows = 512;         // calls of up to this many rows are compacted by the first product itself
 
 struct __attribute__((aligned(16))) RowInfo {
   int32_t src;
@@ -41,250 +44,318 @@ struct __attribute__((aligned(16))) RowInfo {
 };
 
 struct Args {
-  const float* A;          // rows of lda floats; tile row r reads row arow[r] (or r when arow is null)
-  const int32_t* arow;
-  int64_t lda;
-  const float* Bt;         // [N, ldb]
-  int64_t ldb;
-  int N, Kdim;             // Kdim: the whole contraction length (multiple of 32 * gridDim.y)
-  const int32_t* count;    // device: M
-  // stage 1: partial sums, slab s = part + s * slab_stride, dense rows of N floats
+  // STAGE 1: fp32 rows of `d` floats, tile row r reads row rowidx[r]; STAGE 2: split blocks
+  const void* A;
+  int d;
+  const unsigned char* Bt;  // split blocks, ceil(N / 16) x nk
+  int N, nk;                // output columns, slices of 32 of the whole contraction
+  int32_t* count;           // device: M
+  int32_t* rowidx;
+  // STAGE 1 with RANK: the compaction (rows r < active rows with 0 <= krow[r] < T, in order) is done here and left in
+  // rowidx / count
+  const int32_t* krow;
+  const int32_t* active;
+  int rows_per_chain, R, T;
+  // STAGE 1: partial sums, slab s = part + s * slab_stride, dense rows of N floats
   float* part;
   int64_t slab_stride;
-  // stage 2 epilogue: out[src] = acc + gp X[src] + cf mu with (src, gp, cf) = rowinfo[gm], which
-  // reduce_gain_kernel fills: src = rowidx[gm], gp = gperp[krow[src]], cf = coef[krow[src]]
+  // STAGE 2 epilogue: out[src] = acc + gp X[src] + cf mu with (src, gp, cf) = rowinfo[row]
   const RowInfo* rowinfo;
   const float* X;
   float* out;
+  int out_aligned;          // 16-byte stores into out
   const float* mu;
 };
 
+// byte offset of (row, k .. k + 7) of piece 0 in split blocks of nk slices; the pieces are 1024 apart
+__host__ __device__ __forceinline__ size_t block_offset(int row, int k, int nk) {
+  return (static_cast<size_t>(row >> 4) * nk + (k >> 5)) * kBlockBytes + (((k & 31) >> 3) * 16 + (row & 15)) * 16;
+}
+
+// Eight floats -> three vectors of eight bf16 whose sum is exact: each piece is the upper half of what is left.
+__device__ __forceinline__ void split8(const float (&x)[8], u32x4 (&piece)[3]) {
+#pragma unroll
+  for (int h = 0; h < 4; ++h) {
+    uint32_t u[2][3];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      float v = x[2 * h + e];
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        u[e][q] = __builtin_bit_cast(uint32_t, v);
+        v -= __builtin_bit_cast(float, u[e][q] & 0xffff0000u);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) piece[q][h] = __builtin_amdgcn_perm(u[1][q], u[0][q], 0x07060302u);
+  }
+}
+
+// waits until at most N of this wavefront's vector-memory loads are outstanding (they complete in order)
 template <int N>
 __device__ __forceinline__ void wait_loads() {
-  static_assert(N == 0 || N == 4 || N == 8 || N == 16, "add the count");
-  if constexpr (N == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  if constexpr (N == 4) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-  if constexpr (N == 8) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-  if constexpr (N == 16) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+  static_assert(N >= 0 && N < 64, "vmcnt is six bits");
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+template <int OPS, int LEFT>
+__device__ __forceinline__ void wait_stages(int left) {      // at most `left` (<= LEFT) stages outstanding
+  if constexpr (LEFT == 0) wait_loads<0>();
+  else {
+    if (left >= LEFT) wait_loads<LEFT * OPS>();
+    else wait_stages<OPS, LEFT - 1>(left);
+  }
 }
 
 __device__ __forceinline__ void barrier_keep_loads() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-template <int BM, int BN, int WM, int WN, int STAGE, int NS>
-__global__ __launch_bounds__(64 * WM * WN) void kernel(Args p) {
-  constexpr int NW = WM * WN;
-  constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
-  constexpr int APASS = BM / 8 / NW, BPASS = BN / 8 / NW;
-  static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "row groups must divide evenly");
-  static_assert(NW % 2 == 0, "the chunk permutation takes the parity of a row group from the wavefront index");
-  extern __shared__ __align__(1024) unsigned char smem[];
-  unsigned char* As = smem;                                  // [NS][BM][128 B]
-  unsigned char* Bs = smem + NS * BM * 128;                  // [NS][BN][128 B]
+template <int WM, int WN, int TM, int TN, int NS, int STAGE>
+struct Shape {
+  static constexpr int NW = WM * WN, BM = 16 * TM * WM, BN = 16 * TN * WN;
+  static constexpr int NA = STAGE == 1 ? BM / 8 : 3 * BM / 16, NB = 3 * BN / 16;   // 1 KiB loads per slice
+  static constexpr int OPS = (NA + NB) / NW, kSlice = (NA + NB) * 1024;
+  static constexpr size_t lds = static_cast<size_t>(NS) * kSlice;
+  static_assert(NA % NW == 0 && NB % NW == 0, "loads must divide evenly over the wavefronts");
+  static_assert(NS >= 2 && lds + 4 * BM <= 160 * 1024 && (NS - 1) * OPS < 64, "ring");
+};
 
-  const int M = *p.count;
+// Workgroup of WM x WN wavefronts, wavefront tile 16 TM x 16 TN, NS slices of 32 k in an LDS ring.  Grid: (column tiles x
+// row tiles, K ranges).  The weights are the first MFMA operand: a lane holds 4 consecutive output columns of one row.
+template <int WM, int WN, int TM, int TN, int NS, int STAGE, bool RANK>
+__global__ __launch_bounds__(64 * WM * WN) void kernel(Args p) {
+  using S = Shape<WM, WN, TM, TN, NS, STAGE>;
+  constexpr int NW = S::NW, BM = S::BM, BN = S::BN, ASZ = S::NA * 1024;
+  extern __shared__ __align__(1024) unsigned char ring[];
+  __shared__ int src_row[RANK ? BM : 1];
+
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int tiles_n = (p.N + BN - 1) / BN;
   const int tile_m = blockIdx.x / tiles_n, tile_n = blockIdx.x % tiles_n;
+  int M;
+  if constexpr (RANK) {
+    // every wavefront ranks all rows by itself (one load per 64 rows) and notes those of this tile
+    const int Ract = sdi::active_rows(p.active, p.rows_per_chain, p.R);
+    int ks[kRankRows / 64];
+#pragma unroll
+    for (int c = 0; c < kRankRows / 64; ++c) ks[c] = c * 64 + lane < Ract ? p.krow[c * 64 + lane] : -1;
+    M = 0;
+#pragma unroll
+    for (int c = 0; c < kRankRows / 64; ++c) {
+      const bool keep = static_cast<unsigned>(ks[c]) < static_cast<unsigned>(p.T);
+      const unsigned long long m = __ballot(keep);
+      const int pos = M + __popcll(m & ((1ull << lane) - 1ull)) - tile_m * BM;
+      if (keep && pos >= 0 && pos < BM) src_row[pos] = c * 64 + lane;
+      M += __popcll(m);
+    }
+    __syncthreads();
+    if (tile_n == 0 && blockIdx.y == 0) {
+      for (int i = t; i < BM; i += 64 * NW)
+        if (tile_m * BM + i < M) p.rowidx[tile_m * BM + i] = src_row[i];
+      if (tile_m == 0 && t == 0) *p.count = M;
+    }
+  } else {
+    M = *p.count;
+  }
   if (tile_m * BM >= M) return;
-  const int nk = p.Kdim / BK / gridDim.y;                    // slices of this split
-  const int64_t kbase = static_cast<int64_t>(blockIdx.y) * nk * BK * 4;   // byte offset of the split's first k
+  const int k_lo = static_cast<int>(static_cast<int64_t>(p.nk) * blockIdx.y / gridDim.y);
+  const int nk = static_cast<int>(static_cast<int64_t>(p.nk) * (blockIdx.y + 1) / gridDim.y) - k_lo;
+  const bool half_end = STAGE == 1 && (p.d & 16) && k_lo + nk == p.nk;     // the last slice has 16 columns only
 
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int wm = wave / WN, wn = wave % WN;
-  const int half = lane >> 5, l32 = lane & 31;
-  const int lrow = lane >> 3, lchunk = (lane & 7) ^ ((4 * (wave & 1) + (lane >> 4)) & 7);   // (LDS row >> 1) & 7, see above
-
-  // source rows of this lane's loads (rows past M / N are clamped: computed, never stored)
-  const unsigned char* a_src[APASS];
-  const unsigned char* b_src[BPASS];
+  const int wm = wave / WN, wn = wave % WN, l16 = lane & 15, lq = lane >> 4;
+  const unsigned char* src[S::OPS];      // this lane's source per load; rows and columns past the end are clamped
+  int back = 0;                          // bit i: load i reads chunks 4..7, absent from a half slice
 #pragma unroll
-  for (int i = 0; i < APASS; ++i) {
-    int r = tile_m * BM + 8 * (i * NW + wave) + lrow;
-    r = r < M ? r : M - 1;
-    const int64_t row = p.arow ? p.arow[r] : r;
-    a_src[i] = reinterpret_cast<const unsigned char*>(p.A + row * p.lda) + kbase + 16 * lchunk;
+  for (int i = 0; i < S::NA / NW; ++i) {
+    const int g = i * NW + wave;
+    if constexpr (STAGE == 1) {
+      const int row = 8 * g + (lane >> 3), chunk = (lane & 7) ^ ((row >> 1) & 7);
+      int r = tile_m * BM + row;
+      r = r < M ? r : M - 1;
+      const int64_t from = RANK ? src_row[r - tile_m * BM] : p.rowidx[r];
+      src[i] = static_cast<const unsigned char*>(p.A) + from * p.d * 4 + static_cast<int64_t>(k_lo) * 128 + 16 * chunk;
+      back |= (chunk >> 2) << i;
+    } else {
+      const int64_t rb = tile_m * (BM / 16) + g / 3;
+      src[i] = static_cast<const unsigned char*>(p.A) + rb * p.nk * kBlockBytes + (g % 3) * 1024 + 16 * lane;
+    }
   }
 #pragma unroll
-  for (int i = 0; i < BPASS; ++i) {
-    int r = tile_n * BN + 8 * (i * NW + wave) + lrow;
-    r = r < p.N ? r : p.N - 1;
-    b_src[i] = reinterpret_cast<const unsigned char*>(p.Bt + static_cast<int64_t>(r) * p.ldb) + kbase + 16 * lchunk;
+  for (int i = 0; i < S::NB / NW; ++i) {
+    const int g = i * NW + wave;
+    int cb = tile_n * (BN / 16) + g / 3;
+    cb = 16 * cb < p.N ? cb : p.N / 16 - 1;
+    src[S::NA / NW + i] = p.Bt + (static_cast<int64_t>(cb) * p.nk + k_lo) * kBlockBytes + (g % 3) * 1024 + 16 * lane;
   }
+  typedef __attribute__((address_space(3))) void* lds_ptr;
+  typedef const __attribute__((address_space(1))) void* gbl_ptr;
+  auto fetch = [&](int slot, int kt) {
+    unsigned char* base = ring + slot * S::kSlice;
+    const bool half = half_end && kt == nk - 1;
+#pragma unroll
+    for (int i = 0; i < S::NA / NW; ++i) {
+      const unsigned char* a = src[i] + static_cast<int64_t>(kt) * (STAGE == 1 ? 128 : kBlockBytes);
+      if (STAGE == 1 && half) a -= ((back >> i) & 1) * 64;       // any in-bounds chunk: its fragments become zero
+      __builtin_amdgcn_global_load_lds((gbl_ptr)a, (lds_ptr)(base + (i * NW + wave) * 1024), 16, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < S::NB / NW; ++i)
+      __builtin_amdgcn_global_load_lds((gbl_ptr)(src[S::NA / NW + i] + static_cast<int64_t>(kt) * kBlockBytes),
+                                       (lds_ptr)(base + ASZ + (i * NW + wave) * 1024), 16, 0, 0);
+  };
 
-  f32x16 acc[TM][TN];
+  f32x4 acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
-  typedef __attribute__((address_space(3))) void* lds_ptr;
-  typedef const __attribute__((address_space(1))) void* gbl_ptr;
-#define LRGEMM_FETCH(s_, kt_)                                                                          \
-  do {                                                                                                   \
-    _Pragma("unroll") for (int i_ = 0; i_ < APASS; ++i_)                                                 \
-        __builtin_amdgcn_global_load_lds((gbl_ptr)(a_src[i_] + (kt_) * (BK * 4)),                        \
-                                         (lds_ptr)(As + (s_) * BM * 128 + (i_ * NW + wave) * 1024), 16, 0, 0); \
-    _Pragma("unroll") for (int i_ = 0; i_ < BPASS; ++i_)                                                 \
-        __builtin_amdgcn_global_load_lds((gbl_ptr)(b_src[i_] + (kt_) * (BK * 4)),                        \
-                                         (lds_ptr)(Bs + (s_) * BN * 128 + (i_ * NW + wave) * 1024), 16, 0, 0); \
-  } while (0)
-
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int k = 0; k < NS - 1; ++k)
-    if (k < nk) LRGEMM_FETCH(k, k);
+    if (k < nk) fetch(k, k);
 
-  // STAGE 2: everything the epilogue needs from memory is requested here, while the first slices are on
-  // their way: a lane's two rows of the tile (source row and per-row scalars, one 16-byte record each), then
-  // its 64 elements of X as 16 16-byte loads.  Left to the epilogue these are dependent round trips per row
-  // group, as much as the short K loop (K = rank) itself.
-  f32x4 xv[STAGE == 2 ? TM : 1][TN][4];
-  f32x4 muv[STAGE == 2 ? TN : 1][4];
-  int rsrc[TM];
-  float rgp[TM], rcf[TM];
-  if (STAGE == 2) {
+  // STAGE 2: what the epilogue needs from memory is requested while the first slices are on their way (the K loop, K =
+  // rank, is as short as these round trips)
+  const int row0 = tile_m * BM + wm * 16 * TM + l16, col0 = tile_n * BN + wn * 16 * TN + 4 * lq;
+  f32x4 xv[STAGE == 2 ? TM : 1][TN], muv[TN];
+  RowInfo info[TM];
+  if constexpr (STAGE == 2) {
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
-      const int gm = tile_m * BM + wm * (BM / WM) + i * 32 + l32;
-      const RowInfo info = p.rowinfo[gm < M ? gm : M - 1];
-      rsrc[i] = gm < M ? info.src : -1;
-      rgp[i] = info.gp;
-      rcf[i] = info.cf;
+      const int gm = row0 + 16 * i;
+      info[i] = p.rowinfo[gm < M ? gm : M - 1];
     }
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+    for (int j = 0; j < TN; ++j) {
+      const int gn = col0 + 16 * j < p.N ? col0 + 16 * j : 0;
+      muv[j] = *reinterpret_cast<const f32x4*>(p.mu + gn);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int gn = tile_n * BN + wn * (BN / WN) + j * 32 + q * 8 + half * 4;
-        muv[j][q] = gn < p.N ? *reinterpret_cast<const f32x4*>(p.mu + gn) : f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-          xv[i][j][q] = (rsrc[i] >= 0 && gn < p.N)
-                            ? *reinterpret_cast<const f32x4*>(p.X + static_cast<int64_t>(rsrc[i]) * p.N + gn)
-                            : f32x4{0.f, 0.f, 0.f, 0.f};
-      }
+      for (int i = 0; i < TM; ++i) xv[i][j] = *reinterpret_cast<const f32x4*>(p.X + static_cast<int64_t>(info[i].src) * p.N + gn);
+    }
   }
 
-  const int a_row = (wm * (BM / WM) + l32) * 128, b_row = (wn * (BN / WN) + l32) * 128;
-  const int sw = (l32 >> 1) & 7;
+  int slot = 0, free_slot = NS - 1;
   for (int kt = 0; kt < nk; ++kt) {
-    const int s = kt % NS;
-    if (kt + NS - 1 < nk) {
-      wait_loads<(NS - 2) * (APASS + BPASS)>();
-      barrier_keep_loads();
-      LRGEMM_FETCH((kt + NS - 1) % NS, kt + NS - 1);
-    } else {
-      wait_loads<0>();
-      barrier_keep_loads();
+    // slice kt has landed once only the younger ones are outstanding; past the barrier every wavefront has read slice
+    // kt - 1, whose slot takes slice kt + NS - 1
+    wait_stages<S::OPS, NS - 2>(nk - 1 - kt);
+    barrier_keep_loads();
+    if (kt + NS - 1 < nk) fetch(free_slot, kt + NS - 1);
+    const unsigned char* base = ring + slot * S::kSlice;
+    u32x4 a[TM][3];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      if constexpr (STAGE == 1) {
+        const unsigned char* row = base + (wm * 16 * TM + 16 * i + l16) * 128;
+        const f32x4 lo = *reinterpret_cast<const f32x4*>(row + (((2 * lq) ^ ((l16 >> 1) & 7)) << 4));
+        const f32x4 hi = *reinterpret_cast<const f32x4*>(row + (((2 * lq + 1) ^ ((l16 >> 1) & 7)) << 4));
+        const bool none = half_end && kt == nk - 1 && lq >= 2;
+        float x[8];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { x[e] = none ? 0.f : lo[e]; x[4 + e] = none ? 0.f : hi[e]; }
+        split8(x, a[i]);
+      } else {
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+          a[i][q] = *reinterpret_cast<const u32x4*>(base + ((wm * TM + i) * 3 + q) * 1024 + 16 * lane);
+      }
     }
-    const unsigned char* Aw = As + s * BM * 128 + a_row;
-    const unsigned char* Bw = Bs + s * BN * 128 + b_row;
 #pragma unroll
-    for (int m = 0; m < 4; ++m) {
-      const int off = ((2 * m + half) ^ sw) << 4;
-      f32x4 a[TM], b[TN];
+    for (int j = 0; j < TN; ++j) {
+      u32x4 b[3];
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
-        a[i] = __builtin_bit_cast(f32x4, *reinterpret_cast<const u32x4*>(Aw + i * 32 * 128 + off));
+      for (int q = 0; q < 3; ++q)
+        b[q] = *reinterpret_cast<const u32x4*>(base + ASZ + ((wn * TN + j) * 3 + q) * 1024 + 16 * lane);
+      constexpr int pa[6] = {2, 1, 0, 1, 0, 0}, pb[6] = {0, 1, 2, 0, 1, 0};
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
-        b[j] = __builtin_bit_cast(f32x4, *reinterpret_cast<const u32x4*>(Bw + j * 32 * 128 + off));
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
+      for (int q = 0; q < 6; ++q)
 #pragma unroll
         for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(b[j][e], a[i][e], acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, b[pb[q]]),
+                                                              __builtin_bit_cast(bf16x8, a[i][pa[q]]), acc[i][j], 0, 0, 0);
     }
+    free_slot = slot;
+    slot = slot + 1 == NS ? 0 : slot + 1;
   }
-#undef LRGEMM_FETCH
 
-  // acc[i][j][4q + e] is element (row m = l32, column n = 8q + 4 half + e) of its 32x32 tile of C
-  if (STAGE == 1) {
+  // lane (l16, lq): columns col0 + 16 j .. + 3 of row row0 + 16 i
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      const int gm = tile_m * BM + wm * (BM / WM) + i * 32 + l32;
-      if (gm >= M) continue;
-      float* dst = p.part + static_cast<int64_t>(blockIdx.y) * p.slab_stride + static_cast<int64_t>(gm) * p.N;
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int gn = tile_n * BN + wn * (BN / WN) + j * 32 + q * 8 + half * 4;
-          if (gn < p.N)
-            *reinterpret_cast<f32x4*>(dst + gn) =
-                f32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-        }
-    }
-  }
-  if (STAGE == 2) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      if (rsrc[i] < 0) continue;
-      float* dst = p.out + static_cast<int64_t>(rsrc[i]) * p.N;
+  for (int i = 0; i < TM; ++i) {
+    const int gm = row0 + 16 * i;
+    if (gm >= M) continue;
+    if constexpr (STAGE == 1) {
+      float* dst = p.part + blockIdx.y * p.slab_stride + static_cast<int64_t>(gm) * p.N;
 #pragma unroll
       for (int j = 0; j < TN; ++j)
+        if (col0 + 16 * j < p.N) *reinterpret_cast<f32x4*>(dst + col0 + 16 * j) = acc[i][j];
+    } else {
+      float* dst = p.out + static_cast<int64_t>(info[i].src) * p.N;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int gn = tile_n * BN + wn * (BN / WN) + j * 32 + q * 8 + half * 4;
-          if (gn >= p.N) continue;
-          f32x4 o;
+      for (int j = 0; j < TN; ++j) {
+        const int gn = col0 + 16 * j;
+        if (gn >= p.N) continue;
+        f32x4 o;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) o[e] = acc[i][j][4 * q + e] + rgp[i] * xv[i][j][q][e] + rcf[i] * muv[j][q][e];
-          *reinterpret_cast<f32x4*>(dst + gn) = o;
-        }
+        for (int e = 0; e < 4; ++e) o[e] = acc[i][j][e] + info[i].gp * xv[i][j][e] + info[i].cf * muv[j][e];
+        if (p.out_aligned) *reinterpret_cast<f32x4*>(dst + gn) = o;
+        else
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dst[gn + e] = o[e];
+      }
     }
   }
 }
 
-// P'[gm][a] = gain[k][a] * (sum_s part_s[gm][a] - sab[k] qmu[a]),  k = krow[rowidx[gm]]; slabs added in order.
-// Also leaves the per-row record of the second product's epilogue (source row, gperp[k], coef[k]).
+// P'[row][a] = gain[k][a] * (sum_s part_s[row][a] - sab[k] qmu[a]),  k = krow[rowidx[row]], slabs added in order, written
+// as split blocks.  Also leaves the per-row record of the second product's epilogue.  One thread per 8 columns.
 __global__ __launch_bounds__(256) void reduce_gain_kernel(const float* __restrict__ part, int64_t slab_stride, int nsplit,
                                                           const int32_t* __restrict__ count, const int32_t* __restrict__ rowidx,
                                                           const int32_t* __restrict__ krow, const float* __restrict__ gain,
                                                           const float* __restrict__ sab, const float* __restrict__ qmu,
-                                                          float* __restrict__ P, int N, const float* __restrict__ gperp,
+                                                          unsigned char* __restrict__ P, int N, const float* __restrict__ gperp,
                                                           const float* __restrict__ coef, RowInfo* __restrict__ rowinfo) {
   const int M = *count;
-  const int n4 = N / 4;
+  const int n8 = N / 8;
   const int64_t g = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (g >= static_cast<int64_t>(M) * n4) return;
-  const int gm = static_cast<int>(g / n4), c = static_cast<int>(g % n4) * 4;
+  if (g >= static_cast<int64_t>(M) * n8) return;
+  const int gm = static_cast<int>(g / n8), c = static_cast<int>(g % n8) * 8;
   const int src = rowidx[gm];
   const int k = krow[src];
   if (c == 0) rowinfo[gm] = RowInfo{src, gperp[k], coef[k], 0};
-  const int64_t o = static_cast<int64_t>(gm) * N + c;
-  float4 s = *reinterpret_cast<const float4*>(part + o);
+  const float* o = part + static_cast<int64_t>(gm) * N + c;
+  f32x4 s0 = *reinterpret_cast<const f32x4*>(o), s1 = *reinterpret_cast<const f32x4*>(o + 4);
+#pragma unroll 4
   for (int i = 1; i < nsplit; ++i) {
-    const float4 v = *reinterpret_cast<const float4*>(part + i * slab_stride + o);
-    s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+    s0 += *reinterpret_cast<const f32x4*>(o + i * slab_stride);
+    s1 += *reinterpret_cast<const f32x4*>(o + i * slab_stride + 4);
   }
-  const float4 gn = *reinterpret_cast<const float4*>(gain + static_cast<int64_t>(k) * N + c);
-  const float4 q = *reinterpret_cast<const float4*>(qmu + c);
+  const float* gk = gain + static_cast<int64_t>(k) * N + c;
   const float sb = sab[k];
-  float4 r;
-  r.x = gn.x * (s.x - sb * q.x); r.y = gn.y * (s.y - sb * q.y);
-  r.z = gn.z * (s.z - sb * q.z); r.w = gn.w * (s.w - sb * q.w);
-  *reinterpret_cast<float4*>(P + o) = r;
+  float x[8];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    x[e] = gk[e] * (s0[e] - sb * qmu[c + e]);
+    x[4 + e] = gk[4 + e] * (s1[e] - sb * qmu[c + 4 + e]);
+  }
+  u32x4 piece[3];
+  split8(x, piece);
+  unsigned char* dst = P + block_offset(gm, c, N / 32);
+#pragma unroll
+  for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x4*>(dst + 1024 * q) = piece[q];
 }
 
 // Raises the kernel's dynamic-LDS limit on the current device; done for every instantiation when a denoiser is
-// created, never on the launch path (no one-time calls or "already done" flags between a caller and its launches:
-// a HIP graph can capture the very first use).
-template <int BM, int BN, int WM, int WN, int STAGE, int NS>
+// created, never on the launch path (a HIP graph can capture the very first use).
+template <int WM, int WN, int TM, int TN, int NS, int STAGE, bool RANK>
 hipError_t prepare() {
-  constexpr size_t shmem = NS * static_cast<size_t>(BM + BN) * 128;
-  static_assert(NS >= 2 && shmem <= 160 * 1024, "ring must fit the 160 KiB of LDS");
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&kernel<BM, BN, WM, WN, STAGE, NS>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(shmem));
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&kernel<WM, WN, TM, TN, NS, STAGE, RANK>),
+                             hipFuncAttributeMaxDynamicSharedMemorySize,
+                             static_cast<int>(Shape<WM, WN, TM, TN, NS, STAGE>::lds));
 }
 
-template <int BM, int BN, int WM, int WN, int STAGE, int NS>
-hipError_t launch(const Args& a, int Rmax, int nsplit, hipStream_t st) {
-  constexpr size_t shmem = NS * static_cast<size_t>(BM + BN) * 128;
-  const int tiles = ((Rmax + BM - 1) / BM) * ((a.N + BN - 1) / BN);
-  hipLaunchKernelGGL((kernel<BM, BN, WM, WN, STAGE, NS>), dim3(tiles, nsplit), dim3(64 * WM * WN), shmem, st, a);
+template <int WM, int WN, int TM, int TN, int NS, int STAGE, bool RANK>
+hipError_t launch(const Args& a, int R, int nsplit, hipStream_t st) {
+  using S = Shape<WM, WN, TM, TN, NS, STAGE>;
+  const int tiles = ((R + S::BM - 1) / S::BM) * ((a.N + S::BN - 1) / S::BN);
+  hipLaunchKernelGGL((kernel<WM, WN, TM, TN, NS, STAGE, RANK>), dim3(tiles, nsplit), dim3(64 * S::NW), S::lds, st, a);
   return hipGetLastError();
 }
 

@@ -1,6 +1,6 @@
 // E[x0 | x_t] for x0 ~ N(mu, U U^T + s2 I): the closed-form linear denoiser of the image-shaped
-// linear-Gaussian workload, evaluated for all rows of a batched target call with two skinny fp32
-// MFMA GEMMs (paper: the target is queried on all drafted states of a window in one batch,
+// linear-Gaussian workload, evaluated for all rows of a batched target call with two skinny
+// fp32 GEMMs (paper: the target is queried on all drafted states of a window in one batch,
 // Alg. "Speculative Sampling for DDM", (Par.) line).
 //
 // In the eigenbasis Q (d x r, orthonormal columns) of U U^T = Q diag(lam) Q^T the posterior-mean
@@ -12,14 +12,13 @@
 // GEMM 1: P = X Q with the bracket applied per row in the epilogue (each row has its own step k);
 // GEMM 2: out = P' Q^T + g_perp(k) x + (1 - sqrt(ab_k) g_perp(k)) mu.
 //
-// Kernels: for d a multiple of 32 the ring-buffered direct-to-LDS GEMM of lowrank_gemm.h (first
-// product split over K into slabs that a small kernel adds and scales).  Other d fall back to the
-// older kernel below: 128x128 / 64x128 output tile, K-step 16, 4 wavefronts (2x2) of
-// v_mfma_f32_32x32x2f32 tiles, A stored transposed in LDS, global->register prefetch.
+// Both products go through lowrank_gemm.h: bf16 matrix instructions on operands split into three pieces, the first one
+// split over K into slabs that a small kernel adds and scales.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <new>
 #include <vector>
 
@@ -29,146 +28,7 @@
 
 namespace {
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-
-constexpr int BN = 128, BK = 16, kThreads = 256;
-constexpr int LDB = BN + 4;                    // LDS row stride of the B slice (floats)
-
-struct GemmArgs {
-  const float* A;        // [*, lda] row-major; row r of the tile problem is A[arow(r)]
-  int lda;
-  const float* Bm;       // [Kdim, N] row-major
-  int N, Kdim;
-  const int32_t* rowidx; // gathered rows, or nullptr: identity
-  const int32_t* count;  // device: number of rows M
-  int a_gather;          // 1: A rows are rowidx[r]; 0: A rows are r (dense intermediate)
-  // epilogue data
-  const int32_t* krow;   // chain step of source row
-  const float* X;        // [*, d] original rows (stage 2)
-  float* out;            // stage 1: P' [M, r] dense; stage 2: out [*, d] scattered to source rows
-  const float *gain;     // [T, r]
-  const float *sab, *gperp, *coef;   // [T]
-  const float *qmu;      // [r]
-  const float *mu;       // [d]
-};
-
-// BM: rows per workgroup tile (64 or 128).  The first GEMM has only r/128 column tiles, so for
-// small row counts it uses 64-row tiles to put enough workgroups in flight.
-template <int STAGE, int BM>
-__global__ __launch_bounds__(kThreads) void lowrank_gemm_kernel(GemmArgs p) {
-  constexpr int LDA = BM + 4;
-  constexpr int TMI = BM / 64;                   // 32-row MFMA tiles per wavefront
-  constexpr int ACH = BM / 64;                   // float4 loads of A per thread per K-step
-  __shared__ float As[2][BK][LDA];
-  __shared__ float Bs[2][BK][LDB];
-  const int M = *p.count;
-  const int tiles_n = (p.N + BN - 1) / BN;
-  const int tile_m = blockIdx.x / tiles_n, tile_n = blockIdx.x % tiles_n;
-  if (tile_m * BM >= M) return;
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-
-  // global -> LDS assignment: ACH float4 of A and two of B per thread per K-step
-  int a_m[ACH], a_k4[ACH], b_k[2], b_n4[2];
-  const float* a_src[ACH];
-  bool b_ok[2];
-#pragma unroll
-  for (int i = 0; i < ACH; ++i) {
-    const int idx = t + kThreads * i;
-    a_m[i] = idx >> 2; a_k4[i] = idx & 3;
-    const int gm = tile_m * BM + a_m[i];
-    const int r = gm < M ? gm : M - 1;                       // clamp: rows past M are never stored
-    const int src = (p.a_gather && p.rowidx) ? p.rowidx[r] : r;
-    a_src[i] = p.A + static_cast<int64_t>(src) * p.lda + 4 * a_k4[i];
-  }
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int idx = t + kThreads * i;
-    b_k[i] = idx >> 5; b_n4[i] = idx & 31;
-    b_ok[i] = tile_n * BN + 4 * b_n4[i] < p.N;               // N is a multiple of 4
-  }
-  const float* b_src = p.Bm + tile_n * BN;
-
-  f32x16 acc[TMI][2];
-#pragma unroll
-  for (int i = 0; i < TMI; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
-  float4 ra[ACH], rb[2];
-  auto fetch = [&](int k0) {
-#pragma unroll
-    for (int i = 0; i < ACH; ++i) ra[i] = *reinterpret_cast<const float4*>(a_src[i] + k0);
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      rb[i] = b_ok[i] ? *reinterpret_cast<const float4*>(b_src + static_cast<int64_t>(k0 + b_k[i]) * p.N + 4 * b_n4[i])
-                      : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-  };
-  auto stash = [&](int s) {
-#pragma unroll
-    for (int i = 0; i < ACH; ++i) {
-      As[s][4 * a_k4[i] + 0][a_m[i]] = ra[i].x;
-      As[s][4 * a_k4[i] + 1][a_m[i]] = ra[i].y;
-      As[s][4 * a_k4[i] + 2][a_m[i]] = ra[i].z;
-      As[s][4 * a_k4[i] + 3][a_m[i]] = ra[i].w;
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i) *reinterpret_cast<float4*>(&Bs[s][b_k[i]][4 * b_n4[i]]) = rb[i];
-  };
-
-  const int nk = p.Kdim / BK;                                // Kdim is a multiple of BK (checked on host)
-  fetch(0);
-  stash(0);
-  __syncthreads();
-  const int half = lane >> 5, l32 = lane & 31;
-  for (int kt = 0; kt < nk; ++kt) {
-    const int s = kt & 1;
-    if (kt + 1 < nk) fetch((kt + 1) * BK);
-#pragma unroll
-    for (int k = 0; k < BK; k += 2) {
-      float a[TMI], b[2];
-#pragma unroll
-      for (int i = 0; i < TMI; ++i) a[i] = As[s][k + half][wm * (BM / 2) + i * 32 + l32];
-#pragma unroll
-      for (int j = 0; j < 2; ++j) b[j] = Bs[s][k + half][wn * 64 + j * 32 + l32];
-#pragma unroll
-      for (int i = 0; i < TMI; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
-    }
-    if (kt + 1 < nk) stash(s ^ 1);
-    __syncthreads();
-  }
-
-  // ---- epilogue.  acc[i][j][v] is element (row = (v/4)*8 + half*4 + v%4, col = l32) of its 32x32 tile
-#pragma unroll
-  for (int i = 0; i < TMI; ++i) {
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int gm = tile_m * BM + wm * (BM / 2) + i * 32 + (v >> 2) * 8 + half * 4 + (v & 3);
-      if (gm >= M) continue;
-      const int src = p.rowidx ? p.rowidx[gm] : gm;
-      const int k = p.krow[src];
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int gn = tile_n * BN + wn * 64 + j * 32 + l32;
-        if (gn >= p.N) continue;
-        const float c = acc[i][j][v];
-        if (STAGE == 1) {
-          p.out[static_cast<int64_t>(gm) * p.N + gn] =
-              p.gain[static_cast<int64_t>(k) * p.N + gn] * (c - p.sab[k] * p.qmu[gn]);
-        } else {
-          const int64_t o = static_cast<int64_t>(src) * p.N + gn;
-          p.out[o] = c + p.gperp[k] * p.X[o] + p.coef[k] * p.mu[gn];
-        }
-      }
-    }
-  }
-}
+constexpr int kDimStep = 16;      // d: whole 16-column blocks
 
 // Cyclic Jacobi eigen-decomposition of a symmetric n x n matrix (fp64, host).
 // On return A's diagonal holds the eigenvalues and V's columns the eigenvectors.
@@ -207,47 +67,54 @@ void jacobi_eigen(std::vector<double>& A, std::vector<double>& V, int n) {
   }
 }
 
+// One instantiation of the product kernel and whether it also compacts the rows.
+#define SD_LR_SHAPES(X)                                                                            \
+  X(1, 2, 2, 4, 4, 2, false) X(1, 2, 2, 2, 2, 2, false) X(1, 2, 1, 1, 2, 4, false) X(1, 1, 1, 1, 1, 6, false) \
+  X(1, 2, 2, 2, 2, 2, true) X(1, 2, 1, 1, 2, 4, true) X(1, 1, 1, 1, 1, 6, true)                    \
+  X(2, 2, 2, 2, 4, 2, false) X(2, 2, 2, 2, 2, 3, false) X(2, 2, 1, 1, 2, 4, false) X(2, 1, 1, 1, 1, 6, false)
+
+int64_t tiles(int R, int N, int bm, int bn) { return static_cast<int64_t>((R + bm - 1) / bm) * ((N + bn - 1) / bn); }
+
 struct LowRankDenoiser final : sdden {
-  int eval_ring(int R, const float* X, const int32_t* krow, float* out, hipStream_t st);
-  int r = 0, rpad = 0;          // rank, rank padded to a multiple of BK (extra columns are zero)
+  int r = 0, rpad = 0;          // rank, rank padded to a multiple of a slice (extra columns are zero)
+  int nk = 0;                   // slices of the first product's contraction: ceil(d / 32)
   float* dev = nullptr;         // all float tables in one allocation
-  float *Q = nullptr, *QT = nullptr, *gain = nullptr, *sab = nullptr, *gperp = nullptr, *coef = nullptr,
-        *qmu = nullptr, *mu = nullptr;
+  unsigned char* wdev = nullptr;   // Q and Q^T as split blocks
+  unsigned char *wQ = nullptr, *wQT = nullptr;
+  float *gain = nullptr, *sab = nullptr, *gperp = nullptr, *coef = nullptr, *qmu = nullptr, *mu = nullptr;
   // per-call scratch, sized by sdden_reserve
   int32_t* rowidx = nullptr;
   int32_t* count = nullptr;
-  float* P = nullptr;
-  float* part = nullptr;        // K-split partial sums of the first product
+  unsigned char* P = nullptr;   // the second product's A as split blocks, whole row tiles
+  float* part = nullptr;        // K-split partial sums of the first product, one slab of R rows per K range
   lrgemm::RowInfo* rowinfo = nullptr;   // per compacted row: source row and the second product's per-row scalars
-  int64_t part_rows = 0;
   int nsplit = 1;               // K split of the first product: fixed per denoiser, so that the order in which a
                                 // prediction's terms are added never depends on how many rows a call carries
   int cap_rows = 0;
 
-  ~LowRankDenoiser() override {
-    if (dev) (void)hipFree(dev);
+  void free_scratch() {
     if (rowidx) (void)hipFree(rowidx);
-    if (count) (void)hipFree(count);
     if (P) (void)hipFree(P);
     if (part) (void)hipFree(part);
     if (rowinfo) (void)hipFree(rowinfo);
+    rowidx = nullptr; P = nullptr; part = nullptr; rowinfo = nullptr; cap_rows = 0;
+  }
+
+  ~LowRankDenoiser() override {
+    free_scratch();
+    if (dev) (void)hipFree(dev);
+    if (wdev) (void)hipFree(wdev);
+    if (count) (void)hipFree(count);
   }
 
   int reserve(int R) override {
     if (R <= cap_rows) return SD_OK;
-    if (rowidx) (void)hipFree(rowidx);
-    if (P) (void)hipFree(P);
-    if (part) (void)hipFree(part);
-    if (rowinfo) (void)hipFree(rowinfo);
-    rowidx = nullptr; P = nullptr; part = nullptr; rowinfo = nullptr; cap_rows = 0; part_rows = 0;
-    SD_HIP_TRY(err, hipMalloc(&rowidx, sizeof(int32_t) * static_cast<size_t>(R)));
-    SD_HIP_TRY(err, hipMalloc(&P, sizeof(float) * static_cast<size_t>(R) * rpad));
-    if (d % lrgemm::BK == 0) {
-      const int64_t rows = static_cast<int64_t>(nsplit) * R;       // one slab of R rows per K range
-      SD_HIP_TRY(err, hipMalloc(&part, sizeof(float) * static_cast<size_t>(rows) * rpad));
-      part_rows = rows;
-      SD_HIP_TRY(err, hipMalloc(&rowinfo, sizeof(lrgemm::RowInfo) * static_cast<size_t>(R)));
-    }
+    free_scratch();
+    const size_t rows = static_cast<size_t>(R), whole = (rows + lrgemm::kRowTile - 1) / lrgemm::kRowTile * lrgemm::kRowTile;
+    SD_HIP_TRY(err, hipMalloc(&rowidx, sizeof(int32_t) * rows));
+    SD_HIP_TRY(err, hipMalloc(&P, whole / 16 * (rpad / lrgemm::BK) * lrgemm::kBlockBytes));
+    SD_HIP_TRY(err, hipMalloc(&part, sizeof(float) * nsplit * rows * rpad));
+    SD_HIP_TRY(err, hipMalloc(&rowinfo, sizeof(lrgemm::RowInfo) * rows));
     if (!count) SD_HIP_TRY(err, hipMalloc(&count, sizeof(int32_t)));
     cap_rows = R;
     return SD_OK;
@@ -257,53 +124,72 @@ struct LowRankDenoiser final : sdden {
     if (!sdi::aligned16(X)) return sdi::fail(err, SD_ERR_ARG, "sdden_eval(lowrank): X must be 16-byte aligned");
     if (R > cap_rows)
       return sdi::fail(err, SD_ERR_WORKSPACE, "sdden_eval(lowrank): %d rows exceed the %d reserved (sdden_reserve)", R, cap_rows);
-    hipLaunchKernelGGL(sdrows::compact_rows_kernel, dim3(sdrows::compact_rows_grid(R)), dim3(sdrows::kScan), 0, st, krow, rowidx, count,
-                       active, rows_per_chain, R, T);
-    if (part && sdi::aligned16(out)) return eval_ring(R, X, krow, out, st);     // 16-byte stores into out
-    GemmArgs a;
-    a.rowidx = rowidx; a.count = count; a.krow = krow; a.X = X;
-    a.gain = gain; a.sab = sab; a.gperp = gperp; a.coef = coef; a.qmu = qmu; a.mu = mu;
-    // stage 1: P' = gain .* (X Q - sab qmu)       [M, rpad]
-    a.A = X; a.lda = d; a.Bm = Q; a.N = rpad; a.Kdim = d; a.a_gather = 1; a.out = P;
+    // Tiles: the largest that still gives every CU work, two workgroups each for the 128 x 128 one (80 KiB of LDS, two
+    // per CU).  Measured, us, K split 4 (d = 3072, r = 256):
+    //   first product   20480 rows 128x128 166, 64x64 195    2048 rows 44 / 26    512 rows 64x64 19, 32x32 16, 16x16 23
+    //                   133 rows 64x64 18, 32x32 13, 16x16 11
+    //   second product  20480 rows 64x128 231, 64x64 250     2048 rows 27 / 25    512 rows 64x64 11, 32x32 13
+    //                   133 rows 64x64 7.6, 32x32 6.6, 16x16 9.1; at d = 1104, r = 64: 4.7, 4.0, 3.9
+    // Up to kRankRows rows every workgroup finds its rows itself (+1 us) in place of a compaction launch (5 us).
+    const int s1 = rpad > 64 && tiles(R, rpad, 128, 128) * nsplit >= 512 ? 0
+                   : tiles(R, rpad, 64, 64) * nsplit >= 256              ? 1
+                   : tiles(R, rpad, 32, 32) * nsplit >= 256              ? 2
+                                                                         : 3;
+    const int s2 = tiles(R, d, 64, 128) >= 2048 ? 0 : tiles(R, d, 64, 64) >= 256 ? 1 : tiles(R, d, 32, 32) >= 256 ? 2 : 3;
+    const bool rank = R <= lrgemm::kRankRows && s1 > 0;
+    if (!rank)
+      hipLaunchKernelGGL(sdrows::compact_rows_kernel, dim3(sdrows::compact_rows_grid(R)), dim3(sdrows::kScan), 0, st, krow, rowidx,
+                         count, active, rows_per_chain, R, T);
+    // part_s = X[rowidx] Q over K range s, then P' = gain .* (sum_s part_s - sab qmu)
+    lrgemm::Args a{};
+    a.A = X; a.d = d; a.Bt = wQT; a.N = rpad; a.nk = nk; a.count = count; a.rowidx = rowidx;
+    a.krow = krow; a.active = active; a.rows_per_chain = rows_per_chain; a.R = R; a.T = T;
+    a.part = part; a.slab_stride = static_cast<int64_t>(R) * rpad;
     prof.mark(1, st);
-    if (R <= 4096)   // few rows (the window-start call): smaller tiles put more workgroups in flight
-      hipLaunchKernelGGL((lowrank_gemm_kernel<1, 64>), dim3(((R + 63) / 64) * ((rpad + BN - 1) / BN)), dim3(kThreads), 0, st, a);
-    else
-      hipLaunchKernelGGL((lowrank_gemm_kernel<1, 128>), dim3(((R + 127) / 128) * ((rpad + BN - 1) / BN)), dim3(kThreads), 0, st, a);
+    hipError_t e = s1 == 0 ? lrgemm::launch<2, 2, 4, 4, 2, 1, false>(a, R, nsplit, st)
+                   : rank  ? (s1 == 1   ? lrgemm::launch<2, 2, 2, 2, 2, 1, true>(a, R, nsplit, st)
+                              : s1 == 2 ? lrgemm::launch<2, 1, 1, 2, 4, 1, true>(a, R, nsplit, st)
+                                        : lrgemm::launch<1, 1, 1, 1, 6, 1, true>(a, R, nsplit, st))
+                           : (s1 == 1   ? lrgemm::launch<2, 2, 2, 2, 2, 1, false>(a, R, nsplit, st)
+                              : s1 == 2 ? lrgemm::launch<2, 1, 1, 2, 4, 1, false>(a, R, nsplit, st)
+                                        : lrgemm::launch<1, 1, 1, 1, 6, 1, false>(a, R, nsplit, st));
+    SD_HIP_TRY(err, e);
     prof.mark(1, st);
-    // stage 2: out = P' Q^T + gperp x + coef mu   [rows, d]
-    a.A = P; a.lda = rpad; a.Bm = QT; a.N = d; a.Kdim = rpad; a.a_gather = 0; a.out = out;
+    const int64_t octs = static_cast<int64_t>(R) * (rpad / 8);
+    hipLaunchKernelGGL(lrgemm::reduce_gain_kernel, dim3(static_cast<unsigned>((octs + 255) / 256)), dim3(256), 0, st, part,
+                       a.slab_stride, nsplit, count, rowidx, krow, gain, sab, qmu, P, rpad, gperp, coef, rowinfo);
+    // out = P' Q^T + gperp x + coef mu
+    lrgemm::Args b{};
+    b.A = P; b.d = d; b.Bt = wQ; b.N = d; b.nk = rpad / lrgemm::BK; b.count = count;
+    b.rowinfo = rowinfo; b.X = X; b.out = out; b.out_aligned = sdi::aligned16(out); b.mu = mu;
     prof.mark(2, st);
-    hipLaunchKernelGGL((lowrank_gemm_kernel<2, 128>), dim3(((R + 127) / 128) * ((d + BN - 1) / BN)), dim3(kThreads), 0, st, a);
+    e = s2 == 0   ? lrgemm::launch<2, 2, 2, 4, 2, 2, false>(b, R, 1, st)
+        : s2 == 1 ? lrgemm::launch<2, 2, 2, 2, 3, 2, false>(b, R, 1, st)
+        : s2 == 2 ? lrgemm::launch<2, 1, 1, 2, 4, 2, false>(b, R, 1, st)
+                  : lrgemm::launch<1, 1, 1, 1, 6, 2, false>(b, R, 1, st);
+    SD_HIP_TRY(err, e);
     prof.mark(2, st);
     SD_HIP_TRY(err, hipGetLastError());
     return SD_OK;
   }
 };
 
-int LowRankDenoiser::eval_ring(int R, const float* X, const int32_t* krow, float* out, hipStream_t st) {
-  // first product: part_s = X[rowidx] Q (K range s), then P' = gain .* (sum_s part_s - sab qmu)
-  // 64-row tiles: three workgroups fit a CU instead of two and the idle tail of the launch is shorter; over a pass
-  // of the 3072-wide workload they take 6 % less time than 128-row tiles (the tile height changes no sum: same K
-  // order per element).
-  lrgemm::Args a{};
-  a.A = X; a.arow = rowidx; a.lda = d; a.Bt = QT; a.ldb = d; a.N = rpad; a.Kdim = d; a.count = count;
-  a.part = part; a.slab_stride = static_cast<int64_t>(R) * rpad;
-  prof.mark(1, st);
-  SD_HIP_TRY(err, (lrgemm::launch<64, 128, 1, 4, 1, 2>(a, R, nsplit, st)));
-  prof.mark(1, st);
-  const int64_t quads = static_cast<int64_t>(R) * (rpad / 4);
-  hipLaunchKernelGGL(lrgemm::reduce_gain_kernel, dim3(static_cast<unsigned>((quads + 255) / 256)), dim3(256), 0, st, part,
-                     a.slab_stride, nsplit, count, rowidx, krow, gain, sab, qmu, P, rpad, gperp, coef, rowinfo);
-  // second product: out = P' Q^T + gperp x + coef mu
-  lrgemm::Args b{};
-  b.A = P; b.arow = nullptr; b.lda = rpad; b.Bt = Q; b.ldb = rpad; b.N = d; b.Kdim = rpad; b.count = count;
-  b.rowinfo = rowinfo; b.X = X; b.out = out; b.mu = mu;
-  prof.mark(2, st);
-  SD_HIP_TRY(err, (lrgemm::launch<64, 128, 1, 4, 2, 2>(b, R, 1, st)));
-  prof.mark(2, st);
-  SD_HIP_TRY(err, hipGetLastError());
-  return SD_OK;
+// One weight as three bf16 (round to nearest even; |q| <= 1 here), whose sum is within 2^-25 of it.
+void split_weight(float q, uint16_t (&piece)[3]) {
+  for (int i = 0; i < 3; ++i) {
+    uint32_t u;
+    std::memcpy(&u, &q, 4);
+    u = (u + 0x7fffu + ((u >> 16) & 1u)) & 0xffff0000u;
+    piece[i] = static_cast<uint16_t>(u >> 16);
+    float f;
+    std::memcpy(&f, &u, 4);
+    q -= f;
+  }
+}
+
+void store_split(uint16_t* blocks, int row, int k, int nk, const uint16_t (&piece)[3]) {
+  uint16_t* at = blocks + lrgemm::block_offset(row, k & ~7, nk) / 2 + (k & 7);
+  at[0] = piece[0]; at[512] = piece[1]; at[1024] = piece[2];
 }
 
 }  // namespace
@@ -313,9 +199,9 @@ extern "C" int sdden_lowrank_create(int32_t d, int32_t r, const float* mu, const
   std::string& E = sdi::g_den_create_error;
   if (!mu || !U || !alpha_bar_state || !out || d <= 0 || r <= 0 || T <= 0 || !(s2 > 0.f))
     return sdi::fail(E, SD_ERR_ARG, "sdden_lowrank_create: bad argument");
-  if (d % BK != 0)
-    return sdi::fail(E, SD_ERR_UNSUPPORTED, "sdden_lowrank_create: d=%d must be a multiple of %d", d, BK);
-  const int rpad = ((r + lrgemm::BK - 1) / lrgemm::BK) * lrgemm::BK;     // multiple of both kernels' K-steps
+  if (d % kDimStep != 0)
+    return sdi::fail(E, SD_ERR_UNSUPPORTED, "sdden_lowrank_create: d=%d must be a multiple of %d", d, kDimStep);
+  const int rpad = ((r + lrgemm::BK - 1) / lrgemm::BK) * lrgemm::BK;     // whole slices
   // Gram matrix G = U^T U (r x r), its eigen-decomposition, and Q = U V diag(lam^-1/2)
   std::vector<double> G(static_cast<size_t>(r) * r, 0.0), V;
   for (int i = 0; i < d; ++i) {
@@ -336,9 +222,12 @@ extern "C" int sdden_lowrank_create(int32_t d, int32_t r, const float* mu, const
     if (lam[a] > 1e-12 * trace) scale[a] = 1.0 / std::sqrt(lam[a]);
     else { lam[a] = 0.0; scale[a] = 0.0; }                 // rank-deficient direction: no gain there
   }
-  const size_t dr = static_cast<size_t>(d) * rpad;
-  std::vector<float> h(2 * dr + static_cast<size_t>(T) * rpad + 3 * static_cast<size_t>(T) + rpad + d, 0.f);
-  float* hQ = h.data(); float* hQT = hQ + dr; float* hgain = hQT + dr;
+  const int nk = (d + lrgemm::BK - 1) / lrgemm::BK;
+  const size_t bytes_QT = static_cast<size_t>(rpad / 16) * nk * lrgemm::kBlockBytes;                  // rows: rank, k: d
+  const size_t bytes_Q = static_cast<size_t>(d / 16) * (rpad / lrgemm::BK) * lrgemm::kBlockBytes;     // rows: d, k: rank
+  std::vector<uint16_t> hw((bytes_QT + bytes_Q) / 2, 0);
+  std::vector<float> h(static_cast<size_t>(T) * rpad + 3 * static_cast<size_t>(T) + rpad + d, 0.f);
+  float* hgain = h.data();
   float* hsab = hgain + static_cast<size_t>(T) * rpad; float* hgperp = hsab + T; float* hcoef = hgperp + T;
   float* hqmu = hcoef + T; float* hmu = hqmu + rpad;
   std::vector<double> qmu(r, 0.0), qrow(r);
@@ -352,8 +241,10 @@ extern "C" int sdden_lowrank_create(int32_t d, int32_t r, const float* mu, const
     }
     for (int a = 0; a < r; ++a) {
       const double q = qrow[a] * scale[a];
-      hQ[static_cast<size_t>(i) * rpad + a] = static_cast<float>(q);
-      hQT[static_cast<size_t>(a) * d + i] = static_cast<float>(q);
+      uint16_t piece[3];
+      split_weight(static_cast<float>(q), piece);
+      store_split(hw.data(), a, i, nk, piece);
+      store_split(hw.data() + bytes_QT / 2, i, a, rpad / lrgemm::BK, piece);
       qmu[a] += q * mu[i];
     }
     hmu[i] = mu[i];
@@ -372,22 +263,26 @@ extern "C" int sdden_lowrank_create(int32_t d, int32_t r, const float* mu, const
   }
   LowRankDenoiser* L = new (std::nothrow) LowRankDenoiser;
   if (!L) return sdi::fail(E, SD_ERR_ARG, "sdden_lowrank_create: out of host memory");
-  L->d = d; L->T = T; L->r = r; L->rpad = rpad;
-  {
-    // K split of the first product: the largest one (at most 16) that leaves every workgroup 24 slices or more
-    const int nk = d / lrgemm::BK;
-    for (int ns = 1; ns <= 16; ++ns)
-      if (nk % ns == 0 && nk / ns >= 24) L->nsplit = ns;
-  }
-  hipError_t e = lrgemm::prepare<64, 128, 1, 4, 1, 2>();    // dynamic-LDS limits of the two GEMM stages
-  if (e == hipSuccess) e = lrgemm::prepare<64, 128, 1, 4, 2, 2>();
+  L->d = d; L->T = T; L->r = r; L->rpad = rpad; L->nk = nk;
+  // K split of the first product: ranges of 8 slices or more (a call of few rows has nothing else to fill the chip
+  // with), and slabs that move no more bytes than two thirds of the rows themselves (at 20480 rows, d = 3072, r = 256:
+  // the first product takes 166 us with 4 slabs and 173 with 8, and the reduction twice as long)
+  L->nsplit = std::max(1, std::min({nk / 8, d / (3 * rpad), 16}));
+  hipError_t e = hipSuccess;                                // dynamic-LDS limits of the product kernels
+#define SD_LR_PREPARE(ST, WM, WN, TM, TN, NS, RANK) \
+  if (e == hipSuccess) e = lrgemm::prepare<WM, WN, TM, TN, NS, ST, RANK>();
+  SD_LR_SHAPES(SD_LR_PREPARE)
+#undef SD_LR_PREPARE
   if (e == hipSuccess) e = hipMalloc(&L->dev, h.size() * sizeof(float));
   if (e == hipSuccess) e = hipMemcpy(L->dev, h.data(), h.size() * sizeof(float), hipMemcpyHostToDevice);
+  if (e == hipSuccess) e = hipMalloc(&L->wdev, bytes_QT + bytes_Q);
+  if (e == hipSuccess) e = hipMemcpy(L->wdev, hw.data(), bytes_QT + bytes_Q, hipMemcpyHostToDevice);
   if (e != hipSuccess) {
     delete L;
     return sdi::fail(E, SD_ERR_HIP, "sdden_lowrank_create: %s", hipGetErrorString(e));
   }
-  L->Q = L->dev; L->QT = L->Q + dr; L->gain = L->QT + dr; L->sab = L->gain + static_cast<size_t>(T) * rpad;
+  L->wQT = L->wdev; L->wQ = L->wdev + bytes_QT;
+  L->gain = L->dev; L->sab = L->gain + static_cast<size_t>(T) * rpad;
   L->gperp = L->sab + T; L->coef = L->gperp + T; L->qmu = L->coef + T; L->mu = L->qmu + rpad;
   *out = L;
   return SD_OK;

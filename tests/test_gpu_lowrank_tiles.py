@@ -1,0 +1,55 @@
+"""The low-rank denoiser's tiles: row counts at the edges of every tile height (16, 32, 64, 128) and of the compacting form
+(512), a half slice at the end of a row (d = 16 mod 32), ranks that are padded, masked rows, a device-side chain count and
+an output that is not 16-byte aligned, against the oracle.
+
+Tolerance: the products keep 24 bits of every operand and add in fp32, so the error is that of fp32 sums over d terms in
+ranges of at most 1024: below 2e-6 of the row's scale (measured 3e-7 to 7e-7).  The bits do not depend on the call's
+size."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from oracle.denoisers import LowRankDenoiser
+
+from _gpu import as_f32_f64, dev, f32, host, rel_err
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d,r", [(16, 3), (48, 33), (1104, 50), (3072, 256)])
+def test_row_counts_at_tile_edges(d, r):
+    from paper_2501_05370_amd.binding import Denoiser
+    rng = np.random.default_rng(11)
+    T, rows = 25, 18001 if d == 3072 else 4100
+    p = W.lowrank_gaussian(rng, d, r)
+    sched = W.cosine_schedule(T)
+    g = Denoiser.sdden_lowrank_create(p.mu, p.U, p.s2, sched.alpha_bar_state)
+    g.sdden_reserve(rows)
+    x = as_f32_f64(rng.standard_normal((rows, d)))
+    k = rng.integers(-2, T + 2, size=rows).astype(np.int32)
+    k[[0, 15, 16, 31, 32, 63, 64, 127, 128, 511, 512]] = [3, -1, T, 0, T - 1, 5, -1, 2, 7, 1, 4]
+    live = (k >= 0) & (k < T)
+    few = np.flatnonzero(live)[:600]
+    want = LowRankDenoiser(p, sched.alpha_bar_state)(x[few], k[few])
+    xg, kg = f32(x), dev(k, torch.int32)
+    whole = torch.full((rows, d), 777.0, dtype=torch.float32, device="cuda")
+    g.sdden_eval(rows, xg, kg, whole)
+    assert np.all(host(whole)[~live] == 777.0)
+    err = rel_err(host(whole)[few], want)
+    print(f"[lowrank d={d} r={r}] rel err {err:.2e}")
+    assert err < 2e-6
+    for R in (1, 15, 16, 17, 32, 33, 65, 129, 512, 513, 2049):
+        out = torch.full((R, d), 777.0, dtype=torch.float32, device="cuda")
+        g.sdden_eval(R, xg[:R], kg[:R], out)
+        assert torch.equal(out, whole[:R]), R
+        flat = torch.full((R * d + 1,), 777.0, dtype=torch.float32, device="cuda")
+        g.sdden_eval(R, xg[:R], kg[:R], flat[1:].view(R, d))          # 4-byte aligned output
+        assert torch.equal(flat[1:].view(R, d), whole[:R]) and flat[0] == 777.0, R
+    count = torch.tensor([9], dtype=torch.int32, device="cuda")       # 9 chains of 13 rows, read on the device
+    g.sdden_set_active_count(count, 13)
+    for R in (500, 2000):
+        out = torch.full((R, d), 777.0, dtype=torch.float32, device="cuda")
+        g.sdden_eval(R, xg[:R], kg[:R], out)
+        assert torch.equal(out[:117], whole[:117]) and torch.all(out[117:] == 777.0), R
+    g.sdden_set_active_count(None, 1)
