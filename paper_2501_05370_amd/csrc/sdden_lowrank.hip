@@ -128,10 +128,11 @@ struct LowRankDenoiser final : sdden {
     // per CU).  Measured, us, K split 4 (d = 3072, r = 256):
     //   first product   20480 rows 128x128 166, 64x64 195    2048 rows 44 / 26    512 rows 64x64 19, 32x32 16, 16x16 23
     //                   133 rows 64x64 18, 32x32 13, 16x16 11
+    //   (18000 rows, r = 160, where a second 128-column tile is mostly padding: 128x128 147, 64x64 136)
     //   second product  20480 rows 64x128 231, 64x64 250     2048 rows 27 / 25    512 rows 64x64 11, 32x32 13
     //                   133 rows 64x64 7.6, 32x32 6.6, 16x16 9.1; at d = 1104, r = 64: 4.7, 4.0, 3.9
     // Up to kRankRows rows every workgroup finds its rows itself (+1 us) in place of a compaction launch (5 us).
-    const int s1 = rpad > 64 && tiles(R, rpad, 128, 128) * nsplit >= 512 ? 0
+    const int s1 = 5 * rpad > 4 * 128 * ((rpad + 127) / 128) && tiles(R, rpad, 128, 128) * nsplit >= 512 ? 0
                    : tiles(R, rpad, 64, 64) * nsplit >= 256              ? 1
                    : tiles(R, rpad, 32, 32) * nsplit >= 256              ? 2
                                                                          : 3;
