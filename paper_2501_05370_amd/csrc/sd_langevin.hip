@@ -8,8 +8,8 @@
 //   reject:  x_out = y~_{j-1} - gamma grad E(y~_{j-1}) + sqrt(2 gamma) (z - 2 (z.Delta/|Delta|^2) Delta)
 // with E(x) = -log sum_m w_m N(x; mu_m, s^2 I), grad E = (x - sum_m r_m(x) mu_m) / s^2.
 //
-// Three kernels.  For d <= 1024 a WAVEFRONT owns a chain (langevin_window_wave_kernel), for larger d a workgroup does
-// (langevin_window_kernel).  State, frozen gradient and Delta stay in registers, and because the whole chain lives in
+// Four kernels.  For d <= 128 several chains share a wavefront (langevin_short_kernel), for d <= 1024 a WAVEFRONT owns
+// a chain (langevin_window_wave_kernel), for larger d a workgroup does (langevin_window_kernel).  State, frozen gradient and Delta stay in registers, and because the whole chain lives in
 // one place the walk simply stops at the first rejection: no work is spent on drafts that would be discarded.  The 16
 // logits and the two dot products of a position are summed in fp64.  The phi^4 lattice energy has kernels of its own at
 // the end of the file.
@@ -543,6 +543,246 @@ __global__ __launch_bounds__(64 * kWaveChains, 2) void langevin_window_wave_kern
   }
 }
 
+// ---------------------------------------------------------------------------------------------
+// Short chains (d <= 128): G lanes per chain, one group of four coordinates each, 64 / G chains per wavefront.
+// The wavefront kernel above leaves all but ceil(d / 4) lanes of its 64 idle here and walks one chain at a time.  A step
+// of the loop is one position of every chain of the wavefront: its gradient (at a window's first position the frozen
+// one), accept test and new state, so chains stay in step whatever their windows; what a chain computes does not depend
+// on its neighbours.  The 16 logits are summed transposed over the chain's lanes (16 / G of them per lane), the
+// weights come back through a slice of LDS.  Bound by vector instructions at many chains, by one step's latency at few.
+// Whole runs, us (before: a wavefront per chain):
+//   16384 chains: d = 5, M = 4, 150 steps 401 (3164)   d = 16, M = 16, 100 steps 309 (2421)   d = 60, M = 10, 100 steps
+//   616 (2139)   d = 120, M = 16, 100 steps 1119 (2101)
+//   2000 chains d = 37, M = 16, 150 steps 344 (520)   100 chains d = 100, M = 8, 150 steps 324 (451)   3 chains d = 3,
+//   M = 16, 300 steps 594 (755)
+// With the means in LDS, as the wavefront kernel has them, 375 / 354 / 615 / 1142 / 437 / 324 / 940.
+// ---------------------------------------------------------------------------------------------
+template <int MASK, int TO>
+__device__ __forceinline__ double group_max(double v) {
+  v = fmax(v, sdlane::lane_xor<MASK>(v));
+  if constexpr (2 * MASK < TO) return group_max<2 * MASK, TO>(v);
+  else return v;
+}
+template <int MASK, int TO>
+__device__ __forceinline__ double group_add(double v) {     // over the lanes that differ in the bits MASK .. TO / 2
+  v += sdlane::lane_xor<MASK>(v);
+  if constexpr (2 * MASK < TO) return group_add<2 * MASK, TO>(v);
+  else return v;
+}
+// a[0 .. N) summed over the lanes of a group, transposed: halves exchanged at MASK, MASK / 2, ...
+template <int MASK, int N>
+__device__ __forceinline__ void reduce_transposed(double (&a)[16]) {
+  if constexpr (N > 1) {
+#pragma unroll
+    for (int i = 0; i < N / 2; ++i) a[i] = sdlane::halving_add<MASK>(a[i], a[i + N / 2]);
+  } else {
+    a[0] += sdlane::lane_xor<MASK>(a[0]);
+  }
+  if constexpr (MASK > 1) reduce_transposed<MASK / 2, (N > 1 ? N / 2 : 1)>(a);
+}
+
+template <int G, bool RUN>
+__global__ __launch_bounds__(256, 2) void langevin_short_kernel(LangevinArgs p) {
+  constexpr int CPWV = 64 / G, NV = G < 16 ? 16 / G : 1, PAIR = G == 32 ? 2 : 1;   // G = 32: two lanes hold a logit
+  __shared__ __align__(16) double sh_r[4 * CPWV][18];       // a chain's weights (stride 144 B: spread over the banks)
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6, sub = lane / G, gl = lane % G;
+  const int d = p.d, M = p.M;
+  const int slot = wave * CPWV + sub;
+  const int Bact = p.active ? min(p.B, max(0, *p.active)) : p.B;
+  const int b_raw = blockIdx.x * (4 * CPWV) + slot;
+  const bool valid = b_raw < Bact;
+  const int b = valid ? b_raw : 0;
+  int n = valid ? p.n[b] : p.T;
+  const int64_t id = valid ? p.id[b] : 0;
+  const double gamma = p.gamma, inv_s2 = p.inv_s2;
+  const double sq2g = sqrt(2.0 * gamma), sqg2 = sqrt(0.5 * gamma), inv_sqg2 = 1.0 / sqg2;
+  const int my_m = gl / PAIR * NV;                          // first of the NV components whose logits this lane holds
+  double my_logw[NV], my_hn[NV];
+  // my four coordinates of every mean (0 beyond M and d), in registers: read twice a step, they would be half of its
+  // time out of LDS
+  double mu[kWaveM][4], hn[16];
+#pragma unroll
+  for (int m = 0; m < kWaveM; ++m) {
+    hn[m] = 0.0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int i = 4 * gl + e;
+      mu[m][e] = (m < M && i < d) ? static_cast<double>(p.means[static_cast<int64_t>(m) * d + i]) : 0.0;
+      hn[m] = fma(mu[m][e], mu[m][e], hn[m]);
+    }
+  }
+  reduce_transposed<G / 2, 16>(hn);
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    my_logw[i] = my_m + i < M ? static_cast<double>(p.logw[my_m + i]) : 0.0;
+    my_hn[i] = 0.5 * hn[i];
+  }
+  bool own[4];
+  double cur[4], g0[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    own[e] = 4 * gl + e < d;
+    cur[e] = (valid && own[e]) ? static_cast<double>(p.x[static_cast<int64_t>(b) * d + 4 * gl + e]) : 0.0;
+  }
+  double* r_slot = sh_r[slot];
+
+  // grad E at `cur`; every lane of the wavefront takes part
+  auto gradient = [&](double g[4]) {
+    auto dot4 = [&](int m) { return fma(cur[3], mu[m][3], fma(cur[2], mu[m][2], fma(cur[1], mu[m][1], cur[0] * mu[m][0]))); };
+    double dot[16];
+#pragma unroll
+    for (int m = 0; m < kWaveM / 2; ++m) {                  // the first halving step as the products come
+      const double lower = dot4(m), upper = M > kWaveM / 2 ? dot4(m + kWaveM / 2) : 0.0;
+      dot[m] = sdlane::halving_add<G / 2>(lower, upper);
+    }
+    if constexpr (G > 2) reduce_transposed<G / 4, 8>(dot);
+    double logit[NV], mx = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      logit[i] = my_m + i < M ? my_logw[i] + (dot[i] - my_hn[i]) * inv_s2 : -INFINITY;
+      mx = fmax(mx, logit[i]);
+    }
+    mx = group_max<PAIR, G>(mx);
+    if (gl % PAIR == 0) {
+#pragma unroll
+      for (int i = 0; i < NV; ++i) r_slot[my_m + i] = my_m + i < M ? exp(logit[i] - mx) : 0.0;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    // every lane adds the 16 weights itself, in one order whatever G: with it nothing depends on G (the lanes past a
+    // short row add zeros to every other sum), so G can follow the number of chains
+    double r[16];
+#pragma unroll
+    for (int m = 0; m < kWaveM; m += 2) {
+      const double2 v = *reinterpret_cast<const double2*>(r_slot + m);
+      r[m] = v.x;
+      r[m + 1] = v.y;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const double sum = (((r[0] + r[1]) + (r[2] + r[3])) + ((r[4] + r[5]) + (r[6] + r[7]))) +
+                       (((r[8] + r[9]) + (r[10] + r[11])) + ((r[12] + r[13]) + (r[14] + r[15])));
+    const double inv_sum = 1.0 / sum;
+    double bar[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int m = 0; m < kWaveM; ++m) {
+      const double rm = r[m] * inv_sum;
+      if (__ballot(!(rm < 1e-25)) == 0ull) continue;        // negligible as in the wavefront kernel, for every chain here
+      const double w = rm < 1e-25 ? 0.0 : rm;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) bar[e] = fma(w, mu[m][e], bar[e]);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) g[e] = (cur[e] - bar[e]) * inv_s2;
+  };
+
+  int Kt = max(0, min(p.K, p.T - n));
+  int j = 0, windows = 0, adv = 0;
+  bool active = valid && Kt > 0, rejected = false;
+  int lu_base = 0;                                          // first absolute step of the uniforms held in lu_batch
+  bool lu_have = false;
+  double lu_batch = 0.0;
+  unsigned long long acc_adv = 0, acc_win = 0, acc_rej = 0, acc_kt = 0;
+
+  // Ends: a step moves every active chain one position on, a window of Kt positions ends after at most Kt steps and
+  // advances n by at least 1, and a chain stops at n = T or after max_windows windows.
+  while (__ballot(active) != 0ull) {
+    double g[4];
+    gradient(g);
+    if (active) {                                           // the lanes of a chain agree
+      const int k1 = n + j + 1;                             // absolute step this position produces
+      float z[4];
+      sdrng::normal4(p.seed, id, static_cast<uint32_t>(k1), sdrng::kStreamNoise, static_cast<uint32_t>(gl), z);
+      if (!lu_have || k1 - lu_base >= G) {
+        lu_base = k1;
+        lu_have = true;
+        lu_batch = sdrng::log_uniform(p.seed, id, static_cast<uint32_t>(k1 + gl));
+      }
+      const double lu = __shfl(lu_batch, sub * G + (k1 - lu_base), 64);
+      double lr = 0.0, dl[4] = {0.0, 0.0, 0.0, 0.0}, coef = 0.0;
+      rejected = false;
+      if (j == 0) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) g0[e] = g[e];
+      } else {
+        double a1 = 0.0, a2 = 0.0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          z[e] = own[e] ? z[e] : 0.f;
+          dl[e] = sqg2 * (g[e] - g0[e]);                    // 0 past d: state and means are 0 there
+          a1 = fma(static_cast<double>(z[e]), dl[e], a1);
+          a2 = fma(dl[e], dl[e], a2);
+        }
+        const double S1 = group_add<1, G>(a1), S2 = group_add<1, G>(a2);
+        lr = (-S1 - 0.5 * S2) * p.inv_tau;
+        rejected = !(S2 == 0.0 || (lr == lr && lu <= fmin(0.0, lr)));   // a log-ratio that is not a number rejects
+        coef = S2 > 0.0 ? S1 / S2 : 0.0;
+      }
+      if (!RUN && gl == 0) {
+        if (p.logratio) p.logratio[static_cast<int64_t>(b) * p.K + j] = static_cast<float>(lr);
+        if (p.logu) p.logu[static_cast<int64_t>(b) * p.K + j] = static_cast<float>(lu);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (!own[e]) continue;
+        if (rejected)                                       // target gradient = g0 + Delta / sqrt(gamma/2)
+          cur[e] = cur[e] - gamma * (g0[e] + dl[e] * inv_sqg2) + sq2g * (static_cast<double>(z[e]) - 2.0 * coef * dl[e]);
+        else
+          cur[e] = cur[e] - gamma * g0[e] + sq2g * static_cast<double>(z[e]);
+      }
+      ++j;
+      if (rejected || j == Kt) {
+        adv = j;
+        n += j;
+        ++windows;
+        if (RUN) {                                          // the state passes through fp32, as between separate calls
+          acc_adv += j; acc_win += 1; acc_rej += rejected ? 1 : 0; acc_kt += Kt;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) cur[e] = static_cast<double>(static_cast<float>(cur[e]));
+        }
+        j = 0;
+        Kt = max(0, min(p.K, p.T - n));
+        active = RUN && Kt > 0 && windows < p.max_windows;
+      }
+    }
+  }
+
+  if (RUN && p.counters) {                                  // one atomic per wavefront and counter
+    unsigned long long c[4] = {acc_adv, acc_win, acc_rej, acc_kt};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      c[q] = gl == 0 ? c[q] : 0ull;
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) c[q] += __shfl_xor(c[q], o, 64);
+      if (lane == 0 && c[q]) atomicAdd(&p.counters[q == 3 ? 4 : q], c[q]);
+    }
+  }
+  if (!valid) return;
+  if (gl == 0) {
+    if (RUN) {
+      p.n_out[b] = n;
+    } else {
+      p.adv[b] = adv;
+      if (p.rej) p.rej[b] = rejected ? 1 : 0;
+      for (int q = adv; q < p.K; ++q) {                     // positions not reached report 0
+        if (p.logratio) p.logratio[static_cast<int64_t>(b) * p.K + q] = 0.f;
+        if (p.logu) p.logu[static_cast<int64_t>(b) * p.K + q] = 0.f;
+      }
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    if (own[e]) p.x_out[static_cast<int64_t>(b) * d + 4 * gl + e] = static_cast<float>(cur[e]);
+}
+
+template <int G>
+void launch_short(const LangevinArgs& p, bool run, hipStream_t st) {
+  const unsigned grid = static_cast<unsigned>((p.B + 256 / G - 1) / (256 / G));
+  if (run) hipLaunchKernelGGL((langevin_short_kernel<G, true>), dim3(grid), dim3(256), 0, st, p);
+  else hipLaunchKernelGGL((langevin_short_kernel<G, false>), dim3(grid), dim3(256), 0, st, p);
+}
+
 // The chain dispenser starts every launch at zero: a one-thread kernel ahead of the launch (a kernel, not a
 // memset, so that the sequence can be captured in a HIP graph), never a rewind at the end of the previous one --
 // a launch that does not run to its end must not leave the next call without chains.
@@ -946,6 +1186,21 @@ int langevin_launch(const char* who, sd_ctx* ctx, int32_t B, const float* x, con
   p.max_windows = max_windows; p.n_out = n_out; p.counters = reinterpret_cast<unsigned long long*>(counters);
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int dpad = 4 * groups;
+  if (groups <= 32) {                       // several chains per wavefront
+    const bool run = max_windows > 1;
+    // Lanes per chain: the row's groups, but with chains too few for a wavefront on every SIMD up to 16, one logit per
+    // lane: a step is then latency, and eight exponentials in a row are a third of it.  Both give the same bits.
+    int G = groups <= 2 ? 2 : groups <= 4 ? 4 : groups <= 8 ? 8 : groups <= 16 ? 16 : 32;
+    while (G < 16 && static_cast<int64_t>(B) * 2 * G <= 64ll * 4 * ctx->cus) G *= 2;
+    if (G == 2) launch_short<2>(p, run, st);
+    else if (G == 4) launch_short<4>(p, run, st);
+    else if (G == 8) launch_short<8>(p, run, st);
+    else if (G == 16) launch_short<16>(p, run, st);
+    else launch_short<32>(p, run, st);
+    if (run && counters) hipLaunchKernelGGL(bump_launches_kernel, dim3(1), dim3(1), 0, st, p.counters);
+    SD_HIP_TRY(ctx->err, hipGetLastError());
+    return SD_OK;
+  }
   if (dpad <= 1024) {                       // a wavefront per chain, means in LDS (16 rows of doubles, <= 128 KiB)
     hipError_t e;
     const bool whole = ctx->d % 4 == 0;
