@@ -34,7 +34,7 @@ DEFAULT_WORKLOAD = "c4"
 DESCRIPTIONS = {
     "c1": "c1: toy DDPM d=2, 64 chains, ring GMM posterior mean, linear beta T=100, K=4",
     "c2": "c2: GMM DDPM d=64, 4096 chains, 32-component posterior mean, cosine T=200, K=8",
-    "c3": "c3: linear-Gaussian DDPM d=3072, 2048 chains, rank-256 Woodbury denoiser (fp32 MFMA), cosine T=250, K=10",
+    "c3": "c3: linear-Gaussian DDPM d=3072, 2048 chains, rank-256 Woodbury denoiser (fp32), cosine T=250, K=10",
     "c4": "c4: MLP DDPM d=12288, 512 chains, 3-layer width-4096 SiLU MLP (bf16 MFMA), linear T=500, K=16",
     "c5": "c5: speculative ULA d=1000, 16384 chains, 16-component GMM score, gamma=1e-2, T=2000, K=16",
     "phi4": "phi4: speculative ULA on the phi^4 lattice energy, 8x8 periodic grid, beta=100, gamma=1e-3, 16384 chains, T=2000, K=20",
@@ -47,7 +47,8 @@ DESCRIPTIONS = {
 MEASURED_TRAFFIC_BYTES = {"c4": 1225.1e6, "c3": 277.8e6}
 
 # published MI355X peaks used as roofline denominators
-PEAK = {"hbm": (8000.0, "GB/s"), "mfma_bf16": (2500.0, "TFLOP/s"), "mfma_fp32": (157.3, "TFLOP/s"),
+PEAK = {"hbm": (8000.0, "GB/s"), "mfma_bf16": (2500.0, "TFLOP/s"),
+        "mfma_split": (2500.0 / 6, "TFLOP/s"),   # fp32 products, six bf16 ones each
         "alu_fp64": (78.6, "TFLOP/s"), "alu_fp32": (157.3, "TFLOP/s"),
         # vector instruction issue: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz lane-instructions per second (the fp32
         # figure is this times 2 for the FMA and 2 for the packed form)
@@ -70,8 +71,9 @@ def roofline_plan(cfg):
                     work=lambda c: 2.0 * (c[4] - c[1]) * d * H)
     if cfg.kind == "lowrank":
         rpad = -(-cfg.params.U.shape[1] // 16) * 16
-        return dict(kernel="lrgemm::kernel<64,128,1,4,STAGE=2,NS=2> (P' Q^T + epilogue, fp32 MFMA) of the batched target call", den_which=2,
-                    den_min_rows=cfg.B + 1, bound="mfma", peak="mfma_fp32", scale=1e-12,
+        return dict(kernel="lrgemm::kernel<2,2,2,4,2,STAGE=2> (P' Q^T + epilogue, fp32 operands as three bf16 pieces, six MFMAs per product) "
+                           "of the batched target call", den_which=2,
+                    den_min_rows=cfg.B + 1, bound="mfma", peak="mfma_split", scale=1e-12,
                     work=lambda c: 2.0 * (c[4] - c[1]) * d * rpad)
     if cfg.kind == "gmm":
         # the analytic denoiser bounds these windows (about 3/4 of the kernel time).  fp64 flops per
