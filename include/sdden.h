@@ -74,7 +74,8 @@ int sdden_eval_mirror(sdden* den, int32_t R, const float* X, const uint16_t* Xbf
  * in : y [B,d], n [B], chain_id [B]; draft_den: the draft network (EXPLICIT mode: the independent draft model), else
  *      ignored; D_frozen [B,d]: the carried prediction (FROZEN_REUSED), else ignored                         (dev)
  * out: out [*, d], row index = chain_id; B_active: dev int32, set to 0; counters: dev int64[5] or NULL, accumulated as in
- *      sd_advance (windows: those of the chain that needed most).
+ *      sd_advance (windows: those of the chain that needed most).  A chain handed over at step T leaves its state in
+ *      `out` and counts one chain-window, as there.
  * SD_ERR_UNSUPPORTED, with nothing enqueued, when this denoiser (or draft_den) has no such form, is being timed
  * (sdden_profile) or runs under a device-resident count: the caller then makes the separate calls.  Calls on one context
  * must be ordered, as for sd_langevin_window. */

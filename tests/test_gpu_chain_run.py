@@ -62,3 +62,36 @@ def test_chain_run_equals_the_window_loop(drafter, B, d, M, K, T):
     # a second run accumulates into the counters when asked to, and starts from zero otherwise
     assert a.run(ids, reset_counters=False)[1] == [2 * c for c in want]
     assert a.run(ids, windows_per_sync=3)[1] == want
+
+
+# Chains handed over at any step, step T included: such a chain's window copies its state, sd_advance leaves that in `out`
+# and counts the chain-window.
+@pytest.mark.parametrize("drafter,B,d,M", [("frozen", 40, 7, 5), ("reused", 40, 30, 7), ("independent", 40, 9, 4), ("frozen", 2050, 3, 2)])
+@pytest.mark.parametrize("at_end", ["some", "all"])
+def test_chains_handed_over_at_ragged_steps(drafter, B, d, M, at_end):
+    K, T = 5, 24
+    rng = np.random.default_rng(B + d)
+    n = np.full(B, T) if at_end == "all" else rng.integers(0, T + 1, B)
+    if at_end == "some":
+        n[[0, 1, 2, B - 1]] = [T, T - 1, 0, T]
+    ids = torch.randperm(B, device="cuda").to(torch.int64)
+    smp = []
+    for _ in range(2):
+        s = _sampler(drafter, B, d, M, K, T)
+        s.start(ids)
+        s.buf.n.copy_(torch.as_tensor(n, dtype=torch.int32))
+        if drafter == "reused":
+            s.den.sdden_eval(B, s.buf.y, s.buf.n, s.buf.Dfz)
+        s.buf.out.fill_(777.0)
+        smp.append(s)
+    a, b = smp
+    assert a._run_chains(B)
+    left = B
+    while left > 0:
+        b.window(left)
+        b.advance(left)
+        left = int(b.buf.B_active.item())
+    out, ref = host(a.buf.out), host(b.buf.out)
+    assert not np.any(ref == 777.0)
+    assert a.buf.counters.tolist() == b.buf.counters.tolist() and int(a.buf.B_active.item()) == 0
+    assert np.max(np.abs(out - ref) / np.maximum(1.0, np.abs(ref).max(axis=1, keepdims=True))) < 1e-5
