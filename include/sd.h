@@ -258,7 +258,8 @@ int sd_langevin_run(sd_ctx* ctx, int32_t B, const float* x, const int32_t* n, co
  * itself (1024 < d <= 4096): same bits, chains that reach T leave their state in out[chain_id].
  * in : as sd_langevin_run
  * out: out [*, d], row index = chain_id; B_active: dev int32, set to 0; counters: dev int64[5] or NULL, accumulated as in
- *      sd_advance (windows: those of the chain that needed most).
+ *      sd_advance (windows: those of the chain that needed most).  A chain handed over at step T leaves its state in
+ *      `out` and counts one chain-window, as there.
  * SD_ERR_UNSUPPORTED, with nothing enqueued, for other d, more than 16 components or under a device-resident count: the
  * caller then loops over windows.  Ordering of calls on one context as for sd_langevin_window. */
 int sd_langevin_chains(sd_ctx* ctx, int32_t B, const float* x, const int32_t* n, const int64_t* chain_id,

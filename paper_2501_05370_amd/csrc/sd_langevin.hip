@@ -208,8 +208,8 @@ __global__ __launch_bounds__(MAXT) void langevin_window_kernel(LangevinArgs p) {
 
   int jr = -1;
   unsigned long long acc_adv = 0, acc_win = 0, acc_rej = 0, acc_kt = 0;
-  do {                                         // the windows (RUN), each of which advances the chain; Kt is uniform
-  if (RUN && Kt == 0) break;                   // a chain handed over at step T: no window
+  do {                                         // the windows (RUN), each of which advances the chain; Kt is uniform.
+                                               // A chain handed over at step T has one, of no positions: its state stays
   double g0[4];
   gradient_begin();
   // log u of the window's positions: lane j of every wavefront draws position j + 1 (the window has at most 64)
@@ -274,7 +274,7 @@ __global__ __launch_bounds__(MAXT) void langevin_window_kernel(LangevinArgs p) {
   } while (RUN && Kt > 0);
 
   if (RUN) {
-    if (t == 0 && acc_win) {
+    if (t == 0) {
       if (p.counters) {
         atomicAdd(&p.counters[0], acc_adv);
         atomicAdd(&p.counters[1], acc_win);
@@ -283,7 +283,6 @@ __global__ __launch_bounds__(MAXT) void langevin_window_kernel(LangevinArgs p) {
       }
       atomicMax(&p.queue[1], static_cast<int32_t>(acc_win));
     }
-    if (acc_win == 0) return;
   } else if (t == 0) {
     p.adv[b] = jr >= 0 ? jr + 1 : Kt;
     if (p.rej) p.rej[b] = jr >= 0 ? 1 : 0;

@@ -60,3 +60,31 @@ def test_whole_chains_equal_the_window_loop(B, d, M, K, T, tau):
     assert np.max(np.abs(host(b.y_out)[:B] - xo)[same] / scale[same]) < 1e-5
     reached = (np.arange(K)[None, :] < adv[:, None]) & same[:, None]
     assert np.max(np.abs(host(glr) - lr)[reached] / np.maximum(1.0, np.abs(lr[reached]))) < 1e-4
+
+
+@pytest.mark.parametrize("at_end", ["some", "all"])
+def test_chains_handed_over_at_ragged_steps(at_end):
+    """Chains at any step, step T included: such a chain's window copies its state, sd_advance leaves that in `out` and
+    counts the chain-window."""
+    B, d, M, K, T = 30, 1100, 4, 5, 17
+    cfg = W.make_config("c5", B=B, d=d, M=M, K=K, T=T)
+    n = np.random.default_rng(2).integers(0, T + 1, B) if at_end == "some" else np.full(B, T)
+    if at_end == "some":
+        n[[0, 1, 2, B - 1]] = [T, T - 1, 0, T]
+    ids = torch.randperm(B, generator=torch.Generator().manual_seed(3)).cuda()
+    smp = []
+    for _ in range(2):
+        s = _sampler(cfg, B, 1.0)
+        s.start(ids)
+        s.buf.n.copy_(torch.as_tensor(n, dtype=torch.int32))
+        s.buf.out.fill_(777.0)
+        smp.append(s)
+    a, b = smp
+    assert a._run_chains(B)
+    left = B
+    while left > 0:
+        b.window(left)
+        b.advance(left)
+        left = int(b.buf.B_active.item())
+    assert torch.equal(a.buf.out, b.buf.out) and not bool((b.buf.out == 777.0).any())
+    assert a.buf.counters.tolist() == b.buf.counters.tolist() and int(a.buf.B_active.item()) == 0
