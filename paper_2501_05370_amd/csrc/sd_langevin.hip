@@ -1264,14 +1264,13 @@ extern "C" int sd_langevin_chains(sd_ctx* ctx, int32_t B, const float* x, const 
                                   const float* means, const float* logw, float comp_std, int32_t M, float gamma,
                                   float* out, int32_t* B_active, int64_t* counters, void* stream) {
   if (!ctx) return SD_ERR_ARG;
-  if (B < 0 || M <= 0 || !(comp_std > 0.f) || !(gamma > 0.f) ||
-      (B > 0 && (!x || !n || !chain_id || !means || !logw || !out || !B_active)))
+  if (B < 0 || M <= 0 || !(comp_std > 0.f) || !(gamma > 0.f) || !B_active ||
+      (B > 0 && (!x || !n || !chain_id || !means || !logw || !out)))
     return sdi::fail(ctx->err, SD_ERR_ARG, "sd_langevin_chains: bad argument");
   const int groups = (ctx->d + 3) / 4;
   if (M > 16 || ctx->d <= 1024 || groups > kMaxGroups || ctx->active)
     return sdi::fail(ctx->err, SD_ERR_UNSUPPORTED, "sd_langevin_chains: 1024 < d <= %d, at most 16 components, no device-side count",
                      4 * kMaxGroups);
-  if (B == 0) return SD_OK;
   LangevinArgs p{};
   p.x = x; p.n = n; p.id = chain_id; p.means = means; p.logw = logw; p.x_out = out; p.queue = ctx->dev_queue;
   p.B = B; p.d = ctx->d; p.K = ctx->K; p.T = ctx->T; p.M = M; p.seed = ctx->seed;
@@ -1279,7 +1278,7 @@ extern "C" int sd_langevin_chains(sd_ctx* ctx, int32_t B, const float* x, const 
   p.counters = reinterpret_cast<unsigned long long*>(counters);
   hipStream_t st = static_cast<hipStream_t>(stream);
   hipLaunchKernelGGL(reset_queue_kernel, dim3(1), dim3(1), 0, st, p.queue, 1);
-  launch_wide<true>(p, groups, st);
+  if (B > 0) launch_wide<true>(p, groups, st);
   hipLaunchKernelGGL(chains_end_kernel, dim3(1), dim3(1), 0, st, p.queue + 1, p.counters, B_active);
   SD_HIP_TRY(ctx->err, hipGetLastError());
   return SD_OK;

@@ -511,7 +511,8 @@ int GmmDenoiser::run(sdden* draft, sd_ctx* ctx, int B, const float* y, const int
   const bool lds = d <= 256 && table <= 36 * 1024;
   const size_t shmem = xs + (lds ? table : 0);
   hipLaunchKernelGGL(run_begin_kernel, dim3(1), dim3(1), 0, st, p.longest);
-  if (d <= 64) lds ? launch_run<1, 1, true>(p, indep, grid, block, shmem, st) : launch_run<1, 1, false>(p, indep, grid, block, shmem, st);
+  if (B == 0) {}                           // no chains: the end kernel leaves the count
+  else if (d <= 64) lds ? launch_run<1, 1, true>(p, indep, grid, block, shmem, st) : launch_run<1, 1, false>(p, indep, grid, block, shmem, st);
   else if (d <= 128) lds ? launch_run<2, 1, true>(p, indep, grid, block, shmem, st) : launch_run<2, 1, false>(p, indep, grid, block, shmem, st);
   else if (d <= 256) lds ? launch_run<4, 1, true>(p, indep, grid, block, shmem, st) : launch_run<4, 1, false>(p, indep, grid, block, shmem, st);
   else if (d <= 512) launch_run<4, 2, false>(p, indep, grid, block, shmem, st);
@@ -619,8 +620,8 @@ int sdden_eval(sdden* den, int32_t R, const float* X, const int32_t* krow, float
 int sdden_run(sdden* den, sdden* draft_den, sd_ctx* ctx, int32_t B, const float* y, const int32_t* n, const int64_t* chain_id,
               const float* D_frozen, float* out, int32_t* B_active, int64_t* counters, void* stream) {
   if (!den || !ctx) return SD_ERR_ARG;
-  if (B <= 0 || !y || !n || !chain_id || !out || !B_active || (ctx->mode == SD_DRAFT_EXPLICIT && !draft_den) ||
-      (ctx->mode == SD_DRAFT_FROZEN_REUSED && !D_frozen))
+  if (B < 0 || !B_active || (ctx->mode == SD_DRAFT_EXPLICIT && !draft_den) ||
+      (B > 0 && (!y || !n || !chain_id || !out || (ctx->mode == SD_DRAFT_FROZEN_REUSED && !D_frozen))))
     return sdi::fail(den->err, SD_ERR_ARG, "sdden_run: bad argument");
   if (den->d != ctx->d || den->T < ctx->T || (ctx->mode == SD_DRAFT_EXPLICIT && (draft_den->d != ctx->d || draft_den->T < ctx->T)))
     return sdi::fail(den->err, SD_ERR_ARG, "sdden_run: denoiser and context describe chains of different sizes");

@@ -95,3 +95,12 @@ def test_chains_handed_over_at_ragged_steps(drafter, B, d, M, at_end):
     assert not np.any(ref == 777.0)
     assert a.buf.counters.tolist() == b.buf.counters.tolist() and int(a.buf.B_active.item()) == 0
     assert np.max(np.abs(out - ref) / np.maximum(1.0, np.abs(ref).max(axis=1, keepdims=True))) < 1e-5
+
+
+def test_no_chains():
+    """B = 0: the count says so, as sd_advance leaves it."""
+    a = _sampler("frozen", 4, 6, 3, 4, 12)
+    b = a.buf
+    b.B_active.fill_(9)
+    assert a.den.sdden_run(a.ctx, 0, b.y, b.n, b.chain_id, b.out, b.B_active, b.counters)
+    assert int(b.B_active.item()) == 0 and b.counters.tolist() == [0] * 5

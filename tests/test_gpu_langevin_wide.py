@@ -88,3 +88,12 @@ def test_chains_handed_over_at_ragged_steps(at_end):
         left = int(b.buf.B_active.item())
     assert torch.equal(a.buf.out, b.buf.out) and not bool((b.buf.out == 777.0).any())
     assert a.buf.counters.tolist() == b.buf.counters.tolist() and int(a.buf.B_active.item()) == 0
+
+
+def test_no_chains():
+    """B = 0: the count says so, as sd_advance leaves it."""
+    s = _sampler(W.make_config("c5", B=3, d=1100, M=4, K=5, T=17), 3, 1.0)
+    b = s.buf
+    b.B_active.fill_(9)
+    assert s.ctx.sd_langevin_chains(0, b.y, b.n, b.chain_id, s.means, s.logw, s.comp_std, s.M, s.gamma, b.out, b.B_active, b.counters)
+    assert int(b.B_active.item()) == 0 and b.counters.tolist() == [0] * 5
