@@ -109,9 +109,15 @@ class _SamplerBase:
         finished do nothing.  ``graph`` additionally captures window + advance for a bound in a HIP
         graph (through torch.cuda.CUDAGraph) and replays it: for workloads whose windows are a few
         tens of microseconds of kernels, launch cost is what is left.  Results do not depend on
-        either option (noise is keyed by chain id and step, never by the launch)."""
+        either option (noise is keyed by chain id and step, never by the launch).
+
+        Mixtures of at most 64 components and Langevin chains of more than 1024 coordinates have a form in which the
+        library walks every chain's windows in one launch (``sdden_run``, ``sd_langevin_chains``).  It is taken when
+        nothing between the library's own calls would be seen or changed by anyone else (no stage timer, no ``window``,
+        ``advance``, denoiser or context call replaced); there is no loop then, and both options have no effect.
+        Of the buffers only ``out``, ``B_active`` and ``counters`` are defined after a run."""
         B = self.start(chain_ids, reset_counters)
-        if B > 0 and isinstance(self.timer, _NoTimer) and self._run_chains(B):
+        if B > 0 and isinstance(self.timer, _NoTimer) and self._makes_library_calls() and self._run_chains(B):
             return self.buf.out, self.buf.counters.tolist()
         if windows_per_sync <= 1 and not graph:
             while B > 0:
@@ -139,6 +145,15 @@ class _SamplerBase:
         finally:
             self._set_active(None)
         return b.out, b.counters.tolist()
+
+    def _makes_library_calls(self) -> bool:
+        """Whether the loop would make exactly the calls of ``_LOOP_CALLS``: none replaced by a subclass (of the sampler, the
+        denoiser or the context), on an object, or by a denoiser of the caller's own."""
+        for cls in type(self).__mro__:
+            if cls in _LOOP_CALLS:
+                return all(getattr(getattr(getattr(self, owner) if owner else self, name, None), "__func__", None) is function
+                           for owner, name, function in _LOOP_CALLS[cls])
+        return False
 
     def _run_chains(self, B: int) -> bool:
         """All windows of the started chains in one launch, where the library has such a form for this sampler's denoiser:
@@ -362,3 +377,18 @@ class Phi4LangevinSampler(_SamplerBase):
                 self.ctx.sd_langevin_run_phi4(B, b.y, b.n, b.chain_id, self.L, self.beta, self.gamma,
                                               max(2, self.ctx.T), b.y_out, b.n, b.counters)
         return b.y_out[:B], b.counters.tolist()
+
+
+def _loop_calls():
+    """Per sampler with a one-launch form: what one pass of its loop calls, as (attribute or None for itself, name, function)."""
+    def of(cls, context, denoisers=()):
+        return ([(None, n, getattr(cls, n)) for n in ("window", "advance")] +
+                [("ctx", n, getattr(Context, n)) for n in context + ("sd_advance",)] +
+                [(d, "sdden_eval", Denoiser.sdden_eval) for d in denoisers])
+    return {DiffusionSampler: of(DiffusionSampler, ("sd_draft", "sd_verify"), ("den",)),
+            IndependentDrafterSampler: of(IndependentDrafterSampler, ("sd_draft_step", "sd_verify"), ("den", "draft_den")),
+            EfficientFrozenSampler: of(EfficientFrozenSampler, ("sd_draft", "sd_verify"), ("den",)),
+            LangevinSampler: of(LangevinSampler, ("sd_langevin_window",))}
+
+
+_LOOP_CALLS = _loop_calls()
