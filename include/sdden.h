@@ -76,9 +76,9 @@ int sdden_eval_mirror(sdden* den, int32_t R, const float* X, const uint16_t* Xbf
  * out: out [*, d], row index = chain_id; B_active: dev int32, set to 0; counters: dev int64[5] or NULL, accumulated as in
  *      sd_advance (windows: those of the chain that needed most).  A chain handed over at step T leaves its state in
  *      `out` and counts one chain-window, as there.
- * SD_ERR_UNSUPPORTED, with nothing enqueued, when this denoiser (or draft_den) has no such form, is being timed
- * (sdden_profile) or runs under a device-resident count: the caller then makes the separate calls.  Calls on one context
- * must be ordered, as for sd_langevin_window. */
+ * SD_ERR_UNSUPPORTED, with nothing enqueued, when this denoiser (or draft_den) has no such form or fewer steps than
+ * the chains, is being timed (sdden_profile) or runs under a device-resident count: the caller then makes the separate
+ * calls.  Calls on one context must be ordered, as for sd_langevin_window. */
 int sdden_run(sdden* den, sdden* draft_den, sd_ctx* ctx, int32_t B, const float* y, const int32_t* n,
               const int64_t* chain_id, const float* D_frozen, float* out, int32_t* B_active, int64_t* counters,
               void* stream);

@@ -623,8 +623,12 @@ int sdden_run(sdden* den, sdden* draft_den, sd_ctx* ctx, int32_t B, const float*
   if (B < 0 || !B_active || (ctx->mode == SD_DRAFT_EXPLICIT && !draft_den) ||
       (B > 0 && (!y || !n || !chain_id || !out || (ctx->mode == SD_DRAFT_FROZEN_REUSED && !D_frozen))))
     return sdi::fail(den->err, SD_ERR_ARG, "sdden_run: bad argument");
-  if (den->d != ctx->d || den->T < ctx->T || (ctx->mode == SD_DRAFT_EXPLICIT && (draft_den->d != ctx->d || draft_den->T < ctx->T)))
+  const bool indep = ctx->mode == SD_DRAFT_EXPLICIT;
+  if (den->d != ctx->d || (indep && draft_den->d != ctx->d))
     return sdi::fail(den->err, SD_ERR_ARG, "sdden_run: denoiser and context describe chains of different sizes");
+  // steps the denoiser does not have: sdden_eval masks their rows, the loop goes on with what the buffers hold
+  if (den->T < ctx->T || (indep && draft_den->T < ctx->T))
+    return sdi::fail(den->err, SD_ERR_UNSUPPORTED, "sdden_run: the denoiser has fewer steps than the chains");
   return den->run(draft_den, ctx, B, y, n, chain_id, D_frozen, out, B_active, counters, static_cast<hipStream_t>(stream));
 }
 

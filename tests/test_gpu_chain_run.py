@@ -97,6 +97,30 @@ def test_chains_handed_over_at_ragged_steps(drafter, B, d, M, at_end):
     assert np.max(np.abs(out - ref) / np.maximum(1.0, np.abs(ref).max(axis=1, keepdims=True))) < 1e-5
 
 
+def test_denoiser_of_fewer_steps_than_the_chains():
+    """Rows at a step the denoiser does not have are masked by sdden_eval; the loop over such a denoiser still runs."""
+    import workloads as W
+    from paper_2501_05370_amd.binding import Denoiser
+    from paper_2501_05370_amd.sampler import DiffusionSampler, IndependentDrafterSampler
+    from _gpu import make_context
+    T, d, M, B = 12, 6, 3, 10
+    s = W.cosine_schedule(T)
+    mu, sd, lw = _mixture(np.random.default_rng(1), M, d)
+    den = Denoiser.sdden_gmm_create(mu, sd, lw, s.alpha_bar_state[:10])
+    full = Denoiser.sdden_gmm_create(mu, sd, lw, s.alpha_bar_state)
+    ids = torch.arange(B, device="cuda")
+    for make in (lambda: DiffusionSampler(make_context(s, d, 4, 3), den, B),
+                 lambda: IndependentDrafterSampler(make_context(s, d, 4, 3), full, den, B)):
+        a, b = make(), make()
+        out, counters = a.run(ids)
+        left = b.start(ids)
+        while left > 0:
+            b.window(left)
+            b.advance(left)
+            left = int(b.buf.B_active.item())
+        assert torch.equal(out, b.buf.out) and counters == b.buf.counters.tolist()
+
+
 def test_no_chains():
     """B = 0: the count says so, as sd_advance leaves it."""
     a = _sampler("frozen", 4, 6, 3, 4, 12)
