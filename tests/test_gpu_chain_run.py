@@ -97,6 +97,23 @@ def test_chains_handed_over_at_ragged_steps(drafter, B, d, M, at_end):
     assert np.max(np.abs(out - ref) / np.maximum(1.0, np.abs(ref).max(axis=1, keepdims=True))) < 1e-5
 
 
+def test_widest_rows_of_one_component():
+    """M = 1 pads a row to 2048 coordinates, 16 KiB of LDS per wavefront: four of them and the counters pass 64 KiB."""
+    B, d, K, T = 2048, 1874, 2, 3
+    ids = torch.arange(B, device="cuda")
+    a, b = _sampler("frozen", B, d, 1, K, T), _sampler("frozen", B, d, 1, K, T)
+    a.start(ids)
+    assert a._run_chains(B)
+    left = b.start(ids)
+    while left > 0:
+        b.window(left)
+        b.advance(left)
+        left = int(b.buf.B_active.item())
+    out, ref = host(a.buf.out), host(b.buf.out)
+    assert a.buf.counters.tolist() == b.buf.counters.tolist()
+    assert np.max(np.abs(out - ref) / np.maximum(1.0, np.abs(ref).max(axis=1, keepdims=True))) < 1e-5
+
+
 def test_denoiser_of_fewer_steps_than_the_chains():
     """Rows at a step the denoiser does not have are masked by sdden_eval; the loop over such a denoiser still runs."""
     import workloads as W
