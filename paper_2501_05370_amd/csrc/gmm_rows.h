@@ -120,8 +120,13 @@ __device__ __forceinline__ double responsibility(double q, double base, bool liv
 // Coordinates of a lane: group c, element e -> E * (lane + 64 c) + e.  E * 64 * C >= d.
 // ab, sab = sqrt(ab): signal level of the row's step; base = lane_constant of that step.
 // `x` holds 0 at coordinates >= d; `xs` is wavefront-private LDS of nslots * PARTS doubles.  `tab` (LDS form only): the
-// lane table as (mean, variance) doubles, slot j of lane l at j * kTabStride + l.
-template <int E, int C, bool LDS>
+// lane table as (mean, variance) doubles, slot j of lane l at j * kTabStride + l.  AHEAD (not the LDS form): table entries
+// are requested a group or more ahead of their use, and a scheduling barrier keeps them there.  Left to itself the compiler
+// has one load in flight where registers are short, a memory round trip per entry.  One chain of 64 components, us a step
+// with / without: d = 1800 79 / 208, d = 1000 43 / 54; 1000 rows of d = 1000 81 / 157.  Row evaluations of up to 512
+// coordinates do without it: the compiler keeps their four loads together, and the registers cost more than the latency
+// where many wavefronts share a SIMD (32768 rows, 8 components: d = 200 60 / 58, d = 400 105 / 100).
+template <int E, int C, bool LDS, bool AHEAD>
 __device__ __forceinline__ void posterior_mean(const Model& g, const double2* tab, double* xs, const float (&x)[C][E], double ab,
                                                double sab, double base, int lane, float (&out)[C][E]) {
   const int lp = 6 - g.lm;
@@ -142,29 +147,53 @@ __device__ __forceinline__ void posterior_mean(const Model& g, const double2* ta
   // range holds a product of four variances anywhere in the fp32 range.
   double q = 0.0;
   const double* xp = xs + part;
-  auto pair = [&](int j, double& v, double& nu) {
-    double mu, s2;
-    if (LDS) {
-      const double2 t = tab[j * kTabStride + lane];
-      mu = t.x; s2 = t.y;
-    } else {
-      const float2 t = g.lane_tab[j * 64 + lane];
-      mu = t.x;
-      s2 = static_cast<double>(t.y) * t.y;
-    }
+  auto term = [&](double xj, double mu, double s2, double& v, double& nu) {
     v = fma(ab, s2, om);
-    const double df = fma(-sab, mu, xp[j << lp]);              // a slot past d: 0 - 0
+    const double df = fma(-sab, mu, xj);                       // a slot past d: 0 - 0
     nu = df * df;
   };
+  auto pair = [&](int j, double& v, double& nu) {
+    if (LDS) {
+      const double2 t = tab[j * kTabStride + lane];
+      term(xp[j << lp], t.x, t.y, v, nu);
+    } else {
+      const float2 t = g.lane_tab[j * 64 + lane];
+      term(xp[j << lp], t.x, static_cast<double>(t.y) * t.y, v, nu);
+    }
+  };
+  auto add4 = [&](double v0, double v1, double v2, double v3, double n0, double n1, double n2, double n3) {
+    const double n01 = fma(n0, v1, n1 * v0), v01 = v0 * v1, n23 = fma(n2, v3, n3 * v2), v23 = v2 * v3;
+    q = fma(fma(n01, v23, n23 * v01), reciprocal_one_step(v01 * v23), q);
+  };
   int j = 0;
-  for (; j + 3 < g.nslots; j += 4) {
+  if (AHEAD && g.nslots >= 4) {
+    float2 t[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) t[i] = g.lane_tab[i * 64 + lane];
+    for (; j + 3 < g.nslots; j += 4) {
+      const int jn = j + 7 < g.nslots ? j + 4 : j;
+      float2 next[4];
+      double xj[4], v[4], nu[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) next[i] = g.lane_tab[(jn + i) * 64 + lane];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) xj[i] = xp[(j + i) << lp];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        term(xj[i], t[i].x, static_cast<double>(t[i].y) * t[i].y, v[i], nu[i]);
+        t[i] = next[i];
+      }
+      add4(v[0], v[1], v[2], v[3], nu[0], nu[1], nu[2], nu[3]);
+    }
+  }
+  for (; !AHEAD && j + 3 < g.nslots; j += 4) {
     double v0, v1, v2, v3, n0, n1, n2, n3;
     pair(j, v0, n0);
     pair(j + 1, v1, n1);
     pair(j + 2, v2, n2);
     pair(j + 3, v3, n3);
-    const double n01 = fma(n0, v1, n1 * v0), v01 = v0 * v1, n23 = fma(n2, v3, n3 * v2), v23 = v2 * v3;
-    q = fma(fma(n01, v23, n23 * v01), reciprocal_one_step(v01 * v23), q);
+    add4(v0, v1, v2, v3, n0, n1, n2, n3);
   }
   for (; j < g.nslots; ++j) {
     double v, nu;
@@ -198,6 +227,32 @@ __device__ __forceinline__ void posterior_mean(const Model& g, const double2* ta
       s2 = static_cast<double>(t.y) * t.y;
     }
   };
+  auto add_one = [&](int c, int e, double r0, double mu, double s2) {
+    const double iv = reciprocal_one_step(fma(ab, s2, om));
+    const double df = fma(-sab, mu, static_cast<double>(x[c][e]));
+    acc[c][e] = fma(r0, fma(sab * s2 * iv, df, mu), acc[c][e]);
+  };
+  auto add_four = [&](int c, int e, double r0, double r1, double r2, double r3, double mu0, double mu1, double mu2, double mu3,
+                      double s0, double s1, double s2, double s3) {
+    const double xi = static_cast<double>(x[c][e]);
+    const double v0 = fma(ab, s0, om), v1 = fma(ab, s1, om), v2 = fma(ab, s2, om), v3 = fma(ab, s3, om);
+    const double n0 = r0 * s0 * fma(-sab, mu0, xi), n1 = r1 * s1 * fma(-sab, mu1, xi);
+    const double n2 = r2 * s2 * fma(-sab, mu2, xi), n3 = r3 * s3 * fma(-sab, mu3, xi);
+    const double n01 = fma(n0, v1, n1 * v0), v01 = v0 * v1, n23 = fma(n2, v3, n3 * v2), v23 = v2 * v3;
+    acc[c][e] = fma(r0, mu0, acc[c][e]);
+    acc[c][e] = fma(r1, mu1, acc[c][e]);
+    acc[c][e] = fma(r2, mu2, acc[c][e]);
+    acc[c][e] = fma(r3, mu3, acc[c][e]);
+    acc[c][e] = fma(sab * fma(n01, v23, n23 * v01), reciprocal_one_step(v01 * v23), acc[c][e]);
+  };
+  auto request = [&](int mc, int c, float2 (&to)[E]) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int i = E * (lane + 64 * c) + e;
+      to[e] = g.row_tab[static_cast<int64_t>(mc) * g.d + (i < g.d ? i : 0)];
+    }
+  };
+  auto var = [](float2 t) { return static_cast<double>(t.y) * t.y; };
   while (live) {                           // uniform: the mask is the same on every lane
     // up to four components at a time over a common denominator, as above; a missing one repeats the last with weight 0
     int bit = __builtin_ctzll(live);
@@ -205,17 +260,30 @@ __device__ __forceinline__ void posterior_mean(const Model& g, const double2* ta
     const int m0 = bit >> lp;
     const double r0 = readlane_f64(r, bit);
     if (!live) {
+      if constexpr (AHEAD) {
+        float2 t[3][E];                    // two groups ahead
+        request(m0, 0, t[0]);
+        if (C > 1) request(m0, 1, t[1]);
 #pragma unroll
-      for (int c = 0; c < C; ++c)
+        for (int c = 0; c < C; ++c) {
+          if (c + 2 < C) {
+            request(m0, c + 2, t[(c + 2) % 3]);
+            __builtin_amdgcn_sched_barrier(0);
+          }
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
-          const int i = E * (lane + 64 * c) + e;
-          double mu, s2;
-          at(m0, i < g.d ? i : 0, mu, s2);
-          const double iv = reciprocal_one_step(fma(ab, s2, om));
-          const double df = fma(-sab, mu, static_cast<double>(x[c][e]));
-          acc[c][e] = fma(r0, fma(sab * s2 * iv, df, mu), acc[c][e]);
+          for (int e = 0; e < E; ++e) add_one(c, e, r0, t[c % 3][e].x, var(t[c % 3][e]));
         }
+      } else {
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+#pragma unroll
+          for (int e = 0; e < E; ++e) {
+            const int i = E * (lane + 64 * c) + e;
+            double mu, s2;
+            at(m0, i < g.d ? i : 0, mu, s2);
+            add_one(c, e, r0, mu, s2);
+          }
+      }
       break;
     }
     bit = __builtin_ctzll(live);
@@ -230,27 +298,33 @@ __device__ __forceinline__ void posterior_mean(const Model& g, const double2* ta
     const int m3 = bit >> lp;
     const double r3 = live ? readlane_f64(r, bit) : 0.0;
     live &= live - 1;
+    if constexpr (AHEAD) {
 #pragma unroll
-    for (int c = 0; c < C; ++c)
+      for (int c = 0; c < C; ++c) {        // the four components of a group together
+        float2 t[4][E];
+        request(m0, c, t[0]);
+        request(m1, c, t[1]);
+        request(m2, c, t[2]);
+        request(m3, c, t[3]);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int e = 0; e < E; ++e) {
-        const int i = E * (lane + 64 * c) + e, ii = i < g.d ? i : 0;
-        const double xi = static_cast<double>(x[c][e]);
-        double mu0, mu1, mu2, mu3, s0, s1, s2, s3;
-        at(m0, ii, mu0, s0);
-        at(m1, ii, mu1, s1);
-        at(m2, ii, mu2, s2);
-        at(m3, ii, mu3, s3);
-        const double v0 = fma(ab, s0, om), v1 = fma(ab, s1, om), v2 = fma(ab, s2, om), v3 = fma(ab, s3, om);
-        const double n0 = r0 * s0 * fma(-sab, mu0, xi), n1 = r1 * s1 * fma(-sab, mu1, xi);
-        const double n2 = r2 * s2 * fma(-sab, mu2, xi), n3 = r3 * s3 * fma(-sab, mu3, xi);
-        const double n01 = fma(n0, v1, n1 * v0), v01 = v0 * v1, n23 = fma(n2, v3, n3 * v2), v23 = v2 * v3;
-        acc[c][e] = fma(r0, mu0, acc[c][e]);
-        acc[c][e] = fma(r1, mu1, acc[c][e]);
-        acc[c][e] = fma(r2, mu2, acc[c][e]);
-        acc[c][e] = fma(r3, mu3, acc[c][e]);
-        acc[c][e] = fma(sab * fma(n01, v23, n23 * v01), reciprocal_one_step(v01 * v23), acc[c][e]);
+        for (int e = 0; e < E; ++e)
+          add_four(c, e, r0, r1, r2, r3, t[0][e].x, t[1][e].x, t[2][e].x, t[3][e].x, var(t[0][e]), var(t[1][e]), var(t[2][e]), var(t[3][e]));
       }
+    } else {
+#pragma unroll
+      for (int c = 0; c < C; ++c)
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          const int i = E * (lane + 64 * c) + e, ii = i < g.d ? i : 0;
+          double mu0, mu1, mu2, mu3, s0, s1, s2, s3;
+          at(m0, ii, mu0, s0);
+          at(m1, ii, mu1, s1);
+          at(m2, ii, mu2, s2);
+          at(m3, ii, mu3, s3);
+          add_four(c, e, r0, r1, r2, r3, mu0, mu1, mu2, mu3, s0, s1, s2, s3);
+        }
+    }
   }
 #pragma unroll
   for (int c = 0; c < C; ++c)

@@ -63,8 +63,8 @@ __global__ __launch_bounds__(64 * kRowsPerBlock) void gmm_rows_kernel(GmmArgs p)
       const int i = E * (lane + 64 * c) + e;
       x[c][e] = i < p.g.d ? row[i] : 0.f;
     }
-  sdgmm::posterior_mean<E, C, false>(p.g, nullptr, smem + static_cast<size_t>(wave) * (p.g.nslots << (6 - p.g.lm)), x, st.x, st.y, base,
-                                     lane, y);
+  sdgmm::posterior_mean<E, C, false, (C > 2)>(p.g, nullptr, smem + static_cast<size_t>(wave) * (p.g.nslots << (6 - p.g.lm)), x,
+                                              st.x, st.y, base, lane, y);
   float* o = p.out + static_cast<int64_t>(r) * p.g.d;
 #pragma unroll
   for (int c = 0; c < C; ++c)
@@ -301,7 +301,7 @@ __global__ __launch_bounds__(256) void gmm_run_kernel(RunArgs p) {
         lane_normals<E, C>(nb, zs, p.seed, id, k + 1, lane, z);
         // The step's one target evaluation, at the state it starts from: the frozen prediction of the window (first
         // position of the frozen drafter), else what the draft is tested against.
-        sdgmm::posterior_mean<E, C, LDS>(p.t, tab_t, xs, y, ab, sab, base_t, lane, dq);
+        sdgmm::posterior_mean<E, C, LDS, !LDS>(p.t, tab_t, xs, y, ab, sab, base_t, lane, dq);
         if (frozen && j == 0) {
 #pragma unroll
           for (int c = 0; c < C; ++c)
@@ -309,8 +309,8 @@ __global__ __launch_bounds__(256) void gmm_run_kernel(RunArgs p) {
             for (int e = 0; e < E; ++e) d0[c][e] = dq[c][e];
         }
         if (INDEP)                         // the draft model's prediction
-          sdgmm::posterior_mean<E, C, LDS>(p.q, tab_q, xs, y, sdgmm::readlane_f64(sb.q.x, at), sdgmm::readlane_f64(sb.q.y, at),
-                                           base_q, lane, mp);
+          sdgmm::posterior_mean<E, C, LDS, !LDS>(p.q, tab_q, xs, y, sdgmm::readlane_f64(sb.q.x, at),
+                                                 sdgmm::readlane_f64(sb.q.y, at), base_q, lane, mp);
 #pragma unroll
         for (int c = 0; c < C; ++c)
 #pragma unroll
@@ -395,8 +395,9 @@ __global__ __launch_bounds__(256) void gmm_run_kernel(RunArgs p) {
         } else {
           if (n - sb.base >= 64) sb.refill(p, INDEP, n, id, lane);
           const int at = n - sb.base;
-          sdgmm::posterior_mean<E, C, LDS>(p.t, tab_t, xs, dr, sdgmm::readlane_f64(sb.t.x, at), sdgmm::readlane_f64(sb.t.y, at),
-                                           next_t, lane, d0);     // next_t: step n's, requested when step n - 1 was taken
+          // next_t: step n's, requested when step n - 1 was taken
+          sdgmm::posterior_mean<E, C, LDS, !LDS>(p.t, tab_t, xs, dr, sdgmm::readlane_f64(sb.t.x, at),
+                                                 sdgmm::readlane_f64(sb.t.y, at), next_t, lane, d0);
         }
       }
     }
