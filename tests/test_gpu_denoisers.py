@@ -297,3 +297,29 @@ def test_row_compaction_over_several_workgroups(R, pattern):
     print(f"[row compaction R={R} {pattern}] rows {int((k >= 0).sum())}/{R}, rel err {err:.2e}")
     assert err < 1e-5
     assert np.all(got[k < 0] == 777.0)
+
+
+@pytest.mark.parametrize("d", [1, 63, 64, 65, 300, 1873])
+def test_one_component_rows(d):
+    """One component has its own kernel: the same bits as two equal components of half the weight would give in exact
+    arithmetic (3e-7 as above), and a row that is not finite becomes NaN as a whole and touches no other."""
+    from paper_2501_05370_amd.binding import Denoiser
+    rng = np.random.default_rng(d)
+    T, R = 15, 41
+    ab = as_f32_f64(W.cosine_schedule(T).alpha_bar_state)
+    mu, sd = rng.normal(0, 2.0, (1, d)), rng.uniform(0.2, 1.0, (1, d))
+    one = Denoiser.sdden_gmm_create(mu, sd, np.zeros(1), ab)
+    two = Denoiser.sdden_gmm_create(np.tile(mu, (2, 1)), np.tile(sd, (2, 1)), np.full(2, -np.log(2.0)), ab)
+    x, k = _rows(rng, R, T, d, 2.0)
+    bad = {7: np.nan, 20: np.inf, 40: -np.inf}
+    for r, v in bad.items():
+        x[r, rng.integers(0, d)] = v
+        k[r] = 3
+    xg, kg = f32(x), dev(k, torch.int32)
+    got, ref = [torch.full((R, d), 777.0, dtype=torch.float32, device="cuda") for _ in range(2)]
+    one.sdden_eval(R, xg, kg, got)
+    two.sdden_eval(R, xg, kg, ref)
+    got, ref = host(got), host(ref)
+    finite = np.isfinite(x).all(axis=1)
+    assert np.isnan(got[list(bad)]).all() and np.isnan(ref[list(bad)]).all()
+    assert rel_err(got[finite], ref[finite]) < 3e-7
