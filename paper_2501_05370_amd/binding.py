@@ -338,7 +338,9 @@ class Denoiser:
         h = c_void_p()
         rc = lib.sdden_gmm_create(M, d, mu.ctypes.data, sd.ctypes.data, lw.ctypes.data, ab.shape[0] - 1,
                                   ab.ctypes.data, ctypes.byref(h))
-        return cls(cls._created(rc, h, "sdden_gmm_create"), d)
+        den = cls(cls._created(rc, h, "sdden_gmm_create"), d)
+        den.components = M
+        return den
 
     @classmethod
     def sdden_lowrank_create(cls, mu, U, s2, alpha_bar_state):

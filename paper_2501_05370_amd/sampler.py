@@ -112,12 +112,14 @@ class _SamplerBase:
         either option (noise is keyed by chain id and step, never by the launch).
 
         Mixtures of at most 64 components and Langevin chains of more than 1024 coordinates have a form in which the
-        library walks every chain's windows in one launch (``sdden_run``, ``sd_langevin_chains``).  It is taken when
-        nothing between the library's own calls would be seen or changed by anyone else (no stage timer, no ``window``,
-        ``advance``, denoiser or context call replaced); there is no loop then, and both options have no effect.
+        library walks every chain's windows in one launch (``sdden_run``, ``sd_langevin_chains``).  It is taken, unless
+        the loop is expected to be faster (``_windows_are_faster``), when nothing between the library's own calls would be
+        seen or changed by anyone else (no stage timer, no ``window``, ``advance``, denoiser or context call replaced);
+        there is no loop then, and both options have no effect.
         Of the buffers only ``out``, ``B_active`` and ``counters`` are defined after a run."""
         B = self.start(chain_ids, reset_counters)
-        if B > 0 and isinstance(self.timer, _NoTimer) and self._makes_library_calls() and self._run_chains(B):
+        if (B > 0 and isinstance(self.timer, _NoTimer) and self._makes_library_calls() and
+                not self._prefers_windows(B, graph or windows_per_sync > 1) and self._run_chains(B)):
             return self.buf.out, self.buf.counters.tolist()
         if windows_per_sync <= 1 and not graph:
             while B > 0:
@@ -160,6 +162,10 @@ class _SamplerBase:
         same noise, same decisions, no launches or readback between windows.  False: nothing was done."""
         return False
 
+    def _prefers_windows(self, B: int, batched_readbacks: bool) -> bool:
+        """Whether the loop is the faster of the two where both can run."""
+        return False
+
     def _bound(self, B: int) -> int:
         """Launch bound for B remaining chains: B rounded up to 1/8 steps of the capacity, so that a
         handful of graphs serves a whole run."""
@@ -190,6 +196,26 @@ class _SamplerBase:
         return cache[bound]
 
 
+def _windows_are_faster(ctx: Context, den: Denoiser, B: int, carried: bool, batched_readbacks: bool) -> bool:
+    """Few chains of long predictions: one wavefront per chain predicts position after position, while a window's
+    separate calls predict all of its positions side by side.  The line lies where the positions a window is expected to
+    advance cost one wavefront more than the window costs the separate calls.  In us, fitted to 300 measured runs (64 to
+    1800 coordinates, 1 to 64 components, K = 16 to 64, T = 200 to 1000, 1 to 128 chains; none of them goes to the slower
+    side), with p the (component, coordinate) pairs per lane: a position 2.4 + 0.041 p, 4 more above 1024 coordinates; a
+    window 42 + 0.08 p + 0.4 K (its carried form 34 + 0.04 p + 0.4 K), a little more per row, 20 more with a readback each; its
+    advance about 8 sqrt(T / 200) (64 / d)^0.21, less near K.  One chain, T = 1000, K = 64, us a step in one launch / by
+    windows: d = 64, M = 32 2.3 / 3.7; d = 200, M = 48 10.5 / 5.6; d = 1000, M = 64 44 / 17."""
+    M, K, d = getattr(den, "components", 0), ctx.K, ctx.d
+    if not 1 <= M <= 64 or B * K > 2048:
+        return False
+    pairs = -(-d // (64 >> (M - 1).bit_length()))
+    position = 2.4 + 0.041 * pairs + (4 if d > 1024 else 0)
+    window = ((34 + 0.04 * pairs if carried else 42 + 0.08 * pairs) + 0.4 * K + B * K * (0.006 + 0.000014 * pairs) +
+              (4 if batched_readbacks else 20))
+    advance = 1.0 / (1.0 / K + 1.0 / (8.0 * (ctx.T / 200.0) ** 0.5 * (64.0 / d) ** 0.21))
+    return (advance + carried) * position > window
+
+
 class DiffusionSampler(_SamplerBase):
     def __init__(self, ctx: Context, den: Denoiser, B: int, out_rows: Optional[int] = None):
         self.den = den
@@ -201,6 +227,9 @@ class DiffusionSampler(_SamplerBase):
     def _run_chains(self, B: int) -> bool:
         b = self.buf
         return self.den.sdden_run(self.ctx, B, b.y, b.n, b.chain_id, b.out, b.B_active, b.counters)
+
+    def _prefers_windows(self, B: int, batched_readbacks: bool) -> bool:
+        return _windows_are_faster(self.ctx, self.den, B, False, batched_readbacks)
 
     def window(self, B: int, diagnostics=None):
         """One pass of the while-loop body for the first B chains of the buffers."""
@@ -305,6 +334,9 @@ class EfficientFrozenSampler(_SamplerBase):
     def _run_chains(self, B: int) -> bool:
         b = self.buf
         return self.den.sdden_run(self.ctx, B, b.y, b.n, b.chain_id, b.out, b.B_active, b.counters, D_frozen=b.Dfz)
+
+    def _prefers_windows(self, B: int, batched_readbacks: bool) -> bool:
+        return _windows_are_faster(self.ctx, self.den, B, True, batched_readbacks)
 
     def window(self, B: int, diagnostics=None):
         b, ctx, d, K, t = self.buf, self.ctx, self.ctx.d, self.ctx.K, self.timer

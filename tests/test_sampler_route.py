@@ -134,3 +134,24 @@ def test_a_context_that_changes_a_call(cls, name, calls):
         return getattr(binding.Context, name)(self, *a, **k)
     _make(cls, ctx_cls=type("Traced", (binding.Context,), {name: override})).run(IDS)
     assert seen and "sd_advance" in calls
+
+
+@pytest.mark.parametrize("cls", [DiffusionSampler, EfficientFrozenSampler])
+def test_few_chains_of_long_predictions_take_the_loop(cls, calls):
+    """One chain, long windows, thousands of pairs per wavefront: the separate calls; the sizes of the low-dimensional
+    study, many chains, or a denoiser that does not say how many components it has: one launch."""
+    def launches(components, **kw):
+        calls.clear()
+        s = _make(cls, **kw)
+        s.ctx.T = 1000
+        if components:
+            s.den.components = components
+        s.run(torch.arange(kw.get("B", 2)))
+        return "sdden_run" in calls
+    assert not launches(64, B=1, d=1000, K=16)
+    assert not launches(48, B=4, d=200, K=64)
+    assert launches(64, B=200, d=1000, K=16)
+    assert launches(32, B=1, d=64, K=64)
+    assert launches(8, B=1, d=2, K=4)
+    assert launches(0, B=1, d=1000, K=16)
+    assert launches(65, B=1, d=1000, K=16)               # the library itself says no to these
