@@ -107,15 +107,21 @@ int launch_gemm(const mlpgemm::Args& a, int R, hipStream_t st, std::string& err,
 }
 
 // Which calls take mlp_few_rows.h.  Its workgroups pull the weights once per 64 rows (out of L2 after the first), so its
-// time grows with that product where the LDS tiles of launch_gemm stay flat until they fill the chip.  Measured for
-// the three products, few rows against LDS tiles without their compaction and conversion, in us:
-//   d = 12288, H = 4096 (117 M weights)   100 rows 92 / 171   300 rows 158 / 186   500 rows 211 / 224
-//   d = 3072, H = 1024 (7.3 M)            100 rows 23 / 47    500 rows 34 / 49
-//   d = 1024, H = 512 (1.3 M)             100 rows 14 / 28    500 rows 19 / 28
-// The line lies between the 5 and the 8 tiles of the first size; kMaxRows is what pack_rows_kernel ranks.
+// time grows with that product where the LDS tiles of launch_gemm stay flat until they fill the chip.  Measured, whole
+// calls, few rows / LDS tiles, in us:
+//   d = 12288, H = 4096 (117 M weights)   320 rows 164 / 212   384 rows 177 / 208   (448 rows: LDS tiles 209)
+//   d = 12288, H = 2048 (55 M)            768 rows 165 / 178   832 rows 174 / 161   896 rows 184 / 162
+//   d = 4096, H = 4096 (50 M)             512 rows 83 / 103    768 rows 132 / 132   896 rows 150 / 142
+//   d = 3072, H = 4096 (42 M)             640 rows 104 / 141   832 rows 130 / 129   1024 rows 136 / 132
+//   d = 5120, H = 3072 (41 M)             640 rows 94 / 164    896 rows 139 / 141   1024 rows 142 / 144
+//   d = 8192, H = 2048 (38 M)             768 rows 108 / 125   1024 rows 131 / 137
+//   d = 3072, H = 1024 (7.3 M)            512 rows 32 / 56     1024 rows 45 / 61
+//   d = 256, H = 256 (0.2 M)              512 rows 15 / 25     1024 rows 16 / 26
+// The first line lies between the 6 and the 7 tiles of the first size, the second between 12 and 13 tiles and the 41 and
+// the 42 M weights; kMaxRows is what pack_rows_kernel ranks.
 bool few_rows(int R, int d, int H) {
-  const int64_t weights = static_cast<int64_t>(H) * (2 * static_cast<int64_t>(d) + H);
-  return R <= mlpfew::kMaxRows && ((R + 63) / 64) * weights <= 800000000;
+  const int64_t weights = static_cast<int64_t>(H) * (2 * static_cast<int64_t>(d) + H), tiles = (R + 63) / 64;
+  return R <= mlpfew::kMaxRows && tiles * weights <= 800000000 && (tiles <= 12 || weights <= 41000000);
 }
 
 // Tile of mlp_few_rows.h: rows in steps of 16 up to one tile of 64, and the narrowest of 16, 32 or 64 columns whose
