@@ -2,6 +2,8 @@
 with window + advance captured in a HIP graph must give exactly the results of the plain loop:
 same kernels, same inputs, noise keyed by chain id and step.  Graph replays are repeated, with
 eager work and synchronisations in between, and every run is compared with the eager result.
+Mixtures would take the one-launch form, in which there is no loop: it is switched off on the sampler, and compared
+with the loop at the end (fp64 sums in another order: 1e-5 as in its own tests).
 """
 import numpy as np
 import pytest
@@ -26,19 +28,31 @@ def test_device_count_and_graph_runs_equal_the_eager_run(name, kw, drafter):
     cfg = W.make_config(name, **kw)
     ids = torch.arange(cfg.B, dtype=torch.int64, device="cuda")
     smp = make_sampler(cfg, drafter=drafter)
+    windows = []
+    plain = smp.window
+    smp._run_chains = lambda B: False
+    smp.window = lambda B: (windows.append(B), plain(B))
     out, c0 = smp.run(ids)
+    assert len(windows) == c0[3]
     ref = host(out).copy()
     assert c0[0] == cfg.B * cfg.T
     # several windows per readback, batch size read from the device by every kernel
     out, c1 = smp.run(ids, windows_per_sync=5)
     assert np.array_equal(host(out), ref) and c1 == c0
     # graph replays: three runs, eager work and synchronisations between them
+    windows.clear()
     for rep in range(3):
         out, c2 = smp.run(ids, windows_per_sync=3, graph=True)
         assert np.array_equal(host(out), ref), f"replay run {rep}"
         assert c2 == c0
         scratch = torch.randn(1 << 16, device="cuda").sum().item()      # unrelated eager work + a sync
         assert np.isfinite(scratch)
+    assert 0 < len(windows) <= 9                                        # once per captured batch size
     # and the plain loop still gives the same afterwards (device count switched off again)
     out, c3 = smp.run(ids)
     assert np.array_equal(host(out), ref) and c3 == c0
+    del smp._run_chains, smp.window
+    if cfg.kind == "gmm":
+        out, c4 = smp.run(ids)
+        err = np.max(np.abs(host(out) - ref) / np.maximum(1.0, np.abs(ref).max(axis=1, keepdims=True)))
+        assert c4 == c0 and err < 1e-5
