@@ -42,7 +42,8 @@ int sdden_lowrank_create(int32_t d, int32_t r, const float* mu, const float* U, 
  * host.  Time embedding of width E: emb[i] = sin(k w_i), emb[E/2+i] = cos(k w_i),
  * w_i = 10000^(-2i/E); its product with the last E rows of W1 is folded into a per-step bias
  * table at create time.  Rmax: rows reserved right away (as by sdden_reserve).
- * d and H must be multiples of 256. */
+ * d and H must be multiples of 256.  The denoiser keeps every weight twice on the device, 4 (2 d H + H H) bytes in all: in
+ * the layout of the kernels for many rows and in that of the kernels for few. */
 int sdden_mlp_create(int32_t d, int32_t H, int32_t E, const uint16_t* W1, const float* b1,
                      const uint16_t* W2, const float* b2, const uint16_t* W3, const float* b3,
                      int32_t T, int32_t Rmax, sdden** out);

@@ -2,7 +2,7 @@
 range (1024), widths at the edges of the column rule, masked rows and a device-side chain count, against the oracle.
 
 Tolerance 2e-2 of the row's scale, as for the other MLP tests: bf16 weights and activations, fp32 sums.  Against the
-kernels for many rows the results are the same bits: every kernel sums over k in the same order."""
+kernels for many rows the results are the same bits: every kernel sums over k in one chain and in order."""
 import numpy as np
 import pytest
 import torch
@@ -56,3 +56,22 @@ def test_row_counts_at_tile_edges(d, H):
     out.fill_(777.0)
     g.sdden_eval(R, xg[:R], torch.full((R,), -1, dtype=torch.int32, device="cuda"), out)
     assert bool((out == 777.0).all())
+
+
+def test_every_tile_gives_the_same_bits():
+    """The same rows in calls of every kernel: few rows (64, 1000), 64 x 128 tiles in four and two stages (1025, 4096), 128 x 128
+    (8192), the 256 x 256 kernel of the batched call (10240 rows: 160 tiles of d = H = 1024 in one round of 256 CUs)."""
+    from paper_2501_05370_amd.binding import Denoiser
+    rng = np.random.default_rng(3)
+    d = H = 1024
+    T, R = 25, 10240
+    g = Denoiser.sdden_mlp_create(W.random_mlp(rng, d, H, 16), T, R)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    x = torch.randn(R, d, device="cuda", generator=gen)
+    k = torch.randint(0, T, (R,), device="cuda", generator=gen, dtype=torch.int32)
+    whole = torch.zeros(R, d, device="cuda")
+    g.sdden_eval(R, x, k, whole)
+    for rows in (64, 1000, 1025, 4096, 8192):
+        out = torch.zeros(rows, d, device="cuda")
+        g.sdden_eval(rows, x[:rows], k[:rows], out)
+        assert torch.equal(out, whole[:rows]), rows
