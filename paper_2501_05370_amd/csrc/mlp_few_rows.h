@@ -6,8 +6,9 @@
 // slices.  Here a tile is 16 * MT rows x 16 * NT columns, so 16 columns already give every CU one at N = 4096, and a
 // ring in LDS keeps RING - 1 stages of S steps of 32 k on their way per workgroup (56 KiB for one row tile).
 //
-// Every output is summed over k in one chain, 32 at a time and in order, as the tiles of mlp_gemm.h do, so a
-// prediction has the same bits whatever kernel and however many rows a call has.  Splitting k over the wavefronts of a
+// Every output is summed over k in one chain and in order, as in the tiles of mlp_gemm.h and mlp_gemm_pp.h (32 at a time
+// here and in kernel_pp, 16 in the others), and predictions have come out with the same bits from every one of them,
+// however many rows a call had (tested against each tile; the instruction set does not promise it).  Splitting k over the wavefronts of a
 // workgroup measured 44 us against 51 for one row and 61 against 77 for 64 (the three products at d = 12288,
 // H = 4096), but moves every prediction by 3e-4 (a hidden activation that rounds to the other bf16 moves all that
 // follow), and with it the drafts that are made from it.
@@ -185,9 +186,10 @@ __global__ __launch_bounds__(64 * MT) void kernel(Args p) {
   int slot = 0, free_slot = RING - 1;
   for (int kt = 0; kt < nk; ++kt) {
     // stage kt has landed once only the younger ones are outstanding; past the barrier every wavefront has read stage
-    // kt - 1, whose slot takes stage kt + RING - 1
+    // kt - 1 (a lone one has waited for its reads), whose slot takes stage kt + RING - 1
     wait_stages<OPS, RING - 2>(nk - 1 - kt);
     if (MT > 1) mlpgemm::barrier_keep_loads();
+    else asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     if (kt + RING - 1 < nk) fetch(free_slot, kt + RING - 1);
     const unsigned char* base = ring + slot * kStage + 16 * lane;
     u32x4 a[S], w[S][NT];
