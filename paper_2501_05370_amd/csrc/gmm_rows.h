@@ -42,11 +42,21 @@ __device__ __forceinline__ double reciprocal_one_step(double v) {
   return y * fma(-v, y, 2.0);
 }
 
-// 1/v to fp64 rounding: a second Newton step.
+// 1/v to fp64 rounding: with e = 1 - v y, y (1 + e + e^2) leaves e^3, for one instruction more than the Newton step.
 __device__ __forceinline__ double reciprocal(double v) {
-  const double y = reciprocal_one_step(v);
-  return y * fma(-v, y, 2.0);
+  const double y = __builtin_amdgcn_rcp(v), e = fma(-v, y, 1.0);
+  return fma(y, fma(e, e, e), y);
 }
+template <bool FINE>
+__device__ __forceinline__ double reciprocal_of(double v) {
+  if constexpr (FINE) return reciprocal(v);
+  else return reciprocal_one_step(v);
+}
+
+// Which mixtures keep reciprocal variances to fp64 rounding: those of more than 32 components or of more than 32 pairs per
+// lane, which have always had them so.  (The others had 4e-14 before they had reciprocal_one_step.)  No fp32 result shows
+// the difference: all but 3e-7 of the outputs are the correctly rounded ones with either.
+inline bool needs_fine(int M, int d, int lm) { return M > 32 || (static_cast<int64_t>(d) << lm) > 32 * 64; }
 
 // exp(x) for x <= 0; 0 below -64, where exp(x) < 2^-92 adds nothing to a sum that contains exp(0).
 // x = n ln2 + f, |f| <= ln2 / 2, and the Taylor polynomial of degree 13 (remainder 4e-18), even and odd halves
@@ -126,7 +136,7 @@ __device__ __forceinline__ double responsibility(double q, double base, bool liv
 // with / without: d = 1800 79 / 208, d = 1000 43 / 54; 1000 rows of d = 1000 81 / 157.  Row evaluations of up to 512
 // coordinates do without it: the compiler keeps their four loads together, and the registers cost more than the latency
 // where many wavefronts share a SIMD (32768 rows, 8 components: d = 200 60 / 58, d = 400 105 / 100).
-template <int E, int C, bool LDS, bool AHEAD>
+template <int E, int C, bool LDS, bool AHEAD, bool FINE>
 __device__ __forceinline__ void posterior_mean(const Model& g, const double2* tab, double* xs, const float (&x)[C][E], double ab,
                                                double sab, double base, int lane, float (&out)[C][E]) {
   const int lp = 6 - g.lm;
@@ -163,7 +173,7 @@ __device__ __forceinline__ void posterior_mean(const Model& g, const double2* ta
   };
   auto add4 = [&](double v0, double v1, double v2, double v3, double n0, double n1, double n2, double n3) {
     const double n01 = fma(n0, v1, n1 * v0), v01 = v0 * v1, n23 = fma(n2, v3, n3 * v2), v23 = v2 * v3;
-    q = fma(fma(n01, v23, n23 * v01), reciprocal_one_step(v01 * v23), q);
+    q = fma(fma(n01, v23, n23 * v01), reciprocal_of<FINE>(v01 * v23), q);
   };
   int j = 0;
   if (AHEAD && g.nslots >= 4) {
@@ -198,7 +208,7 @@ __device__ __forceinline__ void posterior_mean(const Model& g, const double2* ta
   for (; j < g.nslots; ++j) {
     double v, nu;
     pair(j, v, nu);
-    q = fma(nu, reciprocal_one_step(v), q);
+    q = fma(nu, reciprocal_of<FINE>(v), q);
   }
   double r;
   switch (g.lm) {                          // uniform: one jump instead of a branch per exchange level
@@ -228,7 +238,7 @@ __device__ __forceinline__ void posterior_mean(const Model& g, const double2* ta
     }
   };
   auto add_one = [&](int c, int e, double r0, double mu, double s2) {
-    const double iv = reciprocal_one_step(fma(ab, s2, om));
+    const double iv = reciprocal_of<FINE>(fma(ab, s2, om));
     const double df = fma(-sab, mu, static_cast<double>(x[c][e]));
     acc[c][e] = fma(r0, fma(sab * s2 * iv, df, mu), acc[c][e]);
   };
@@ -243,7 +253,7 @@ __device__ __forceinline__ void posterior_mean(const Model& g, const double2* ta
     acc[c][e] = fma(r1, mu1, acc[c][e]);
     acc[c][e] = fma(r2, mu2, acc[c][e]);
     acc[c][e] = fma(r3, mu3, acc[c][e]);
-    acc[c][e] = fma(sab * fma(n01, v23, n23 * v01), reciprocal_one_step(v01 * v23), acc[c][e]);
+    acc[c][e] = fma(sab * fma(n01, v23, n23 * v01), reciprocal_of<FINE>(v01 * v23), acc[c][e]);
   };
   auto request = [&](int mc, int c, float2 (&to)[E]) {
 #pragma unroll

@@ -43,7 +43,7 @@ struct GmmArgs {
 // Bound by fp64 issue: 6.5 vector instructions per (component, coordinate) pair of the logit phase, about 11 per
 // coordinate and live component.  32768 rows of 64 coordinates and 32 components: 66 us (80 with the component means of
 // every row kept in registers and exchanged); 2000 rows of 200 and 48: 33 us (88 with a kernel that had no registers for it).
-template <int E, int C>
+template <int E, int C, bool FINE>
 __global__ __launch_bounds__(64 * kRowsPerBlock) void gmm_rows_kernel(GmmArgs p) {
   extern __shared__ double smem[];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -63,8 +63,8 @@ __global__ __launch_bounds__(64 * kRowsPerBlock) void gmm_rows_kernel(GmmArgs p)
       const int i = E * (lane + 64 * c) + e;
       x[c][e] = i < p.g.d ? row[i] : 0.f;
     }
-  sdgmm::posterior_mean<E, C, false, (C > 2)>(p.g, nullptr, smem + static_cast<size_t>(wave) * (p.g.nslots << (6 - p.g.lm)), x,
-                                              st.x, st.y, base, lane, y);
+  double* xs = smem + static_cast<size_t>(wave) * (p.g.nslots << (6 - p.g.lm));
+  sdgmm::posterior_mean<E, C, false, (C > 2), FINE>(p.g, nullptr, xs, x, st.x, st.y, base, lane, y);
   float* o = p.out + static_cast<int64_t>(r) * p.g.d;
 #pragma unroll
   for (int c = 0; c < C; ++c)
@@ -264,7 +264,8 @@ __device__ __forceinline__ float readlane_f32(float v, int src_lane) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), src_lane));
 }
 
-template <int E, int C, bool LDS, bool INDEP>
+// FINE: reciprocal variances to fp64 rounding (sdgmm::needs_fine); the vector caches' form always has them.
+template <int E, int C, bool LDS, bool INDEP, bool FINE>
 __global__ __launch_bounds__(256) void gmm_run_kernel(RunArgs p) {
   extern __shared__ __align__(16) unsigned char run_smem[];
   __shared__ unsigned long long sh_cnt[4];
@@ -328,7 +329,7 @@ __global__ __launch_bounds__(256) void gmm_run_kernel(RunArgs p) {
         lane_normals<E, C>(nb, zs, p.seed, id, k + 1, lane, z);
         // The step's one target evaluation, at the state it starts from: the frozen prediction of the window (first
         // position of the frozen drafter), else what the draft is tested against.
-        sdgmm::posterior_mean<E, C, LDS, !LDS>(p.t, tab_t, xs, y, ab, sab, base_t, lane, dq);
+        sdgmm::posterior_mean<E, C, LDS, !LDS, FINE>(p.t, tab_t, xs, y, ab, sab, base_t, lane, dq);
         if (frozen && j == 0) {
 #pragma unroll
           for (int c = 0; c < C; ++c)
@@ -336,8 +337,8 @@ __global__ __launch_bounds__(256) void gmm_run_kernel(RunArgs p) {
             for (int e = 0; e < E; ++e) d0[c][e] = dq[c][e];
         }
         if (INDEP)                         // the draft model's prediction
-          sdgmm::posterior_mean<E, C, LDS, !LDS>(p.q, tab_q, xs, y, sdgmm::readlane_f64(sb.q.x, at),
-                                                 sdgmm::readlane_f64(sb.q.y, at), base_q, lane, mp);
+          sdgmm::posterior_mean<E, C, LDS, !LDS, FINE>(p.q, tab_q, xs, y, sdgmm::readlane_f64(sb.q.x, at),
+                                                       sdgmm::readlane_f64(sb.q.y, at), base_q, lane, mp);
 #pragma unroll
         for (int c = 0; c < C; ++c)
 #pragma unroll
@@ -423,8 +424,8 @@ __global__ __launch_bounds__(256) void gmm_run_kernel(RunArgs p) {
           if (n - sb.base >= 64) sb.refill(p, INDEP, n, id, lane);
           const int at = n - sb.base;
           // next_t: step n's, requested when step n - 1 was taken
-          sdgmm::posterior_mean<E, C, LDS, !LDS>(p.t, tab_t, xs, dr, sdgmm::readlane_f64(sb.t.x, at),
-                                                 sdgmm::readlane_f64(sb.t.y, at), next_t, lane, d0);
+          sdgmm::posterior_mean<E, C, LDS, !LDS, FINE>(p.t, tab_t, xs, dr, sdgmm::readlane_f64(sb.t.x, at),
+                                                       sdgmm::readlane_f64(sb.t.y, at), next_t, lane, d0);
         }
       }
     }
@@ -465,6 +466,12 @@ __global__ void run_end_kernel(const int32_t* longest, unsigned long long* count
   *B_active = 0;
 }
 
+template <int E, int C>
+void launch_rows(const GmmArgs& p, bool fine, dim3 grid, size_t shmem, hipStream_t st) {
+  if (fine) hipLaunchKernelGGL((gmm_rows_kernel<E, C, true>), grid, dim3(64 * kRowsPerBlock), shmem, st, p);
+  else hipLaunchKernelGGL((gmm_rows_kernel<E, C, false>), grid, dim3(64 * kRowsPerBlock), shmem, st, p);
+}
+
 struct GmmDenoiser final : sdden {
   sdgmm::Model g{};
   float* dev_f = nullptr;     // fp32 tables: row table and lane table, or (more than 64 components) mu, sd, muT, sdT, ab
@@ -486,12 +493,13 @@ struct GmmDenoiser final : sdden {
       hipLaunchKernelGGL(gmm_one_component_kernel, grid, block, 0, st, p);
     } else if (lanes) {
       const size_t shmem = sizeof(double) * kRowsPerBlock * (static_cast<size_t>(g.nslots) << (6 - g.lm));
-      if (d <= 64) hipLaunchKernelGGL((gmm_rows_kernel<1, 1>), grid, block, shmem, st, p);
-      else if (d <= 128) hipLaunchKernelGGL((gmm_rows_kernel<2, 1>), grid, block, shmem, st, p);
-      else if (d <= 256) hipLaunchKernelGGL((gmm_rows_kernel<4, 1>), grid, block, shmem, st, p);
-      else if (d <= 512) hipLaunchKernelGGL((gmm_rows_kernel<4, 2>), grid, block, shmem, st, p);
-      else if (d <= 1024) hipLaunchKernelGGL((gmm_rows_kernel<4, 4>), grid, block, shmem, st, p);
-      else hipLaunchKernelGGL((gmm_rows_kernel<4, 8>), grid, block, shmem, st, p);
+      const bool fine = sdgmm::needs_fine(g.M, d, g.lm);
+      if (d <= 64) launch_rows<1, 1>(p, fine, grid, shmem, st);
+      else if (d <= 128) launch_rows<2, 1>(p, fine, grid, shmem, st);
+      else if (d <= 256) launch_rows<4, 1>(p, fine, grid, shmem, st);
+      else if (d <= 512) launch_rows<4, 2>(p, fine, grid, shmem, st);
+      else if (d <= 1024) launch_rows<4, 4>(p, fine, grid, shmem, st);
+      else hipLaunchKernelGGL((gmm_rows_kernel<4, 8, true>), grid, block, shmem, st, p);
     } else {
       const size_t shmem = sizeof(double) * kRowsPerBlock * static_cast<size_t>(g.M + d);
       hipLaunchKernelGGL(gmm_many_components_kernel, grid, block, shmem, st, p);
@@ -504,10 +512,10 @@ struct GmmDenoiser final : sdden {
           float* out, int32_t* B_active, int64_t* counters, hipStream_t st) override;
 };
 
-template <int E, int C, bool LDS>
+template <int E, int C, bool LDS, bool FINE = !LDS>
 void launch_run(const RunArgs& p, bool indep, unsigned grid, unsigned block, size_t shmem, hipStream_t st) {
-  if (indep) hipLaunchKernelGGL((gmm_run_kernel<E, C, LDS, true>), dim3(grid), dim3(block), shmem, st, p);
-  else hipLaunchKernelGGL((gmm_run_kernel<E, C, LDS, false>), dim3(grid), dim3(block), shmem, st, p);
+  if (indep) hipLaunchKernelGGL((gmm_run_kernel<E, C, LDS, true, FINE>), dim3(grid), dim3(block), shmem, st, p);
+  else hipLaunchKernelGGL((gmm_run_kernel<E, C, LDS, false, FINE>), dim3(grid), dim3(block), shmem, st, p);
 }
 
 int GmmDenoiser::run(sdden* draft, sd_ctx* ctx, int B, const float* y, const int32_t* n, const int64_t* chain_id,
@@ -541,7 +549,10 @@ int GmmDenoiser::run(sdden* draft, sd_ctx* ctx, int B, const float* y, const int
   const bool lds = d <= 256 && table <= 36 * 1024;
   const size_t shmem = xs + (lds ? table : 0);
   hipLaunchKernelGGL(run_begin_kernel, dim3(1), dim3(1), 0, st, p.longest);
+  // a table that fits LDS has at most 32 pairs per lane, and at d > 64 at most 32 components too
+  const bool fine = g.M > 32 || (q && q->g.M > 32);
   if (B == 0) {}                           // no chains: the end kernel leaves the count
+  else if (lds && fine) launch_run<1, 1, true, true>(p, indep, grid, block, shmem, st);
   else if (d <= 64) lds ? launch_run<1, 1, true>(p, indep, grid, block, shmem, st) : launch_run<1, 1, false>(p, indep, grid, block, shmem, st);
   else if (d <= 128) lds ? launch_run<2, 1, true>(p, indep, grid, block, shmem, st) : launch_run<2, 1, false>(p, indep, grid, block, shmem, st);
   else if (d <= 256) lds ? launch_run<4, 1, true>(p, indep, grid, block, shmem, st) : launch_run<4, 1, false>(p, indep, grid, block, shmem, st);
