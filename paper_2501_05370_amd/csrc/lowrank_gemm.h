@@ -6,7 +6,9 @@
 // the six products of order 2^0, 2^-8 and 2^-16 keep everything above 2^-24 of a term, go through v_mfma_f32_16x16x32_bf16
 // with fp32 accumulation, small ones first, and cost 6/16 of the fp32 instruction's time.  Error against fp64 sums
 // (N(0.3, 1) times N(0, 1/K), relative 2-norm, the same K ranges): K = 256 2.3e-7 (fp32 MFMA 2.9e-7), K = 768 4.2e-7
-// (5.0e-7), K = 3072 8.6e-7 (9.8e-7): fewer roundings per term, so slightly closer than the fp32 instruction.
+// (5.0e-7), K = 3072 8.6e-7 (9.8e-7): fewer roundings per term, so slightly closer than the fp32 instruction.  Whole calls,
+// dense bases: rank 1 1.0e-7 (1.3e-7), rank 8 1.2e-7 (1.6e-7), rank 50 2.6e-7 (6.0e-7).  A basis along the axes gives the
+// same bits; one with two entries per column 6.9e-8 (6.4e-8): this instruction rounds its sums down, not to nearest.
 // Truncation cannot overflow; an infinite or NaN input makes its own row NaN (as inf * q of both signs did).
 //
 // Layout.  16 rows x 32 k of a split operand are one block: three pieces of 1 KiB in which lane (l16, lq) of a wavefront
@@ -72,8 +74,11 @@ __host__ __device__ __forceinline__ size_t block_offset(int row, int k, int nk) 
   return (static_cast<size_t>(row >> 4) * nk + (k >> 5)) * kBlockBytes + (((k & 31) >> 3) * 16 + (row & 15)) * 16;
 }
 
-// Eight floats -> three vectors of eight bf16 whose sum is exact: each piece is the upper half of what is left.
+// Eight floats -> three vectors of eight bf16 whose sum is exact: each piece is the upper half of what is left.  No
+// contraction: where x is a product, the first difference would be formed from the unrounded one, and the pieces would add
+// up to the product cut off at 24 bits instead of rounded to them.
 __device__ __forceinline__ void split8(const float (&x)[8], u32x4 (&piece)[3]) {
+#pragma clang fp contract(off)
 #pragma unroll
   for (int h = 0; h < 4; ++h) {
     uint32_t u[2][3];

@@ -53,3 +53,33 @@ def test_row_counts_at_tile_edges(d, r):
         g.sdden_eval(R, xg[:R], kg[:R], out)
         assert torch.equal(out[:117], whole[:117]) and torch.all(out[117:] == 777.0), R
     g.sdden_set_active_count(None, 1)
+
+
+@pytest.mark.parametrize("r,R", [(1, 70), (2, 600), (4, 4096), (33, 4096)])
+def test_axis_aligned_basis_rounds_once_per_operation(r, R):
+    """Columns of U along coordinate axes: the basis holds zeros and ones, both products are exact, and what is left are the
+    roundings of one multiplication (the gain) and one fused multiply-add, the same bits as in numpy.  (The fp64 image of
+    that multiply-add is rounded twice: it can miss the bits once in 2^29.)"""
+    from paper_2501_05370_amd.binding import Denoiser
+    rng = np.random.default_rng(r)
+    d, T, s2 = 80, 25, np.float32(0.01)
+    axes = rng.permutation(d)[:r]
+    U = np.zeros((d, r), np.float32)
+    U[axes, np.arange(r)] = rng.uniform(0.5, 3.0, r)
+    sched = W.cosine_schedule(T)
+    g = Denoiser.sdden_lowrank_create(np.zeros(d), U, s2, sched.alpha_bar_state)
+    g.sdden_reserve(R)
+    k = (np.arange(R) % T).astype(np.int32)
+    x = rng.standard_normal((R, d)).astype(np.float32)
+    out = torch.zeros(R, d, device="cuda")
+    g.sdden_eval(R, f32(x), dev(k, torch.int32), out)
+    ab = np.asarray(sched.alpha_bar_state, np.float32).astype(np.float64)[k][:, None]
+    sab, s2 = np.sqrt(ab), float(s2)
+    ls = (U.astype(np.float64) ** 2).sum(0)[None, :] + s2
+    gperp = sab * s2 / (ab * s2 + 1 - ab)
+    gain = (sab * ls / (ab * ls + 1 - ab) - gperp).astype(np.float32)
+    gperp = gperp.astype(np.float32)
+    want = gperp * x
+    p = gain * x[:, axes]
+    want[:, axes] = (p.astype(np.float64) + gperp.astype(np.float64) * x[:, axes]).astype(np.float32)
+    assert np.array_equal(host(out), want)
