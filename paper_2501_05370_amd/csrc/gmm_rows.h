@@ -319,7 +319,8 @@ __device__ __forceinline__ void posterior_mean(const Model& g, const double2* ta
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int e = 0; e < E; ++e)
-          add_four(c, e, r0, r1, r2, r3, t[0][e].x, t[1][e].x, t[2][e].x, t[3][e].x, var(t[0][e]), var(t[1][e]), var(t[2][e]), var(t[3][e]));
+          add_four(c, e, r0, r1, r2, r3, t[0][e].x, t[1][e].x, t[2][e].x, t[3][e].x, var(t[0][e]), var(t[1][e]), var(t[2][e]),
+                   var(t[3][e]));
       }
     } else {
 #pragma unroll

@@ -26,6 +26,7 @@
 
 #include <cstdint>
 
+#include "lds_ring.h"
 #include "sdden_internal.h"
 
 namespace lrgemm {
@@ -95,23 +96,6 @@ __device__ __forceinline__ void split8(const float (&x)[8], u32x4 (&piece)[3]) {
     for (int q = 0; q < 3; ++q) piece[q][h] = __builtin_amdgcn_perm(u[1][q], u[0][q], 0x07060302u);
   }
 }
-
-// waits until at most N of this wavefront's vector-memory loads are outstanding (they complete in order)
-template <int N>
-__device__ __forceinline__ void wait_loads() {
-  static_assert(N >= 0 && N < 64, "vmcnt is six bits");
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-template <int OPS, int LEFT>
-__device__ __forceinline__ void wait_stages(int left) {      // at most `left` (<= LEFT) stages outstanding
-  if constexpr (LEFT == 0) wait_loads<0>();
-  else {
-    if (left >= LEFT) wait_loads<LEFT * OPS>();
-    else wait_stages<OPS, LEFT - 1>(left);
-  }
-}
-
-__device__ __forceinline__ void barrier_keep_loads() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 template <int WM, int WN, int TM, int TN, int NS, int STAGE>
 struct Shape {
@@ -241,8 +225,8 @@ __global__ __launch_bounds__(64 * WM * WN) void kernel(Args p) {
   for (int kt = 0; kt < nk; ++kt) {
     // slice kt has landed once only the younger ones are outstanding; past the barrier every wavefront has read slice
     // kt - 1, whose slot takes slice kt + NS - 1
-    wait_stages<S::OPS, NS - 2>(nk - 1 - kt);
-    barrier_keep_loads();
+    ldsring::wait_stages<S::OPS, NS - 2>(nk - 1 - kt);
+    ldsring::barrier_keep_loads();
     if (kt + NS - 1 < nk) fetch(free_slot, kt + NS - 1);
     const unsigned char* base = ring + slot * S::kSlice;
     u32x4 a[TM][3];

@@ -8,10 +8,10 @@
 //
 // Every output is summed over k in one chain and in order, as in the tiles of mlp_gemm.h and mlp_gemm_pp.h (32 at a time
 // here and in kernel_pp, 16 in the others), and predictions have come out with the same bits from every one of them,
-// however many rows a call had (tested against each tile; the instruction set does not promise it).  Splitting k over the wavefronts of a
-// workgroup measured 44 us against 51 for one row and 61 against 77 for 64 (the three products at d = 12288,
-// H = 4096), but moves every prediction by 3e-4 (a hidden activation that rounds to the other bf16 moves all that
-// follow), and with it the drafts that are made from it.
+// however many rows a call had (tested against each tile; the instruction set does not promise it).  Splitting k over the
+// wavefronts of a workgroup measured 44 us against 51 for one row and 61 against 77 for 64 (the three products at
+// d = 12288, H = 4096), but moves every prediction by 3e-4 (a hidden activation that rounds to the other bf16 moves all
+// that follow), and with it the drafts that are made from it.
 //
 // Layout.  Both operands are stored in fragment order: 16 rows x 32 k are one block of 1 KiB in which lane (l16, lq)
 // of the wavefront finds its 16 bytes (row l16, k = 8 lq .. 8 lq + 7) at 16 * lane, and the blocks of 16 rows follow
@@ -26,6 +26,7 @@
 //   d = 3072, H = 1024     1 row 17 / 39 us    32 rows 17 / 46    64 rows 20 / 46    200 rows 25 / 48
 // 237 MB of weights in 47 us are 5 TB/s; from 64 rows on it is the operands' path out of L2 that counts.
 #pragma once
+#include "lds_ring.h"
 #include "mlp_gemm.h"
 #include "sdden_internal.h"
 
@@ -129,21 +130,6 @@ struct Args {
   float* outf;              // EPI 3: fp32 [*, N] at source rows
 };
 
-// waits until at most N of this wavefront's vector-memory loads are outstanding (they complete in order)
-template <int N>
-__device__ __forceinline__ void wait_loads() {
-  static_assert(N >= 0 && N < 64, "vmcnt is six bits");
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-template <int OPS, int LEFT>
-__device__ __forceinline__ void wait_stages(int left) {      // at most `left` (<= LEFT) stages outstanding
-  if constexpr (LEFT == 0) wait_loads<0>();
-  else {
-    if (left >= LEFT) wait_loads<LEFT * OPS>();
-    else wait_stages<OPS, LEFT - 1>(left);
-  }
-}
-
 // EPI as in mlp_gemm.h.  Grid: (N / (16 NT), tiles of 16 MT rows), MT wavefronts; wavefront i owns rows 16 i .. 16 i + 15
 // of the tile.  A stage of the ring is S steps of 32 k: per step MT blocks of A, then NT of W.  Rows >= M of the last
 // tile are computed on whatever is there and never stored.
@@ -187,9 +173,9 @@ __global__ __launch_bounds__(64 * MT) void kernel(Args p) {
   for (int kt = 0; kt < nk; ++kt) {
     // stage kt has landed once only the younger ones are outstanding; past the barrier every wavefront has read stage
     // kt - 1 (a lone one has waited for its reads), whose slot takes stage kt + RING - 1
-    wait_stages<OPS, RING - 2>(nk - 1 - kt);
-    if (MT > 1) mlpgemm::barrier_keep_loads();
-    else asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    ldsring::wait_stages<OPS, RING - 2>(nk - 1 - kt);
+    if (MT > 1) ldsring::barrier_keep_loads();
+    else ldsring::wait_reads();
     if (kt + RING - 1 < nk) fetch(free_slot, kt + RING - 1);
     const unsigned char* base = ring + slot * kStage + 16 * lane;
     u32x4 a[S], w[S][NT];

@@ -25,6 +25,8 @@
 
 #include <cstdint>
 
+#include "lds_ring.h"
+
 namespace mlpgemm {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -58,21 +60,8 @@ __device__ __forceinline__ uint16_t to_bf16_bits(float x) {
   return u;
 }
 
-// waits until at most N of this wavefront's vector-memory loads are outstanding (they complete in order)
-template <int N>
-__device__ __forceinline__ void wait_loads() {
-  static_assert(N == 0 || N == 4 || N == 6 || N == 8 || N == 12 || N == 16 || N == 24, "add the count");
-  if constexpr (N == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  if constexpr (N == 4) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-  if constexpr (N == 6) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
-  if constexpr (N == 8) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-  if constexpr (N == 12) asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
-  if constexpr (N == 16) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
-  if constexpr (N == 24) asm volatile("s_waitcnt vmcnt(24)" ::: "memory");
-}
-
-// workgroup barrier that leaves vector-memory loads in flight (LDS traffic of this wavefront is drained)
-__device__ __forceinline__ void barrier_keep_loads() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+using ldsring::barrier_keep_loads;
+using ldsring::wait_loads;
 
 // EPI 1: out = bf16(silu(acc + bias[krow[src]][n]));  EPI 2: out = bf16(silu(acc + bias[n]));
 // EPI 3: outf[src][n] = acc + bias[n].

@@ -18,7 +18,8 @@ struct sd_ctx {
   float* dev_a = nullptr;       // [T] each, one allocation of 3T floats
   float* dev_c = nullptr;
   float* dev_sigma = nullptr;
-  int32_t* dev_queue = nullptr;  // counter behind the schedule: chain dispenser of the Langevin wavefront kernel
+  int32_t* dev_queue = nullptr;  // behind the schedule: [0] chain dispenser of the Langevin wavefront kernel, [1] windows of
+                                 // the longest chain of a one-launch run (sdden_run, sd_langevin_chains)
   int cus = 256;                 // compute units of the context's device
   const int32_t* active = nullptr;
   const float* carry_src = nullptr;    // FROZEN_REUSED: predictions [B,K+1,d] of the window just verified

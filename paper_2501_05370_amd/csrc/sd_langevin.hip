@@ -8,11 +8,11 @@
 //   reject:  x_out = y~_{j-1} - gamma grad E(y~_{j-1}) + sqrt(2 gamma) (z - 2 (z.Delta/|Delta|^2) Delta)
 // with E(x) = -log sum_m w_m N(x; mu_m, s^2 I), grad E = (x - sum_m r_m(x) mu_m) / s^2.
 //
-// Four kernels.  For d <= 128 several chains share a wavefront (langevin_short_kernel), for d <= 1024 a WAVEFRONT owns
-// a chain (langevin_window_wave_kernel), for larger d a workgroup does (langevin_window_kernel).  State, frozen gradient and Delta stay in registers, and because the whole chain lives in
-// one place the walk simply stops at the first rejection: no work is spent on drafts that would be discarded.  The 16
-// logits and the two dot products of a position are summed in fp64.  The phi^4 lattice energy has kernels of its own at
-// the end of the file.
+// Three kernels.  For d <= 128 several chains share a wavefront (langevin_short_kernel), for d <= 1024 a WAVEFRONT owns a
+// chain (langevin_window_wave_kernel), for larger d a workgroup does (langevin_window_kernel).  State, frozen gradient and
+// Delta stay in registers, and because the whole chain lives in one place the walk simply stops at the first rejection: no
+// work is spent on drafts that would be discarded.  The 16 logits and the two dot products of a position are summed in
+// fp64.  The phi^4 lattice energy has kernels of its own at the end of the file.
 #include <hip/hip_runtime.h>
 
 #include <cmath>

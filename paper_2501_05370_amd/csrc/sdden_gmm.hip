@@ -553,9 +553,12 @@ int GmmDenoiser::run(sdden* draft, sd_ctx* ctx, int B, const float* y, const int
   const bool fine = g.M > 32 || (q && q->g.M > 32);
   if (B == 0) {}                           // no chains: the end kernel leaves the count
   else if (lds && fine) launch_run<1, 1, true, true>(p, indep, grid, block, shmem, st);
-  else if (d <= 64) lds ? launch_run<1, 1, true>(p, indep, grid, block, shmem, st) : launch_run<1, 1, false>(p, indep, grid, block, shmem, st);
-  else if (d <= 128) lds ? launch_run<2, 1, true>(p, indep, grid, block, shmem, st) : launch_run<2, 1, false>(p, indep, grid, block, shmem, st);
-  else if (d <= 256) lds ? launch_run<4, 1, true>(p, indep, grid, block, shmem, st) : launch_run<4, 1, false>(p, indep, grid, block, shmem, st);
+  else if (lds && d <= 64) launch_run<1, 1, true>(p, indep, grid, block, shmem, st);
+  else if (lds && d <= 128) launch_run<2, 1, true>(p, indep, grid, block, shmem, st);
+  else if (lds) launch_run<4, 1, true>(p, indep, grid, block, shmem, st);
+  else if (d <= 64) launch_run<1, 1, false>(p, indep, grid, block, shmem, st);
+  else if (d <= 128) launch_run<2, 1, false>(p, indep, grid, block, shmem, st);
+  else if (d <= 256) launch_run<4, 1, false>(p, indep, grid, block, shmem, st);
   else if (d <= 512) launch_run<4, 2, false>(p, indep, grid, block, shmem, st);
   else if (d <= 1024) launch_run<4, 4, false>(p, indep, grid, block, shmem, st);
   else launch_run<4, 8, false>(p, indep, grid, block, shmem, st);

@@ -125,7 +125,8 @@ struct LowRankDenoiser final : sdden {
     if (R > cap_rows)
       return sdi::fail(err, SD_ERR_WORKSPACE, "sdden_eval(lowrank): %d rows exceed the %d reserved (sdden_reserve)", R, cap_rows);
     // Tiles: the largest that still gives every CU work, two workgroups each for the 128 x 128 one (80 KiB of LDS, two
-    // per CU).  Measured, us, K split 4 (d = 3072, r = 256):
+    // per CU).  Measured back to back on one set of rows, us, K split 4 (d = 3072, r = 256; inside a pass, where the rows
+    // come from HBM, the first product takes 34 to 37 at 2048 rows):
     //   first product   20480 rows 128x128 166, 64x64 195    2048 rows 44 / 26    512 rows 64x64 19, 32x32 16, 16x16 23
     //                   133 rows 64x64 18, 32x32 13, 16x16 11
     //   (18000 rows, r = 160, where a second 128-column tile is mostly padding: 128x128 147, 64x64 136)

@@ -153,8 +153,9 @@ struct MlpDenoiser final : sdden {
 
   ~MlpDenoiser() override {
     for (void* q : {static_cast<void*>(W1t), static_cast<void*>(W2t), static_cast<void*>(W3t), static_cast<void*>(F1),
-                    static_cast<void*>(F2), static_cast<void*>(F3), static_cast<void*>(tb), static_cast<void*>(b2), static_cast<void*>(b3), static_cast<void*>(rowidx), static_cast<void*>(count),
-                    static_cast<void*>(Xb), static_cast<void*>(H1), static_cast<void*>(H2)})
+                    static_cast<void*>(F2), static_cast<void*>(F3), static_cast<void*>(tb), static_cast<void*>(b2),
+                    static_cast<void*>(b3), static_cast<void*>(rowidx), static_cast<void*>(count), static_cast<void*>(Xb),
+                    static_cast<void*>(H1), static_cast<void*>(H2)})
       if (q) (void)hipFree(q);
   }
 
