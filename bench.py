@@ -44,7 +44,7 @@ DESCRIPTIONS = {
 # WRITE_SIZE counters, the factors being what the same counters read for a plain device copy), taken from
 # profiles/hbm_traffic_all_kernels_c4.md and _c3.md (mean over the launches of a pass); workloads without such a
 # counter run report null
-MEASURED_TRAFFIC_BYTES = {"c4": 1225.1e6, "c3": 277.8e6}
+MEASURED_TRAFFIC_BYTES = {"c4": 1225.1e6, "c3": 634.6e6}
 
 # published MI355X peaks used as roofline denominators
 PEAK = {"hbm": (8000.0, "GB/s"), "mfma_bf16": (2500.0, "TFLOP/s"),
@@ -55,7 +55,7 @@ PEAK = {"hbm": (8000.0, "GB/s"), "mfma_bf16": (2500.0, "TFLOP/s"),
         "alu_lane": (39.3, "T four-cycle lane-op/s")}
 
 
-def roofline_plan(cfg):
+def roofline_plan(cfg, loop="eager", drafter="frozen"):
     """Which kernel is reported for a workload, how it is timed and its algorithmic work.
 
     Returns dict(kernel, stage or den_which, bound, peak key, work(counters) -> total units)."""
@@ -76,11 +76,16 @@ def roofline_plan(cfg):
                     den_min_rows=cfg.B + 1, bound="mfma", peak="mfma_split", scale=1e-12,
                     work=lambda c: 2.0 * (c[4] - c[1]) * d * rpad)
     if cfg.kind == "gmm":
-        # the analytic denoiser bounds these windows (about 3/4 of the kernel time).  fp64 flops per
-        # (component, coordinate) pair: variance 3, reciprocal counted as 1, x - sqrt(ab) mu 2, quadratic form 3,
-        # gain 2, component mean 2, weighting and the sum over components 2
+        # the analytic denoiser bounds these windows.  fp64 flops per (component, coordinate) pair: variance 3, reciprocal
+        # counted as 1, x - sqrt(ab) mu 2, quadratic form 3, gain 2, component mean 2, weighting and the sum over components 2
         M = cfg.params.means.shape[0]
-        return dict(kernel="gmm_posterior_mean_reg_kernel (mixture posterior mean, fp64) of the batched target call", den_which=1,
+        if loop == "fused":
+            # one prediction per step; the efficient frozen drafter's carried one per window; the draft model's per step
+            rows = {"frozen": lambda c: c[0], "independent": lambda c: 1.5 * c[0]}.get(drafter, lambda c: c[0] + c[1])
+            return dict(kernel="gmm_run_kernel (sdden_run: every chain's windows back to back in one launch, mixture posterior mean in "
+                               "fp64 inside it)", stage="chains_run", bound="alu", peak="alu_fp64", scale=1e-12,
+                        work=lambda c: 15.0 * M * d * rows(c))
+        return dict(kernel="gmm_rows_kernel (mixture posterior mean, fp64) of the batched target call", den_which=1,
                     den_min_rows=cfg.B + 1, bound="alu", peak="alu_fp64", scale=1e-12,
                     work=lambda c: 15.0 * M * d * (c[4] - c[1]))
     if cfg.kind == "langevin":
@@ -126,10 +131,24 @@ def run_gpu(cfg, steps, warmup, stages, drafter="frozen", loop="eager", wps=1, v
     if gemm_variant:
         smp.den.sdden_mlp_select_gemm(gemm_variant)
     ids = torch.arange(cfg.B, dtype=torch.int64, device="cuda")
-    plan = roofline_plan(cfg)
+    plan = roofline_plan(cfg, loop, drafter)
     run_kw = {} if loop in ("eager", "fused") else dict(windows_per_sync=wps, graph=(loop == "graph"))
-    run = smp.run_fused if loop == "fused" else smp.run
-    if loop == "fused":
+    run = smp.run_fused if loop == "fused" and cfg.kind != "gmm" else smp.run
+    chain_events = []
+    if cfg.kind == "gmm":
+        # run() would pick the one-launch form by itself: with --loop fused it is bracketed by events, with the others it is
+        # kept out, so that all passes of a line run the same kernels
+        one_launch = smp._run_chains
+
+        def bracketed(B):
+            pair = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            pair[0].record()
+            done = one_launch(B)
+            pair[1].record()
+            chain_events.append(pair)
+            return done
+        smp._run_chains = bracketed if loop == "fused" else lambda B: False
+    elif loop == "fused":
         plan = dict(plan, stage="langevin_run")
     for w in range(warmup):
         smp.ctx.sd_set_seed(cfg.seed + 1000 + w)
@@ -138,7 +157,7 @@ def run_gpu(cfg, steps, warmup, stages, drafter="frozen", loop="eager", wps=1, v
 
     den = getattr(smp, "den", None)
     events_in_loop = loop in ("eager", "fused")   # per-stage events cannot be recorded into replayed graphs
-    if events_in_loop:
+    if events_in_loop and plan.get("stage") != "chains_run":     # a stage timer would keep run() from the one-launch form
         if stages:
             smp.timer = StageTimer()
         elif "stage" in plan:
@@ -147,6 +166,7 @@ def run_gpu(cfg, steps, warmup, stages, drafter="frozen", loop="eager", wps=1, v
             den.sdden_profile_min_rows(plan.get("den_min_rows", 0))
             den.sdden_profile(plan["den_which"])
     smp.buf.counters.zero_()
+    chain_events.clear()
     torch.cuda.synchronize()
     t0 = time.perf_counter()
     for s in range(steps):
@@ -169,6 +189,9 @@ def run_gpu(cfg, steps, warmup, stages, drafter="frozen", loop="eager", wps=1, v
     else:
         counters_roof = counters
     timed = smp.timer.collect() if hasattr(smp.timer, "collect") else {}
+    if plan.get("stage") == "chains_run":
+        assert len(chain_events) == steps, "the one-launch form was not taken"
+        timed["chains_run"] = (sum(a.elapsed_time(b) for a, b in chain_events), steps, cfg.B * steps)
     if "den_which" in plan:
         k_ms, k_launches = den.sdden_profile_collect()
         den.sdden_profile(0)
@@ -246,14 +269,23 @@ def run_context(cfg, drafter="frozen"):
     del smp
     seq_cfg = W.make_config(cfg.name, K=1)
     seq = make_sampler(seq_cfg)
-    seq.ctx.sd_set_seed(cfg.seed)
-    seq.run(ids)
-    torch.cuda.synchronize()
-    t0 = time.perf_counter()
-    seq.ctx.sd_set_seed(cfg.seed + 1)
-    _, c = seq.run(ids)
-    torch.cuda.synchronize()
-    dt = time.perf_counter() - t0
+
+    def timed_pass():
+        seq.ctx.sd_set_seed(cfg.seed)
+        seq.run(ids)
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        seq.ctx.sd_set_seed(cfg.seed + 1)
+        _, c = seq.run(ids)
+        torch.cuda.synchronize()
+        return time.perf_counter() - t0, c
+
+    if cfg.kind == "gmm":
+        dt, c = timed_pass()
+        out["sequential_gpu_one_launch"] = {"value": round(c[0] / dt, 1), "unit": "diffusion steps/s", "ms_per_pass": round(1e3 * dt, 3),
+                                            "note": "a window of one step inside the one-launch form (sdden_run)"}
+        seq._run_chains = lambda B: False
+    dt, c = timed_pass()
     out["sequential_gpu"] = {"value": round(c[0] / dt, 1), "unit": "diffusion steps/s", "ms_per_pass": round(1e3 * dt, 3),
                              "target_calls_per_pass": c[3],
                              "note": "same kernels with a window of one step: T sequential target calls per chain"}
@@ -564,9 +596,9 @@ def main():
     ap.add_argument("--loop", default=None, choices=["eager", "multi", "graph", "fused"],
                     help="window loop: eager = one host readback of the batch size per window; multi = batch size kept "
                          "on the device, --windows-per-sync windows per readback; graph = multi with window + advance "
-                         "replayed from a HIP graph; fused (c5, phi4) = every chain's windows back to back in one launch "
-                         "(sd_langevin_run: bit-identical results, no compaction needed).  Default: graph for c1, multi for "
-                         "c2 and c3, fused for c5 and phi4 (whichever measured faster), eager for c4 (windows of 2 ms: no difference)")
+                         "replayed from a HIP graph; fused (c1, c2, c5, phi4) = every chain's windows back to back in one launch "
+                         "(sdden_run, sd_langevin_run: no compaction needed).  Default: fused where there is one, multi for c3 "
+                         "(whichever measured faster), eager for c4 (windows of 2 ms: no difference)")
     ap.add_argument("--windows-per-sync", type=int, default=4)
     ap.add_argument("--verify-shape", type=int, default=0,
                     help="launch shape of the accept / reflect kernel in the sampler (sd_set_verify_shape; 0 = default)")
@@ -622,10 +654,10 @@ def main():
     steps = args.steps if args.steps is not None else {"c1": 20, "c2": 10, "c3": 3, "c4": 3, "c5": 2, "phi4": 3}[cfg.name]
     if args.drafter != "frozen" and cfg.kind in ("langevin", "phi4"):
         raise SystemExit("bench.py: the drafter variants are built for the diffusion workloads c1-c4")
-    if args.loop == "fused" and cfg.kind not in ("langevin", "phi4"):
-        raise SystemExit("bench.py: --loop fused is the one-launch form of the Langevin workloads (c5, phi4)")
-    loop = args.loop or ({"c1": "graph", "c2": "multi", "c3": "multi", "c5": "fused", "phi4": "fused"}.get(cfg.name, "eager")
-                         if args.drafter == "frozen" else "eager")
+    if args.loop == "fused" and cfg.kind not in ("gmm", "langevin", "phi4"):
+        raise SystemExit("bench.py: --loop fused is the one-launch form of the mixture and Langevin workloads (c1, c2, c5, phi4)")
+    loop = args.loop or ("fused" if cfg.kind in ("gmm", "langevin", "phi4") else
+                         "multi" if cfg.name == "c3" and args.drafter == "frozen" else "eager")
     # the oracle is timed first: its worker processes are forked, which must not happen once the GPU is initialised
     baseline = None if args.no_cpu_baseline else cpu_baseline(cfg, drafter=args.drafter)
     elapsed, counters, roofline, stage_table = run_gpu(cfg, steps, args.warmup, args.stages, args.drafter, loop,
