@@ -535,7 +535,7 @@ int GmmDenoiser::run(sdden* draft, sd_ctx* ctx, int B, const float* y, const int
   p.carry_last = ctx->carry_rule == SD_CARRY_LAST_ACCEPTED;
   p.counters = reinterpret_cast<unsigned long long*>(counters);
   p.longest = ctx->dev_queue + 1;
-  // Few chains: a workgroup each, spread over the CUs.  From 1024 on four share a workgroup and its table.
+  // Few chains: a workgroup each, spread over the CUs.  From 1024 on two, from 2048 on four share a workgroup and its table.
   const int waves = B >= 2048 ? 4 : (B >= 1024 ? 2 : 1);
   const unsigned grid = static_cast<unsigned>((B + waves - 1) / waves), block = 64u * waves;
   size_t npad = static_cast<size_t>(g.nslots) << (6 - g.lm), slots = g.nslots;
