@@ -20,10 +20,16 @@ FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-fno-gpu-rdc",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wall", "-Wno-unused-function", "-Wno-unknown-warning-option"]
 
+# The loops of these kernels run for a whole chain, and the compiler moves the constants of every logarithm and exponential
+# in them, rare branches included, to registers ahead of the loop: up to a hundred of them, which cost wavefronts or go to
+# scratch memory.
+FILE_FLAGS = {"sd_langevin.hip": ["-mllvm", "-disable-machine-licm"]}
+
 
 def _compile(src: str) -> str:
-    obj = os.path.join(OBJDIR, os.path.basename(src) + ".o")
-    cmd = ["hipcc", *FLAGS, "-c", src, "-o", obj]
+    name = os.path.basename(src)
+    obj = os.path.join(OBJDIR, name + ".o")
+    cmd = ["hipcc", *FLAGS, *FILE_FLAGS.get(name, []), "-c", src, "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"hipcc failed for {src}:\n{r.stdout}\n{r.stderr}")

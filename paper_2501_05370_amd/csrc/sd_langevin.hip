@@ -61,9 +61,65 @@ __device__ __forceinline__ double dpp_xor(double v, int mask) {
 }
 
 // ---------------------------------------------------------------------------------------------
+// While one component holds a state, its logits need not be computed.  The log-odds of component a over m,
+//   l_a(x) - l_m(x) = log w_a - log w_m + (|x - mu_m|^2 - |x - mu_a|^2) / 2 s^2,
+// are linear in x with slope |mu_a - mu_m| / s^2.  With x0 a state where they were computed, they stay above kSoleGap for
+// every m while |x - x0| < min_m (odds_m(x0) - kSoleGap) s^2 / |mu_a - mu_m|; and wherever |x - mu_a| <
+// min_m ((|mu_a - mu_m|^2 / 2 s^2 + log w_a - log w_m) - kSoleGap) s^2 / |mu_a - mu_m|, the ball's radius.  All other
+// responsibilities are then below e^-60 < 1e-25, which the weighted mean skips and the softmax sum rounds away: the
+// responsibility of a is exactly 1, the gradient (x - mu_a) / s^2, the same bits as with all logits.  On mixtures whose
+// components lie a few standard deviations per coordinate apart a chain is in a ball almost all the time; elsewhere the
+// logits are computed as ever.  Distances walked are bounded from above, radii from below: fp32 with a margin far above its
+// rounding.  Whatever is not a number fails the comparison with 0 and takes the long way.
+// ---------------------------------------------------------------------------------------------
+constexpr double kSoleGap = 60.0;
+constexpr float kUp = 1.0001f, kDown = 0.9999f;
+
+struct Sole {
+  float slack = -1.f;        // how far the state may still move with component `top` alone
+  float radius = 0.f;        // of the ball around mu_top
+  float rho = 0.f;           // upper bound of |x - mu_top|
+  int top = -1;              // component the distances belong to
+  __device__ __forceinline__ bool holds() const { return __builtin_amdgcn_readfirstlane(slack > 0.f ? 1 : 0) != 0; }
+  // the state is at (at most) `r` from mu_top
+  __device__ __forceinline__ void at_distance(float r) {
+    rho = r;
+    slack = fmaxf(slack, radius - r);      // the better of two bounds; one that is not a number gives way
+  }
+  __device__ __forceinline__ void moved(float by) {
+    slack -= by;
+    rho += by;
+  }
+};
+
+// Sum over the wavefront in fp32, the same bits on every lane.
+__device__ __forceinline__ float wave_sum_f32(float v) {
+  auto x = [](float u, int mask) {
+    const int b = __float_as_int(u);
+    return __int_as_float(mask == 1 ? sdlane::lane_xor<1>(b) : mask == 2 ? sdlane::lane_xor<2>(b) : mask == 4 ? sdlane::lane_xor<4>(b)
+                          : mask == 8 ? sdlane::lane_xor<8>(b) : mask == 16 ? sdlane::lane_xor<16>(b) : sdlane::lane_xor<32>(b));
+  };
+  v += x(v, 1);
+  v += x(v, 2);
+  v += x(v, 4);
+  v += x(v, 8);
+  v += x(v, 16);
+  return v + x(v, 32);
+}
+
+// Least value over the other components, lane l speaking for component l >> 2; one that is not a number counts as -inf.
+__device__ __forceinline__ float least_of_others(float v, bool other) {
+  v = other ? (v == v ? v : -INFINITY) : INFINITY;
+  v = fminf(v, __int_as_float(sdlane::lane_xor<4>(__float_as_int(v))));
+  v = fminf(v, __int_as_float(sdlane::lane_xor<8>(__float_as_int(v))));
+  v = fminf(v, __int_as_float(sdlane::lane_xor<16>(__float_as_int(v))));
+  return fminf(v, __int_as_float(sdlane::lane_xor<32>(__float_as_int(v))));
+}
+
+// ---------------------------------------------------------------------------------------------
 // One WAVEFRONT per chain (d <= 1024 * CPT/4): no workgroup barrier on the walk at all.
 // A lane owns CPT groups of four coordinates; the mixture means sit in LDS as fp64, once per workgroup
-// (its kWaveChains wavefronts share them; the workgroups stay resident for the whole launch and their
+// (its wavefronts share them; the workgroups stay resident for the whole launch and their
 // wavefronts draw chains from a counter).  Logits use  log w_m + (x.mu_m - |mu_m|^2/2)/s^2  (the |x|^2
 // term cancels in the softmax), so a position costs two passes over the means: 16 dot products and the
 // responsibility-weighted mean.  The 16 per-lane partial dot products are reduced with a transposed
@@ -71,7 +127,10 @@ __device__ __forceinline__ double dpp_xor(double v, int mask) {
 // swaps in the vector ALU); responsibilities are then broadcast through scalar registers.
 // RUN: the chain's windows follow each other inside the kernel (sd_langevin_run).
 // ---------------------------------------------------------------------------------------------
-constexpr int kWaveChains = 8;             // chains (wavefronts) per workgroup: one workgroup fills a CU at 2 per SIMD
+// Wavefronts of the one workgroup a CU holds, as many as the registers of CPT groups of coordinates let reside: 2, 3 or 4 per
+// SIMD.  16384 chains, d = 250 1.85 ms (2.27 with two per SIMD); 8000 chains, d = 400 1.24 (1.43); with few chains the
+// workgroups take a wavefront or two each instead of filling some CUs: 100 chains, d = 201 0.31 (0.40).
+constexpr int wave_chains(int cpt) { return cpt <= 2 ? 16 : cpt == 3 ? 12 : 8; }
 constexpr int kWaveM = 16;                 // components handled by the transposed reduction
 
 // the steps of reduce16_transposed after the first
@@ -102,32 +161,82 @@ __device__ __forceinline__ double readlane_f64(double v, int src_lane) {
   return __longlong_as_double((static_cast<long long>(hi) << 32) | static_cast<unsigned int>(lo));
 }
 
+// Sum over the 16 lanes of a row, the same bits on each.
+__device__ __forceinline__ double row_sum(double v) {
+  v += sdlane::lane_xor<1>(v);
+  v += sdlane::lane_xor<2>(v);
+  v += sdlane::lane_xor<4>(v);
+  return v + sdlane::lane_xor<8>(v);
+}
+__device__ __forceinline__ float row_sum(float v) {
+  v += __int_as_float(sdlane::lane_xor<1>(__float_as_int(v)));
+  v += __int_as_float(sdlane::lane_xor<2>(__float_as_int(v)));
+  v += __int_as_float(sdlane::lane_xor<4>(__float_as_int(v)));
+  return v + __int_as_float(sdlane::lane_xor<8>(__float_as_int(v)));
+}
+
+// Sum over each half of the wavefront.
+__device__ __forceinline__ double half_wave_sum(double v) { return sdlane::pair_sum_rows<16>(row_sum(v)); }
+__device__ __forceinline__ float half_wave_sum(float v) {
+  v = row_sum(v);
+  return v + __int_as_float(sdlane::lane_xor<16>(__float_as_int(v)));
+}
+
+// sdlane::halving_add in fp32
+template <int MASK>
+__device__ __forceinline__ float halving_add_f32(float lower, float upper) {
+  if constexpr (MASK == 32 || MASK == 16) {
+    const sdlane::uint2v r = MASK == 32 ? __builtin_amdgcn_permlane32_swap(__float_as_uint(lower), __float_as_uint(upper), false, false)
+                                        : __builtin_amdgcn_permlane16_swap(__float_as_uint(lower), __float_as_uint(upper), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  } else {
+    const bool up = __lane_id() & MASK;
+    const float keep = up ? upper : lower, send = up ? lower : upper;
+    return keep + __int_as_float(sdlane::lane_xor<MASK>(__float_as_int(send)));
+  }
+}
+
+// As reduce16_transposed: in 16 per-lane sums, out the total of value ((lane >> 2) & 15).
+__device__ __forceinline__ float reduce16_transposed_f32(float (&a)[16]) {
+#pragma unroll
+  for (int i = 0; i < 8; ++i) a[i] = halving_add_f32<32>(a[i], a[i + 8]);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) a[i] = halving_add_f32<16>(a[i], a[i + 4]);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) a[i] = halving_add_f32<8>(a[i], a[i + 2]);
+  float v = halving_add_f32<4>(a[0], a[1]);
+  v += __int_as_float(sdlane::lane_xor<2>(__float_as_int(v)));
+  return v + __int_as_float(sdlane::lane_xor<1>(__float_as_int(v)));
+}
+
 // d > 1024: a workgroup per chain, a thread per group of four coordinates (= one Philox block), up to 1024 threads.
-// What bounds it is one chain's walk, a serial chain of gradients: every chain has its own CU (and at 1024 threads
-// the whole of it), so what counts is the time from one gradient to the next.  Hence one group per thread -- its
-// slice of the 16 means is 64 registers; with four groups per thread of a 256-thread workgroup it was 256 and lived
-// in scratch memory -- and two workgroup barriers per position instead of five: every wavefront adds the partial sums
-// of all and runs the softmax itself, the responsibilities never leave scalar registers, and the partial sums
-// alternate between two buffers.  The position's noise is drawn while the partial sums settle, the window's uniforms
-// once, one position per lane.  200 chains, K = 8, in us a window (before: 256 threads x up to 4 groups): d = 1100 33 (55),
-// d = 2500 44 (458), d = 4000 69 (441).
+// What bounds it is one chain's walk, a serial chain of gradients, and at 1024 threads the issue of its 16 wavefronts.  Hence
+// one group per thread; the means in LDS as fp32 where they fit (else from the caches: held in registers they were 64 of
+// them, and at 1024 threads 60 to 160 others lived in scratch memory); the sums of a position, two to a butterfly, in one
+// exchange over LDS that every wavefront adds up itself; buffers that alternate, so one barrier per exchange; the next
+// position's noise drawn while the sums settle; uniforms 64 steps at a time.  A position has one exchange, and a second one
+// ahead of it (16 squared distances in fp64) only where no component is known to be alone.  Where one was at the last state,
+// fp32 distances with a bound on their error travel with the sums: what they do not confirm is done again the long way.
+// Whole runs, us (before: means in registers, all logits at every position): 200 chains, 60 steps d = 1100 195 (242), d = 2500
+// 232 (322); 500 chains, 60 steps d = 4000 500 (1186); 30 chains, 250 steps d = 4001 741 (1829).
 // MAXT: bound on the workgroup's threads (512, 768 or 1024: 256, 168 or 128 registers per thread).
 // RUN: the chain's windows follow each other inside the kernel, what sd_advance does to the chain between two of them
-// included (the state passes through fp32, so the bits are those of separate calls).  60 steps of those chains: 0.26,
-// 0.34 and 0.59 ms, against 0.86, 1.19 and 1.85 with a launch, a compaction and its share of a readback per window.
-template <int MAXT, bool RUN>
+// included (the state passes through fp32, so the bits are those of separate calls).
+template <int MAXT, bool RUN, bool LDS>
 __global__ __launch_bounds__(MAXT) void langevin_window_kernel(LangevinArgs p) {
-  constexpr int MC = 16, NWMAX = MAXT / 64;
-  __shared__ double sh_part[2][NWMAX][MC];
-  __shared__ double2 sh_s[NWMAX];
+  constexpr int MC = 16, NW = 16;              // slots of the sums over wavefronts; those the launch does not have hold 0
+  extern __shared__ __align__(16) float4 sh_means[];       // LDS: [M][blockDim.x], 0 beyond d
+  __shared__ double sh_part[2][NW][MC];
+  __shared__ float sh_near[2][NW][MC];
+  __shared__ double sh_s[2][2][NW];            // z.Delta, |Delta|^2
+  __shared__ float sh_n[2][2][NW];             // |z|^2, |g|^2
 
   const int b = blockIdx.x;
   const int Bact = p.active ? min(p.B, max(0, *p.active)) : p.B;
   if (b >= Bact) return;                       // uniform over the workgroup
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  int n = p.n[b];
-  int Kt = max(0, min(p.K, p.T - n));
+  int n = __builtin_amdgcn_readfirstlane(p.n[b]);
   const int64_t id = p.id[b];
   const int d = p.d, M = p.M;
   const double gamma = p.gamma, inv_s2 = p.inv_s2;
@@ -135,53 +244,77 @@ __global__ __launch_bounds__(MAXT) void langevin_window_kernel(LangevinArgs p) {
   const int my_m = lane >> 2;                  // component whose totals this lane holds after a reduction
   const double my_logw = my_m < M ? static_cast<double>(p.logw[my_m]) : 0.0;
 
-  // the sums over wavefronts run over all NWMAX slots, unrolled: the slots of wavefronts the launch does not have hold 0
-  for (int q = t; q < 2 * NWMAX * MC; q += blockDim.x) (&sh_part[0][0][0])[q] = 0.0;
-  if (t < NWMAX) sh_s[t] = make_double2(0.0, 0.0);
-  __syncthreads();
+  for (int q = t; q < 2 * NW * MC; q += blockDim.x) {
+    (&sh_part[0][0][0])[q] = 0.0;
+    (&sh_near[0][0][0])[q] = 0.f;
+  }
+  if (t < 4 * NW) {
+    (&sh_s[0][0][0])[t] = 0.0;
+    (&sh_n[0][0][0])[t] = 0.f;
+  }
 
-  // ---- my coordinates, my slice of the means (0 beyond M and d)
+  // ---- my coordinates, my slice of the means (0 beyond d; noise is 0 there too, so state, gradient and Delta stay 0)
   bool own[4];
   double cur[4];                               // y~_{j-1}: the state the target gradient is evaluated at
-  float mu[MC][4];
   const int i0 = 4 * t;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     own[e] = i0 + e < d;
     cur[e] = own[e] ? static_cast<double>(p.x[static_cast<int64_t>(b) * d + i0 + e]) : 0.0;
-#pragma unroll
-    for (int m = 0; m < MC; ++m) mu[m][e] = (own[e] && m < M) ? p.means[static_cast<int64_t>(m) * d + i0 + e] : 0.f;
   }
-
-  // grad E at `cur` for my coordinates, in two parts so that the caller can put work between them.  Uniform control
-  // flow: called by every thread.  A buffer is written again two gradients later, past the barrier of the next one.
-  int buf = 0;
-  auto gradient_begin = [&]() {
-    auto dist2 = [&](int m) {
-      double q = 0.0;
+  auto from_memory = [&](int m) {
+    const float* row = p.means + static_cast<int64_t>(m) * d;
+    return make_float4(own[0] ? row[i0] : 0.f, own[1] ? row[i0 + 1] : 0.f, own[2] ? row[i0 + 2] : 0.f, own[3] ? row[i0 + 3] : 0.f);
+  };
+  if (LDS)
+    for (int m = 0; m < M; ++m) sh_means[m * blockDim.x + t] = from_memory(m);
+  auto mean = [&](int m) { return LDS ? sh_means[m * blockDim.x + t] : from_memory(m); };
+  __syncthreads();
+  auto draw = [&](int k, float (&z)[4]) {
+    sdrng::normal4(p.seed, id, static_cast<uint32_t>(k), sdrng::kStreamNoise, static_cast<uint32_t>(t), z);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        asm volatile("" : "+v"(mu[m][e]));     // keeps the compiler from holding 64 converted copies across the walk
-        const double df = cur[e] - static_cast<double>(mu[m][e]);
-        q = fma(df, df, q);                    // unowned coordinates contribute 0 - 0
-      }
-      return q;
+    for (int e = 0; e < 4; ++e) z[e] = own[e] ? z[e] : 0.f;
+  };
+
+  Sole sole;
+  float per_nat = 0.f, norm_top = 0.f;         // s^2 / |mu_top - mu_{my_m}|, at most; |mu_top|
+  float4 mt = make_float4(0.f, 0.f, 0.f, 0.f);             // mu_top
+  bool near = false;                           // `top` was alone at the last state looked at
+
+  // 16 squared distances between `from` and the means, over the workgroup: lane l holds that of component l >> 2.  A buffer is
+  // written again two calls later, past the barrier of the next one.  Uniform control flow: called by every thread.
+  int buf = 0;
+  auto distances = [&](const double (&from)[4], int self) {
+    auto dist2 = [&](int m) {
+      if (m >= M) return 0.0;
+      const float4 mu = mean(m);
+      const bool own_place = m == self;        // the vector itself in place of its distance from itself
+      const double d0 = from[0] - (own_place ? 0.0 : mu.x), d1 = from[1] - (own_place ? 0.0 : mu.y);
+      const double d2 = from[2] - (own_place ? 0.0 : mu.z), d3 = from[3] - (own_place ? 0.0 : mu.w);
+      return fma(d3, d3, fma(d2, d2, fma(d1, d1, d0 * d0)));               // unowned coordinates contribute 0 - 0
     };
     double q[MC / 2];                          // the first halving step as the sums come, to keep half of them
 #pragma unroll
     for (int m = 0; m < MC / 2; ++m) {
       const double lower = dist2(m), upper = dist2(m + MC / 2);
       q[m] = sdlane::halving_add<32>(lower, upper);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    const double tot = reduce8_transposed(q);
-    if ((lane & 3) == 0) sh_part[buf][wave][my_m] = tot;
-  };
-  auto gradient_end = [&](double g[4]) {
+    const double part = reduce8_transposed(q);
+    if ((lane & 3) == 0) sh_part[buf][wave][my_m] = part;
     __syncthreads();
-    double tot = 0.0;
+    double tot = 0.0;                          // the four lanes of a component add four wavefronts each
 #pragma unroll
-    for (int w = 0; w < NWMAX; ++w) tot += sh_part[buf][w][my_m];
+    for (int w = 0; w < NW; w += 4) tot += sh_part[buf][w + (lane & 3)][my_m];
+    tot += sdlane::lane_xor<1>(tot);
+    tot += sdlane::lane_xor<2>(tot);
     buf ^= 1;
+    return tot;
+  };
+
+  // grad E at `cur`, all logits; every wavefront runs the softmax itself
+  auto gradient = [&](double (&g)[4]) {
+    const double tot = distances(cur, -1);
     const double logit = my_m < M ? my_logw - 0.5 * tot * inv_s2 : -INFINITY;
     double mx = logit;
 #pragma unroll
@@ -195,86 +328,186 @@ __global__ __launch_bounds__(MAXT) void langevin_window_kernel(LangevinArgs p) {
 #pragma unroll
     for (int m = 0; m < MC; ++m) {
       const double r = readlane_f64(r_mine, 4 * m);        // uniform: lives in scalar registers
-      if (r < 1e-25) continue;                 // moves nothing by more than 1e-25 |mu| (see the wavefront kernel)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        asm volatile("" : "+v"(mu[m][e]));
-        bar[e] = fma(r, static_cast<double>(mu[m][e]), bar[e]);
-      }
+      if (r < 1e-25 || m >= M) continue;       // moves nothing by more than 1e-25 |mu| (see the wavefront kernel)
+      const float4 mu = mean(m);
+      bar[0] = fma(r, static_cast<double>(mu.x), bar[0]);
+      bar[1] = fma(r, static_cast<double>(mu.y), bar[1]);
+      bar[2] = fma(r, static_cast<double>(mu.z), bar[2]);
+      bar[3] = fma(r, static_cast<double>(mu.w), bar[3]);
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e) g[e] = (cur[e] - bar[e]) * inv_s2;
+    if (!RUN) return;
+    // is the largest logit alone, and how far does that carry?
+    sole.slack = -1.f;
+    near = false;
+    const unsigned long long at_max = __ballot(logit == mx && my_m < M);
+    const int top = at_max ? __builtin_ctzll(at_max) >> 2 : -1;
+    const bool other = my_m < M && my_m != top;
+    const double gap = mx - logit - kSoleGap;
+    if (top < 0 || __ballot(other && !(gap > 0.0)) != 0ull) return;        // the same in every wavefront
+    near = true;
+    if (top != sole.top) {
+      sole.top = top;
+      mt = mean(top);
+      const double from[4] = {mt.x, mt.y, mt.z, mt.w};
+      const double d2 = distances(from, top);              // |mu_top|^2 in its own place
+      per_nat = 1.f / (static_cast<float>(inv_s2) * (kUp * static_cast<float>(sqrt(d2))));
+      norm_top = kUp * static_cast<float>(sqrt(readlane_f64(d2, 4 * top)));
+      const double odds = 0.5 * d2 * inv_s2 + readlane_f64(my_logw, 4 * top) - my_logw - kSoleGap;
+      sole.radius = kDown * least_of_others(static_cast<float>(odds) * per_nat, other);
+    }
+    sole.slack = kDown * least_of_others(static_cast<float>(gap) * per_nat, other);
   };
 
-  int jr = -1;
+  // One pass of the loop is one position of a window: the gradient at the state (at a window's first position the frozen
+  // one, and the position is accepted: Delta = 0), accept test, new state.  With a sole component it has one barrier.
+  int Kt = max(0, min(p.K, p.T - n)), j = 0, jdone = 0, sbuf = 0;
+  bool rejected = false;
   unsigned long long acc_adv = 0, acc_win = 0, acc_rej = 0, acc_kt = 0;
-  do {                                         // the windows (RUN), each of which advances the chain; Kt is uniform.
-                                               // A chain handed over at step T has one, of no positions: its state stays
-  double g0[4];
-  gradient_begin();
-  // log u of the window's positions: lane j of every wavefront draws position j + 1 (the window has at most 64)
-  const double lu_mine = lane < Kt ? sdrng::log_uniform(p.seed, id, static_cast<uint32_t>(n + lane + 1)) : 0.0;
-  gradient_end(g0);
-
-  jr = -1;
-  double coef = 0.0;
-  double gj[4], dl[4];
+  double g0[4] = {0.0, 0.0, 0.0, 0.0};
+  float gn0 = 0.f;
+  int lu_base = 0;                             // log u of 64 steps, lane l holding step lu_base + l
+  bool lu_have = false;
+  double lu_batch = 0.0;
   float z[4];
-  for (int j = 0; j < Kt; ++j) {               // tests state n+j+1; Kt is uniform over the workgroup
-    if (j > 0) gradient_begin();               // position 1: the target gradient IS g0, Delta = 0
-    sdrng::normal4(p.seed, id, static_cast<uint32_t>(n + j + 1), sdrng::kStreamNoise, static_cast<uint32_t>(t), z);
-    const double lu = readlane_f64(lu_mine, j);
-    double lr = 0.0;
-    bool reject = false;
-    if (j > 0) {
-      gradient_end(gj);
+  if (Kt > 0) draw(n + 1, z);
+  while (Kt > 0) {                             // Kt is uniform; every window advances the chain by at least one step
+    const int k1 = n + j + 1;                  // step this position produces
+    double g[4], dl[4] = {0.0, 0.0, 0.0, 0.0};
+    if (!lu_have || k1 - lu_base >= 64) {
+      lu_base = k1;
+      lu_have = true;
+      lu_batch = sdrng::log_uniform(p.seed, id, static_cast<uint32_t>(k1 + lane));
+    }
+    float z_next[4], zz, gg;
+    double S1, S2;
+    // All branches are uniform: every wavefront holds the same totals.  With `top` alone, or alone at the last state, the
+    // gradient is that of one component; in the second case fp32 distances travel with the sums and confirm it.
+    bool alone = RUN && sole.holds(), confirm = RUN && !alone && near;
+    for (;;) {
+      if (alone || confirm) {
+        g[0] = (cur[0] - static_cast<double>(mt.x)) * inv_s2;
+        g[1] = (cur[1] - static_cast<double>(mt.y)) * inv_s2;
+        g[2] = (cur[2] - static_cast<double>(mt.z)) * inv_s2;
+        g[3] = (cur[3] - static_cast<double>(mt.w)) * inv_s2;
+      } else {
+        gradient(g);
+      }
+      if (j == 0) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) g0[e] = g[e];
+      }
       double a1 = 0.0, a2 = 0.0;
+      zz = gg = 0.f;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        dl[e] = own[e] ? sqg2 * (gj[e] - g0[e]) : 0.0;
+        dl[e] = sqg2 * (g[e] - g0[e]);
         a1 = fma(static_cast<double>(z[e]), dl[e], a1);
         a2 = fma(dl[e], dl[e], a2);
+        zz = fmaf(z[e], z[e], zz);
+        gg = fmaf(static_cast<float>(g[e]), static_cast<float>(g[e]), gg);
       }
-      a1 = wave_sum(a1);
-      a2 = wave_sum(a2);
-      if (lane == 0) sh_s[wave] = make_double2(a1, a2);    // last read ahead of this position's first barrier
-      __syncthreads();
-      double S1 = 0.0, S2 = 0.0;
+      // two sums in one butterfly: the lower half of the wavefront carries the first, the upper half the second
+      const double both = half_wave_sum(sdlane::halving_add<32>(a1, a2));
+      float norms = 0.f;
+      if (RUN) norms = half_wave_sum(halving_add_f32<32>(zz, gg));
+      if ((lane & 31) == 0) {                  // last read two rounds ago
+        sh_s[sbuf][lane >> 5][wave] = both;
+        if (RUN) sh_n[sbuf][lane >> 5][wave] = norms;
+      }
+      if (confirm) {
+        const float x0 = static_cast<float>(cur[0]), x1 = static_cast<float>(cur[1]);
+        const float x2 = static_cast<float>(cur[2]), x3 = static_cast<float>(cur[3]);
+        float q[MC];
 #pragma unroll
-      for (int w = 0; w < NWMAX; ++w) { S1 += sh_s[w].x; S2 += sh_s[w].y; }
+        for (int m = 0; m < MC; ++m) {
+          q[m] = 0.f;
+          if (m >= M) continue;
+          const float4 mu = mean(m);
+          const float d0 = x0 - mu.x, d1 = x1 - mu.y, d2 = x2 - mu.z, d3 = x3 - mu.w;
+          q[m] = fmaf(d3, d3, fmaf(d2, d2, fmaf(d1, d1, d0 * d0)));
+        }
+        const float part = reduce16_transposed_f32(q);
+        if ((lane & 3) == 0) sh_near[sbuf][wave][my_m] = part;
+      }
+      draw(k1 + 1, z_next);                    // the next position's noise, while the sums settle
+      __syncthreads();
+      const double s_half = row_sum(sh_s[sbuf][lane >> 5][lane & 15]);
+      S1 = readlane_f64(s_half, 0);
+      S2 = readlane_f64(s_half, 32);
+      if (RUN) {
+        const float n_half = row_sum(sh_n[sbuf][lane >> 5][lane & 15]);
+        zz = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(n_half), 0));
+        gg = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(n_half), 32));
+      }
+      float dm = 0.f;
+      if (confirm) {
+#pragma unroll
+        for (int w = 0; w < NW; w += 4) dm += sh_near[sbuf][w + (lane & 3)][my_m];
+        dm += __int_as_float(sdlane::lane_xor<1>(__float_as_int(dm)));
+        dm += __int_as_float(sdlane::lane_xor<2>(__float_as_int(dm)));
+      }
+      sbuf ^= 1;
+      if (!confirm) break;
+      // error of an fp32 squared distance D: the sum's roundings (30 of 2^-24 D at most) and those of x (2^-24 |x| each way)
+      const float is2 = static_cast<float>(inv_s2), dt = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(dm), 4 * sole.top));
+      const float rd = __builtin_amdgcn_sqrtf(dm), rt = __builtin_amdgcn_sqrtf(dt);
+      const float err = 1e-5f * (dm + dt) + 1e-6f * (norm_top + rt) * (rd + rt);
+      const float gap = is2 * (0.5f * (dm - dt) - err) + static_cast<float>(readlane_f64(my_logw, 4 * sole.top) - my_logw - kSoleGap);
+      const bool other = my_m < M && my_m != sole.top;
+      if (__ballot(other && !(gap > 0.f)) == 0ull) {
+        sole.slack = kDown * least_of_others(gap * per_nat, other);
+        break;
+      }
+      near = confirm = false;                  // not so (or not certain): the long way
+    }
+    const double lu = readlane_f64(lu_batch, k1 - lu_base);
+    double lr = 0.0, coef = 0.0;
+    bool reject = false;
+    if (j > 0) {
       lr = (-S1 - 0.5 * S2) * p.inv_tau;
       reject = !(S2 == 0.0 || (lr == lr && lu <= fmin(0.0, lr)));   // a log-ratio that is not a number rejects
+      reject = __builtin_amdgcn_readfirstlane(reject ? 1 : 0) != 0;
       coef = S2 > 0.0 ? S1 / S2 : 0.0;
     }
-    if (t == 0) {
+    if (!RUN && t == 0) {
       if (p.logratio) p.logratio[static_cast<int64_t>(b) * p.K + j] = static_cast<float>(lr);
       if (p.logu) p.logu[static_cast<int64_t>(b) * p.K + j] = static_cast<float>(lu);
     }
-    if (reject) {                              // every thread holds the same totals: uniform branch
-      jr = j;
+    if (RUN) {
+      const float gn = kUp * __builtin_amdgcn_sqrtf(gg);
+      if (j == 0) gn0 = gn;
+      if (sole.holds()) sole.at_distance(gn * kUp * static_cast<float>(1.0 / inv_s2));
+      sole.moved(kUp * (static_cast<float>(gamma) * (reject ? gn : gn0) + static_cast<float>(sq2g) * __builtin_amdgcn_sqrtf(zz)));
+    }
+    if (reject) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (own[e]) cur[e] = cur[e] - gamma * gj[e] + sq2g * (static_cast<double>(z[e]) - 2.0 * coef * dl[e]);
-      break;
+      for (int e = 0; e < 4; ++e) cur[e] = cur[e] - gamma * g[e] + sq2g * (static_cast<double>(z[e]) - 2.0 * coef * dl[e]);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) cur[e] = cur[e] - gamma * g0[e] + sq2g * static_cast<double>(z[e]);
     }
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (own[e])                              // unowned slots stay 0 so they never reach a sum
-        cur[e] = cur[e] - gamma * g0[e] + sq2g * static_cast<double>(z[e]);
-  }
+    for (int e = 0; e < 4; ++e) z[e] = z_next[e];
+    ++j;
+    if (!reject && j < Kt) continue;
 
-  if (RUN) {
-    const int jdone = jr >= 0 ? jr + 1 : Kt;
-    n += jdone;
-    acc_adv += jdone; acc_win += 1; acc_rej += jr >= 0 ? 1 : 0; acc_kt += Kt;
+    jdone = j;                                 // end of the window
+    rejected = reject;
+    if (!RUN) break;
+    n += j;
+    j = 0;
+    acc_adv += jdone; acc_win += 1; acc_rej += reject ? 1 : 0; acc_kt += Kt;
     Kt = max(0, min(p.K, p.T - n));
 #pragma unroll
     for (int e = 0; e < 4; ++e) cur[e] = static_cast<double>(static_cast<float>(cur[e]));
+    sole.moved(6.1e-8f * (norm_top + sole.rho));           // half an fp32 unit of the state's length
   }
-  } while (RUN && Kt > 0);
 
   if (RUN) {
     if (t == 0) {
+      if (acc_win == 0) acc_win = 1;           // handed over at T: one window, of no positions
       if (p.counters) {
         atomicAdd(&p.counters[0], acc_adv);
         atomicAdd(&p.counters[1], acc_win);
@@ -284,12 +517,11 @@ __global__ __launch_bounds__(MAXT) void langevin_window_kernel(LangevinArgs p) {
       atomicMax(&p.queue[1], static_cast<int32_t>(acc_win));
     }
   } else if (t == 0) {
-    p.adv[b] = jr >= 0 ? jr + 1 : Kt;
-    if (p.rej) p.rej[b] = jr >= 0 ? 1 : 0;
-    const int jdone = jr >= 0 ? jr + 1 : Kt;   // positions not reached report 0
-    for (int j = jdone; j < p.K; ++j) {
-      if (p.logratio) p.logratio[static_cast<int64_t>(b) * p.K + j] = 0.f;
-      if (p.logu) p.logu[static_cast<int64_t>(b) * p.K + j] = 0.f;
+    p.adv[b] = jdone;
+    if (p.rej) p.rej[b] = rejected ? 1 : 0;
+    for (int q = jdone; q < p.K; ++q) {        // positions not reached report 0
+      if (p.logratio) p.logratio[static_cast<int64_t>(b) * p.K + q] = 0.f;
+      if (p.logu) p.logu[static_cast<int64_t>(b) * p.K + q] = 0.f;
     }
   }
   const int64_t row = RUN ? id : b;            // sd_advance leaves a finished chain's state at its id
@@ -301,8 +533,9 @@ __global__ __launch_bounds__(MAXT) void langevin_window_kernel(LangevinArgs p) {
 // WHOLE: d is a multiple of 4, so a group of four coordinates is inside d or outside it as a whole (one mask
 // per group instead of four).
 template <int CPT, bool WHOLE, bool RUN>
-__global__ __launch_bounds__(64 * kWaveChains, 2) void langevin_window_wave_kernel(LangevinArgs p, int dpad) {
-  // [kWaveM][dpad] as fp64 (rows beyond M and the pad are 0): converted once here instead of once per use --
+__global__ __launch_bounds__(64 * wave_chains(CPT), wave_chains(CPT) / 4) void langevin_window_wave_kernel(LangevinArgs p, int workers) {
+  constexpr int kWaveChains = wave_chains(CPT);
+  // [kWaveM][256 CPT] as fp64 (rows beyond M and the pad are 0): converted once here instead of once per use --
   // the logit pass is one FMA per table element, and a conversion beside each would be a fifth of all
   // vector instructions of the kernel.  16 x 1024 doubles = 128 KiB: one workgroup of 8 wavefronts per CU.
   extern __shared__ __align__(16) double sh_mu[];
@@ -341,6 +574,7 @@ __global__ __launch_bounds__(64 * kWaveChains, 2) void langevin_window_wave_kern
     if ((lane & 3) == 0) sh_hn[lane >> 2] = 0.5 * tot;
   }
   __syncthreads();                                         // last workgroup-wide barrier
+  if (wave >= workers) return;                             // few chains: spread over the CUs, the rest only staged the table
 
   const int Bact = p.active ? min(p.B, max(0, *p.active)) : p.B;
   const double gamma = p.gamma, inv_s2 = p.inv_s2;
@@ -353,14 +587,13 @@ __global__ __launch_bounds__(64 * kWaveChains, 2) void langevin_window_wave_kern
   // workgroup, not once per four chains) and its wavefronts, independent from here on, take chains one at a
   // time from a counter: a chain's window ends at its first rejection, so the work per chain varies by an
   // order of magnitude and a fixed split would leave most of the chip waiting for the unluckiest wavefront.
-  constexpr bool run = RUN;                                // windows back to back: the chain stays in registers
   unsigned long long acc_adv = 0, acc_win = 0, acc_rej = 0, acc_kt = 0;   // run mode: this wavefront's share of the counters
   for (;;) {
   int ticket = 0;
   if (lane == 0) ticket = atomicAdd(&p.queue[0], 1);
   const int b = __builtin_amdgcn_readfirstlane(ticket);
   if (b >= Bact) break;
-  int n = p.n[b];
+  int n = __builtin_amdgcn_readfirstlane(p.n[b]);
   const int64_t id = p.id[b];
 
   bool own[CPT][4];
@@ -370,28 +603,88 @@ __global__ __launch_bounds__(64 * kWaveChains, 2) void langevin_window_wave_kern
     const int i0 = 4 * (lane + 64 * c);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      own[c][e] = WHOLE ? i0 < d : i0 + e < d;
+      own[c][e] = c < CPT - 1 || (WHOLE ? i0 < d : i0 + e < d);    // CPT is the smallest that holds d
       cur[c][e] = own[c][e] ? static_cast<double>(p.x[static_cast<int64_t>(b) * d + i0 + e]) : 0.0;
     }
   }
 
+  Sole sole;
+  float dist_mine = 0.f, norm_top = 0.f;                   // |mu_top - mu_{my_m}|; |mu_top|
+  float gn = 0.f, last = 0.f;                              // upper bound of |g| of the gradient at hand; the last step's length
+
+  auto norm_of = [&](const double g[CPT][4]) {
+    double q = 0.0;
+#pragma unroll
+    for (int c = 0; c < CPT; ++c)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) q = fma(g[c][e], g[c][e], q);
+    return kUp * __builtin_amdgcn_sqrtf(wave_sum_f32(static_cast<float>(q)));
+  };
+
+  // After the logits of `cur`: is the largest one alone, and how far does that carry?
+  auto look_for_sole = [&](double logit, double mx) {
+    const unsigned long long at_max = __ballot(logit == mx && my_m < M);
+    const int top = at_max ? __builtin_ctzll(at_max) >> 2 : -1;
+    const bool other = my_m < M && my_m != top;
+    const double gap = mx - logit - kSoleGap;
+    sole.slack = -1.f;
+    if (top < 0 || __ballot(other && !(gap > 0.0)) != 0ull) return;
+    if (top != sole.top) {
+      sole.top = top;
+      double part[16];
+#pragma unroll
+      for (int m = 0; m < kWaveM; ++m) part[m] = 0.0;
+#pragma unroll 1
+      for (int c = 0; c < 2 * CPT; ++c) {
+        const double2 a = sh_mu2[top * (kRow / 2) + 64 * c + lane];
+#pragma unroll
+        for (int m = 0; m < kWaveM; ++m) {
+          const double2 v = sh_mu2[m * (kRow / 2) + 64 * c + lane];
+          part[m] = fma(a.x - v.x, a.x - v.x, part[m]);
+          part[m] = fma(a.y - v.y, a.y - v.y, part[m]);
+        }
+      }
+      const double d2 = reduce16_transposed(part, lane);
+      dist_mine = kUp * static_cast<float>(sqrt(d2));
+      norm_top = kUp * static_cast<float>(sqrt(2.0 * sh_hn[top]));
+      const double odds = 0.5 * d2 * inv_s2 + readlane_f64(my_logw, 4 * top) - my_logw - kSoleGap;
+      sole.radius = kDown * least_of_others(static_cast<float>(odds / (inv_s2 * dist_mine)), other);
+    }
+    sole.slack = kDown * least_of_others(static_cast<float>(gap / (inv_s2 * dist_mine)), other);
+  };
+
   // grad E at `cur` for my coordinates
   auto gradient = [&](double g[CPT][4]) {
+    if (RUN && sole.holds()) {
+      const int top = __builtin_amdgcn_readfirstlane(sole.top);
+#pragma unroll
+      for (int c = 0; c < CPT; ++c) {
+        const double2 lo = sh_mu2[top * (kRow / 2) + c * 128 + lane], hi = sh_mu2[top * (kRow / 2) + c * 128 + 64 + lane];
+        g[c][0] = (cur[c][0] - lo.x) * inv_s2;
+        g[c][1] = (cur[c][1] - lo.y) * inv_s2;
+        g[c][2] = (cur[c][2] - hi.x) * inv_s2;
+        g[c][3] = (cur[c][3] - hi.y) * inv_s2;
+      }
+      if (__builtin_amdgcn_readfirstlane(sole.slack < 2.5f * last ? 1 : 0))      // about to run out: where in the ball is it?
+        sole.at_distance(norm_of(g) * kUp * static_cast<float>(1.0 / inv_s2));
+      gn = kUp * sole.rho * static_cast<float>(inv_s2);
+      return;
+    }
+    int at = lane;                                         // opaque: the table's reads must not leave the walk's loop
+    asm volatile("" : "+v"(at));
     double dot[16];
 #pragma unroll
     for (int m = 0; m < kWaveM; ++m) dot[m] = 0.0;
 #pragma unroll
-    for (int c = 0; c < CPT; ++c) {                        // 16 independent accumulation chains
-      const int g4 = lane + 64 * c;
-      if (4 * g4 < dpad) {
+    for (int c = 0; c < CPT; ++c) {                        // 16 independent accumulation chains; rows are padded with zeros
 #pragma unroll
-        for (int m = 0; m < kWaveM; ++m) {
-          const double2 lo = sh_mu2[m * (kRow / 2) + c * 128 + lane], hi = sh_mu2[m * (kRow / 2) + c * 128 + 64 + lane];
-          dot[m] = fma(cur[c][0], lo.x, dot[m]);
-          dot[m] = fma(cur[c][1], lo.y, dot[m]);
-          dot[m] = fma(cur[c][2], hi.x, dot[m]);
-          dot[m] = fma(cur[c][3], hi.y, dot[m]);
-        }
+      for (int m = 0; m < kWaveM; ++m) {
+        const double2 lo = sh_mu2[m * (kRow / 2) + c * 128 + at], hi = sh_mu2[m * (kRow / 2) + c * 128 + 64 + at];
+        dot[m] = fma(cur[c][0], lo.x, dot[m]);
+        dot[m] = fma(cur[c][1], lo.y, dot[m]);
+        dot[m] = fma(cur[c][2], hi.x, dot[m]);
+        dot[m] = fma(cur[c][3], hi.y, dot[m]);
+        if (m % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // eight reads in flight: more would not fit the registers
       }
     }
     const double tot = reduce16_transposed(dot, lane);     // x . mu_{my_m}
@@ -399,6 +692,7 @@ __global__ __launch_bounds__(64 * kWaveChains, 2) void langevin_window_wave_kern
     double mx = logit;
 #pragma unroll
     for (int s = 4; s <= 32; s <<= 1) mx = fmax(mx, dpp_xor(mx, s));
+    if (RUN) look_for_sole(logit, mx);
     const double ex = my_m < M ? exp(logit - mx) : 0.0;
     double sum = ex;
 #pragma unroll
@@ -418,53 +712,66 @@ __global__ __launch_bounds__(64 * kWaveChains, 2) void langevin_window_wave_kern
       if (r < 1e-25) continue;
 #pragma unroll
       for (int c = 0; c < CPT; ++c) {
-        const int g4 = lane + 64 * c;
-        if (4 * g4 < dpad) {
-          const double2 lo = sh_mu2[m * (kRow / 2) + c * 128 + lane], hi = sh_mu2[m * (kRow / 2) + c * 128 + 64 + lane];
-          bar[c][0] = fma(r, lo.x, bar[c][0]);
-          bar[c][1] = fma(r, lo.y, bar[c][1]);
-          bar[c][2] = fma(r, hi.x, bar[c][2]);
-          bar[c][3] = fma(r, hi.y, bar[c][3]);
-        }
+        const double2 lo = sh_mu2[m * (kRow / 2) + c * 128 + at], hi = sh_mu2[m * (kRow / 2) + c * 128 + 64 + at];
+        bar[c][0] = fma(r, lo.x, bar[c][0]);
+        bar[c][1] = fma(r, lo.y, bar[c][1]);
+        bar[c][2] = fma(r, hi.x, bar[c][2]);
+        bar[c][3] = fma(r, hi.y, bar[c][3]);
       }
     }
 #pragma unroll
     for (int c = 0; c < CPT; ++c)
 #pragma unroll
       for (int e = 0; e < 4; ++e) g[c][e] = (cur[c][e] - bar[c][e]) * inv_s2;
+    if (RUN) {
+      gn = norm_of(g);
+      if (sole.holds()) sole.at_distance(gn * kUp * static_cast<float>(1.0 / inv_s2));
+    }
   };
 
-  int Kt = 0, jr = -1;
-  for (int w = 0; w < (RUN ? p.max_windows : 1); ++w) {    // every window advances the chain by at least one step
-  Kt = max(0, min(p.K, p.T - n));
-  if ((RUN || w > 0) && Kt == 0) break;                    // the chain has reached T (a chain handed over at T: no window)
+  // One pass of the loop is one position of a window: the gradient at the state (at a window's first position the frozen
+  // one, and the position is accepted: Delta = 0), noise, accept test, new state.
+  int Kt = max(0, min(p.K, p.T - n)), j = 0, jdone = 0, windows = 0;
+  bool rejected = false;
   double g0[CPT][4];
-  gradient(g0);
-
-  // log u of the window's positions: lane j draws position j + 1 (the window has at most 64), once per
-  // window; a draw per position would cost every lane a Philox block and an fp64 log each time
-  const double lu_mine = lane < Kt ? sdrng::log_uniform(p.seed, id, static_cast<uint32_t>(n + lane + 1)) : 0.0;
-
-  jr = -1;
-  double coef = 0.0;
-  double dl[CPT][4];                                       // gradient at the draft, then Delta
-  float z[CPT][4];
-  for (int j = 0; j < Kt; ++j) {                           // Kt is uniform over the wavefront
-    const uint32_t k1 = static_cast<uint32_t>(n + j + 1);
-    double lr = 0.0;
-    bool reject = false;
-    if (j > 0) gradient(dl);                               // position 1: the target gradient IS g0
-    // the noise and the uniform are drawn after the gradient, which is the register-hungry part
+  float gn0 = 0.f;
+  // log u of 64 steps, lane l holding step lu_base + l: they are keyed by the step alone, so a batch outlives its window
+  int lu_base = 0;
+  double lu_batch = 0.0;
+  bool lu_have = false;
+  while (Kt > 0) {                                         // Kt is uniform over the wavefront; every window advances the chain
+    double dl[CPT][4];                                     // gradient at the draft, then Delta
+    gradient(dl);
+    const int k1 = n + j + 1;                              // step this position produces
+    if (!lu_have || k1 - lu_base >= 64) {
+      lu_base = k1;
+      lu_have = true;
+      lu_batch = sdrng::log_uniform(p.seed, id, static_cast<uint32_t>(k1 + lane));
+    }
+    // the noise is drawn after the gradient, which is the register-hungry part
     // Coordinates past d (the tail of the last group) get no noise: their state starts at 0 and the means table
     // is 0 there, so state, gradients and Delta stay exactly 0 and need no masking anywhere else.
+    float z[CPT][4], zn = 0.f;                             // zn: |z|, which the reflection keeps
 #pragma unroll
     for (int c = 0; c < CPT; ++c) {
-      sdrng::normal4(p.seed, id, k1, sdrng::kStreamNoise, static_cast<uint32_t>(lane + 64 * c), z[c]);
+      sdrng::normal4(p.seed, id, static_cast<uint32_t>(k1), sdrng::kStreamNoise, static_cast<uint32_t>(lane + 64 * c), z[c]);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) z[c][e] = own[c][e] ? z[c][e] : 0.f;
+      for (int e = 0; e < 4; ++e) {
+        z[c][e] = own[c][e] ? z[c][e] : 0.f;
+        if (RUN) zn = fmaf(z[c][e], z[c][e], zn);
+      }
     }
-    const double lu = readlane_f64(lu_mine, j);
-    if (j > 0) {
+    if (RUN) zn = __builtin_amdgcn_sqrtf(wave_sum_f32(zn));
+    const double lu = readlane_f64(lu_batch, k1 - lu_base);
+    double lr = 0.0, coef = 0.0;
+    bool reject = false;
+    if (j == 0) {
+      gn0 = gn;
+#pragma unroll
+      for (int c = 0; c < CPT; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) g0[c][e] = dl[c][e];
+    } else {
       double a1 = 0.0, a2 = 0.0;
 #pragma unroll
       for (int c = 0; c < CPT; ++c)
@@ -477,52 +784,61 @@ __global__ __launch_bounds__(64 * kWaveChains, 2) void langevin_window_wave_kern
       const double S1 = wave_sum(a1), S2 = wave_sum(a2);
       lr = (-S1 - 0.5 * S2) * p.inv_tau;
       reject = !(S2 == 0.0 || (lr == lr && lu <= fmin(0.0, lr)));   // a log-ratio that is not a number rejects
+      reject = __builtin_amdgcn_readfirstlane(reject ? 1 : 0) != 0;   // all lanes hold the same totals
       coef = S2 > 0.0 ? S1 / S2 : 0.0;
     }
-    if (lane == 0) {
+    if (!RUN && lane == 0) {
       if (p.logratio) p.logratio[static_cast<int64_t>(b) * p.K + j] = static_cast<float>(lr);
       if (p.logu) p.logu[static_cast<int64_t>(b) * p.K + j] = static_cast<float>(lu);
     }
-    if (reject) {                                          // all lanes hold the same totals
-      jr = j;
+    if (RUN) {
+      last = kUp * (static_cast<float>(gamma) * (reject ? gn : gn0) + static_cast<float>(sq2g) * zn);
+      sole.moved(last);
+    }
+    if (reject) {
 #pragma unroll
       for (int c = 0; c < CPT; ++c)
 #pragma unroll
         for (int e = 0; e < 4; ++e)
           cur[c][e] = cur[c][e] - gamma * (g0[c][e] + dl[c][e] * inv_sqg2) +   // target gradient = g0 + Delta / sqrt(gamma/2)
                       sq2g * (static_cast<double>(z[c][e]) - 2.0 * coef * dl[c][e]);
-      break;
+    } else {
+#pragma unroll
+      for (int c = 0; c < CPT; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          cur[c][e] = cur[c][e] - gamma * g0[c][e] + sq2g * static_cast<double>(z[c][e]);
     }
-#pragma unroll
-    for (int c = 0; c < CPT; ++c)
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        cur[c][e] = cur[c][e] - gamma * g0[c][e] + sq2g * static_cast<double>(z[c][e]);
-  }
+    ++j;
+    if (!reject && j < Kt) continue;
 
-  if (run) {
+    // end of the window
+    jdone = j;
+    rejected = reject;
+    if (!RUN) break;
     // what sd_advance and the next sd_langevin_window would do: the step count moves on and the state passes
     // through fp32, so a run is bit for bit the window entry point applied again and again
-    const int jdone = jr >= 0 ? jr + 1 : Kt;
-    n += jdone;
-    acc_adv += jdone; acc_win += 1; acc_rej += jr >= 0 ? 1 : 0; acc_kt += Kt;
+    n += j;
+    j = 0;
+    ++windows;
+    acc_adv += jdone; acc_win += 1; acc_rej += reject ? 1 : 0; acc_kt += Kt;
 #pragma unroll
     for (int c = 0; c < CPT; ++c)
 #pragma unroll
       for (int e = 0; e < 4; ++e) cur[c][e] = static_cast<double>(static_cast<float>(cur[c][e]));
+    sole.moved(6.1e-8f * (norm_top + sole.rho));           // half an fp32 unit of the state's length
+    Kt = windows < p.max_windows ? max(0, min(p.K, p.T - n)) : 0;
   }
-  }                                                        // next window of this chain
 
   if (lane == 0) {
-    if (run) {
+    if (RUN) {
       p.n_out[b] = n;
     } else {
-      p.adv[b] = jr >= 0 ? jr + 1 : Kt;
-      if (p.rej) p.rej[b] = jr >= 0 ? 1 : 0;
-      const int jdone = jr >= 0 ? jr + 1 : Kt;
-      for (int j = jdone; j < p.K; ++j) {
-        if (p.logratio) p.logratio[static_cast<int64_t>(b) * p.K + j] = 0.f;
-        if (p.logu) p.logu[static_cast<int64_t>(b) * p.K + j] = 0.f;
+      p.adv[b] = jdone;
+      if (p.rej) p.rej[b] = rejected ? 1 : 0;
+      for (int q = jdone; q < p.K; ++q) {                  // positions not reached report 0
+        if (p.logratio) p.logratio[static_cast<int64_t>(b) * p.K + q] = 0.f;
+        if (p.logu) p.logu[static_cast<int64_t>(b) * p.K + q] = 0.f;
       }
     }
   }
@@ -534,7 +850,7 @@ __global__ __launch_bounds__(64 * kWaveChains, 2) void langevin_window_wave_kern
       if (own[c][e]) p.x_out[static_cast<int64_t>(b) * d + i0 + e] = static_cast<float>(cur[c][e]);
   }
   }                                                        // next chain of this wavefront
-  if (run && p.counters && lane == 0 && acc_win) {
+  if (RUN && p.counters && lane == 0 && acc_win) {
     atomicAdd(&p.counters[0], acc_adv);
     atomicAdd(&p.counters[1], acc_win);
     atomicAdd(&p.counters[2], acc_rej);
@@ -794,12 +1110,28 @@ __global__ void chains_end_kernel(const int32_t* longest, unsigned long long* co
 }
 
 // The workgroup-per-chain kernel at the thread count of the row length.
+constexpr int kWideMeansLds = 148 * 1024;  // of 160 KiB; the sums' buffers take 8
+
+template <int MAXT, bool RUN>
+void launch_wide(const LangevinArgs& p, dim3 block, hipStream_t st) {
+  const dim3 grid(static_cast<unsigned>(p.B));
+  const size_t means = sizeof(float4) * p.M * block.x;
+  if (means <= kWideMeansLds) hipLaunchKernelGGL((langevin_window_kernel<MAXT, RUN, true>), grid, block, means, st, p);
+  else hipLaunchKernelGGL((langevin_window_kernel<MAXT, RUN, false>), grid, block, 0, st, p);
+}
+
 template <bool RUN>
 void launch_wide(const LangevinArgs& p, int groups, hipStream_t st) {
-  const dim3 grid(static_cast<unsigned>(p.B)), block(static_cast<unsigned>((groups + 63) / 64 * 64));
-  if (block.x <= 512) hipLaunchKernelGGL((langevin_window_kernel<512, RUN>), grid, block, 0, st, p);
-  else if (block.x <= 768) hipLaunchKernelGGL((langevin_window_kernel<768, RUN>), grid, block, 0, st, p);
-  else hipLaunchKernelGGL((langevin_window_kernel<1024, RUN>), grid, block, 0, st, p);
+  const dim3 block(static_cast<unsigned>((groups + 63) / 64 * 64));
+  if (block.x <= 512) launch_wide<512, RUN>(p, block, st);
+  else if (block.x <= 768) launch_wide<768, RUN>(p, block, st);
+  else launch_wide<1024, RUN>(p, block, st);
+}
+
+template <int MAXT, bool RUN>
+hipError_t prepare_wide() {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&langevin_window_kernel<MAXT, RUN, true>),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, kWideMeansLds);
 }
 
 // run mode: one launch counts as one entry of the `windows` counter
@@ -814,12 +1146,14 @@ hipError_t prepare_wave() {
 // prepare_wave<...>() has run for every instantiation when the context was created (sdi::langevin_prepare);
 // `resident` = workgroups the chip holds at once (one per CU), from the same call.
 template <int CPT, bool WHOLE, bool RUN>
-hipError_t launch_wave(const LangevinArgs& p, int dpad, int resident, hipStream_t st) {
+hipError_t launch_wave(const LangevinArgs& p, int resident, hipStream_t st) {
   const size_t shmem = sizeof(double) * kWaveM * static_cast<size_t>(256 * CPT);
-  const int groups = (p.B + kWaveChains - 1) / kWaveChains;
+  const int per_cu = (p.B + resident - 1) / resident;
+  const int workers = per_cu < wave_chains(CPT) ? per_cu : wave_chains(CPT);
+  const int groups = (p.B + workers - 1) / workers;
   const unsigned grid = static_cast<unsigned>(groups < resident ? groups : resident);
   hipLaunchKernelGGL(reset_queue_kernel, dim3(1), dim3(1), 0, st, p.queue, 0);
-  hipLaunchKernelGGL((langevin_window_wave_kernel<CPT, WHOLE, RUN>), dim3(grid), dim3(64 * kWaveChains), shmem, st, p, dpad);
+  hipLaunchKernelGGL((langevin_window_wave_kernel<CPT, WHOLE, RUN>), dim3(grid), dim3(64 * wave_chains(CPT)), shmem, st, p, workers);
   return hipGetLastError();
 }
 
@@ -1157,6 +1491,11 @@ hipError_t sdi::langevin_prepare(int* cus) {
   if (e == hipSuccess) e = prepare_wave<c_, true, true>();
   SD_PREP(1) SD_PREP(2) SD_PREP(3) SD_PREP(4)
 #undef SD_PREP
+#define SD_PREP(t_) \
+  if (e == hipSuccess) e = prepare_wide<t_, false>(); \
+  if (e == hipSuccess) e = prepare_wide<t_, true>();
+  SD_PREP(512) SD_PREP(768) SD_PREP(1024)
+#undef SD_PREP
   int dev = 0, n = 0;
   if (e == hipSuccess) e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev);
@@ -1205,22 +1544,22 @@ int langevin_launch(const char* who, sd_ctx* ctx, int32_t B, const float* x, con
     const bool whole = ctx->d % 4 == 0;
     const int sel = ((groups + 63) / 64 - 1) * 4 + (whole ? 2 : 0) + (max_windows > 1 ? 1 : 0);
     switch (sel) {
-      case 0: e = launch_wave<1, false, false>(p, dpad, ctx->cus, st); break;
-      case 1: e = launch_wave<1, false, true>(p, dpad, ctx->cus, st); break;
-      case 2: e = launch_wave<1, true, false>(p, dpad, ctx->cus, st); break;
-      case 3: e = launch_wave<1, true, true>(p, dpad, ctx->cus, st); break;
-      case 4: e = launch_wave<2, false, false>(p, dpad, ctx->cus, st); break;
-      case 5: e = launch_wave<2, false, true>(p, dpad, ctx->cus, st); break;
-      case 6: e = launch_wave<2, true, false>(p, dpad, ctx->cus, st); break;
-      case 7: e = launch_wave<2, true, true>(p, dpad, ctx->cus, st); break;
-      case 8: e = launch_wave<3, false, false>(p, dpad, ctx->cus, st); break;
-      case 9: e = launch_wave<3, false, true>(p, dpad, ctx->cus, st); break;
-      case 10: e = launch_wave<3, true, false>(p, dpad, ctx->cus, st); break;
-      case 11: e = launch_wave<3, true, true>(p, dpad, ctx->cus, st); break;
-      case 12: e = launch_wave<4, false, false>(p, dpad, ctx->cus, st); break;
-      case 13: e = launch_wave<4, false, true>(p, dpad, ctx->cus, st); break;
-      case 14: e = launch_wave<4, true, false>(p, dpad, ctx->cus, st); break;
-      default: e = launch_wave<4, true, true>(p, dpad, ctx->cus, st); break;
+      case 0: e = launch_wave<1, false, false>(p, ctx->cus, st); break;
+      case 1: e = launch_wave<1, false, true>(p, ctx->cus, st); break;
+      case 2: e = launch_wave<1, true, false>(p, ctx->cus, st); break;
+      case 3: e = launch_wave<1, true, true>(p, ctx->cus, st); break;
+      case 4: e = launch_wave<2, false, false>(p, ctx->cus, st); break;
+      case 5: e = launch_wave<2, false, true>(p, ctx->cus, st); break;
+      case 6: e = launch_wave<2, true, false>(p, ctx->cus, st); break;
+      case 7: e = launch_wave<2, true, true>(p, ctx->cus, st); break;
+      case 8: e = launch_wave<3, false, false>(p, ctx->cus, st); break;
+      case 9: e = launch_wave<3, false, true>(p, ctx->cus, st); break;
+      case 10: e = launch_wave<3, true, false>(p, ctx->cus, st); break;
+      case 11: e = launch_wave<3, true, true>(p, ctx->cus, st); break;
+      case 12: e = launch_wave<4, false, false>(p, ctx->cus, st); break;
+      case 13: e = launch_wave<4, false, true>(p, ctx->cus, st); break;
+      case 14: e = launch_wave<4, true, false>(p, ctx->cus, st); break;
+      default: e = launch_wave<4, true, true>(p, ctx->cus, st); break;
     }
     if (e != hipSuccess) return sdi::fail(ctx->err, SD_ERR_HIP, "%s: %s", who, hipGetErrorString(e));
     if (max_windows > 1 && counters) hipLaunchKernelGGL(bump_launches_kernel, dim3(1), dim3(1), 0, st, p.counters);
