@@ -577,8 +577,8 @@ __global__ __launch_bounds__(64 * wave_chains(CPT), wave_chains(CPT) / 4) void l
   if (wave >= workers) return;                             // few chains: spread over the CUs, the rest only staged the table
 
   const int Bact = p.active ? min(p.B, max(0, *p.active)) : p.B;
-  const double gamma = p.gamma, inv_s2 = p.inv_s2;
-  const double sq2g = sqrt(2.0 * gamma), sqg2 = sqrt(0.5 * gamma), inv_sqg2 = 1.0 / sqg2;
+  const double inv_s2 = p.inv_s2, sq2g = sqrt(2.0 * p.gamma);
+  const double per_s2 = p.gamma * inv_s2, to_delta = sqrt(0.5 * p.gamma) * inv_s2;       // Delta = to_delta (s^2 grad - the frozen one)
   const int my_m = lane >> 2;                              // component this lane holds after a reduction
   const double my_logw = my_m < M ? static_cast<double>(p.logw[my_m]) : 0.0;
   const double my_hn = sh_hn[my_m];
@@ -609,8 +609,8 @@ __global__ __launch_bounds__(64 * wave_chains(CPT), wave_chains(CPT) / 4) void l
   }
 
   Sole sole;
-  float dist_mine = 0.f, norm_top = 0.f;                   // |mu_top - mu_{my_m}|; |mu_top|
-  float gn = 0.f, last = 0.f;                              // upper bound of |g| of the gradient at hand; the last step's length
+  float per_nat = 0.f, norm_top = 0.f;                     // s^2 / |mu_top - mu_{my_m}|, at most; |mu_top|
+  float gn = 0.f, last = 0.f;                              // upper bound of |s^2 grad| at hand; the last step's length
 
   auto norm_of = [&](const double g[CPT][4]) {
     double q = 0.0;
@@ -645,29 +645,29 @@ __global__ __launch_bounds__(64 * wave_chains(CPT), wave_chains(CPT) / 4) void l
         }
       }
       const double d2 = reduce16_transposed(part, lane);
-      dist_mine = kUp * static_cast<float>(sqrt(d2));
+      per_nat = 1.f / (static_cast<float>(inv_s2) * (kUp * static_cast<float>(sqrt(d2))));
       norm_top = kUp * static_cast<float>(sqrt(2.0 * sh_hn[top]));
       const double odds = 0.5 * d2 * inv_s2 + readlane_f64(my_logw, 4 * top) - my_logw - kSoleGap;
-      sole.radius = kDown * least_of_others(static_cast<float>(odds / (inv_s2 * dist_mine)), other);
+      sole.radius = kDown * least_of_others(static_cast<float>(odds) * per_nat, other);
     }
-    sole.slack = kDown * least_of_others(static_cast<float>(gap / (inv_s2 * dist_mine)), other);
+    sole.slack = kDown * least_of_others(static_cast<float>(gap) * per_nat, other);
   };
 
-  // grad E at `cur` for my coordinates
+  // s^2 grad E at `cur` for my coordinates: the state's distance from the weighted mean
   auto gradient = [&](double g[CPT][4]) {
     if (RUN && sole.holds()) {
       const int top = __builtin_amdgcn_readfirstlane(sole.top);
 #pragma unroll
       for (int c = 0; c < CPT; ++c) {
         const double2 lo = sh_mu2[top * (kRow / 2) + c * 128 + lane], hi = sh_mu2[top * (kRow / 2) + c * 128 + 64 + lane];
-        g[c][0] = (cur[c][0] - lo.x) * inv_s2;
-        g[c][1] = (cur[c][1] - lo.y) * inv_s2;
-        g[c][2] = (cur[c][2] - hi.x) * inv_s2;
-        g[c][3] = (cur[c][3] - hi.y) * inv_s2;
+        g[c][0] = cur[c][0] - lo.x;
+        g[c][1] = cur[c][1] - lo.y;
+        g[c][2] = cur[c][2] - hi.x;
+        g[c][3] = cur[c][3] - hi.y;
       }
       if (__builtin_amdgcn_readfirstlane(sole.slack < 2.5f * last ? 1 : 0))      // about to run out: where in the ball is it?
-        sole.at_distance(norm_of(g) * kUp * static_cast<float>(1.0 / inv_s2));
-      gn = kUp * sole.rho * static_cast<float>(inv_s2);
+        sole.at_distance(norm_of(g));
+      gn = sole.rho;
       return;
     }
     int at = lane;                                         // opaque: the table's reads must not leave the walk's loop
@@ -722,10 +722,10 @@ __global__ __launch_bounds__(64 * wave_chains(CPT), wave_chains(CPT) / 4) void l
 #pragma unroll
     for (int c = 0; c < CPT; ++c)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) g[c][e] = (cur[c][e] - bar[c][e]) * inv_s2;
+      for (int e = 0; e < 4; ++e) g[c][e] = cur[c][e] - bar[c][e];
     if (RUN) {
       gn = norm_of(g);
-      if (sole.holds()) sole.at_distance(gn * kUp * static_cast<float>(1.0 / inv_s2));
+      if (sole.holds()) sole.at_distance(gn);
     }
   };
 
@@ -740,7 +740,7 @@ __global__ __launch_bounds__(64 * wave_chains(CPT), wave_chains(CPT) / 4) void l
   double lu_batch = 0.0;
   bool lu_have = false;
   while (Kt > 0) {                                         // Kt is uniform over the wavefront; every window advances the chain
-    double dl[CPT][4];                                     // gradient at the draft, then Delta
+    double dl[CPT][4];                                     // s^2 grad at the draft, then its difference from the frozen one
     gradient(dl);
     const int k1 = n + j + 1;                              // step this position produces
     if (!lu_have || k1 - lu_base >= 64) {
@@ -763,7 +763,7 @@ __global__ __launch_bounds__(64 * wave_chains(CPT), wave_chains(CPT) / 4) void l
     }
     if (RUN) zn = __builtin_amdgcn_sqrtf(wave_sum_f32(zn));
     const double lu = readlane_f64(lu_batch, k1 - lu_base);
-    double lr = 0.0, coef = 0.0;
+    double lr = 0.0, twice = 0.0;
     bool reject = false;
     if (j == 0) {
       gn0 = gn;
@@ -777,22 +777,24 @@ __global__ __launch_bounds__(64 * wave_chains(CPT), wave_chains(CPT) / 4) void l
       for (int c = 0; c < CPT; ++c)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          dl[c][e] = sqg2 * (dl[c][e] - g0[c][e]);
+          dl[c][e] -= g0[c][e];
           a1 = fma(static_cast<double>(z[c][e]), dl[c][e], a1);
           a2 = fma(dl[c][e], dl[c][e], a2);
         }
-      const double S1 = wave_sum(a1), S2 = wave_sum(a2);
+      // both sums in one butterfly: the lower half of the wavefront carries the first, the upper half the second
+      const double both = half_wave_sum(sdlane::halving_add<32>(a1, a2));
+      const double S1 = to_delta * readlane_f64(both, 0), S2 = to_delta * to_delta * readlane_f64(both, 32);
       lr = (-S1 - 0.5 * S2) * p.inv_tau;
       reject = !(S2 == 0.0 || (lr == lr && lu <= fmin(0.0, lr)));   // a log-ratio that is not a number rejects
       reject = __builtin_amdgcn_readfirstlane(reject ? 1 : 0) != 0;   // all lanes hold the same totals
-      coef = S2 > 0.0 ? S1 / S2 : 0.0;
+      twice = S2 > 0.0 ? 2.0 * to_delta * (S1 / S2) : 0.0;
     }
     if (!RUN && lane == 0) {
       if (p.logratio) p.logratio[static_cast<int64_t>(b) * p.K + j] = static_cast<float>(lr);
       if (p.logu) p.logu[static_cast<int64_t>(b) * p.K + j] = static_cast<float>(lu);
     }
     if (RUN) {
-      last = kUp * (static_cast<float>(gamma) * (reject ? gn : gn0) + static_cast<float>(sq2g) * zn);
+      last = kUp * (static_cast<float>(per_s2) * (reject ? gn : gn0) + static_cast<float>(sq2g) * zn);
       sole.moved(last);
     }
     if (reject) {
@@ -800,14 +802,13 @@ __global__ __launch_bounds__(64 * wave_chains(CPT), wave_chains(CPT) / 4) void l
       for (int c = 0; c < CPT; ++c)
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          cur[c][e] = cur[c][e] - gamma * (g0[c][e] + dl[c][e] * inv_sqg2) +   // target gradient = g0 + Delta / sqrt(gamma/2)
-                      sq2g * (static_cast<double>(z[c][e]) - 2.0 * coef * dl[c][e]);
+          cur[c][e] = cur[c][e] - per_s2 * (g0[c][e] + dl[c][e]) + sq2g * (static_cast<double>(z[c][e]) - twice * dl[c][e]);
     } else {
 #pragma unroll
       for (int c = 0; c < CPT; ++c)
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          cur[c][e] = cur[c][e] - gamma * g0[c][e] + sq2g * static_cast<double>(z[c][e]);
+          cur[c][e] = cur[c][e] - per_s2 * g0[c][e] + sq2g * static_cast<double>(z[c][e]);
     }
     ++j;
     if (!reject && j < Kt) continue;

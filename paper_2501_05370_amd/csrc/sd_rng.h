@@ -57,7 +57,8 @@ __device__ __forceinline__ Words block_words(uint64_t seed, int64_t chain_id, ui
 }
 
 __device__ __forceinline__ float word_to_uniform(uint32_t w) {
-  return (static_cast<float>(w >> 9) + 0.5f) * 0x1p-23f;
+  // the 23 bits as the mantissa of a number in [1, 2), minus 1 - 2^-24: both exact, two instructions
+  return __uint_as_float(__builtin_amdgcn_alignbit(0x7Fu, w, 9u)) - 0x0.ffffffp0f;
 }
 
 __device__ __forceinline__ void box_muller(uint32_t w_even, uint32_t w_odd, float& z_even,
