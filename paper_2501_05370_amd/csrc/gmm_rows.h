@@ -17,6 +17,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "sd_lanes.h"
 
@@ -30,6 +31,7 @@ struct Model {
   const float2* row_tab;     // [M, d] (mean, std)
   const double* cst;         // [T, M] log w_m - 1/2 sum_i log v_mi(k)
   const double2* steps;      // [T] (ab, sqrt(ab))
+  const float* radius2;      // [M, T] where a component is alone (gmm_radius_kernel)
   int M, d, T;
   int lm;                    // log2 of Mp (PARTS = 64 >> lm)
   int nslots;                // ceil(d / PARTS), from 3 on rounded up to a multiple of 4
@@ -127,6 +129,88 @@ __device__ __forceinline__ double responsibility(double q, double base, bool liv
   return ex * reciprocal(sum);
 }
 
+__device__ __forceinline__ float wave_sum(float v) {
+  auto other = [](float u, auto mask) { return __int_as_float(sdlane::lane_xor<decltype(mask)::value>(__float_as_int(u))); };
+  v += other(v, std::integral_constant<int, 1>{});
+  v += other(v, std::integral_constant<int, 2>{});
+  v += other(v, std::integral_constant<int, 4>{});
+  v += other(v, std::integral_constant<int, 8>{});
+  v += other(v, std::integral_constant<int, 16>{});
+  return v + other(v, std::integral_constant<int, 32>{});
+}
+
+// The component a chain was last seen with alone, where its state was then, and the squared radii (gmm_radius_kernel) of that
+// component's balls at 64 steps, one per lane: in a ball nothing is loaded per step.
+struct Alone {
+  int top = -1;
+  float rho2 = 0.f;
+  int base = 0;
+  float radius2 = 0.f;
+  __device__ __forceinline__ void load(const Model& g, int k, int lane) {
+    base = k;
+    radius2 = g.radius2[static_cast<int64_t>(top) * g.T + min(k + lane, g.T - 1)];
+  }
+};
+
+// The constants of the steps a chain evaluates, requested one step ahead while it needs them (not in a ball).
+struct Constants {
+  double cur = 0.0, next = 0.0;
+  int cur_k = -1, next_k = -1;
+  __device__ __forceinline__ double at(const Model& g, int k, int lane) {
+    if (cur_k != k) {
+      cur = next_k == k ? next : lane_constant(g, k, lane);
+      cur_k = k;
+      next_k = min(k + 1, g.T - 1);
+      next = lane_constant(g, next_k, lane);
+    }
+    return cur;
+  }
+};
+
+// The posterior mean where component `was.top` is alone: its own mean, the same bits as with all responsibilities.  False: it
+// is not known to be alone here, and `out` holds nothing.  A squared distance that is not a number is not below the radius.
+template <int E, int C, bool LDS, bool FINE>
+__device__ __forceinline__ bool mean_of_one(const Model& g, const double2* tab, const float (&x)[C][E], double ab, double sab,
+                                            int k, int lane, Alone& was, float (&out)[C][E]) {
+  if (was.top < 0) return false;
+  const int lp = 6 - g.lm, top = was.top;
+  if (static_cast<unsigned>(k - was.base) >= 64u) was.load(g, k, lane);
+  const float r2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(was.radius2), k - was.base));
+  if (!(r2 > 0.8f * was.rho2)) return false;       // far outside when last looked at: not worth the distance
+  const double om = 1.0 - ab;
+  double rho2 = 0.0;
+  float2 t[C][E];
+  if (!LDS) {
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const int i = E * (lane + 64 * c) + e;
+        t[c][e] = g.row_tab[static_cast<int64_t>(top) * g.d + (i < g.d ? i : 0)];
+      }
+  }
+#pragma unroll
+  for (int c = 0; c < C; ++c)
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int i = E * (lane + 64 * c) + e, ii = i < g.d ? i : 0;
+      double mu, s2;
+      if (LDS) {
+        const double2 u = tab[(ii >> lp) * kTabStride + (ii & ((1 << lp) - 1)) + (top << lp)];
+        mu = u.x; s2 = u.y;
+      } else {
+        mu = t[c][e].x;
+        s2 = static_cast<double>(t[c][e].y) * t[c][e].y;
+      }
+      const double iv = reciprocal_of<FINE>(fma(ab, s2, om));
+      const double df = fma(-sab, mu, static_cast<double>(x[c][e]));
+      rho2 = i < g.d ? fma(df * df, iv, rho2) : rho2;
+      out[c][e] = i < g.d ? static_cast<float>(fma(sab * s2 * iv, df, mu)) : 0.f;
+    }
+  was.rho2 = wave_sum(static_cast<float>(rho2));
+  return __builtin_amdgcn_readfirstlane(was.rho2 < r2 ? 1 : 0) != 0;
+}
+
 // Coordinates of a lane: group c, element e -> E * (lane + 64 c) + e.  E * 64 * C >= d.
 // ab, sab = sqrt(ab): signal level of the row's step; base = lane_constant of that step.
 // `x` holds 0 at coordinates >= d; `xs` is wavefront-private LDS of nslots * PARTS doubles.  `tab` (LDS form only): the
@@ -138,7 +222,7 @@ __device__ __forceinline__ double responsibility(double q, double base, bool liv
 // where many wavefronts share a SIMD (32768 rows, 8 components: d = 200 60 / 58, d = 400 105 / 100).
 template <int E, int C, bool LDS, bool AHEAD, bool FINE>
 __device__ __forceinline__ void posterior_mean(const Model& g, const double2* tab, double* xs, const float (&x)[C][E], double ab,
-                                               double sab, double base, int lane, float (&out)[C][E]) {
+                                               double sab, double base, int lane, float (&out)[C][E], Alone* was = nullptr, int k = 0) {
   const int lp = 6 - g.lm;
   const int parts = 1 << lp, part = lane & (parts - 1), m = lane >> lp;
   const int npad = g.nslots << lp;
@@ -221,6 +305,16 @@ __device__ __forceinline__ void posterior_mean(const Model& g, const double2* ta
     default: r = responsibility<6>(q, base, live_lane); break;
   }
   unsigned long long live = __ballot(live_lane && part == 0 && !(r < 1e-25));   // a NaN counts as live and reaches the result
+
+  if (was) {
+    const bool one = live != 0 && (live & (live - 1)) == 0;
+    const int top = one ? __builtin_ctzll(live) >> lp : -1;
+    if (top != was->top) {
+      was->top = top;
+      was->rho2 = 0.f;
+      if (one) was->load(g, k, lane);      // used from the next evaluation on
+    }
+  }
 
   double acc[C][E];
 #pragma unroll

@@ -160,6 +160,46 @@ __global__ __launch_bounds__(64 * kRowsPerBlock) void gmm_many_components_kernel
   }
 }
 
+// Where one component is alone.  With q_m = |x - sqrt(ab) mu_m|^2 in the metric 1 / v_m(k) and rho^2 = q_a, the triangle
+// inequality in the metric of m gives sqrt(q_m) >= D - s rho, D the distance of the two means there and s^2 the largest v_a / v_m:
+//   l_a - l_m >= cst_a - cst_m + (D - s rho)^2 / 2 - rho^2 / 2    for rho <= D / s,
+// which falls with rho.  The radius of component a at step k is where the least of them reaches kAloneGap: inside, every other
+// responsibility is below e^-60 < 1e-25, adds nothing to the mean and nothing to the softmax sum's 53 bits.  Rounded down by
+// far more than the arithmetic of either side is off.  One wavefront per (step, component), a lane per other component, once
+// per denoiser; also counts the balls that hold a typical state.
+constexpr double kAloneGap = 60.0;
+__global__ __launch_bounds__(64 * kRowsPerBlock) void gmm_radius_kernel(sdgmm::Model g, float* radius2, int32_t* holds) {
+  const int64_t at = static_cast<int64_t>(blockIdx.x) * kRowsPerBlock + (threadIdx.x >> 6);
+  if (at >= static_cast<int64_t>(g.T) * g.M) return;
+  const int m = threadIdx.x & 63, k = static_cast<int>(at / g.M), a = static_cast<int>(at % g.M);
+  const double2 st = g.steps[k];
+  const double ab = st.x, om = 1.0 - ab, *cst = g.cst + static_cast<int64_t>(k) * g.M;
+  float least = INFINITY;
+  if (m < g.M && m != a && cst[m] != -INFINITY) {
+    const float2 *pa = g.row_tab + static_cast<int64_t>(a) * g.d, *pm = g.row_tab + static_cast<int64_t>(m) * g.d;
+    double d2 = 0.0, s2 = 0.0;
+#pragma unroll 4
+    for (int i = 0; i < g.d; ++i) {
+      const float2 ta = pa[i], tm = pm[i];
+      const double iv = reciprocal(fma(ab, static_cast<double>(tm.y) * tm.y, om));
+      const double df = st.y * (static_cast<double>(ta.x) - tm.x);
+      d2 = fma(df * df, iv, d2);
+      s2 = fmax(s2, fma(ab, static_cast<double>(ta.y) * ta.y, om) * iv);
+    }
+    // the smaller root of c + D^2 / 2 - s D rho + (s^2 - 1) rho^2 / 2, at most D / s; none: positive all the way there
+    const double top = 2.0 * (cst[a] - cst[m] - kAloneGap) + d2, sD2 = s2 * d2, disc = sD2 - (s2 - 1.0) * top;
+    double rho = disc >= 0.0 ? top / (sqrt(sD2) + sqrt(disc)) : INFINITY;
+    rho = fmin(rho, sqrt(d2 / s2));
+    least = top > 0.0 ? static_cast<float>(rho) : 0.f;     // also where something is not a number
+  }
+  for (int o = 32; o >= 1; o >>= 1) least = fminf(least, __shfl_xor(least, o, 64));
+  if (m == 0) {
+    const float r2 = 0.999f * least * least;
+    radius2[static_cast<int64_t>(a) * g.T + k] = r2;
+    if (r2 > static_cast<float>(g.d)) atomicAdd(holds, 1);
+  }
+}
+
 // ---------------------------------------------------------------------------------------------
 // Every chain of a batch from its step to T in one launch: one wavefront owns a chain and walks its windows, each of
 // which computes what (window-start prediction, draft, batched prediction, verify, advance) computes for it.  Chains
@@ -168,9 +208,9 @@ __global__ __launch_bounds__(64 * kRowsPerBlock) void gmm_many_components_kernel
 // step it takes (plus the carried one of the efficient frozen drafter) instead of K per window.
 // Values: drafts, predictions and states are rounded to fp32 exactly where the separate calls store them; log-ratios
 // are fp64 sums of the same terms.
-// Measured against windows of separate calls: 4096 chains, d = 64, 32 components, 200 steps 1.05 ms against 4.76; 64 chains,
+// Measured against windows of separate calls: 4096 chains, d = 64, 32 components, 200 steps 0.87 ms against 4.76; 64 chains,
 // d = 2, 8 components, 100 steps 0.16 ms against 1.81; 300 chains, d = 75, 12 components, a draft model, 60 steps 0.25 ms
-// against 8.1.  The first is bound by fp64 issue (560 vector instructions per step and chain, the vector units 82 % busy),
+// against 8.1.  The first is bound by fp64 issue, over half of it in the quarter of the steps in which many components are live,
 // the others by the latency of one wavefront's step (1.5 us): hence no branch per exchange level, no load and no
 // generator pass per step.
 // ---------------------------------------------------------------------------------------------
@@ -265,7 +305,13 @@ __device__ __forceinline__ float readlane_f32(float v, int src_lane) {
 }
 
 // FINE: reciprocal variances to fp64 rounding (sdgmm::needs_fine); the vector caches' form always has them.
-template <int E, int C, bool LDS, bool INDEP, bool FINE>
+// ALONE: a step is first tried with the component its chain was last seen with alone, which takes no pass over the pairs, no
+// exchange of the row and no softmax; about 300 of 550 instructions at 32 pairs per lane, while the attempts and the wider
+// loop cost the other steps 4 %.  us of a run with / without: 4096 chains, d = 64, M = 32 870 / 1050; 300 chains, d = 190,
+// M = 40 940 / 1660; 1 chain, d = 100, M = 20 510 / 770; 300 chains, d = 75, M = 12, two models 240 / 255; but 2000 chains,
+// d = 30, M = 20 475 / 456, 64 chains, d = 2, M = 8 172 / 164.  Taken where the share of the balls that hold a typical state
+// (radius^2 > d) times the pairs per lane reaches 6: these six have 16, 110, 29, 11, 3.4 and 0.
+template <int E, int C, bool LDS, bool INDEP, bool FINE, bool ALONE>
 __global__ __launch_bounds__(256) void gmm_run_kernel(RunArgs p) {
   extern __shared__ __align__(16) unsigned char run_smem[];
   __shared__ unsigned long long sh_cnt[4];
@@ -306,9 +352,11 @@ __global__ __launch_bounds__(256) void gmm_run_kernel(RunArgs p) {
     sb.base = -64;
     NoiseBatch nb;
     nb.init(d);
-    // component constants of the next step to be evaluated, requested one step ahead
-    double next_t = sdgmm::lane_constant(p.t, min(n, p.T - 1), lane), next_q = 0.0;
-    if (INDEP) next_q = sdgmm::lane_constant(p.q, min(n, p.T - 1), lane);
+    sdgmm::Constants cst_t, cst_q;         // ALONE
+    // else component constants of the next step to be evaluated, requested one step ahead
+    double next_t = ALONE ? 0.0 : sdgmm::lane_constant(p.t, min(n, p.T - 1), lane), next_q = 0.0;
+    if (INDEP && !ALONE) next_q = sdgmm::lane_constant(p.q, min(n, p.T - 1), lane);
+    sdgmm::Alone alone_t, alone_q;
 
     while (n < p.T) {                      // every window advances the chain by at least one step
       const int Kt = min(p.K, p.T - n);
@@ -322,23 +370,32 @@ __global__ __launch_bounds__(256) void gmm_run_kernel(RunArgs p) {
         const int at = k - sb.base;
         const float a = readlane_f32(sb.a, at), cf = readlane_f32(sb.c, at), s = readlane_f32(sb.s, at);
         const double ab = sdgmm::readlane_f64(sb.t.x, at), sab = sdgmm::readlane_f64(sb.t.y, at);
-        const double base_t = next_t, base_q = next_q;
-        next_t = sdgmm::lane_constant(p.t, min(k + 1, p.T - 1), lane);
-        if (INDEP) next_q = sdgmm::lane_constant(p.q, min(k + 1, p.T - 1), lane);
+        double base_t = next_t, base_q = next_q;
+        if (!ALONE) {
+          next_t = sdgmm::lane_constant(p.t, min(k + 1, p.T - 1), lane);
+          if (INDEP) next_q = sdgmm::lane_constant(p.q, min(k + 1, p.T - 1), lane);
+        }
         float z[C][E], mp[C][E];
         lane_normals<E, C>(nb, zs, p.seed, id, k + 1, lane, z);
         // The step's one target evaluation, at the state it starts from: the frozen prediction of the window (first
         // position of the frozen drafter), else what the draft is tested against.
-        sdgmm::posterior_mean<E, C, LDS, !LDS, FINE>(p.t, tab_t, xs, y, ab, sab, base_t, lane, dq);
+        if (!ALONE || !sdgmm::mean_of_one<E, C, LDS, FINE>(p.t, tab_t, y, ab, sab, k, lane, alone_t, dq)) {
+          if (ALONE) base_t = cst_t.at(p.t, k, lane);
+          sdgmm::posterior_mean<E, C, LDS, !LDS, FINE>(p.t, tab_t, xs, y, ab, sab, base_t, lane, dq, ALONE ? &alone_t : nullptr, k);
+        }
         if (frozen && j == 0) {
 #pragma unroll
           for (int c = 0; c < C; ++c)
 #pragma unroll
             for (int e = 0; e < E; ++e) d0[c][e] = dq[c][e];
         }
-        if (INDEP)                         // the draft model's prediction
-          sdgmm::posterior_mean<E, C, LDS, !LDS, FINE>(p.q, tab_q, xs, y, sdgmm::readlane_f64(sb.q.x, at),
-                                                       sdgmm::readlane_f64(sb.q.y, at), base_q, lane, mp);
+        if (INDEP) {                       // the draft model's prediction
+          const double abq = sdgmm::readlane_f64(sb.q.x, at), sabq = sdgmm::readlane_f64(sb.q.y, at);
+          if (!ALONE || !sdgmm::mean_of_one<E, C, LDS, FINE>(p.q, tab_q, y, abq, sabq, k, lane, alone_q, mp)) {
+            if (ALONE) base_q = cst_q.at(p.q, k, lane);
+            sdgmm::posterior_mean<E, C, LDS, !LDS, FINE>(p.q, tab_q, xs, y, abq, sabq, base_q, lane, mp, ALONE ? &alone_q : nullptr, k);
+          }
+        }
 #pragma unroll
         for (int c = 0; c < C; ++c)
 #pragma unroll
@@ -423,9 +480,10 @@ __global__ __launch_bounds__(256) void gmm_run_kernel(RunArgs p) {
         } else {
           if (n - sb.base >= 64) sb.refill(p, INDEP, n, id, lane);
           const int at = n - sb.base;
-          // next_t: step n's, requested when step n - 1 was taken
-          sdgmm::posterior_mean<E, C, LDS, !LDS, FINE>(p.t, tab_t, xs, dr, sdgmm::readlane_f64(sb.t.x, at),
-                                                       sdgmm::readlane_f64(sb.t.y, at), next_t, lane, d0);
+          const double abn = sdgmm::readlane_f64(sb.t.x, at), sabn = sdgmm::readlane_f64(sb.t.y, at);
+          if (!ALONE || !sdgmm::mean_of_one<E, C, LDS, FINE>(p.t, tab_t, dr, abn, sabn, n, lane, alone_t, d0))
+            sdgmm::posterior_mean<E, C, LDS, !LDS, FINE>(p.t, tab_t, xs, dr, abn, sabn, ALONE ? cst_t.at(p.t, n, lane) : next_t, lane, d0,
+                                                         ALONE ? &alone_t : nullptr, n);
         }
       }
     }
@@ -474,9 +532,10 @@ void launch_rows(const GmmArgs& p, bool fine, dim3 grid, size_t shmem, hipStream
 
 struct GmmDenoiser final : sdden {
   sdgmm::Model g{};
-  float* dev_f = nullptr;     // fp32 tables: row table and lane table, or (more than 64 components) mu, sd, muT, sdT, ab
+  float* dev_f = nullptr;     // fp32 tables: row table, lane table and radii, or (more than 64 components) mu, sd, muT, sdT, ab
   double* dev_d = nullptr;    // cst [T,M], then (ab, sqrt(ab)) [T]
   bool lanes = false;         // at most 64 components: gmm_rows.h
+  bool often_alone = false;   // gmm_run_kernel, ALONE
   const float *mu = nullptr, *sd = nullptr, *muT = nullptr, *sdT = nullptr, *ab = nullptr;
   ~GmmDenoiser() override {
     if (dev_f) (void)hipFree(dev_f);
@@ -512,10 +571,17 @@ struct GmmDenoiser final : sdden {
           float* out, int32_t* B_active, int64_t* counters, hipStream_t st) override;
 };
 
-template <int E, int C, bool LDS, bool FINE = !LDS>
+template <int E, int C, bool LDS, bool FINE, bool ALONE>
 void launch_run(const RunArgs& p, bool indep, unsigned grid, unsigned block, size_t shmem, hipStream_t st) {
-  if (indep) hipLaunchKernelGGL((gmm_run_kernel<E, C, LDS, true, FINE>), dim3(grid), dim3(block), shmem, st, p);
-  else hipLaunchKernelGGL((gmm_run_kernel<E, C, LDS, false, FINE>), dim3(grid), dim3(block), shmem, st, p);
+  if (indep) hipLaunchKernelGGL((gmm_run_kernel<E, C, LDS, true, FINE, ALONE>), dim3(grid), dim3(block), shmem, st, p);
+  else hipLaunchKernelGGL((gmm_run_kernel<E, C, LDS, false, FINE, ALONE>), dim3(grid), dim3(block), shmem, st, p);
+}
+// A table in the vector caches has more than 34 pairs per lane: there an attempt costs next to nothing.
+template <int E, int C, bool LDS, bool FINE = !LDS>
+void launch_run(const RunArgs& p, bool indep, bool alone, unsigned grid, unsigned block, size_t shmem, hipStream_t st) {
+  if constexpr (!LDS) launch_run<E, C, LDS, FINE, true>(p, indep, grid, block, shmem, st);
+  else if (alone) launch_run<E, C, LDS, FINE, true>(p, indep, grid, block, shmem, st);
+  else launch_run<E, C, LDS, FINE, false>(p, indep, grid, block, shmem, st);
 }
 
 int GmmDenoiser::run(sdden* draft, sd_ctx* ctx, int B, const float* y, const int32_t* n, const int64_t* chain_id,
@@ -552,16 +618,16 @@ int GmmDenoiser::run(sdden* draft, sd_ctx* ctx, int B, const float* y, const int
   // a table that fits LDS has at most 32 pairs per lane, and at d > 64 at most 32 components too
   const bool fine = g.M > 32 || (q && q->g.M > 32);
   if (B == 0) {}                           // no chains: the end kernel leaves the count
-  else if (lds && fine) launch_run<1, 1, true, true>(p, indep, grid, block, shmem, st);
-  else if (lds && d <= 64) launch_run<1, 1, true>(p, indep, grid, block, shmem, st);
-  else if (lds && d <= 128) launch_run<2, 1, true>(p, indep, grid, block, shmem, st);
-  else if (lds) launch_run<4, 1, true>(p, indep, grid, block, shmem, st);
-  else if (d <= 64) launch_run<1, 1, false>(p, indep, grid, block, shmem, st);
-  else if (d <= 128) launch_run<2, 1, false>(p, indep, grid, block, shmem, st);
-  else if (d <= 256) launch_run<4, 1, false>(p, indep, grid, block, shmem, st);
-  else if (d <= 512) launch_run<4, 2, false>(p, indep, grid, block, shmem, st);
-  else if (d <= 1024) launch_run<4, 4, false>(p, indep, grid, block, shmem, st);
-  else launch_run<4, 8, false>(p, indep, grid, block, shmem, st);
+  else if (lds && fine) launch_run<1, 1, true, true>(p, indep, often_alone, grid, block, shmem, st);
+  else if (lds && d <= 64) launch_run<1, 1, true>(p, indep, often_alone, grid, block, shmem, st);
+  else if (lds && d <= 128) launch_run<2, 1, true>(p, indep, often_alone, grid, block, shmem, st);
+  else if (lds) launch_run<4, 1, true>(p, indep, often_alone, grid, block, shmem, st);
+  else if (d <= 64) launch_run<1, 1, false>(p, indep, often_alone, grid, block, shmem, st);
+  else if (d <= 128) launch_run<2, 1, false>(p, indep, often_alone, grid, block, shmem, st);
+  else if (d <= 256) launch_run<4, 1, false>(p, indep, often_alone, grid, block, shmem, st);
+  else if (d <= 512) launch_run<4, 2, false>(p, indep, often_alone, grid, block, shmem, st);
+  else if (d <= 1024) launch_run<4, 4, false>(p, indep, often_alone, grid, block, shmem, st);
+  else launch_run<4, 8, false>(p, indep, often_alone, grid, block, shmem, st);
   hipLaunchKernelGGL(run_end_kernel, dim3(1), dim3(1), 0, st, p.longest, p.counters, B_active);
   SD_HIP_TRY(err, hipGetLastError());
   return SD_OK;
@@ -591,7 +657,7 @@ int sdden_gmm_create(int32_t M, int32_t d, const float* means, const float* stds
   std::vector<double> dbl(static_cast<size_t>(T) * M + 1 + 2 * static_cast<size_t>(T));
   const size_t step_off = (static_cast<size_t>(T) * M + 1) / 2 * 2;       // 16-byte aligned
   if (lanes) {
-    h.resize(2 * md + 128 * static_cast<size_t>(nslots));
+    h.resize(2 * md + 128 * static_cast<size_t>(nslots) + static_cast<size_t>(T) * M + 1);
     for (size_t i = 0; i < md; ++i) {
       h[2 * i] = means[i];
       h[2 * i + 1] = stds[i];
@@ -646,6 +712,19 @@ int sdden_gmm_create(int32_t M, int32_t d, const float* means, const float* stds
   if (lanes) {
     g->g.row_tab = reinterpret_cast<const float2*>(g->dev_f);
     g->g.lane_tab = reinterpret_cast<const float2*>(g->dev_f + 2 * md);
+    float* radius2 = g->dev_f + 2 * md + 128 * static_cast<size_t>(nslots);
+    g->g.radius2 = radius2;
+    const unsigned grid = static_cast<unsigned>((static_cast<int64_t>(T) * M + kRowsPerBlock - 1) / kRowsPerBlock);
+    int32_t* count = reinterpret_cast<int32_t*>(radius2 + static_cast<size_t>(T) * M);      // 0 by the copy above
+    int32_t holds = 0;
+    hipLaunchKernelGGL(gmm_radius_kernel, dim3(grid), dim3(64 * kRowsPerBlock), 0, nullptr, g->g, radius2, count);
+    e = hipGetLastError();
+    if (e == hipSuccess) e = hipMemcpy(&holds, count, sizeof(holds), hipMemcpyDeviceToHost);
+    if (e != hipSuccess) {
+      delete g;
+      return sdi::fail(E, SD_ERR_HIP, "sdden_gmm_create: %s", hipGetErrorString(e));
+    }
+    g->often_alone = static_cast<double>(holds) * nslots >= 6.0 * static_cast<double>(T) * M;
   } else {
     g->mu = g->dev_f; g->sd = g->dev_f + md; g->muT = g->dev_f + 2 * md; g->sdT = g->dev_f + 3 * md; g->ab = g->dev_f + 4 * md;
   }

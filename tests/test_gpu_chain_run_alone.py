@@ -1,0 +1,65 @@
+"""Whole mixture chains in one launch where a step is tried with one component first (a ball around its mean in which no other
+can matter): against the window loop, which always weighs all components.  Same counters and states as in
+test_gpu_chain_run, whose tolerance holds here for the same reason.  Mixtures at the rule's edges: standard deviations that
+differ by a factor of 500, coincident means, components without weight, means far from the origin, a single component."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from _gpu import host
+
+pytestmark = pytest.mark.gpu
+
+
+def _mixture(kind, M, d):
+    rng = np.random.default_rng(M * 1000 + d)
+    mu, sd, lw = rng.normal(0, 3.0, (M, d)), rng.uniform(0.2, 1.0, (M, d)), np.full(M, -math.log(M))
+    if kind == "stds":
+        sd = np.exp(rng.uniform(math.log(0.01), math.log(5.0), (M, d)))
+    elif kind == "twins" and M > 1:
+        mu[1], sd[1] = mu[0], sd[0]
+    elif kind == "weights" and M > 2:
+        lw = lw - 40.0 * np.arange(M)
+        lw[1] = -np.inf
+    elif kind == "offset":
+        mu = mu + 50.0
+    return mu, sd, lw
+
+
+def _sampler(kind, drafter, B, d, M, K, T):
+    import workloads as W
+    from paper_2501_05370_amd.binding import Denoiser
+    from paper_2501_05370_amd.sampler import DiffusionSampler, EfficientFrozenSampler, IndependentDrafterSampler
+    from _gpu import make_context
+    s = W.cosine_schedule(T)
+    ctx = make_context(s, d, K, 3)
+    mu, sd, lw = _mixture(kind, M, d)
+    den = Denoiser.sdden_gmm_create(mu, sd, lw, s.alpha_bar_state)
+    if drafter == "independent":
+        h = np.arange(0, M, 2)
+        return IndependentDrafterSampler(ctx, den, Denoiser.sdden_gmm_create(mu[h], sd[h], lw[h], s.alpha_bar_state), B)
+    if drafter.startswith("reused"):
+        return EfficientFrozenSampler(ctx, den, B, carry="last_accepted" if drafter.endswith("last") else "draft")
+    return DiffusionSampler(ctx, den, B)
+
+
+@pytest.mark.parametrize("kind", ["apart", "stds", "twins", "weights", "offset"])
+@pytest.mark.parametrize("drafter,B,d,M,K,T", [("frozen", 30, 64, 16, 5, 90), ("frozen", 2050, 60, 32, 8, 20), ("reused", 9, 100, 20, 4, 70),
+                                               ("reused_last", 9, 128, 9, 4, 70), ("independent", 40, 75, 12, 5, 70),
+                                               ("frozen", 3, 700, 33, 5, 40), ("frozen", 5, 90, 1, 3, 30)])
+def test_runs_equal_the_window_loop(kind, drafter, B, d, M, K, T):
+    ids = torch.randperm(B, device="cuda").to(torch.int64)
+    a, b = (_sampler(kind, drafter, B, d, M, K, T) for _ in range(2))
+    left = b.start(ids)
+    while left > 0:
+        b.window(left)
+        b.advance(left)
+        left = int(b.buf.B_active.item())
+    a.start(ids)
+    assert a._run_chains(B)
+    out, ref = host(a.buf.out), host(b.buf.out)
+    got, want = a.buf.counters.tolist(), b.buf.counters.tolist()
+    assert got == want and got[0] == B * T
+    assert np.max(np.abs(out - ref) / np.maximum(1.0, np.abs(ref).max(axis=1, keepdims=True))) < 1e-5
