@@ -223,6 +223,7 @@ struct RunArgs {
   const float *a, *c, *sigma;
   int B, K, T;
   int reused, carry_last;    // efficient frozen drafter and its second carry rule
+  int pair;                  // independent drafter: two wavefronts a chain, one for each model
   uint64_t seed;
   double inv_tau;
   unsigned long long* counters;   // optional: sum adv, chain-windows, rejections, windows, sum Kt
@@ -325,14 +326,17 @@ __global__ __launch_bounds__(256) void gmm_run_kernel(RunArgs p) {
   npad = (npad + 1) & ~1;                  // 16-byte pieces
   double* xs = xs0 + static_cast<size_t>(wave) * npad;
   float* zs = reinterpret_cast<float*>(xs0 + static_cast<size_t>(blockDim.x >> 6) * npad) + 256 * wave;   // E < 4 only
+  const bool pair = INDEP && p.pair;
+  float* both = zs + 256 * ((E < 4 ? 2 : 0) - wave);       // pair: [2][2][64 E C] predictions, buffers that alternate
+  int par = 0;
   stage_table<LDS>(p.t, tab_t);
   if (INDEP) stage_table<LDS>(p.q, tab_q);
   if (threadIdx.x < 4) sh_cnt[threadIdx.x] = 0;
   if (threadIdx.x == 0) sh_longest = 0;
   __syncthreads();
 
-  const int b = blockIdx.x * static_cast<int>(blockDim.x >> 6) + wave;
-  if (b < p.B) {                           // uniform over the wavefront
+  const int b = pair ? static_cast<int>(blockIdx.x) : static_cast<int>(blockIdx.x) * static_cast<int>(blockDim.x >> 6) + wave;
+  if (b < p.B) {                           // uniform over the wavefront; pair: over the workgroup
     const int d = p.t.d;
     const int64_t id = p.id[b];
     int n = __builtin_amdgcn_readfirstlane(p.n[b]);
@@ -379,7 +383,8 @@ __global__ __launch_bounds__(256) void gmm_run_kernel(RunArgs p) {
         lane_normals<E, C>(nb, zs, p.seed, id, k + 1, lane, z);
         // The step's one target evaluation, at the state it starts from: the frozen prediction of the window (first
         // position of the frozen drafter), else what the draft is tested against.
-        if (!ALONE || !sdgmm::mean_of_one<E, C, LDS, FINE>(p.t, tab_t, y, ab, sab, k, lane, alone_t, dq)) {
+        if (pair && wave == 1) {}          // the other wavefront's
+        else if (!ALONE || !sdgmm::mean_of_one<E, C, LDS, FINE>(p.t, tab_t, y, ab, sab, k, lane, alone_t, dq)) {
           if (ALONE) base_t = cst_t.at(p.t, k, lane);
           sdgmm::posterior_mean<E, C, LDS, !LDS, FINE>(p.t, tab_t, xs, y, ab, sab, base_t, lane, dq, ALONE ? &alone_t : nullptr, k);
         }
@@ -389,12 +394,30 @@ __global__ __launch_bounds__(256) void gmm_run_kernel(RunArgs p) {
 #pragma unroll
             for (int e = 0; e < E; ++e) d0[c][e] = dq[c][e];
         }
-        if (INDEP) {                       // the draft model's prediction
+        if (INDEP && !(pair && wave == 0)) {       // the draft model's prediction
           const double abq = sdgmm::readlane_f64(sb.q.x, at), sabq = sdgmm::readlane_f64(sb.q.y, at);
           if (!ALONE || !sdgmm::mean_of_one<E, C, LDS, FINE>(p.q, tab_q, y, abq, sabq, k, lane, alone_q, mp)) {
             if (ALONE) base_q = cst_q.at(p.q, k, lane);
             sdgmm::posterior_mean<E, C, LDS, !LDS, FINE>(p.q, tab_q, xs, y, abq, sabq, base_q, lane, mp, ALONE ? &alone_q : nullptr, k);
           }
+        }
+        if (pair) {                        // both go on with both: all that follows is the same on the two
+          float* mine = both + (par * 2 + wave) * 64 * E * C;
+          const float* theirs = both + (par * 2 + 1 - wave) * 64 * E * C;
+#pragma unroll
+          for (int c = 0; c < C; ++c)
+#pragma unroll
+            for (int e = 0; e < E; ++e) mine[(c * E + e) * 64 + lane] = wave == 0 ? dq[c][e] : mp[c][e];
+          __syncthreads();
+#pragma unroll
+          for (int c = 0; c < C; ++c)
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+              const float v = theirs[(c * E + e) * 64 + lane];
+              if (wave == 0) mp[c][e] = v;
+              else dq[c][e] = v;
+            }
+          par ^= 1;
         }
 #pragma unroll
         for (int c = 0; c < C; ++c)
@@ -488,15 +511,16 @@ __global__ __launch_bounds__(256) void gmm_run_kernel(RunArgs p) {
       }
     }
     windows = max(windows, 1);             // handed over at T: one window, of no positions, that keeps the state
+    const bool writes = !pair || wave == 0;
     float* o = p.out + id * d;
 #pragma unroll
     for (int c = 0; c < C; ++c)
 #pragma unroll
       for (int e = 0; e < E; ++e) {
         const int i = E * (lane + 64 * c) + e;
-        if (i < d) o[i] = y[c][e];
+        if (writes && i < d) o[i] = y[c][e];
       }
-    if (lane == 0) {
+    if (writes && lane == 0) {
       atomicAdd(&sh_cnt[0], static_cast<unsigned long long>(n - n_start));
       atomicAdd(&sh_cnt[1], static_cast<unsigned long long>(windows));
       atomicAdd(&sh_cnt[2], static_cast<unsigned long long>(rejections));
@@ -513,6 +537,259 @@ __global__ __launch_bounds__(256) void gmm_run_kernel(RunArgs p) {
       if (sh_cnt[3]) atomicAdd(p.counters + 4, sh_cnt[3]);
     }
     if (sh_longest) atomicMax(p.longest, sh_longest);
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// The same for few chains (frozen and efficient frozen drafter): a workgroup of W wavefronts owns a chain, and what the
+// sampling is made for happens inside it.  With the frozen prediction known every draft of the window is, so in one round
+// wavefront w predicts (and tests) the w-th position from here; the first rejection, or the end of the window, decides where
+// the chain goes on.  One wavefront takes the state behind the window's last draft, which is the next window's start where
+// everything is accepted.  A chain then costs a round per W positions and one more after a rejection (the frozen drafter's new
+// start) instead of a prediction per position.  Every wavefront holds the chain's state and walks the drafts to its position
+// itself (two operations each, noise from a ring in LDS that the wavefronts fill ahead in turn); a round's states, predictions
+// and verdicts go through LDS, in buffers that alternate, behind one barrier.  Values and decisions are those of the
+// kernel above: same operations on the same numbers.
+// Bound by a round's latency, about 2 us: 64 chains of the toy (d = 2, M = 8, K = 4, 3.8 of 4 accepted) 121 us a run, 164 with a
+// wavefront a chain; more in GmmDenoiser::run.
+// ---------------------------------------------------------------------------------------------
+template <int E, bool LDS, bool FINE, bool ALONE>
+__global__ __launch_bounds__(512) void gmm_window_run_kernel(RunArgs p) {
+  extern __shared__ __align__(16) unsigned char run_smem[];
+  constexpr int kRow = 64 * E;
+  const int W = static_cast<int>(blockDim.x >> 6);
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int npad = ((p.t.nslots << (6 - p.t.lm)) + 1) & ~1;
+  double2* tab = reinterpret_cast<double2*>(run_smem);
+  double* xs = reinterpret_cast<double*>(tab + (LDS ? p.t.nslots * sdgmm::kTabStride : 0)) + static_cast<size_t>(w) * npad;
+  float* states = reinterpret_cast<float*>(reinterpret_cast<double*>(tab + (LDS ? p.t.nslots * sdgmm::kTabStride : 0)) +
+                                           static_cast<size_t>(W) * npad);      // [2][W][kRow]
+  float* means = states + 2 * W * kRow;                                         // [2][W][kRow]
+  float* ring = means + 2 * W * kRow;                                           // [passes][256]
+  __shared__ int verdict[2][8];
+  stage_table<LDS>(p.t, tab);
+
+  const int b = blockIdx.x, d = p.t.d;
+  const int64_t id = p.id[b];
+  int n = __builtin_amdgcn_readfirstlane(p.n[b]);
+  const int n_start = n;
+  float y[E], d0[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int i = E * lane + e;
+    y[e] = i < d ? p.y[static_cast<int64_t>(b) * d + i] : 0.f;
+    d0[e] = p.reused && i < d ? p.Dfz[static_cast<int64_t>(b) * d + i] : 0.f;
+  }
+
+  // Noise: one pass of a wavefront draws 64 >> shift consecutive steps (E < 4; a block per lane) or one, 256 floats; pass q holds
+  // steps q << sh .. and lies in slot q % passes.  Wavefront q % W draws it.  A round that starts at step k0 reads the noise of
+  // k0 + 1 .. k0 + W + 1 and ends at k0 + W + 1 at most: what is drawn up to k0 + 2 W + 2 serves the next one whatever it decides,
+  // and the slots it takes are those of steps up to k0.
+  int shift = 6;                                   // log2 of the blocks a step takes, 64 for E = 4
+  if (E < 4) {
+    shift = 0;
+    while ((4 << shift) < d) ++shift;
+  }
+  const int sh = 6 - shift, passes = ((2 * W + 1) >> sh) + 2;
+  int drawn = (n + 1) >> sh;                       // this wavefront's next pass
+  while (drawn % W != w) ++drawn;
+  auto draw_up_to = [&](int last_step) {
+    for (; drawn <= last_step >> sh; drawn += W) {
+      float z[4];
+      sdrng::normal4(p.seed, id, static_cast<uint32_t>((drawn << sh) + (lane >> shift)), sdrng::kStreamNoise,
+                     static_cast<uint32_t>(lane & ((1 << shift) - 1)), z);
+      *reinterpret_cast<float4*>(ring + (drawn % passes) * 256 + 4 * lane) = make_float4(z[0], z[1], z[2], z[3]);
+    }
+  };
+  auto noise = [&](int k, float (&z)[E]) {         // of the step that ends in state k
+    const float* pass = ring + ((k >> sh) % passes) * 256;
+    const int from = ((k & ((1 << sh) - 1)) << (shift + 2)) + E * lane;
+#pragma unroll
+    for (int e = 0; e < E; ++e) z[e] = pass[(from + e) & 255];                  // lanes past d: not used
+  };
+  draw_up_to(n + 2 * W + 2);
+  __syncthreads();
+
+  StepBatch sb;
+  sb.base = -64 - W;                               // a round looks at steps up to k0 + W + 1
+  sdgmm::Alone alone;
+  int cst_k = -1;                                  // constants of the step this wavefront is expected to predict next
+  double cst = 0.0;
+  auto expect = [&](int k) {
+    cst_k = min(k, p.T - 1);
+    cst = sdgmm::lane_constant(p.t, cst_k, lane);
+  };
+  auto predict = [&](const float (&x)[E], int k, float (&out)[E]) {
+    const int at = k - sb.base;
+    const double ab = sdgmm::readlane_f64(sb.t.x, at), sab = sdgmm::readlane_f64(sb.t.y, at);
+    float xx[1][E], oo[1][E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) xx[0][e] = x[e];
+    if (!ALONE || !sdgmm::mean_of_one<E, 1, LDS, FINE>(p.t, tab, xx, ab, sab, k, lane, alone, oo))
+      sdgmm::posterior_mean<E, 1, LDS, !LDS, FINE>(p.t, tab, xs, xx, ab, sab, cst_k == k ? cst : sdgmm::lane_constant(p.t, k, lane), lane, oo,
+                                                   ALONE ? &alone : nullptr, k);
+#pragma unroll
+    for (int e = 0; e < E; ++e) out[e] = oo[0][e];
+  };
+  auto draft = [&](const float (&x)[E], int k, float (&to)[E]) {               // state k + 1 from state k
+    const int at = k - sb.base;
+    const float a = readlane_f32(sb.a, at), cf = readlane_f32(sb.c, at), s = readlane_f32(sb.s, at);
+    float z[E];
+    noise(k + 1, z);
+#pragma unroll
+    for (int e = 0; e < E; ++e) to[e] = E * lane + e < d ? fmaf(a, x[e], fmaf(cf, d0[e], s * z[e])) : 0.f;
+  };
+  auto put = [&](float* rows, int par, int r, const float (&v)[E]) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) rows[(par * W + r) * kRow + E * lane + e] = v[e];
+  };
+  auto get = [&](const float* rows, int par, int r, float (&v)[E]) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) v[e] = rows[(par * W + r) * kRow + E * lane + e];
+  };
+
+  int windows = 0, rejections = 0, j = 0, par = 0;
+  long long kt_sum = 0;
+  bool have_d0 = p.reused != 0;                    // the window's frozen prediction is known
+  bool at_y = false;                               // and is the prediction at y itself: position 0 need not be tested
+  auto know_d0_at_y = [&]() {
+    bool finite = true;
+#pragma unroll
+    for (int e = 0; e < E; ++e) finite = finite && __builtin_isfinite(d0[e]);
+    have_d0 = true;
+    at_y = !p.reused || __ballot(!finite) == 0ull;         // Delta = 0 accepts, a Delta that is not a number does not
+  };
+  // Ends: a round either finds the frozen prediction, which the next one has, or decides at least one position.
+  while (n < p.T) {                                // uniform over the workgroup: every wavefront holds the same numbers
+    const int Kt = min(p.K, p.T - n), k0 = n + j;
+    if (k0 + W + 1 - sb.base >= 64) sb.refill(p, false, k0, id, lane);
+    if (!have_d0) {                                // a window's start
+      if (w == 0) {
+        float m[E];
+        predict(y, n, m);
+        put(means, par, 0, m);
+      }
+      draw_up_to(k0 + 2 * W + 2);
+      __syncthreads();
+      get(means, par, 0, d0);
+      par ^= 1;
+      know_d0_at_y();
+      continue;
+    }
+    const int first = j == 0 && at_y ? 1 : 0, pos = j + first + w;             // window position of this wavefront
+    float x[E], m[E] = {}, res[E] = {};
+#pragma unroll
+    for (int e = 0; e < E; ++e) x[e] = y[e];
+    bool reject = false;
+    if (pos <= Kt) {
+      for (int t = j; t < pos; ++t) draft(x, n + t, x);
+      if (n + pos < p.T) predict(x, n + pos, m);
+#pragma unroll
+      for (int e = 0; e < E; ++e) res[e] = x[e];
+      if (pos < Kt) {
+        const int k = n + pos, at = k - sb.base;
+        const float a = readlane_f32(sb.a, at), cf = readlane_f32(sb.c, at);
+        float dr[E];
+        draft(x, k, dr);
+        double s1 = 0.0, s2 = 0.0;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          if (E * lane + e >= d) continue;
+          const double u = static_cast<double>(dr[e]) - static_cast<double>(a) * x[e] - static_cast<double>(cf) * d0[e];
+          const double dl = static_cast<double>(d0[e]) - static_cast<double>(m[e]);
+          s1 = fma(u, dl, s1);
+          s2 = fma(dl, dl, s2);
+        }
+        double t = sdlane::halving_add<32>(s1, s2);
+        if (d > 16 * E) t = sdlane::pair_sum_rows<16>(t);
+        if (d > 8 * E) t += sdlane::lane_xor<8>(t);
+        t += sdlane::lane_xor<4>(t);
+        t += sdlane::lane_xor<2>(t);
+        t += sdlane::lane_xor<1>(t);
+        const double lu = sdgmm::readlane_f64(sb.log_u, at), inv_s2 = sdgmm::readlane_f64(sb.inv_s2, at);
+        const double cc = static_cast<double>(cf);
+        const double S1 = sdgmm::readlane_f64(t, 0) * cc * inv_s2, S2 = sdgmm::readlane_f64(t, 32) * cc * cc * inv_s2;
+        const double lr = (-S1 - 0.5 * S2) * p.inv_tau;
+        reject = !(S2 == 0.0 || (lr == lr && lu <= fmin(0.0, lr)));            // a log-ratio that is not a number rejects
+        const double f = cc * (1.0 + 2.0 * (S2 > 0.0 ? S1 / S2 : 0.0));
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          res[e] = reject ? static_cast<float>(static_cast<double>(dr[e]) -
+                                               f * (static_cast<double>(d0[e]) - static_cast<double>(m[e]))) : dr[e];
+          if (E * lane + e >= d) res[e] = 0.f;
+        }
+      }
+      put(states, par, w, res);
+      put(means, par, w, m);
+    }
+    if (lane == 0) verdict[par][w] = reject ? 1 : 0;
+    expect(j + first + W < Kt ? n + pos + W : n + Kt + 1 + w);                 // where this wavefront goes if all are accepted
+    draw_up_to(k0 + 2 * W + 2);
+    __syncthreads();
+    const int tested = max(0, min(W, Kt - j - first));                          // positions this round decided on
+    const unsigned long long rejected = __ballot(lane < tested && verdict[par][lane & 7] != 0);
+    bool window_ends = true;
+    int adv = Kt;
+    have_d0 = at_y = false;
+    if (rejected != 0ull) {
+      const int r = __builtin_ctzll(rejected);
+      adv = j + first + r + 1;
+      ++rejections;
+      if (p.reused && n + adv < p.T) {             // the next window's frozen prediction
+        have_d0 = true;
+        if (p.carry_last) {
+          get(means, par, r, d0);
+        } else if (r + 1 < W) {                    // at the rejected draft: the next wavefront's state
+          get(means, par, r + 1, d0);
+        } else {                                   // nobody's: walk there once more
+          if (w == 0) {
+            float dr[E];
+#pragma unroll
+            for (int e = 0; e < E; ++e) dr[e] = y[e];
+            for (int t = j; t < adv; ++t) draft(dr, n + t, dr);
+            predict(dr, n + adv, m);
+            put(means, par ^ 1, 0, m);
+          }
+          __syncthreads();
+          get(means, par ^ 1, 0, d0);
+          __syncthreads();                         // read before the next round writes there
+        }
+      }
+      get(states, par, r, y);
+    } else if (j + first + tested == Kt) {         // all accepted: the state behind the last draft
+      if (tested < W && n + Kt < p.T) {            // and its prediction, if someone had it
+        get(means, par, tested, d0);
+        know_d0_at_y();
+      }
+      get(states, par, tested > 0 ? tested - 1 : 0, y);
+    } else {                                       // the window goes on
+      j += first + tested;
+      get(states, par, tested - 1, y);
+      have_d0 = true;
+      window_ends = false;
+    }
+    par ^= 1;
+    if (window_ends) {
+      n += adv;
+      j = 0;
+      windows += 1;
+      kt_sum += Kt;
+    }
+  }
+  windows = max(windows, 1);                       // handed over at T: one window, of no positions, that keeps the state
+  if (w > 0) return;
+  float* o = p.out + id * d;
+#pragma unroll
+  for (int e = 0; e < E; ++e)
+    if (E * lane + e < d) o[E * lane + e] = y[e];
+  if (lane == 0) {
+    if (p.counters) {
+      if (n > n_start) atomicAdd(p.counters + 0, static_cast<unsigned long long>(n - n_start));
+      atomicAdd(p.counters + 1, static_cast<unsigned long long>(windows));
+      if (rejections) atomicAdd(p.counters + 2, static_cast<unsigned long long>(rejections));
+      if (kt_sum) atomicAdd(p.counters + 4, static_cast<unsigned long long>(kt_sum));
+    }
+    atomicMax(p.longest, windows);
   }
 }
 
@@ -571,6 +848,22 @@ struct GmmDenoiser final : sdden {
           float* out, int32_t* B_active, int64_t* counters, hipStream_t st) override;
 };
 
+template <int E, bool LDS, bool FINE = !LDS>
+void launch_window_run(const RunArgs& p, bool alone, unsigned block, size_t shmem, hipStream_t st) {
+  const dim3 grid(static_cast<unsigned>(p.B));
+  if (!LDS || alone) hipLaunchKernelGGL((gmm_window_run_kernel<E, LDS, FINE, true>), grid, dim3(block), shmem, st, p);
+  else hipLaunchKernelGGL((gmm_window_run_kernel<E, LDS, FINE, LDS ? false : true>), grid, dim3(block), shmem, st, p);
+}
+template <int E, bool LDS, bool FINE>
+hipError_t prepare_window_run() {
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gmm_window_run_kernel<E, LDS, FINE, true>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 256);
+  if (LDS && e == hipSuccess)
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gmm_window_run_kernel<E, LDS, FINE, LDS ? false : true>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 256);
+  return e;
+}
+
 template <int E, int C, bool LDS, bool FINE, bool ALONE>
 void launch_run(const RunArgs& p, bool indep, unsigned grid, unsigned block, size_t shmem, hipStream_t st) {
   if (indep) hipLaunchKernelGGL((gmm_run_kernel<E, C, LDS, true, FINE, ALONE>), dim3(grid), dim3(block), shmem, st, p);
@@ -602,8 +895,12 @@ int GmmDenoiser::run(sdden* draft, sd_ctx* ctx, int B, const float* y, const int
   p.counters = reinterpret_cast<unsigned long long*>(counters);
   p.longest = ctx->dev_queue + 1;
   // Few chains: a workgroup each, spread over the CUs.  From 1024 on two, from 2048 on four share a workgroup and its table.
-  const int waves = B >= 2048 ? 4 : (B >= 1024 ? 2 : 1);
-  const unsigned grid = static_cast<unsigned>((B + waves - 1) / waves), block = 64u * waves;
+  // The two models of the independent drafter take a wavefront each while there are no more than two per SIMD; us of 60 steps
+  // with / without at 1, 300 and 1000 chains: d = 75, M = 12 180 / 228, 218 / 246, 221 / 256; d = 180, M = 40 578 / 767,
+  // 752 / 800, 756 / 809.
+  p.pair = indep && B <= 1024;
+  const int waves = p.pair ? 2 : B >= 2048 ? 4 : (B >= 1024 ? 2 : 1);
+  const unsigned grid = static_cast<unsigned>(p.pair ? B : (B + waves - 1) / waves), block = 64u * waves;
   size_t npad = static_cast<size_t>(g.nslots) << (6 - g.lm), slots = g.nslots;
   if (q) {
     npad = std::max(npad, static_cast<size_t>(q->g.nslots) << (6 - q->g.lm));
@@ -613,11 +910,29 @@ int GmmDenoiser::run(sdden* draft, sd_ctx* ctx, int B, const float* y, const int
   // The tables go to LDS as fp64 (no conversion and no square per pair) while four workgroups still fit a CU.
   const size_t table = sizeof(double2) * sdgmm::kTabStride * slots, xs = (sizeof(double) * npad + (d <= 128 ? 1024 : 0)) * waves;
   const bool lds = d <= 256 && table <= 36 * 1024;
-  const size_t shmem = xs + (lds ? table : 0);
+  const int per_lane = d <= 64 ? 1 : d <= 128 ? 2 : d <= 256 ? 4 : d <= 512 ? 8 : d <= 1024 ? 16 : 32;
+  const size_t shmem = xs + (lds ? table : 0) + (p.pair ? 1024 * static_cast<size_t>(per_lane) : 0);
   hipLaunchKernelGGL(run_begin_kernel, dim3(1), dim3(1), 0, st, p.longest);
   // a table that fits LDS has at most 32 pairs per lane, and at d > 64 at most 32 components too
   const bool fine = g.M > 32 || (q && q->g.M > 32);
+  // Few chains, frozen prediction: gmm_window_run_kernel with as many wavefronts a chain as a window has positions (and its
+  // next start), up to two per SIMD; us of 100 steps in it / one wavefront a chain at 1, 256 and 1000 chains: d = 2, M = 8, K = 4
+  // 107 / 156, 121 / 168, 199 / 210; d = 60, M = 20, K = 8 128 / 194, 172 / 237, 260 / 282 (with four per SIMD 286).
+  const int useful = p.K + p.reused;
+  int W = indep || d > 256 || p.K < 2 ? 1 : useful >= 6 ? 8 : useful >= 3 ? 4 : 2;
+  while (W > 1 && static_cast<int64_t>(B) * W > 2048) W /= 2;
+  const int row = d <= 64 ? 64 : d <= 128 ? 128 : 256;
+  int sh = row == 256 ? 0 : 6;             // log2 of the steps whose noise one pass draws
+  while (row < 256 && (256 >> sh) < d) --sh;
+  const size_t wshmem = (lds ? table : 0) + sizeof(double) * npad * W + sizeof(float) * (4 * W * row + 256 * (((2 * W + 1) >> sh) + 2));
   if (B == 0) {}                           // no chains: the end kernel leaves the count
+  else if (W > 1 && lds && fine) launch_window_run<1, true, true>(p, often_alone, 64 * W, wshmem, st);
+  else if (W > 1 && lds && d <= 64) launch_window_run<1, true>(p, often_alone, 64 * W, wshmem, st);
+  else if (W > 1 && lds && d <= 128) launch_window_run<2, true>(p, often_alone, 64 * W, wshmem, st);
+  else if (W > 1 && lds) launch_window_run<4, true>(p, often_alone, 64 * W, wshmem, st);
+  else if (W > 1 && d <= 64) launch_window_run<1, false>(p, often_alone, 64 * W, wshmem, st);
+  else if (W > 1 && d <= 128) launch_window_run<2, false>(p, often_alone, 64 * W, wshmem, st);
+  else if (W > 1) launch_window_run<4, false>(p, often_alone, 64 * W, wshmem, st);
   else if (lds && fine) launch_run<1, 1, true, true>(p, indep, often_alone, grid, block, shmem, st);
   else if (lds && d <= 64) launch_run<1, 1, true>(p, indep, often_alone, grid, block, shmem, st);
   else if (lds && d <= 128) launch_run<2, 1, true>(p, indep, often_alone, grid, block, shmem, st);
@@ -720,6 +1035,18 @@ int sdden_gmm_create(int32_t M, int32_t d, const float* means, const float* stds
     hipLaunchKernelGGL(gmm_radius_kernel, dim3(grid), dim3(64 * kRowsPerBlock), 0, nullptr, g->g, radius2, count);
     e = hipGetLastError();
     if (e == hipSuccess) e = hipMemcpy(&holds, count, sizeof(holds), hipMemcpyDeviceToHost);
+    if (e != hipSuccess) {
+      delete g;
+      return sdi::fail(E, SD_ERR_HIP, "sdden_gmm_create: %s", hipGetErrorString(e));
+    }
+    // LDS of more than 64 KiB: up to 72 at d = 128, up to 104 at d = 256; rows of up to 64 need 56 at most
+    if (d > 128 && d <= 256) {
+      e = prepare_window_run<4, true, false>();
+      if (e == hipSuccess) e = prepare_window_run<4, false, true>();
+    } else if (d > 64 && d <= 128) {
+      e = prepare_window_run<2, true, false>();
+      if (e == hipSuccess) e = prepare_window_run<2, false, true>();
+    }
     if (e != hipSuccess) {
       delete g;
       return sdi::fail(E, SD_ERR_HIP, "sdden_gmm_create: %s", hipGetErrorString(e));

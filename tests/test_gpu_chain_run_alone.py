@@ -63,3 +63,38 @@ def test_runs_equal_the_window_loop(kind, drafter, B, d, M, K, T):
     got, want = a.buf.counters.tolist(), b.buf.counters.tolist()
     assert got == want and got[0] == B * T
     assert np.max(np.abs(out - ref) / np.maximum(1.0, np.abs(ref).max(axis=1, keepdims=True))) < 1e-5
+
+
+# One workgroup per chain with 2, 4 or 8 wavefronts for the positions of a window: windows shorter and longer than a round, more
+# than one round long, cut by the end of the chain; rejections at a round's last position; noise drawn 64, 8, 2 and 1 steps at a
+# time; tables in LDS and out of it; chain counts at which the wavefronts per chain halve.
+@pytest.mark.parametrize("drafter", ["frozen", "reused", "reused_last"])
+@pytest.mark.parametrize("B,d,M,K,T", [(200, 2, 8, 4, 100), (256, 20, 10, 12, 100), (257, 20, 5, 64, 90), (512, 63, 5, 40, 60),
+                                       (513, 7, 3, 2, 40), (1024, 120, 10, 3, 40), (1025, 3, 2, 3, 20), (40, 130, 9, 21, 50),
+                                       (5, 256, 64, 9, 40), (60, 60, 40, 5, 40), (3, 33, 1, 8, 70)])
+def test_positions_side_by_side_equal_the_window_loop(drafter, B, d, M, K, T):
+    test_runs_equal_the_window_loop("apart", drafter, B, d, M, K, T)
+
+
+def test_positions_side_by_side_from_ragged_steps():
+    """Chains handed over at any step, T among them."""
+    B, d, M, K, T = 90, 20, 6, 7, 30
+    n = np.random.default_rng(2).integers(0, T + 1, B)
+    n[[0, 1, 2, B - 1]] = [T, T - 1, 0, T]
+    for drafter in ("frozen", "reused"):
+        ids = torch.randperm(B, device="cuda").to(torch.int64)
+        a, b = (_sampler("apart", drafter, B, d, M, K, T) for _ in range(2))
+        for s in (a, b):
+            s.start(ids)
+            s.buf.n.copy_(torch.as_tensor(n, dtype=torch.int32))
+            if drafter == "reused":
+                s.den.sdden_eval(B, s.buf.y, s.buf.n, s.buf.Dfz)
+        assert a._run_chains(B)
+        left = B
+        while left > 0:
+            b.window(left)
+            b.advance(left)
+            left = int(b.buf.B_active.item())
+        assert a.buf.counters.tolist() == b.buf.counters.tolist()
+        out, ref = host(a.buf.out), host(b.buf.out)
+        assert np.max(np.abs(out - ref) / np.maximum(1.0, np.abs(ref).max(axis=1, keepdims=True))) < 1e-5
