@@ -203,11 +203,10 @@ def _windows_are_faster(ctx: Context, den: Denoiser, B: int, carried: bool, batc
     1800 coordinates, 1 to 64 components, K = 16 to 64, T = 200 to 1000, 1 to 128 chains; none of them goes to the slower
     side), with p the (component, coordinate) pairs per lane: a position 2.4 + 0.041 p, 4 more above 1024 coordinates; a
     window 42 + 0.08 p + 0.4 K (its carried form 34 + 0.04 p + 0.4 K), a little more per row, 20 more with a readback each; its
-    advance about 8 sqrt(T / 200) (64 / d)^0.21, less near K.  One chain, T = 1000, K = 64, d = 1000, M = 64, us a step in one
-    launch / by windows: 44 / 17.  Up to 256 coordinates the launch predicts the positions side by side as well and is always
-    ahead; one chain, T = 500, K = 64, us a step: d = 64, M = 32 0.7 / 4.3; d = 200, M = 48 1.9 / 9.2, carried 1.8 / 8.4."""
+    advance about 8 sqrt(T / 200) (64 / d)^0.21, less near K.  One chain, T = 1000, K = 64, us a step in one launch / by
+    windows: d = 64, M = 32 2.3 / 3.7; d = 200, M = 48 10.5 / 5.6; d = 1000, M = 64 44 / 17."""
     M, K, d = getattr(den, "components", 0), ctx.K, ctx.d
-    if not 1 <= M <= 64 or B * K > 2048 or (d <= 256 and K >= 2):
+    if not 1 <= M <= 64 or B * K > 2048:
         return False
     pairs = -(-d // (64 >> (M - 1).bit_length()))
     position = 2.4 + 0.041 * pairs + (4 if d > 1024 else 0)
