@@ -53,12 +53,11 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(const uint16_t* __res
   *reinterpret_cast<u32x4*>(F + frag_offset(n, k, K)) = *reinterpret_cast<const u32x4*>(W + static_cast<size_t>(n) * K + k);
 }
 
-// The rows r < active rows with 0 <= krow[r] < T, in increasing order, as dense rows of F in fragment order: from the
-// bf16 image when the caller has one, else X rounded to bf16.  Every workgroup ranks all (at most kMaxRows) rows itself
+// The rows r < active rows with 0 <= krow[r] < T, in increasing order, as dense rows of F in fragment order, rounded to bf16:
+// for calls of more than 16 rows without a bf16 image (the others' first product loads the rows itself).  Every workgroup ranks all (at most kMaxRows) rows itself
 // -- one load per 256 rows -- and moves its 16 dense rows x `kchunk` columns; the first column of workgroups leaves
 // rowidx and the count for the products.  One launch in place of a compaction and a conversion.
-__global__ __launch_bounds__(kPackThreads) void pack_rows_kernel(const float* __restrict__ X, const uint16_t* __restrict__ Xb,
-                                                                 const int32_t* __restrict__ krow, const int32_t* active,
+__global__ __launch_bounds__(kPackThreads) void pack_rows_kernel(const float* __restrict__ X, const int32_t* __restrict__ krow, const int32_t* active,
                                                                  int rows_per_chain, int R, int T, int K, int kchunk,
                                                                  uint16_t* __restrict__ F, int32_t* __restrict__ rowidx,
                                                                  int32_t* __restrict__ count) {
@@ -100,90 +99,183 @@ __global__ __launch_bounds__(kPackThreads) void pack_rows_kernel(const float* __
   const int row = t & 15, src = src_row[row];
   if (src < 0) return;
   for (int k = k0 + 8 * (t >> 4); k < k1; k += 8 * (kPackThreads / 16)) {
-    u32x4 o;
-    if (Xb) {
-      o = *reinterpret_cast<const u32x4*>(Xb + static_cast<size_t>(src) * K + k);
-    } else {
-      const float* s = X + static_cast<size_t>(src) * K + k;
-      const f32x4 lo = *reinterpret_cast<const f32x4*>(s), hi = *reinterpret_cast<const f32x4*>(s + 4);
-      bf16x8 b;
+    const float* s = X + static_cast<size_t>(src) * K + k;
+    const f32x4 lo = *reinterpret_cast<const f32x4*>(s), hi = *reinterpret_cast<const f32x4*>(s + 4);
+    bf16x8 o;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        b[e] = static_cast<__bf16>(lo[e]);
-        b[4 + e] = static_cast<__bf16>(hi[e]);
-      }
-      o = __builtin_bit_cast(u32x4, b);
+    for (int e = 0; e < 4; ++e) {
+      o[e] = static_cast<__bf16>(lo[e]);
+      o[4 + e] = static_cast<__bf16>(hi[e]);
     }
-    *reinterpret_cast<u32x4*>(F + frag_offset(first + row, k, K)) = o;
+    *reinterpret_cast<bf16x8*>(F + frag_offset(first + row, k, K)) = o;
   }
 }
 
 struct Args {
-  const uint16_t* A;        // [rows rounded up to a whole tile, K] bf16, fragment order
+  const void* A;            // kPacked: [rows rounded up to a whole tile, K] bf16, fragment order; else row-major rows of K
   const uint16_t* W;        // [N, K] bf16, fragment order
   int N, K;
-  const int32_t* count;     // device: M
-  const int32_t* rowidx;    // dense row -> source row
+  int32_t* count;           // device: M                     (found and left here unless kPacked)
+  int32_t* rowidx;          // dense row -> source row       (the same)
   const int32_t* krow;      // source row -> chain step
+  const int32_t* active;    // not kPacked: which of the R rows count, as in pack_rows_kernel
+  int rows_per_chain, R, T;
   const float* bias;        // EPI 1: per-step table [T, N]; EPI 2, 3: [N]
   uint16_t* outb;           // EPI 1, 2: bf16 [M, N], fragment order (N is the next product's K)
   float* outf;              // EPI 3: fp32 [*, N] at source rows
 };
 
+// Where a product's rows come from.  kPacked: dense rows in fragment order.  kRowsBf16, kRowsF32: the caller's own rows, which the
+// workgroup finds in krow itself (at most 16 loads a lane, ahead of its first weights) and loads without a packing launch;
+// fp32 rows are rounded as fragments are read.  A stage then holds S * 64 (or 128) contiguous bytes of each row, chunk c of
+// row r at c ^ swizzle(r), which makes the fragment reads conflict free on 64 banks.  Without the packing launch (4.6 to 5.6
+// us of kernel) a pass takes, us: 23 chains, d = 3072, H = 1024, K = 9 28.3 (30.0); one chain, d = 12288, H = 4096, K = 16
+// 115 (119), its first product 21.5 as before.  fp32 rows only up to 16 and for short rows: every workgroup loads them all, and
+// at d = 12288 the product takes 40 us with them.
+enum Source { kPacked, kRowsBf16, kRowsF32 };
+
 // EPI as in mlp_gemm.h.  Grid: (N / (16 NT), tiles of 16 MT rows), MT wavefronts; wavefront i owns rows 16 i .. 16 i + 15
-// of the tile.  A stage of the ring is S steps of 32 k: per step MT blocks of A, then NT of W.  Rows >= M of the last
-// tile are computed on whatever is there and never stored.
-template <int EPI, int MT, int NT, int S, int RING>
+// of the tile.  A stage of the ring is S steps of 32 k: the rows' part, then per step NT blocks of W (kPacked: per step MT
+// blocks of A, then NT of W).  Rows >= M of the last tile are computed on whatever is there and never stored.
+template <int EPI, int MT, int NT, int S, int RING, int SRC = kPacked>
 __global__ __launch_bounds__(64 * MT) void kernel(Args p) {
-  constexpr int kStep = (MT + NT) * 1024, kStage = S * kStep;
-  constexpr int WLOADS = S * NT / MT, OPS = S + WLOADS;      // loads per wavefront and stage: its rows' A, a share of W
+  constexpr int AL = (SRC == kRowsF32 ? 2 : 1) * S;          // loads of 1 KiB per wavefront and stage: its rows' A
+  constexpr int kStep = (MT + NT) * 1024, kRows = MT * AL * 1024;
+  constexpr int kStage = SRC == kPacked ? S * kStep : kRows + S * NT * 1024;
+  constexpr int WLOADS = S * NT / MT, OPS = AL + WLOADS;     // and a share of W
   static_assert(S * NT % MT == 0 && RING >= 2 && RING * kStage <= 160 * 1024 && (RING - 1) * OPS < 64, "ring");
+  static_assert(SRC != kRowsF32 || MT == 1, "fp32 rows");
   __shared__ __align__(1024) unsigned char ring[RING * kStage];
+  int* src_row = reinterpret_cast<int*>(ring + (RING - 1) * kStage);   // not kPacked; the last slot is free until the first stage is read
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int row0 = blockIdx.y * 16 * MT, col0 = blockIdx.x * 16 * NT;
-  const int M = *p.count;
-  if (blockIdx.y > 0 && row0 >= M) return;           // the first tile need not wait for the count
+  int M = 0, my_src = 0;
+  if (SRC == kPacked) {
+    M = *p.count;
+    if (blockIdx.y > 0 && row0 >= M) return;         // the first tile need not wait for the count
+  }
 
   const int steps = p.K / 32, nk = steps / S;        // steps: blocks of 1 KiB per 16 rows
-  const unsigned char* asrc = reinterpret_cast<const unsigned char*>(p.A) + static_cast<size_t>(row0 / 16 + wave) * steps * 1024 + 16 * lane;
+  const unsigned char* asrc = static_cast<const unsigned char*>(p.A) + static_cast<size_t>(row0 / 16 + wave) * steps * 1024 + 16 * lane;
   const unsigned char* wsrc = reinterpret_cast<const unsigned char*>(p.W) + static_cast<size_t>(col0 / 16) * steps * 1024 + 16 * lane;
   typedef __attribute__((address_space(3))) void* lds_ptr;
   typedef const __attribute__((address_space(1))) void* gbl_ptr;
-  auto fetch = [&](int slot, int kt) {
+  // rows: load u of a stage brings chunks 64 u + lane of the wavefront's 16 rows, kRowChunks of 16 bytes each
+  constexpr int kRowChunks = 4 * AL;
+  auto swizzle = [](int row) { return kRowChunks == 8 ? (row >> 1) & 7 : row & 15; };
+  const unsigned char* rsrc[AL];
+  auto fetch_a = [&](int slot, int kt) {
+    if constexpr (SRC == kPacked) {
 #pragma unroll
-    for (int u = 0; u < S; ++u)
-      __builtin_amdgcn_global_load_lds((gbl_ptr)(asrc + static_cast<size_t>(kt * S + u) * 1024),
-                                       (lds_ptr)(ring + slot * kStage + u * kStep + wave * 1024), 16, 0, 0);
+      for (int u = 0; u < S; ++u)
+        __builtin_amdgcn_global_load_lds((gbl_ptr)(asrc + static_cast<size_t>(kt * S + u) * 1024),
+                                         (lds_ptr)(ring + slot * kStage + u * kStep + wave * 1024), 16, 0, 0);
+    } else {
+#pragma unroll
+      for (int u = 0; u < AL; ++u)
+        __builtin_amdgcn_global_load_lds((gbl_ptr)(rsrc[u] + static_cast<size_t>(kt) * kRowChunks * 16),
+                                         (lds_ptr)(ring + slot * kStage + (wave * AL + u) * 1024), 16, 0, 0);
+    }
+  };
+  auto fetch_w = [&](int slot, int kt) {
 #pragma unroll
     for (int u = 0; u < WLOADS; ++u) {
       const int b = u * MT + wave, step = b / NT, j = b % NT;          // the stage's W blocks, dealt to the wavefronts
       __builtin_amdgcn_global_load_lds((gbl_ptr)(wsrc + (static_cast<size_t>(j) * steps + kt * S + step) * 1024),
-                                       (lds_ptr)(ring + slot * kStage + step * kStep + (MT + j) * 1024), 16, 0, 0);
+                                       (lds_ptr)(ring + slot * kStage + (SRC == kPacked ? step * kStep + (MT + j) * 1024 : kRows + b * 1024)), 16, 0, 0);
     }
   };
+
+  if constexpr (SRC == kPacked) {
+#pragma unroll
+    for (int k = 0; k < RING - 1; ++k)
+      if (k < nk) {
+        fetch_a(k, k);
+        fetch_w(k, k);
+      }
+  } else {
+    // the rows' numbers are on their way before the first weights and are ranked while those come
+    const int Ract = sdi::active_rows(p.active, p.rows_per_chain, p.R);
+    int ks[kMaxRows / 64];
+#pragma unroll
+    for (int c = 0; c < kMaxRows / 64; ++c) ks[c] = c * 64 + lane < Ract ? p.krow[c * 64 + lane] : -1;
+    if (lane < 16) src_row[16 * wave + lane] = 0;    // rows past the last: any that exists
+#pragma unroll
+    for (int k = 0; k < RING - 1; ++k)
+      if (k < nk) fetch_w(k, k);
+    if (MT > 1) ldsring::barrier_keep_loads();
+    else ldsring::wait_reads();
+#pragma unroll
+    for (int c = 0; c < kMaxRows / 64; ++c) {
+      const bool keep = static_cast<unsigned>(ks[c]) < static_cast<unsigned>(p.T);
+      const unsigned long long m = __ballot(keep);
+      const int pos = M + __popcll(m & ((1ull << lane) - 1ull)) - row0;
+      if (keep && pos >= 0 && pos < 16 * MT) src_row[pos] = c * 64 + lane;   // the same from every wavefront
+      M += __popcll(m);
+    }
+    if (MT > 1) ldsring::barrier_keep_loads();
+    else ldsring::wait_reads();
+    if (blockIdx.x == 0) {
+      for (int i = t; i < 16 * MT; i += 64 * MT)
+        if (row0 + i < M) p.rowidx[row0 + i] = src_row[i];
+      if (blockIdx.y == 0 && t == 0) *p.count = M;
+    }
+    if (blockIdx.y > 0 && row0 >= M) {
+      ldsring::wait_loads<0>();                      // nothing of this workgroup may land in LDS that is another's by then
+      return;
+    }
+#pragma unroll
+    for (int u = 0; u < AL; ++u) {
+      const int c = 64 * u + lane, row = c / kRowChunks, chunk = (c % kRowChunks) ^ swizzle(row);
+      rsrc[u] = static_cast<const unsigned char*>(p.A) + static_cast<size_t>(src_row[16 * wave + row]) * p.K * (SRC == kRowsF32 ? 4 : 2) + 16 * chunk;
+    }
+    my_src = src_row[16 * wave + (lane & 15)];
+#pragma unroll
+    for (int k = 0; k < RING - 1; ++k)
+      if (k < nk) fetch_a(k, k);
+  }
 
   f32x4 acc[NT];
 #pragma unroll
   for (int j = 0; j < NT; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int k = 0; k < RING - 1; ++k)
-    if (k < nk) fetch(k, k);
   int slot = 0, free_slot = RING - 1;
   for (int kt = 0; kt < nk; ++kt) {
     // stage kt has landed once only the younger ones are outstanding; past the barrier every wavefront has read stage
     // kt - 1 (a lone one has waited for its reads), whose slot takes stage kt + RING - 1
-    ldsring::wait_stages<OPS, RING - 2>(nk - 1 - kt);
+    // (rows: the first stages' weights came first and their A stage by stage, so fewer loads are younger than a stage's last)
+    if (SRC != kPacked && kt < RING - 1) ldsring::wait_stages<AL, RING - 2>(nk - 1 - kt);
+    else ldsring::wait_stages<OPS, RING - 2>(nk - 1 - kt);
     if (MT > 1) ldsring::barrier_keep_loads();
     else ldsring::wait_reads();
-    if (kt + RING - 1 < nk) fetch(free_slot, kt + RING - 1);
+    if (kt + RING - 1 < nk) {
+      fetch_a(free_slot, kt + RING - 1);
+      fetch_w(free_slot, kt + RING - 1);
+    }
     const unsigned char* base = ring + slot * kStage + 16 * lane;
+    const unsigned char* rows = ring + slot * kStage + wave * AL * 1024 + (lane & 15) * kRowChunks * 16;
     u32x4 a[S], w[S][NT];
 #pragma unroll
     for (int u = 0; u < S; ++u) {
-      a[u] = *reinterpret_cast<const u32x4*>(base + u * kStep + wave * 1024);
+      const int c = 4 * u + (lane >> 4), x = swizzle(lane & 15);       // chunk of 8 k, the row's permutation
+      if constexpr (SRC == kPacked) {
+        a[u] = *reinterpret_cast<const u32x4*>(base + u * kStep + wave * 1024);
+      } else if constexpr (SRC == kRowsBf16) {
+        a[u] = *reinterpret_cast<const u32x4*>(rows + ((c ^ x) << 4));
+      } else {
+        const f32x4 lo = *reinterpret_cast<const f32x4*>(rows + (((2 * c) ^ x) << 4));
+        const f32x4 hi = *reinterpret_cast<const f32x4*>(rows + (((2 * c + 1) ^ x) << 4));
+        bf16x8 b;
 #pragma unroll
-      for (int j = 0; j < NT; ++j) w[u][j] = *reinterpret_cast<const u32x4*>(base + u * kStep + (MT + j) * 1024);
+        for (int e = 0; e < 4; ++e) {
+          b[e] = static_cast<__bf16>(lo[e]);
+          b[4 + e] = static_cast<__bf16>(hi[e]);
+        }
+        a[u] = __builtin_bit_cast(u32x4, b);
+      }
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+        w[u][j] = *reinterpret_cast<const u32x4*>(base + (SRC == kPacked ? u * kStep + (MT + j) * 1024 : kRows + (u * NT + j) * 1024));
     }
     __builtin_amdgcn_sched_barrier(0);               // every read is on its way before the first product waits for one
     // the weights are the first operand: a lane then holds 4 consecutive output columns of one row
@@ -200,7 +292,7 @@ __global__ __launch_bounds__(64 * MT) void kernel(Args p) {
   // lane (l16, lq): columns col0 + 16 j + 4 lq .. + 3 of row row0 + 16 wave + l16
   const int gm = row0 + 16 * wave + (lane & 15);
   if (gm >= M) return;
-  const int src = EPI == 2 ? 0 : p.rowidx[gm];
+  const int src = EPI == 2 ? 0 : SRC != kPacked ? my_src : p.rowidx[gm];
   const float* b = EPI == 1 ? p.bias + static_cast<size_t>(p.krow[src]) * p.N : p.bias;
 #pragma unroll
   for (int j = 0; j < NT; ++j) {
@@ -217,9 +309,9 @@ __global__ __launch_bounds__(64 * MT) void kernel(Args p) {
   }
 }
 
-template <int EPI, int MT, int NT, int S, int RING>
+template <int EPI, int MT, int NT, int S, int RING, int SRC = kPacked>
 hipError_t launch(const Args& a, int R, hipStream_t st) {
-  hipLaunchKernelGGL((kernel<EPI, MT, NT, S, RING>), dim3(a.N / (16 * NT), (R + 16 * MT - 1) / (16 * MT)), dim3(64 * MT), 0, st, a);
+  hipLaunchKernelGGL((kernel<EPI, MT, NT, S, RING, SRC>), dim3(a.N / (16 * NT), (R + 16 * MT - 1) / (16 * MT)), dim3(64 * MT), 0, st, a);
   return hipGetLastError();
 }
 

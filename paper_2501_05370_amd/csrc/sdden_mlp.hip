@@ -128,15 +128,15 @@ bool few_rows(int R, int d, int H) {
 // workgroups fit the 256 CUs at once: a workgroup of 16 columns takes most of a CU's LDS (10 us at K = 4096), one of 32
 // too (13 us), two of 64 share a CU (20 us alone, 16 per 256 of them).  100 rows, K = 4096, in us at 16 / 32 / 64
 // columns: N = 4096 (512 / 256 / 128 workgroups) 19 / 14 / 19; N = 12288 (1536 / 768 / 384) 53 / 40 / 27.
-template <int EPI>
+template <int EPI, int SRC = mlpfew::kPacked>
 int launch_few(const mlpfew::Args& a, int R, hipStream_t st, std::string& err) {
   const int row_tiles = (R + 63) / 64;
   hipError_t e;
-  if (R <= 16) e = mlpfew::launch<EPI, 1, 1, 8, 4>(a, R, st);
-  else if (R <= 32) e = mlpfew::launch<EPI, 2, 1, 8, 5>(a, R, st);
-  else if (a.N / 16 * row_tiles <= 256) e = mlpfew::launch<EPI, 4, 1, 8, 4>(a, R, st);
-  else if (a.N / 32 * row_tiles <= 256) e = mlpfew::launch<EPI, 4, 2, 4, 6>(a, R, st);
-  else e = mlpfew::launch<EPI, 4, 4, 2, 4>(a, R, st);
+  if (R <= 16) e = mlpfew::launch<EPI, 1, 1, 8, 4, SRC>(a, R, st);
+  else if (R <= 32) e = mlpfew::launch<EPI, 2, 1, 8, 5, SRC>(a, R, st);
+  else if (a.N / 16 * row_tiles <= 256) e = mlpfew::launch<EPI, 4, 1, 8, 4, SRC>(a, R, st);
+  else if (a.N / 32 * row_tiles <= 256) e = mlpfew::launch<EPI, 4, 2, 4, 6, SRC>(a, R, st);
+  else e = mlpfew::launch<EPI, 4, 4, 2, 4, SRC>(a, R, st);
   if (e != hipSuccess) return sdi::fail(err, SD_ERR_HIP, "mlp few-row product launch: %s", hipGetErrorString(e));
   return SD_OK;
 }
@@ -232,14 +232,31 @@ struct MlpDenoiser final : sdden {
 
   // few_rows(R, d, H): Xb, H1 and H2 hold the rows in fragment order.
   int eval_few(int R, const float* X, const uint16_t* Xbf16, const int32_t* krow, float* out, hipStream_t st) {
-    const int kchunk = 512;                        // 32 KiB of fp32 states per workgroup
-    hipLaunchKernelGGL(mlpfew::pack_rows_kernel, dim3((d + kchunk - 1) / kchunk, (R + 15) / 16), dim3(mlpfew::kPackThreads), 0, st, X,
-                       Xbf16, krow, active, rows_per_chain, R, T, d, kchunk, Xb, rowidx, count);
-    mlpfew::Args a;
+    mlpfew::Args a{};
     a.count = count; a.rowidx = rowidx; a.krow = krow;
-    a.A = Xb; a.W = F1; a.N = H; a.K = d; a.bias = tb; a.outb = H1; a.outf = nullptr;
-    prof.mark(1, st);
-    int rc = launch_few<1>(a, R, st, err);
+    a.active = active; a.rows_per_chain = rows_per_chain; a.R = R; a.T = T;
+    a.W = F1; a.N = H; a.K = d; a.bias = tb; a.outb = H1; a.outf = nullptr;
+    int rc;
+    // The first product loads the rows itself, fp32 ones where the packing launch costs more than twice the rows' loads in
+    // every workgroup; us a pass of draft and two predictions, K = 8, without / with that launch for the window start: d = 512, H = 256,
+    // 3 chains 31.7 / 33.4; d = 1024, H = 1024, 1 chain 34.1 / 37.2; d = 2048 34.8 / 33.6; d = 6144 53.0 / 46.2.
+    if (Xbf16 || (R <= 16 && d <= 1024)) {
+      a.A = Xbf16 ? static_cast<const void*>(Xbf16) : X;
+      prof.mark(1, st);
+      if (Xbf16) {
+        rc = launch_few<1, mlpfew::kRowsBf16>(a, R, st, err);
+      } else {
+        const hipError_t e = mlpfew::launch<1, 1, 1, 4, 6, mlpfew::kRowsF32>(a, R, st);
+        rc = e == hipSuccess ? SD_OK : sdi::fail(err, SD_ERR_HIP, "mlp few-row product launch: %s", hipGetErrorString(e));
+      }
+    } else {
+      const int kchunk = 512;                      // 32 KiB of fp32 states per workgroup
+      hipLaunchKernelGGL(mlpfew::pack_rows_kernel, dim3((d + kchunk - 1) / kchunk, (R + 15) / 16), dim3(mlpfew::kPackThreads), 0, st, X,
+                         krow, active, rows_per_chain, R, T, d, kchunk, Xb, rowidx, count);
+      a.A = Xb;
+      prof.mark(1, st);
+      rc = launch_few<1>(a, R, st, err);
+    }
     prof.mark(1, st);
     if (rc) return rc;
     a.A = H1; a.W = F2; a.N = H; a.K = H; a.bias = b2; a.outb = H2;

@@ -75,3 +75,32 @@ def test_every_tile_gives_the_same_bits():
         out = torch.zeros(rows, d, device="cuda")
         g.sdden_eval(rows, x[:rows], k[:rows], out)
         assert torch.equal(out, whole[:rows]), rows
+
+
+@pytest.mark.parametrize("R", [16, 30, 100, 1000])
+def test_rows_found_by_the_first_product(R):
+    """With a bf16 image the first product looks for the rows itself: a device-side chain count, no row at all, rows at the end of
+    the buffer only; the image of masked rows is never read into a result."""
+    from paper_2501_05370_amd.binding import Denoiser
+    d, H, T = 512, 256, 9
+    g = Denoiser.sdden_mlp_create(W.random_mlp(np.random.default_rng(1), d, H, 16), T, 1024)
+    gen = torch.Generator(device="cuda").manual_seed(2)
+    x = torch.randn(R, d, device="cuda", generator=gen)
+    img = x.to(torch.bfloat16).view(torch.int16).contiguous()
+    k = torch.randint(0, T, (R,), device="cuda", generator=gen, dtype=torch.int32)
+    whole = torch.zeros(R, d, device="cuda")
+    g.sdden_eval(R, x, k, whole)
+    last = torch.full_like(k, T)
+    last[-3:] = k[-3:]
+    cnt = torch.tensor([3], dtype=torch.int32, device="cuda")
+    for krow, present, count in ((k, 3 * 5, cnt), (torch.full_like(k, -1), 0, None), (last, None, None)):
+        out = torch.full((R, d), 777.0, device="cuda")
+        img2 = img.clone()
+        g.sdden_set_active_count(count, 5 if count is not None else 1)
+        if present is None:
+            img2[:-3] = 0x7fc0
+        g.sdden_eval_mirror(R, x, img2, krow, out)
+        g.sdden_set_active_count(None, 1)
+        rows = torch.arange(R, device="cuda")
+        there = rows >= R - 3 if present is None else rows < present
+        assert torch.equal(out[there], whole[there]) and bool((out[~there] == 777.0).all())
