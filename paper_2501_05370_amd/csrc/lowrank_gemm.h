@@ -62,6 +62,9 @@ struct Args {
   // STAGE 1: partial sums, slab s = part + s * slab_stride, dense rows of N floats
   float* part;
   int64_t slab_stride;
+  // STAGE 2 with RANK (calls of few rows): P' is made by every workgroup for its own rows, from the slabs above
+  int nsplit;
+  const float *gain, *sab, *qmu, *gperp, *coef;
   // STAGE 2 epilogue: out[src] = acc + gp X[src] + cf mu with (src, gp, cf) = rowinfo[row]
   const RowInfo* rowinfo;
   const float* X;
@@ -106,22 +109,51 @@ struct Shape {
   static_assert(NA % NW == 0 && NB % NW == 0, "loads must divide evenly over the wavefronts");
   static_assert(NS >= 2 && lds + 4 * BM <= 160 * 1024 && (NS - 1) * OPS < 64, "ring");
 };
+// STAGE 2 with RANK: the ring holds B alone, the tile's whole A lies behind it
+template <int WM, int WN, int TM, int TN, int NS>
+constexpr size_t fused_lds(int nk) {
+  return static_cast<size_t>(NS) * Shape<WM, WN, TM, TN, NS, 2>::NB * 1024 + static_cast<size_t>(nk) * Shape<WM, WN, TM, TN, NS, 2>::NA * 1024;
+}
 
+// Eight columns of P': gain[k] .* (sum_s part_s - sab[k] qmu), slabs added in order, as split pieces.
+__device__ __forceinline__ void gained8(const float* __restrict__ o, int64_t slab_stride, int nsplit, const float* __restrict__ gk,
+                                        float sb, const float* __restrict__ qmu, u32x4 (&piece)[3]) {
+  f32x4 s0 = *reinterpret_cast<const f32x4*>(o), s1 = *reinterpret_cast<const f32x4*>(o + 4);
+#pragma unroll 4
+  for (int i = 1; i < nsplit; ++i) {
+    s0 += *reinterpret_cast<const f32x4*>(o + i * slab_stride);
+    s1 += *reinterpret_cast<const f32x4*>(o + i * slab_stride + 4);
+  }
+  float x[8];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    x[e] = gk[e] * (s0[e] - sb * qmu[e]);
+    x[4 + e] = gk[4 + e] * (s1[e] - sb * qmu[4 + e]);
+  }
+  split8(x, piece);
+}
+
+// STAGE 2 with RANK (calls of few rows): every workgroup adds up and scales its own rows of P' into LDS, which for 16 or 32 rows is
+// a few loads per thread, in place of a launch of reduce_gain_kernel and a round trip through memory (LowRankDenoiser::eval has
+// the figures).
 // Workgroup of WM x WN wavefronts, wavefront tile 16 TM x 16 TN, NS slices of 32 k in an LDS ring.  Grid: (column tiles x
 // row tiles, K ranges).  The weights are the first MFMA operand: a lane holds 4 consecutive output columns of one row.
 template <int WM, int WN, int TM, int TN, int NS, int STAGE, bool RANK>
 __global__ __launch_bounds__(64 * WM * WN) void kernel(Args p) {
   using S = Shape<WM, WN, TM, TN, NS, STAGE>;
-  constexpr int NW = S::NW, BM = S::BM, BN = S::BN, ASZ = S::NA * 1024;
+  // FUSED: no loads of A; the ring's slices hold B and the whole tile of A, made here, follows the ring
+  constexpr bool FUSED = STAGE == 2 && RANK;
+  constexpr int NW = S::NW, BM = S::BM, BN = S::BN, ASZ = FUSED ? 0 : S::NA * 1024;
+  constexpr int NA = FUSED ? 0 : S::NA, OPS = (NA + S::NB) / NW, kSlice = (NA + S::NB) * 1024;
   extern __shared__ __align__(1024) unsigned char ring[];
-  __shared__ int src_row[RANK ? BM : 1];
+  __shared__ int src_row[STAGE == 1 && RANK ? BM : 1];
 
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int tiles_n = (p.N + BN - 1) / BN;
   const int tile_m = blockIdx.x / tiles_n, tile_n = blockIdx.x % tiles_n;
   int M;
-  if constexpr (RANK) {
+  if constexpr (STAGE == 1 && RANK) {
     // every wavefront ranks all rows by itself (one load per 64 rows) and notes those of this tile
     const int Ract = sdi::active_rows(p.active, p.rows_per_chain, p.R);
     int ks[kRankRows / 64];
@@ -151,10 +183,10 @@ __global__ __launch_bounds__(64 * WM * WN) void kernel(Args p) {
   const bool half_end = STAGE == 1 && (p.d & 16) && k_lo + nk == p.nk;     // the last slice has 16 columns only
 
   const int wm = wave / WN, wn = wave % WN, l16 = lane & 15, lq = lane >> 4;
-  const unsigned char* src[S::OPS];      // this lane's source per load; rows and columns past the end are clamped
+  const unsigned char* src[OPS];      // this lane's source per load; rows and columns past the end are clamped
   int back = 0;                          // bit i: load i reads chunks 4..7, absent from a half slice
 #pragma unroll
-  for (int i = 0; i < S::NA / NW; ++i) {
+  for (int i = 0; i < NA / NW; ++i) {
     const int g = i * NW + wave;
     if constexpr (STAGE == 1) {
       const int row = 8 * g + (lane >> 3), chunk = (lane & 7) ^ ((row >> 1) & 7);
@@ -173,22 +205,22 @@ __global__ __launch_bounds__(64 * WM * WN) void kernel(Args p) {
     const int g = i * NW + wave;
     int cb = tile_n * (BN / 16) + g / 3;
     cb = 16 * cb < p.N ? cb : p.N / 16 - 1;
-    src[S::NA / NW + i] = p.Bt + (static_cast<int64_t>(cb) * p.nk + k_lo) * kBlockBytes + (g % 3) * 1024 + 16 * lane;
+    src[NA / NW + i] = p.Bt + (static_cast<int64_t>(cb) * p.nk + k_lo) * kBlockBytes + (g % 3) * 1024 + 16 * lane;
   }
   typedef __attribute__((address_space(3))) void* lds_ptr;
   typedef const __attribute__((address_space(1))) void* gbl_ptr;
   auto fetch = [&](int slot, int kt) {
-    unsigned char* base = ring + slot * S::kSlice;
+    unsigned char* base = ring + slot * kSlice;
     const bool half = half_end && kt == nk - 1;
 #pragma unroll
-    for (int i = 0; i < S::NA / NW; ++i) {
+    for (int i = 0; i < NA / NW; ++i) {
       const unsigned char* a = src[i] + static_cast<int64_t>(kt) * (STAGE == 1 ? 128 : kBlockBytes);
       if (STAGE == 1 && half) a -= ((back >> i) & 1) * 64;       // any in-bounds chunk: its fragments become zero
       __builtin_amdgcn_global_load_lds((gbl_ptr)a, (lds_ptr)(base + (i * NW + wave) * 1024), 16, 0, 0);
     }
 #pragma unroll
     for (int i = 0; i < S::NB / NW; ++i)
-      __builtin_amdgcn_global_load_lds((gbl_ptr)(src[S::NA / NW + i] + static_cast<int64_t>(kt) * kBlockBytes),
+      __builtin_amdgcn_global_load_lds((gbl_ptr)(src[NA / NW + i] + static_cast<int64_t>(kt) * kBlockBytes),
                                        (lds_ptr)(base + ASZ + (i * NW + wave) * 1024), 16, 0, 0);
   };
 
@@ -209,8 +241,13 @@ __global__ __launch_bounds__(64 * WM * WN) void kernel(Args p) {
   if constexpr (STAGE == 2) {
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
-      const int gm = row0 + 16 * i;
-      info[i] = p.rowinfo[gm < M ? gm : M - 1];
+      const int gm = row0 + 16 * i < M ? row0 + 16 * i : M - 1;
+      if constexpr (FUSED) {
+        const int from = p.rowidx[gm], k = p.krow[from];
+        info[i] = RowInfo{from, p.gperp[k], p.coef[k], 0};
+      } else {
+        info[i] = p.rowinfo[gm];
+      }
     }
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
@@ -221,14 +258,32 @@ __global__ __launch_bounds__(64 * WM * WN) void kernel(Args p) {
     }
   }
 
+  if constexpr (FUSED) {
+    // the tile's rows of P': a thread keeps its row, rows fastest, so that a wavefront's writes are whole blocks
+    static_assert(64 * NW % BM == 0, "a row per thread");
+    const int rank = 32 * nk, row = t % BM, gm = tile_m * BM + row < M ? tile_m * BM + row : M - 1;
+    const int k = p.krow[p.rowidx[gm]];
+    const float *from = p.part + static_cast<int64_t>(gm) * rank, *gk = p.gain + static_cast<int64_t>(k) * rank;
+    const float sb = p.sab[k];
+#pragma unroll 2
+    for (int c = t / BM * 8; c < rank; c += 64 * NW / BM * 8) {
+      u32x4 piece[3];
+      gained8(from + c, p.slab_stride, p.nsplit, gk + c, sb, p.qmu + c, piece);
+      unsigned char* dst = ring + NS * kSlice + (c >> 5) * S::NA * 1024 + (row >> 4) * kBlockBytes + (((c & 31) >> 3) * 16 + (row & 15)) * 16;
+#pragma unroll
+      for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x4*>(dst + 1024 * q) = piece[q];
+    }                                                        // the first slice's barrier makes it everyone's
+  }
+
   int slot = 0, free_slot = NS - 1;
   for (int kt = 0; kt < nk; ++kt) {
     // slice kt has landed once only the younger ones are outstanding; past the barrier every wavefront has read slice
     // kt - 1, whose slot takes slice kt + NS - 1
-    ldsring::wait_stages<S::OPS, NS - 2>(nk - 1 - kt);
+    ldsring::wait_stages<OPS, NS - 2>(nk - 1 - kt);
     ldsring::barrier_keep_loads();
     if (kt + NS - 1 < nk) fetch(free_slot, kt + NS - 1);
-    const unsigned char* base = ring + slot * S::kSlice;
+    const unsigned char* base = ring + slot * kSlice;
+    const unsigned char* abase = FUSED ? ring + NS * kSlice + kt * S::NA * 1024 : base;
     u32x4 a[TM][3];
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
@@ -244,7 +299,7 @@ __global__ __launch_bounds__(64 * WM * WN) void kernel(Args p) {
       } else {
 #pragma unroll
         for (int q = 0; q < 3; ++q)
-          a[i][q] = *reinterpret_cast<const u32x4*>(base + ((wm * TM + i) * 3 + q) * 1024 + 16 * lane);
+          a[i][q] = *reinterpret_cast<const u32x4*>(abase + ((wm * TM + i) * 3 + q) * 1024 + 16 * lane);
       }
     }
 #pragma unroll
@@ -309,23 +364,8 @@ __global__ __launch_bounds__(256) void reduce_gain_kernel(const float* __restric
   const int src = rowidx[gm];
   const int k = krow[src];
   if (c == 0) rowinfo[gm] = RowInfo{src, gperp[k], coef[k], 0};
-  const float* o = part + static_cast<int64_t>(gm) * N + c;
-  f32x4 s0 = *reinterpret_cast<const f32x4*>(o), s1 = *reinterpret_cast<const f32x4*>(o + 4);
-#pragma unroll 4
-  for (int i = 1; i < nsplit; ++i) {
-    s0 += *reinterpret_cast<const f32x4*>(o + i * slab_stride);
-    s1 += *reinterpret_cast<const f32x4*>(o + i * slab_stride + 4);
-  }
-  const float* gk = gain + static_cast<int64_t>(k) * N + c;
-  const float sb = sab[k];
-  float x[8];
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    x[e] = gk[e] * (s0[e] - sb * qmu[c + e]);
-    x[4 + e] = gk[4 + e] * (s1[e] - sb * qmu[c + 4 + e]);
-  }
   u32x4 piece[3];
-  split8(x, piece);
+  gained8(part + static_cast<int64_t>(gm) * N + c, slab_stride, nsplit, gain + static_cast<int64_t>(k) * N + c, sab[k], qmu + c, piece);
   unsigned char* dst = P + block_offset(gm, c, N / 32);
 #pragma unroll
   for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x4*>(dst + 1024 * q) = piece[q];
@@ -338,6 +378,15 @@ hipError_t prepare() {
   return hipFuncSetAttribute(reinterpret_cast<const void*>(&kernel<WM, WN, TM, TN, NS, STAGE, RANK>),
                              hipFuncAttributeMaxDynamicSharedMemorySize,
                              static_cast<int>(Shape<WM, WN, TM, TN, NS, STAGE>::lds));
+}
+
+// The second product with the reduction in it (STAGE 2, RANK).
+template <int WM, int WN, int TM, int TN, int NS>
+hipError_t launch_fused(const Args& a, int R, hipStream_t st) {
+  using S = Shape<WM, WN, TM, TN, NS, 2>;
+  const int tiles = ((R + S::BM - 1) / S::BM) * ((a.N + S::BN - 1) / S::BN);
+  hipLaunchKernelGGL((kernel<WM, WN, TM, TN, NS, 2, true>), dim3(tiles), dim3(64 * S::NW), (fused_lds<WM, WN, TM, TN, NS>(a.nk)), st, a);
+  return hipGetLastError();
 }
 
 template <int WM, int WN, int TM, int TN, int NS, int STAGE, bool RANK>

@@ -157,18 +157,31 @@ struct LowRankDenoiser final : sdden {
                                         : lrgemm::launch<1, 1, 1, 1, 6, 1, false>(a, R, nsplit, st));
     SD_HIP_TRY(err, e);
     prof.mark(1, st);
-    const int64_t octs = static_cast<int64_t>(R) * (rpad / 8);
-    hipLaunchKernelGGL(lrgemm::reduce_gain_kernel, dim3(static_cast<unsigned>((octs + 255) / 256)), dim3(256), 0, st, part,
-                       a.slab_stride, nsplit, count, rowidx, krow, gain, sab, qmu, P, rpad, gperp, coef, rowinfo);
-    // out = P' Q^T + gperp x + coef mu
     lrgemm::Args b{};
     b.A = P; b.d = d; b.Bt = wQ; b.N = d; b.nk = rpad / lrgemm::BK; b.count = count;
     b.rowinfo = rowinfo; b.X = X; b.out = out; b.out_aligned = sdi::aligned16(out); b.mu = mu;
-    prof.mark(2, st);
-    e = s2 == 0   ? lrgemm::launch<2, 2, 2, 4, 2, 2, false>(b, R, 1, st)
-        : s2 == 1 ? lrgemm::launch<2, 2, 2, 2, 3, 2, false>(b, R, 1, st)
-        : s2 == 2 ? lrgemm::launch<2, 1, 1, 2, 4, 2, false>(b, R, 1, st)
-                  : lrgemm::launch<1, 1, 1, 1, 6, 2, false>(b, R, 1, st);
+    // out = P' Q^T + gperp x + coef mu
+    // The reduction inside the second product is done again by every column tile, a thread per row and eight columns at a time:
+    // ahead of its launch at ranks of up to 64 while a row's slabs hold 512 floats and all tiles' 16 MB at most.  us a call, inside / by a launch: d = 1104,
+    // r = 50 1 row 11.9 / 13.6, 133 rows 13.1 / 14.0; d = 512, r = 30 133 rows 10.3 / 13.3; but d = 3072, r = 50 (768 floats) 13 rows
+    // 14.0 / 13.5, 250 rows (73 MB) 21.3 / 16.6; d = 2000, r = 100 40 rows 14.9 / 14.5; d = 3072, r = 200 1 row 23.3 / 17.6.
+    const int fm = s2 == 2 ? 32 : 16;
+    const bool fused = s2 >= 2 && rpad <= 64 && rpad * nsplit <= 512 && tiles(R, d, fm, fm) * fm * rpad * nsplit * 4 <= (16 << 20);
+    if (fused) {
+      b.rowidx = rowidx; b.krow = krow; b.part = part; b.slab_stride = a.slab_stride; b.nsplit = nsplit;
+      b.gain = gain; b.sab = sab; b.qmu = qmu; b.gperp = gperp; b.coef = coef;
+      prof.mark(2, st);
+      e = s2 == 2 ? lrgemm::launch_fused<2, 1, 1, 2, 4>(b, R, st) : lrgemm::launch_fused<1, 1, 1, 1, 6>(b, R, st);
+    } else {
+      const int64_t octs = static_cast<int64_t>(R) * (rpad / 8);
+      hipLaunchKernelGGL(lrgemm::reduce_gain_kernel, dim3(static_cast<unsigned>((octs + 255) / 256)), dim3(256), 0, st, part,
+                         a.slab_stride, nsplit, count, rowidx, krow, gain, sab, qmu, P, rpad, gperp, coef, rowinfo);
+      prof.mark(2, st);
+      e = s2 == 0   ? lrgemm::launch<2, 2, 2, 4, 2, 2, false>(b, R, 1, st)
+          : s2 == 1 ? lrgemm::launch<2, 2, 2, 2, 3, 2, false>(b, R, 1, st)
+          : s2 == 2 ? lrgemm::launch<2, 1, 1, 2, 4, 2, false>(b, R, 1, st)
+                    : lrgemm::launch<1, 1, 1, 1, 6, 2, false>(b, R, 1, st);
+    }
     SD_HIP_TRY(err, e);
     prof.mark(2, st);
     SD_HIP_TRY(err, hipGetLastError());
