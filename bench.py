@@ -82,17 +82,26 @@ def roofline_plan(cfg, loop="eager", drafter="frozen"):
         if loop == "fused":
             # one prediction per step; the efficient frozen drafter's carried one per window; the draft model's per step
             rows = {"frozen": lambda c: c[0], "independent": lambda c: 1.5 * c[0]}.get(drafter, lambda c: c[0] + c[1])
-            return dict(kernel="gmm_run_kernel (sdden_run: every chain's windows back to back in one launch, mixture posterior mean in "
-                               "fp64 inside it)", stage="chains_run", bound="alu", peak="alu_fp64", scale=1e-12,
+            # (steps held by one component skip the passes over all pairs: the count stays the method's)
+            return dict(kernel=("gmm_window_run_kernel" if cfg.B <= 1024 and d <= 256 and K > 1 and drafter != "independent" else "gmm_run_kernel") +
+                               " (sdden_run: every chain's windows back to back in one launch, mixture posterior mean in fp64 "
+                               "inside it)", stage="chains_run", bound="alu", peak="alu_fp64", scale=1e-12,
                         work=lambda c: 15.0 * M * d * rows(c))
         return dict(kernel="gmm_rows_kernel (mixture posterior mean, fp64) of the batched target call", den_which=1,
                     den_min_rows=cfg.B + 1, bound="alu", peak="alu_fp64", scale=1e-12,
                     work=lambda c: 15.0 * M * d * (c[4] - c[1]))
     if cfg.kind == "langevin":
         M = cfg.params.means.shape[0]
+        if loop == "fused":
+            # the run form computes no logits while one component holds the state, nearly always on this mixture.  Vector work per
+            # coordinate and step in four-cycle units (as for phi4 below), per lane of 16 coordinates: Philox 196, Box-Muller
+            # and uniforms 88, conversions 16, distance from the mean 16, difference from the frozen one 16, dot products and
+            # norms 40, update 32, reductions and accept test 60: 464, 29 per coordinate.
+            return dict(kernel="langevin_window_wave_kernel<4> (sd_langevin_run: every chain's windows back to back in one launch, one "
+                               "wavefront per chain, logits only where more than one component may matter)", stage="langevin_window",
+                        bound="alu", peak="alu_lane", scale=1e-12, work=lambda c: float(c[0]) * d * 29.0)
         # fp64 flops per evaluated position: logits 3 M d, gradient 2 M d + 2 d, Delta / dots / update 12 d
-        return dict(kernel="langevin_window_wave_kernel<4> (fused draft + score + verify, one wavefront per chain; with --loop fused "
-                           "its run form: every chain's windows back to back in one launch)", stage="langevin_window",
+        return dict(kernel="langevin_window_wave_kernel<4> (fused draft + score + verify, one wavefront per chain)", stage="langevin_window",
                     bound="alu", peak="alu_fp64", scale=1e-12,
                     work=lambda c: float(c[0] + c[1]) * d * (5.0 * M + 14.0))
     if cfg.kind == "phi4":
@@ -212,7 +221,7 @@ def run_gpu(cfg, steps, warmup, stages, drafter="frozen", loop="eager", wps=1, v
                 "work_per_launch": work / max(1, k_launches)}
     if timed_note:
         roofline["timed_in"] = timed_note
-    if cfg.kind == "langevin":
+    if cfg.kind == "langevin" and loop != "fused":
         # The algorithmic count prices the weighted mean over all M components (2 M d of the 5 M d); the kernel skips
         # components whose responsibility is below 1e-25, which changes nothing to fp64 rounding.  Live components
         # are counted here on the final states of the run (this well-separated mixture leaves one or two).

@@ -550,7 +550,7 @@ __global__ __launch_bounds__(256) void gmm_run_kernel(RunArgs p) {
 // itself (two operations each, noise from a ring in LDS that the wavefronts fill ahead in turn); a round's states, predictions
 // and verdicts go through LDS, in buffers that alternate, behind one barrier.  Values and decisions are those of the
 // kernel above: same operations on the same numbers.
-// Bound by a round's latency, about 2 us: 64 chains of the toy (d = 2, M = 8, K = 4, 3.8 of 4 accepted) 121 us a run, 164 with a
+// Bound by a round's latency, about 2 us: 64 chains of the toy (d = 2, M = 8, K = 4, 3.8 of 4 accepted) 110 us a run, 161 with a
 // wavefront a chain; more in GmmDenoiser::run.
 // ---------------------------------------------------------------------------------------------
 template <int E, bool LDS, bool FINE, bool ALONE>
