@@ -223,7 +223,6 @@ struct RunArgs {
   const float *a, *c, *sigma;
   int B, K, T;
   int reused, carry_last;    // efficient frozen drafter and its second carry rule
-  int pair;                  // independent drafter: two wavefronts a chain, one for each model
   uint64_t seed;
   double inv_tau;
   unsigned long long* counters;   // optional: sum adv, chain-windows, rejections, windows, sum Kt
@@ -312,7 +311,9 @@ __device__ __forceinline__ float readlane_f32(float v, int src_lane) {
 // M = 40 940 / 1660; 1 chain, d = 100, M = 20 510 / 770; 300 chains, d = 75, M = 12, two models 240 / 255; but 2000 chains,
 // d = 30, M = 20 475 / 456, 64 chains, d = 2, M = 8 172 / 164.  Taken where the share of the balls that hold a typical state
 // (radius^2 > d) times the pairs per lane reaches 6: these six have 16, 110, 29, 11, 3.4 and 0.
-template <int E, int C, bool LDS, bool INDEP, bool FINE, bool ALONE>
+// PAIR (INDEP): two wavefronts a chain, one for each model; an instance of its own, because the branches around the two predictions
+// cost many chains 4 % (4096 chains, d = 10, M = 12, two models, 100 steps 568 us with them, 542 without).
+template <int E, int C, bool LDS, bool INDEP, bool FINE, bool ALONE, bool PAIR>
 __global__ __launch_bounds__(256) void gmm_run_kernel(RunArgs p) {
   extern __shared__ __align__(16) unsigned char run_smem[];
   __shared__ unsigned long long sh_cnt[4];
@@ -326,7 +327,6 @@ __global__ __launch_bounds__(256) void gmm_run_kernel(RunArgs p) {
   npad = (npad + 1) & ~1;                  // 16-byte pieces
   double* xs = xs0 + static_cast<size_t>(wave) * npad;
   float* zs = reinterpret_cast<float*>(xs0 + static_cast<size_t>(blockDim.x >> 6) * npad) + 256 * wave;   // E < 4 only
-  const bool pair = INDEP && p.pair;
   float* both = zs + 256 * ((E < 4 ? 2 : 0) - wave);       // pair: [2][2][64 E C] predictions, buffers that alternate
   int par = 0;
   stage_table<LDS>(p.t, tab_t);
@@ -335,7 +335,7 @@ __global__ __launch_bounds__(256) void gmm_run_kernel(RunArgs p) {
   if (threadIdx.x == 0) sh_longest = 0;
   __syncthreads();
 
-  const int b = pair ? static_cast<int>(blockIdx.x) : static_cast<int>(blockIdx.x) * static_cast<int>(blockDim.x >> 6) + wave;
+  const int b = PAIR ? static_cast<int>(blockIdx.x) : static_cast<int>(blockIdx.x) * static_cast<int>(blockDim.x >> 6) + wave;
   if (b < p.B) {                           // uniform over the wavefront; pair: over the workgroup
     const int d = p.t.d;
     const int64_t id = p.id[b];
@@ -383,7 +383,7 @@ __global__ __launch_bounds__(256) void gmm_run_kernel(RunArgs p) {
         lane_normals<E, C>(nb, zs, p.seed, id, k + 1, lane, z);
         // The step's one target evaluation, at the state it starts from: the frozen prediction of the window (first
         // position of the frozen drafter), else what the draft is tested against.
-        if (pair && wave == 1) {}          // the other wavefront's
+        if (PAIR && wave == 1) {}          // the other wavefront's
         else if (!ALONE || !sdgmm::mean_of_one<E, C, LDS, FINE>(p.t, tab_t, y, ab, sab, k, lane, alone_t, dq)) {
           if (ALONE) base_t = cst_t.at(p.t, k, lane);
           sdgmm::posterior_mean<E, C, LDS, !LDS, FINE>(p.t, tab_t, xs, y, ab, sab, base_t, lane, dq, ALONE ? &alone_t : nullptr, k);
@@ -394,14 +394,14 @@ __global__ __launch_bounds__(256) void gmm_run_kernel(RunArgs p) {
 #pragma unroll
             for (int e = 0; e < E; ++e) d0[c][e] = dq[c][e];
         }
-        if (INDEP && !(pair && wave == 0)) {       // the draft model's prediction
+        if (INDEP && !(PAIR && wave == 0)) {       // the draft model's prediction
           const double abq = sdgmm::readlane_f64(sb.q.x, at), sabq = sdgmm::readlane_f64(sb.q.y, at);
           if (!ALONE || !sdgmm::mean_of_one<E, C, LDS, FINE>(p.q, tab_q, y, abq, sabq, k, lane, alone_q, mp)) {
             if (ALONE) base_q = cst_q.at(p.q, k, lane);
             sdgmm::posterior_mean<E, C, LDS, !LDS, FINE>(p.q, tab_q, xs, y, abq, sabq, base_q, lane, mp, ALONE ? &alone_q : nullptr, k);
           }
         }
-        if (pair) {                        // both go on with both: all that follows is the same on the two
+        if (PAIR) {                        // both go on with both: all that follows is the same on the two
           float* mine = both + (par * 2 + wave) * 64 * E * C;
           const float* theirs = both + (par * 2 + 1 - wave) * 64 * E * C;
 #pragma unroll
@@ -511,7 +511,7 @@ __global__ __launch_bounds__(256) void gmm_run_kernel(RunArgs p) {
       }
     }
     windows = max(windows, 1);             // handed over at T: one window, of no positions, that keeps the state
-    const bool writes = !pair || wave == 0;
+    const bool writes = !PAIR || wave == 0;
     float* o = p.out + id * d;
 #pragma unroll
     for (int c = 0; c < C; ++c)
@@ -866,8 +866,10 @@ hipError_t prepare_window_run() {
 
 template <int E, int C, bool LDS, bool FINE, bool ALONE>
 void launch_run(const RunArgs& p, bool indep, unsigned grid, unsigned block, size_t shmem, hipStream_t st) {
-  if (indep) hipLaunchKernelGGL((gmm_run_kernel<E, C, LDS, true, FINE, ALONE>), dim3(grid), dim3(block), shmem, st, p);
-  else hipLaunchKernelGGL((gmm_run_kernel<E, C, LDS, false, FINE, ALONE>), dim3(grid), dim3(block), shmem, st, p);
+  if (indep && grid == static_cast<unsigned>(p.B) && block == 128)          // a workgroup of two wavefronts per chain
+    hipLaunchKernelGGL((gmm_run_kernel<E, C, LDS, true, FINE, ALONE, true>), dim3(grid), dim3(block), shmem, st, p);
+  else if (indep) hipLaunchKernelGGL((gmm_run_kernel<E, C, LDS, true, FINE, ALONE, false>), dim3(grid), dim3(block), shmem, st, p);
+  else hipLaunchKernelGGL((gmm_run_kernel<E, C, LDS, false, FINE, ALONE, false>), dim3(grid), dim3(block), shmem, st, p);
 }
 // A table in the vector caches has more than 34 pairs per lane: there an attempt costs next to nothing.
 template <int E, int C, bool LDS, bool FINE = !LDS>
@@ -898,9 +900,9 @@ int GmmDenoiser::run(sdden* draft, sd_ctx* ctx, int B, const float* y, const int
   // The two models of the independent drafter take a wavefront each while there are no more than two per SIMD; us of 60 steps
   // with / without at 1, 300 and 1000 chains: d = 75, M = 12 180 / 228, 218 / 246, 221 / 256; d = 180, M = 40 578 / 767,
   // 752 / 800, 756 / 809.
-  p.pair = indep && B <= 1024;
-  const int waves = p.pair ? 2 : B >= 2048 ? 4 : (B >= 1024 ? 2 : 1);
-  const unsigned grid = static_cast<unsigned>(p.pair ? B : (B + waves - 1) / waves), block = 64u * waves;
+  const bool pair = indep && B <= 1024;
+  const int waves = pair ? 2 : B >= 2048 ? 4 : (B >= 1024 ? 2 : 1);
+  const unsigned grid = static_cast<unsigned>(pair ? B : (B + waves - 1) / waves), block = 64u * waves;
   size_t npad = static_cast<size_t>(g.nslots) << (6 - g.lm), slots = g.nslots;
   if (q) {
     npad = std::max(npad, static_cast<size_t>(q->g.nslots) << (6 - q->g.lm));
@@ -911,7 +913,7 @@ int GmmDenoiser::run(sdden* draft, sd_ctx* ctx, int B, const float* y, const int
   const size_t table = sizeof(double2) * sdgmm::kTabStride * slots, xs = (sizeof(double) * npad + (d <= 128 ? 1024 : 0)) * waves;
   const bool lds = d <= 256 && table <= 36 * 1024;
   const int per_lane = d <= 64 ? 1 : d <= 128 ? 2 : d <= 256 ? 4 : d <= 512 ? 8 : d <= 1024 ? 16 : 32;
-  const size_t shmem = xs + (lds ? table : 0) + (p.pair ? 1024 * static_cast<size_t>(per_lane) : 0);
+  const size_t shmem = xs + (lds ? table : 0) + (pair ? 1024 * static_cast<size_t>(per_lane) : 0);
   hipLaunchKernelGGL(run_begin_kernel, dim3(1), dim3(1), 0, st, p.longest);
   // a table that fits LDS has at most 32 pairs per lane, and at d > 64 at most 32 components too
   const bool fine = g.M > 32 || (q && q->g.M > 32);
