@@ -20,6 +20,7 @@
 #include "sd_internal.h"
 #include "sd_lanes.h"
 #include "sd_rng.h"
+#include "sole_bound.h"
 
 namespace {
 
@@ -69,27 +70,15 @@ __device__ __forceinline__ double dpp_xor(double v, int mask) {
 // responsibilities are then below e^-60 < 1e-25, which the weighted mean skips and the softmax sum rounds away: the
 // responsibility of a is exactly 1, the gradient (x - mu_a) / s^2, the same bits as with all logits.  On mixtures whose
 // components lie a few standard deviations per coordinate apart a chain is in a ball almost all the time; elsewhere the
-// logits are computed as ever.  Distances walked are bounded from above, radii from below: fp32 with a margin far above its
-// rounding.  Whatever is not a number fails the comparison with 0 and takes the long way.
+// logits are computed as ever.  Distances walked are bounded from above, radii from below: each in fp32 with a margin (kUp,
+// kDown) far above its rounding, and sums of them for any number of steps (sole_bound.h).  Whatever is not a number fails the comparison with 0 and takes the long way.
 // ---------------------------------------------------------------------------------------------
 constexpr double kSoleGap = 60.0;
 constexpr float kUp = 1.0001f, kDown = 0.9999f;
 
-struct Sole {
-  float slack = -1.f;        // how far the state may still move with component `top` alone
-  float radius = 0.f;        // of the ball around mu_top
-  float rho = 0.f;           // upper bound of |x - mu_top|
+struct Sole : SoleBound {
   int top = -1;              // component the distances belong to
   __device__ __forceinline__ bool holds() const { return __builtin_amdgcn_readfirstlane(slack > 0.f ? 1 : 0) != 0; }
-  // the state is at (at most) `r` from mu_top
-  __device__ __forceinline__ void at_distance(float r) {
-    rho = r;
-    slack = fmaxf(slack, radius - r);      // the better of two bounds; one that is not a number gives way
-  }
-  __device__ __forceinline__ void moved(float by) {
-    slack -= by;
-    rho += by;
-  }
 };
 
 // Sum over the wavefront in fp32, the same bits on every lane.

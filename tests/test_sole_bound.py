@@ -1,0 +1,56 @@
+"""The distance bounds behind the sole-component rule of the Langevin kernels, compiled for the host from the kernels' own header: over any
+number of steps the slack stays at or below what is left of it and the distance at or above what was walked, also where a
+step is below the last bit of either."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SOURCE = r"""
+#include "sole_bound.h"
+extern "C" void walk(float* slack, float* rho, float by, long steps) {
+  SoleBound s;
+  s.slack = *slack;
+  s.rho = *rho;
+  for (long i = 0; i < steps; ++i) s.moved(by);
+  *slack = s.slack;
+  *rho = s.rho;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def walk(tmp_path_factory):
+    d = tmp_path_factory.mktemp("sole")
+    (d / "w.cpp").write_text(SOURCE)
+    lib = str(d / "w.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-I", os.path.join(ROOT, "paper_2501_05370_amd", "csrc"),
+                    str(d / "w.cpp"), "-o", lib], check=True)
+    fn = ctypes.CDLL(lib).walk
+    fn.argtypes = [ctypes.POINTER(ctypes.c_float), ctypes.POINTER(ctypes.c_float), ctypes.c_float, ctypes.c_long]
+
+    def run(slack, by, steps):
+        s, r = ctypes.c_float(slack), ctypes.c_float(slack)
+        fn(s, r, by, steps)
+        return s.value, r.value
+    return run
+
+
+@pytest.mark.parametrize("share", [1e-2, 3e-5, 2.9e-7, 8.9e-8, 4e-8, 2e-8, 1e-9])
+@pytest.mark.parametrize("slack", [1.0, 1.9999999, 3e-4, 7.3e9])
+def test_roundings_do_not_add_up(walk, share, slack):
+    slack = float(np.float32(slack))
+    by = float(np.float32(slack * share))
+    steps = min(200_000, int(0.9 / share))
+    got, rho = walk(slack, by, steps)
+    assert got <= slack - steps * by                     # fp64 to 1e-16
+    assert rho >= slack + steps * by
+    # and the bound is of use: 4e-7 of the distance a step at most
+    assert got >= (slack - steps * by) * (1 - 4e-7 * steps) - 4e-7 * steps * slack
+
+
+def test_a_mixture_of_one_component_never_runs_out(walk):
+    assert walk(float("inf"), 1.0, 1000)[0] == float("inf")
