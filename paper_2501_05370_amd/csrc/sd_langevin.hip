@@ -491,7 +491,7 @@ __global__ __launch_bounds__(MAXT) void langevin_window_kernel(LangevinArgs p) {
     Kt = max(0, min(p.K, p.T - n));
 #pragma unroll
     for (int e = 0; e < 4; ++e) cur[e] = static_cast<double>(static_cast<float>(cur[e]));
-    sole.moved(6.1e-8f * (norm_top + sole.rho));           // half an fp32 unit of the state's length
+    sole.window_ended(6.1e-8f * (norm_top + sole.rho));           // half an fp32 unit of the state's length
   }
 
   if (RUN) {
@@ -816,7 +816,7 @@ __global__ __launch_bounds__(64 * wave_chains(CPT), wave_chains(CPT) / 4) void l
     for (int c = 0; c < CPT; ++c)
 #pragma unroll
       for (int e = 0; e < 4; ++e) cur[c][e] = static_cast<double>(static_cast<float>(cur[c][e]));
-    sole.moved(6.1e-8f * (norm_top + sole.rho));           // half an fp32 unit of the state's length
+    sole.window_ended(6.1e-8f * (norm_top + sole.rho));           // half an fp32 unit of the state's length
     Kt = windows < p.max_windows ? max(0, min(p.K, p.T - n)) : 0;
   }
 

@@ -18,10 +18,18 @@ struct SoleBound {
     rho = r;
     slack = fmaxf(slack, radius - r);      // the better of two bounds; one that is not a number gives way
   }
-  // A chain may be walked for any number of steps between two looks, each of them far below the slack's last bit, so the
-  // roundings must not add up: with u = 2^-24, (1 + u)^2 (1 - 2u) < 1 and (1 - u)^2 (1 + 4u) > 1.
   SOLE_FN void moved(float by) {
-    slack = (slack - by) * (1.f - 0x1p-23f);
-    rho = (rho + by) * (1.f + 0x1p-22f);
+    slack -= by;
+    rho += by;
+  }
+  // A chain may be walked for any number of steps between two looks, each of them below the slack's last bit, so the roundings
+  // must not add up.  A window's 64 steps and this one round by 65 of 2^-24 at most, of the slack at the window's start; a factor
+  // of 1 - 2^-16 takes that back where the slack fell to a quarter or less slowly, and the windows in which it fell faster
+  // leave 65 (1 + 1/4 + ...) 2^-24 = 5.2e-6 of the slack when it was set, which carries a margin of 1e-4.  The distance only
+  // grows: the factor covers it.  Per window and not per step: 1.5 % of a run of 1000 coordinates.
+  SOLE_FN void window_ended(float by) {
+    moved(by);
+    slack *= 1.f - 0x1p-16f;
+    rho *= 1.f + 0x1p-16f;
   }
 };
