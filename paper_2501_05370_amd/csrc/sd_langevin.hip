@@ -15,6 +15,7 @@
 // fp64.  The phi^4 lattice energy has kernels of its own at the end of the file.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 
 #include "sd_internal.h"
@@ -74,6 +75,7 @@ __device__ __forceinline__ double dpp_xor(double v, int mask) {
 // kDown) far above its rounding, and sums of them for any number of steps (sole_bound.h).  Whatever is not a number fails the comparison with 0 and takes the long way.
 // ---------------------------------------------------------------------------------------------
 constexpr double kSoleGap = 60.0;
+constexpr double kSoleEnter = 72.0;        // gap from which the workgroup-per-chain kernel follows one component: not at every flicker
 constexpr float kUp = 1.0001f, kDown = 0.9999f;
 
 struct Sole : SoleBound {
@@ -198,23 +200,34 @@ __device__ __forceinline__ float reduce16_transposed_f32(float (&a)[16]) {
   return v + __int_as_float(sdlane::lane_xor<1>(__float_as_int(v)));
 }
 
+struct FourFloats {                        // four floats at any float's address
+  float x, y, z, w;
+};
+
 // d > 1024: a workgroup per chain, a thread per group of four coordinates (= one Philox block), up to 1024 threads.
 // What bounds it is one chain's walk, a serial chain of gradients, and at 1024 threads the issue of its 16 wavefronts.  Hence
-// one group per thread; the means in LDS as fp32 where they fit (else from the caches: held in registers they were 64 of
-// them, and at 1024 threads 60 to 160 others lived in scratch memory); the sums of a position, two to a butterfly, in one
-// exchange over LDS that every wavefront adds up itself; buffers that alternate, so one barrier per exchange; the next
-// position's noise drawn while the sums settle; uniforms 64 steps at a time.  A position has one exchange, and a second one
-// ahead of it (16 squared distances in fp64) only where no component is known to be alone.  Where one was at the last state,
-// fp32 distances with a bound on their error travel with the sums: what they do not confirm is done again the long way.
-// Whole runs, us (before: means in registers, all logits at every position): 200 chains, 60 steps d = 1100 195 (242), d = 2500
-// 232 (322); 500 chains, 60 steps d = 4000 500 (1186); 30 chains, 250 steps d = 4001 741 (1829).
+// one group per thread; the sums of a position, two to a butterfly, in one exchange over LDS that every wavefront adds up
+// itself; buffers that alternate, so one barrier per exchange; the noise drawn while sums settle; uniforms 64 steps at a time.
+// Two loops, between which a chain changes with its state (RUN; a single window has the first alone), because the second's
+// branches and registers in the first cost a fifth of its time:
+//   all logits: 16 squared distances in fp64, whose exchange is a position's first.
+//   held by one component: no logits and one exchange.  Where the distances walked no longer prove that it is alone, fp32
+//   distances with a bound on their error travel with the sums; what they do not confirm is done the first way.
+// LDS: all means lie there as fp32, else (window form; runs whose means do not fit) the first eight, and the first loop has the
+// others in registers while it runs: two chains of up to 384 threads share a CU where 16 rows each would not.  Both loops ask
+// for the next means before they use the last ones; two pairs ahead, not one or four (5 % more at 320 to 512 threads).
+// Whole runs, 60 steps, us (with all means in registers and all logits at every position): components two standard deviations
+// per coordinate apart 200 chains, d = 1100, M = 9 156 (229), d = 2500 188 (309), 700 chains, d = 1100, M = 16 474 (627),
+// 100 chains, d = 4000, M = 16 292 (519); overlapping components, the same sizes 243 (242), 315 (325), 712 (685), 433 (565).  Windows
+// of 8, 600 chains, d = 1100, M = 16 70 us each (94).
 // MAXT: bound on the workgroup's threads (512, 768 or 1024: 256, 168 or 128 registers per thread).
 // RUN: the chain's windows follow each other inside the kernel, what sd_advance does to the chain between two of them
 // included (the state passes through fp32, so the bits are those of separate calls).
 template <int MAXT, bool RUN, bool LDS>
 __global__ __launch_bounds__(MAXT) void langevin_window_kernel(LangevinArgs p) {
-  constexpr int MC = 16, NW = 16;              // slots of the sums over wavefronts; those the launch does not have hold 0
-  extern __shared__ __align__(16) float4 sh_means[];       // LDS: [M][blockDim.x], 0 beyond d
+  constexpr int MC = 16, MR = LDS ? MC : MC / 2;           // MR: components in LDS
+  constexpr int NW = 16;                       // slots of the sums over wavefronts; those the launch does not have hold 0
+  extern __shared__ __align__(16) float4 sh_means[];       // [min(M, MR)][blockDim.x], 0 beyond d
   __shared__ double sh_part[2][NW][MC];
   __shared__ float sh_near[2][NW][MC];
   __shared__ double sh_s[2][2][NW];            // z.Delta, |Delta|^2
@@ -253,11 +266,15 @@ __global__ __launch_bounds__(MAXT) void langevin_window_kernel(LangevinArgs p) {
   }
   auto from_memory = [&](int m) {
     const float* row = p.means + static_cast<int64_t>(m) * d;
-    return make_float4(own[0] ? row[i0] : 0.f, own[1] ? row[i0 + 1] : 0.f, own[2] ? row[i0 + 2] : 0.f, own[3] ? row[i0 + 3] : 0.f);
+    if (own[3]) {
+      const FourFloats v = *reinterpret_cast<const FourFloats*>(row + i0);
+      return make_float4(v.x, v.y, v.z, v.w);
+    }
+    return make_float4(own[0] ? row[i0] : 0.f, own[1] ? row[i0 + 1] : 0.f, own[2] ? row[i0 + 2] : 0.f, 0.f);
   };
-  if (LDS)
-    for (int m = 0; m < M; ++m) sh_means[m * blockDim.x + t] = from_memory(m);
-  auto mean = [&](int m) { return LDS ? sh_means[m * blockDim.x + t] : from_memory(m); };
+  const int rows = min(M, MR);                 // in LDS
+  for (int m = 0; m < rows; ++m) sh_means[m * blockDim.x + t] = from_memory(m);
+  auto mean_at = [&](int m) { return m < rows ? sh_means[m * blockDim.x + t] : from_memory(m); };
   __syncthreads();
   auto draw = [&](int k, float (&z)[4]) {
     sdrng::normal4(p.seed, id, static_cast<uint32_t>(k), sdrng::kStreamNoise, static_cast<uint32_t>(t), z);
@@ -265,32 +282,18 @@ __global__ __launch_bounds__(MAXT) void langevin_window_kernel(LangevinArgs p) {
     for (int e = 0; e < 4; ++e) z[e] = own[e] ? z[e] : 0.f;
   };
 
-  Sole sole;
-  float per_nat = 0.f, norm_top = 0.f;         // s^2 / |mu_top - mu_{my_m}|, at most; |mu_top|
-  float4 mt = make_float4(0.f, 0.f, 0.f, 0.f);             // mu_top
-  bool near = false;                           // `top` was alone at the last state looked at
-
-  // 16 squared distances between `from` and the means, over the workgroup: lane l holds that of component l >> 2.  A buffer is
-  // written again two calls later, past the barrier of the next one.  Uniform control flow: called by every thread.
+  auto square = [](const double (&from)[4], const float4& mu) {            // unowned coordinates contribute 0 - 0
+    const double d0 = from[0] - mu.x, d1 = from[1] - mu.y, d2 = from[2] - mu.z, d3 = from[3] - mu.w;
+    return fma(d3, d3, fma(d2, d2, fma(d1, d1, d0 * d0)));
+  };
+  // 16 sums over the workgroup, the lower and the upper half of them already added over half a wavefront: lane l gets that
+  // of component l >> 2.  A buffer is written again two calls later, past the barrier of the next one.  Uniform control flow:
+  // called by every thread.
   int buf = 0;
-  auto distances = [&](const double (&from)[4], int self) {
-    auto dist2 = [&](int m) {
-      if (m >= M) return 0.0;
-      const float4 mu = mean(m);
-      const bool own_place = m == self;        // the vector itself in place of its distance from itself
-      const double d0 = from[0] - (own_place ? 0.0 : mu.x), d1 = from[1] - (own_place ? 0.0 : mu.y);
-      const double d2 = from[2] - (own_place ? 0.0 : mu.z), d3 = from[3] - (own_place ? 0.0 : mu.w);
-      return fma(d3, d3, fma(d2, d2, fma(d1, d1, d0 * d0)));               // unowned coordinates contribute 0 - 0
-    };
-    double q[MC / 2];                          // the first halving step as the sums come, to keep half of them
-#pragma unroll
-    for (int m = 0; m < MC / 2; ++m) {
-      const double lower = dist2(m), upper = dist2(m + MC / 2);
-      q[m] = sdlane::halving_add<32>(lower, upper);
-      __builtin_amdgcn_sched_barrier(0);
-    }
+  auto total = [&](double (&q)[MC / 2], auto&& meanwhile) {
     const double part = reduce8_transposed(q);
     if ((lane & 3) == 0) sh_part[buf][wave][my_m] = part;
+    meanwhile();
     __syncthreads();
     double tot = 0.0;                          // the four lanes of a component add four wavefronts each
 #pragma unroll
@@ -300,158 +303,55 @@ __global__ __launch_bounds__(MAXT) void langevin_window_kernel(LangevinArgs p) {
     buf ^= 1;
     return tot;
   };
-
-  // grad E at `cur`, all logits; every wavefront runs the softmax itself
-  auto gradient = [&](double (&g)[4]) {
-    const double tot = distances(cur, -1);
-    const double logit = my_m < M ? my_logw - 0.5 * tot * inv_s2 : -INFINITY;
-    double mx = logit;
+  auto softmax = [&](double logit, double& mx) {
+    mx = logit;
 #pragma unroll
     for (int s = 4; s <= 32; s <<= 1) mx = fmax(mx, dpp_xor(mx, s));
     const double ex = my_m < M ? exp(logit - mx) : 0.0;
     double sum = ex;
 #pragma unroll
     for (int s = 4; s <= 32; s <<= 1) sum += dpp_xor(sum, s);
-    const double r_mine = ex / sum;
-    double bar[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int m = 0; m < MC; ++m) {
-      const double r = readlane_f64(r_mine, 4 * m);        // uniform: lives in scalar registers
-      if (r < 1e-25 || m >= M) continue;       // moves nothing by more than 1e-25 |mu| (see the wavefront kernel)
-      const float4 mu = mean(m);
-      bar[0] = fma(r, static_cast<double>(mu.x), bar[0]);
-      bar[1] = fma(r, static_cast<double>(mu.y), bar[1]);
-      bar[2] = fma(r, static_cast<double>(mu.z), bar[2]);
-      bar[3] = fma(r, static_cast<double>(mu.w), bar[3]);
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) g[e] = (cur[e] - bar[e]) * inv_s2;
-    if (!RUN) return;
-    // is the largest logit alone, and how far does that carry?
-    sole.slack = -1.f;
-    near = false;
-    const unsigned long long at_max = __ballot(logit == mx && my_m < M);
-    const int top = at_max ? __builtin_ctzll(at_max) >> 2 : -1;
-    const bool other = my_m < M && my_m != top;
-    const double gap = mx - logit - kSoleGap;
-    if (top < 0 || __ballot(other && !(gap > 0.0)) != 0ull) return;        // the same in every wavefront
-    near = true;
-    if (top != sole.top) {
-      sole.top = top;
-      mt = mean(top);
-      const double from[4] = {mt.x, mt.y, mt.z, mt.w};
-      const double d2 = distances(from, top);              // |mu_top|^2 in its own place
-      per_nat = 1.f / (static_cast<float>(inv_s2) * (kUp * static_cast<float>(sqrt(d2))));
-      norm_top = kUp * static_cast<float>(sqrt(readlane_f64(d2, 4 * top)));
-      const double odds = 0.5 * d2 * inv_s2 + readlane_f64(my_logw, 4 * top) - my_logw - kSoleGap;
-      sole.radius = kDown * least_of_others(static_cast<float>(odds) * per_nat, other);
-    }
-    sole.slack = kDown * least_of_others(static_cast<float>(gap) * per_nat, other);
+    return ex / sum;
   };
 
-  // One pass of the loop is one position of a window: the gradient at the state (at a window's first position the frozen
-  // one, and the position is accepted: Delta = 0), accept test, new state.  With a sole component it has one barrier.
+  // One pass of either loop below is one position of a window: the gradient at the state (at a window's first position the
+  // frozen one, and the position is accepted: Delta = 0), accept test, new state.
   int Kt = max(0, min(p.K, p.T - n)), j = 0, jdone = 0, sbuf = 0;
   bool rejected = false;
   unsigned long long acc_adv = 0, acc_win = 0, acc_rej = 0, acc_kt = 0;
   double g0[4] = {0.0, 0.0, 0.0, 0.0};
-  float gn0 = 0.f;
   int lu_base = 0;                             // log u of 64 steps, lane l holding step lu_base + l
   bool lu_have = false;
   double lu_batch = 0.0;
   float z[4];
-  if (Kt > 0) draw(n + 1, z);
-  while (Kt > 0) {                             // Kt is uniform; every window advances the chain by at least one step
-    const int k1 = n + j + 1;                  // step this position produces
-    double g[4], dl[4] = {0.0, 0.0, 0.0, 0.0};
+
+  auto uniforms = [&](int k1) {
     if (!lu_have || k1 - lu_base >= 64) {
       lu_base = k1;
       lu_have = true;
       lu_batch = sdrng::log_uniform(p.seed, id, static_cast<uint32_t>(k1 + lane));
     }
-    float z_next[4], zz, gg;
-    double S1, S2;
-    // All branches are uniform: every wavefront holds the same totals.  With `top` alone, or alone at the last state, the
-    // gradient is that of one component; in the second case fp32 distances travel with the sums and confirm it.
-    bool alone = RUN && sole.holds(), confirm = RUN && !alone && near;
-    for (;;) {
-      if (alone || confirm) {
-        g[0] = (cur[0] - static_cast<double>(mt.x)) * inv_s2;
-        g[1] = (cur[1] - static_cast<double>(mt.y)) * inv_s2;
-        g[2] = (cur[2] - static_cast<double>(mt.z)) * inv_s2;
-        g[3] = (cur[3] - static_cast<double>(mt.w)) * inv_s2;
-      } else {
-        gradient(g);
-      }
-      if (j == 0) {
+  };
+  // Delta and this wavefront's share of z.Delta and |Delta|^2: two sums in one butterfly, the lower half of the wavefront carries
+  // the first, the upper half the second
+  auto products = [&](const double (&g)[4], double (&dl)[4]) {
+    if (j == 0) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) g0[e] = g[e];
-      }
-      double a1 = 0.0, a2 = 0.0;
-      zz = gg = 0.f;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        dl[e] = sqg2 * (g[e] - g0[e]);
-        a1 = fma(static_cast<double>(z[e]), dl[e], a1);
-        a2 = fma(dl[e], dl[e], a2);
-        zz = fmaf(z[e], z[e], zz);
-        gg = fmaf(static_cast<float>(g[e]), static_cast<float>(g[e]), gg);
-      }
-      // two sums in one butterfly: the lower half of the wavefront carries the first, the upper half the second
-      const double both = half_wave_sum(sdlane::halving_add<32>(a1, a2));
-      float norms = 0.f;
-      if (RUN) norms = half_wave_sum(halving_add_f32<32>(zz, gg));
-      if ((lane & 31) == 0) {                  // last read two rounds ago
-        sh_s[sbuf][lane >> 5][wave] = both;
-        if (RUN) sh_n[sbuf][lane >> 5][wave] = norms;
-      }
-      if (confirm) {
-        const float x0 = static_cast<float>(cur[0]), x1 = static_cast<float>(cur[1]);
-        const float x2 = static_cast<float>(cur[2]), x3 = static_cast<float>(cur[3]);
-        float q[MC];
-#pragma unroll
-        for (int m = 0; m < MC; ++m) {
-          q[m] = 0.f;
-          if (m >= M) continue;
-          const float4 mu = mean(m);
-          const float d0 = x0 - mu.x, d1 = x1 - mu.y, d2 = x2 - mu.z, d3 = x3 - mu.w;
-          q[m] = fmaf(d3, d3, fmaf(d2, d2, fmaf(d1, d1, d0 * d0)));
-        }
-        const float part = reduce16_transposed_f32(q);
-        if ((lane & 3) == 0) sh_near[sbuf][wave][my_m] = part;
-      }
-      draw(k1 + 1, z_next);                    // the next position's noise, while the sums settle
-      __syncthreads();
-      const double s_half = row_sum(sh_s[sbuf][lane >> 5][lane & 15]);
-      S1 = readlane_f64(s_half, 0);
-      S2 = readlane_f64(s_half, 32);
-      if (RUN) {
-        const float n_half = row_sum(sh_n[sbuf][lane >> 5][lane & 15]);
-        zz = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(n_half), 0));
-        gg = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(n_half), 32));
-      }
-      float dm = 0.f;
-      if (confirm) {
-#pragma unroll
-        for (int w = 0; w < NW; w += 4) dm += sh_near[sbuf][w + (lane & 3)][my_m];
-        dm += __int_as_float(sdlane::lane_xor<1>(__float_as_int(dm)));
-        dm += __int_as_float(sdlane::lane_xor<2>(__float_as_int(dm)));
-      }
-      sbuf ^= 1;
-      if (!confirm) break;
-      // error of an fp32 squared distance D: the sum's roundings (30 of 2^-24 D at most) and those of x (2^-24 |x| each way)
-      const float is2 = static_cast<float>(inv_s2), dt = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(dm), 4 * sole.top));
-      const float rd = __builtin_amdgcn_sqrtf(dm), rt = __builtin_amdgcn_sqrtf(dt);
-      const float err = 1e-5f * (dm + dt) + 1e-6f * (norm_top + rt) * (rd + rt);
-      const float gap = is2 * (0.5f * (dm - dt) - err) + static_cast<float>(readlane_f64(my_logw, 4 * sole.top) - my_logw - kSoleGap);
-      const bool other = my_m < M && my_m != sole.top;
-      if (__ballot(other && !(gap > 0.f)) == 0ull) {
-        sole.slack = kDown * least_of_others(gap * per_nat, other);
-        break;
-      }
-      near = confirm = false;                  // not so (or not certain): the long way
+      for (int e = 0; e < 4; ++e) g0[e] = g[e];
     }
-    const double lu = readlane_f64(lu_batch, k1 - lu_base);
+    double a1 = 0.0, a2 = 0.0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      dl[e] = sqg2 * (g[e] - g0[e]);
+      a1 = fma(static_cast<double>(z[e]), dl[e], a1);
+      a2 = fma(dl[e], dl[e], a2);
+    }
+    return half_wave_sum(sdlane::halving_add<32>(a1, a2));
+  };
+  // accept test and new state, from the sums that lie in sh_s[at]
+  auto decide = [&](int at, const double (&g)[4], const double (&dl)[4]) {
+    const double s_half = row_sum(sh_s[at][lane >> 5][lane & 15]);
+    const double S1 = readlane_f64(s_half, 0), S2 = readlane_f64(s_half, 32), lu = readlane_f64(lu_batch, n + j + 1 - lu_base);
     double lr = 0.0, coef = 0.0;
     bool reject = false;
     if (j > 0) {
@@ -464,12 +364,6 @@ __global__ __launch_bounds__(MAXT) void langevin_window_kernel(LangevinArgs p) {
       if (p.logratio) p.logratio[static_cast<int64_t>(b) * p.K + j] = static_cast<float>(lr);
       if (p.logu) p.logu[static_cast<int64_t>(b) * p.K + j] = static_cast<float>(lu);
     }
-    if (RUN) {
-      const float gn = kUp * __builtin_amdgcn_sqrtf(gg);
-      if (j == 0) gn0 = gn;
-      if (sole.holds()) sole.at_distance(gn * kUp * static_cast<float>(1.0 / inv_s2));
-      sole.moved(kUp * (static_cast<float>(gamma) * (reject ? gn : gn0) + static_cast<float>(sq2g) * __builtin_amdgcn_sqrtf(zz)));
-    }
     if (reject) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) cur[e] = cur[e] - gamma * g[e] + sq2g * (static_cast<double>(z[e]) - 2.0 * coef * dl[e]);
@@ -477,21 +371,242 @@ __global__ __launch_bounds__(MAXT) void langevin_window_kernel(LangevinArgs p) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) cur[e] = cur[e] - gamma * g0[e] + sq2g * static_cast<double>(z[e]);
     }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) z[e] = z_next[e];
     ++j;
-    if (!reject && j < Kt) continue;
-
-    jdone = j;                                 // end of the window
+    return reject;
+  };
+  // end of a window (RUN: the next one begins); Kt = 0: the last one
+  auto end_window = [&](bool reject) {
+    jdone = j;
     rejected = reject;
-    if (!RUN) break;
     n += j;
+    acc_adv += j; acc_win += 1; acc_rej += reject ? 1 : 0; acc_kt += Kt;
     j = 0;
-    acc_adv += jdone; acc_win += 1; acc_rej += reject ? 1 : 0; acc_kt += Kt;
-    Kt = max(0, min(p.K, p.T - n));
+    Kt = RUN ? max(0, min(p.K, p.T - n)) : 0;
+    if (RUN) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) cur[e] = static_cast<double>(static_cast<float>(cur[e]));
-    sole.window_ended(6.1e-8f * (norm_top + sole.rho));           // half an fp32 unit of the state's length
+      for (int e = 0; e < 4; ++e) cur[e] = static_cast<double>(static_cast<float>(cur[e]));
+    }
+  };
+
+  // All branches are uniform: every wavefront holds the same totals.  Kt is uniform; every window advances the chain by at
+  // least one step, and each loop takes at least one position.
+  while (Kt > 0) {
+    // ---- all logits
+    float mreg[MR < MC ? MC - MR : 1][4];      // the components that are not in LDS
+#pragma unroll
+    for (int m = MR; m < MC; ++m) {
+      const float4 v = from_memory(min(m, M - 1));
+      mreg[m - MR][0] = v.x; mreg[m - MR][1] = v.y; mreg[m - MR][2] = v.z; mreg[m - MR][3] = v.w;
+    }
+    auto mean = [&](int m) {                   // m is known at compile time; from M on any that exists, which nobody uses
+      if (m < MR) return sh_means[min(m, rows - 1) * blockDim.x + t];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) asm volatile("" : "+v"(mreg[m - MR][e]));        // no converted copies across the walk
+      return make_float4(mreg[m - MR][0], mreg[m - MR][1], mreg[m - MR][2], mreg[m - MR][3]);
+    };
+    bool one = false;                          // the position's state is held by one component
+    while (Kt > 0 && !one) {
+      uniforms(n + j + 1);
+      double q[MC / 2];                        // the first halving step as the sums come, to keep half of them
+      float4 lo[2], hi[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        lo[u] = mean(u);
+        hi[u] = mean(MC / 2 + u);
+      }
+#pragma unroll
+      for (int m = 0; m < MC / 2; m += 2) {   // two pairs at a time, the next ones on their way
+        float4 lo2[2], hi2[2];
+        if (m + 2 < MC / 2) {
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+            lo2[u] = mean(m + 2 + u);
+            hi2[u] = mean(MC / 2 + m + 2 + u);
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          q[m + u] = sdlane::halving_add<32>(square(cur, lo[u]), square(cur, hi[u]));
+          lo[u] = lo2[u];
+          hi[u] = hi2[u];
+        }
+      }
+      const double tot = total(q, [&]() { draw(n + j + 1, z); });          // the noise while the sums settle
+      const double logit = my_m < M ? my_logw - 0.5 * tot * inv_s2 : -INFINITY;
+      double mx;
+      const double r_mine = softmax(logit, mx);            // every wavefront runs it itself
+      if (RUN) one = __popcll(__ballot(my_m < M && !(mx - logit > kSoleEnter))) <= 4;
+      double g[4], dl[4], bar[4] = {0.0, 0.0, 0.0, 0.0};
+      float4 mu[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) mu[u] = mean(u);
+#pragma unroll
+      for (int m0 = 0; m0 < MC; m0 += 4) {     // four at a time, the next four on their way
+        if (m0 >= M) break;
+        float4 mu2[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (m0 + 4 < MC) mu2[u] = mean(m0 + 4 + u);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const double r = readlane_f64(r_mine, 4 * (m0 + u));             // uniform: lives in scalar registers
+          if (r < 1e-25 || m0 + u >= M) continue;          // moves nothing by more than 1e-25 |mu| (see the wavefront kernel)
+          bar[0] = fma(r, static_cast<double>(mu[u].x), bar[0]);
+          bar[1] = fma(r, static_cast<double>(mu[u].y), bar[1]);
+          bar[2] = fma(r, static_cast<double>(mu[u].z), bar[2]);
+          bar[3] = fma(r, static_cast<double>(mu[u].w), bar[3]);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) mu[u] = mu2[u];
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) g[e] = (cur[e] - bar[e]) * inv_s2;
+      const double both = products(g, dl);
+      const int at = sbuf;
+      if ((lane & 31) == 0) sh_s[at][lane >> 5][wave] = both;              // last read two rounds ago
+      __syncthreads();
+      sbuf ^= 1;
+      const bool reject = decide(at, g, dl);
+      if (reject || j >= Kt) end_window(reject);
+    }
+    if (!RUN) break;
+
+    // ---- held by one component: looked for with all logits at the first position, then followed
+    Sole sole;
+    float per_nat = 0.f, norm_top = 0.f;       // s^2 / |mu_top - mu_{my_m}|, at most; |mu_top|
+    float4 mt = make_float4(0.f, 0.f, 0.f, 0.f);           // mu_top
+    float gn0 = INFINITY;                      // |g0|; a window that is under way has an unknown one
+    auto distances = [&](const double (&from)[4], int self) {
+      auto dist2 = [&](int m) {
+        if (m >= M) return 0.0;
+        float4 mu = mean_at(m);
+        if (m == self) mu = make_float4(0.f, 0.f, 0.f, 0.f);               // the vector itself in place of its distance from itself
+        return square(from, mu);
+      };
+      double q[MC / 2];
+#pragma unroll
+      for (int m = 0; m < MC / 2; ++m) {
+        const double lower = dist2(m), upper = dist2(m + MC / 2);
+        q[m] = sdlane::halving_add<32>(lower, upper);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      return total(q, []() {});
+    };
+    auto gradient = [&](double (&g)[4]) {
+      const double tot = distances(cur, -1);
+      const double logit = my_m < M ? my_logw - 0.5 * tot * inv_s2 : -INFINITY;
+      double mx;
+      const double r_mine = softmax(logit, mx);
+      double bar[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int m = 0; m < MC; ++m) {
+        const double r = readlane_f64(r_mine, 4 * m);
+        if (r < 1e-25 || m >= M) continue;
+        const float4 mu = mean_at(m);
+        bar[0] = fma(r, static_cast<double>(mu.x), bar[0]);
+        bar[1] = fma(r, static_cast<double>(mu.y), bar[1]);
+        bar[2] = fma(r, static_cast<double>(mu.z), bar[2]);
+        bar[3] = fma(r, static_cast<double>(mu.w), bar[3]);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) g[e] = (cur[e] - bar[e]) * inv_s2;
+      // is the largest logit alone, and how far does that carry?
+      const unsigned long long at_max = __ballot(logit == mx && my_m < M);
+      const int top = at_max ? __builtin_ctzll(at_max) >> 2 : -1;
+      const bool other = my_m < M && my_m != top;
+      const double gap = mx - logit - kSoleGap;
+      if (top < 0 || __ballot(other && !(gap > 0.0)) != 0ull) return;      // the same in every wavefront
+      sole.top = top;
+      mt = mean_at(top);
+      const double from[4] = {mt.x, mt.y, mt.z, mt.w};
+      const double d2 = distances(from, top);              // |mu_top|^2 in its own place
+      per_nat = 1.f / (static_cast<float>(inv_s2) * (kUp * static_cast<float>(sqrt(d2))));
+      norm_top = kUp * static_cast<float>(sqrt(readlane_f64(d2, 4 * top)));
+      const double odds = 0.5 * d2 * inv_s2 + readlane_f64(my_logw, 4 * top) - my_logw - kSoleGap;
+      sole.radius = kDown * least_of_others(static_cast<float>(odds) * per_nat, other);
+      sole.slack = kDown * least_of_others(static_cast<float>(gap) * per_nat, other);
+    };
+    draw(n + j + 1, z);
+    while (Kt > 0) {                           // with a sole component a position has one barrier
+      uniforms(n + j + 1);
+      double g[4], dl[4];
+      // With `top` alone, or alone at the last state, the gradient is that of one component; in the second case fp32 distances
+      // travel with the sums and confirm it.
+      const bool look = sole.top < 0, confirm = !look && !sole.holds();
+      if (look) {
+        gradient(g);
+      } else {
+        g[0] = (cur[0] - static_cast<double>(mt.x)) * inv_s2;
+        g[1] = (cur[1] - static_cast<double>(mt.y)) * inv_s2;
+        g[2] = (cur[2] - static_cast<double>(mt.z)) * inv_s2;
+        g[3] = (cur[3] - static_cast<double>(mt.w)) * inv_s2;
+      }
+      const double both = products(g, dl);
+      float zz = 0.f, gg = 0.f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        zz = fmaf(z[e], z[e], zz);
+        gg = fmaf(static_cast<float>(g[e]), static_cast<float>(g[e]), gg);
+      }
+      const float norms = half_wave_sum(halving_add_f32<32>(zz, gg));
+      const int at = sbuf;
+      if ((lane & 31) == 0) {                  // last read two rounds ago
+        sh_s[at][lane >> 5][wave] = both;
+        sh_n[at][lane >> 5][wave] = norms;
+      }
+      if (confirm) {
+        const float x0 = static_cast<float>(cur[0]), x1 = static_cast<float>(cur[1]);
+        const float x2 = static_cast<float>(cur[2]), x3 = static_cast<float>(cur[3]);
+        float q[MC];
+#pragma unroll
+        for (int m = 0; m < MC; ++m) {
+          q[m] = 0.f;
+          if (m >= M) continue;
+          const float4 mu = mean_at(m);
+          const float d0 = x0 - mu.x, d1 = x1 - mu.y, d2 = x2 - mu.z, d3 = x3 - mu.w;
+          q[m] = fmaf(d3, d3, fmaf(d2, d2, fmaf(d1, d1, d0 * d0)));
+        }
+        const float part = reduce16_transposed_f32(q);
+        if ((lane & 3) == 0) sh_near[at][wave][my_m] = part;
+      }
+      float z_next[4];
+      draw(n + j + 2, z_next);                 // the next position's noise, while the sums settle
+      __syncthreads();
+      sbuf ^= 1;
+      const float n_half = row_sum(sh_n[at][lane >> 5][lane & 15]);
+      zz = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(n_half), 0));
+      gg = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(n_half), 32));
+      if (confirm) {
+        float dm = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; w += 4) dm += sh_near[at][w + (lane & 3)][my_m];
+        dm += __int_as_float(sdlane::lane_xor<1>(__float_as_int(dm)));
+        dm += __int_as_float(sdlane::lane_xor<2>(__float_as_int(dm)));
+        // error of an fp32 squared distance D: the sum's roundings (30 of 2^-24 D at most) and those of x (2^-24 |x| each way)
+        const float is2 = static_cast<float>(inv_s2), dt = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(dm), 4 * sole.top));
+        const float rd = __builtin_amdgcn_sqrtf(dm), rt = __builtin_amdgcn_sqrtf(dt);
+        const float err = 1e-5f * (dm + dt) + 1e-6f * (norm_top + rt) * (rd + rt);
+        const float gap = is2 * (0.5f * (dm - dt) - err) + static_cast<float>(readlane_f64(my_logw, 4 * sole.top) - my_logw - kSoleGap);
+        const bool other = my_m < M && my_m != sole.top;
+        if (__ballot(other && !(gap > 0.f)) != 0ull) break;                // not so (or not certain): this position the long way
+        sole.slack = kDown * least_of_others(gap * per_nat, other);
+      }
+      const bool first = j == 0;
+      const bool reject = decide(at, g, dl);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) z[e] = z_next[e];
+      const float gn = kUp * __builtin_amdgcn_sqrtf(gg);
+      if (first) gn0 = gn;
+      if (sole.holds()) sole.at_distance(gn * kUp * static_cast<float>(1.0 / inv_s2));
+      sole.moved(kUp * (static_cast<float>(gamma) * (reject ? gn : gn0) + static_cast<float>(sq2g) * __builtin_amdgcn_sqrtf(zz)));
+      if (reject || j >= Kt) {
+        end_window(reject);
+        sole.window_ended(6.1e-8f * (norm_top + sole.rho));                // half an fp32 unit of the state's length
+      }
+      if (sole.top < 0) break;                 // no component is alone
+    }
   }
 
   if (RUN) {
@@ -1105,9 +1220,25 @@ constexpr int kWideMeansLds = 148 * 1024;  // of 160 KiB; the sums' buffers take
 template <int MAXT, bool RUN>
 void launch_wide(const LangevinArgs& p, dim3 block, hipStream_t st) {
   const dim3 grid(static_cast<unsigned>(p.B));
-  const size_t means = sizeof(float4) * p.M * block.x;
-  if (means <= kWideMeansLds) hipLaunchKernelGGL((langevin_window_kernel<MAXT, RUN, true>), grid, block, means, st, p);
-  else hipLaunchKernelGGL((langevin_window_kernel<MAXT, RUN, false>), grid, block, 0, st, p);
+  const size_t row = sizeof(float4) * block.x, means = row * p.M;
+  if constexpr (RUN) {
+    if (MAXT <= 512 || means <= kWideMeansLds) {           // 16 rows of up to 512 threads always fit
+      hipLaunchKernelGGL((langevin_window_kernel<MAXT, true, true>), grid, block, means, st, p);
+      return;
+    }
+  }
+  if constexpr (!RUN || MAXT > 512)
+    hipLaunchKernelGGL((langevin_window_kernel<MAXT, RUN, false>), grid, block, std::min(means, 8 * row), st, p);
+}
+
+template <int MAXT>
+hipError_t prepare_wide() {
+  auto allow = [](const void* kernel) { return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kWideMeansLds); };
+  hipError_t e = allow(reinterpret_cast<const void*>(&langevin_window_kernel<MAXT, false, false>));
+  if (e == hipSuccess) e = allow(reinterpret_cast<const void*>(&langevin_window_kernel<MAXT, true, true>));
+  if constexpr (MAXT > 512)
+    if (e == hipSuccess) e = allow(reinterpret_cast<const void*>(&langevin_window_kernel<MAXT, true, false>));
+  return e;
 }
 
 template <bool RUN>
@@ -1116,12 +1247,6 @@ void launch_wide(const LangevinArgs& p, int groups, hipStream_t st) {
   if (block.x <= 512) launch_wide<512, RUN>(p, block, st);
   else if (block.x <= 768) launch_wide<768, RUN>(p, block, st);
   else launch_wide<1024, RUN>(p, block, st);
-}
-
-template <int MAXT, bool RUN>
-hipError_t prepare_wide() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&langevin_window_kernel<MAXT, RUN, true>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, kWideMeansLds);
 }
 
 // run mode: one launch counts as one entry of the `windows` counter
@@ -1481,11 +1606,9 @@ hipError_t sdi::langevin_prepare(int* cus) {
   if (e == hipSuccess) e = prepare_wave<c_, true, true>();
   SD_PREP(1) SD_PREP(2) SD_PREP(3) SD_PREP(4)
 #undef SD_PREP
-#define SD_PREP(t_) \
-  if (e == hipSuccess) e = prepare_wide<t_, false>(); \
-  if (e == hipSuccess) e = prepare_wide<t_, true>();
-  SD_PREP(512) SD_PREP(768) SD_PREP(1024)
-#undef SD_PREP
+  if (e == hipSuccess) e = prepare_wide<512>();
+  if (e == hipSuccess) e = prepare_wide<768>();
+  if (e == hipSuccess) e = prepare_wide<1024>();
   int dev = 0, n = 0;
   if (e == hipSuccess) e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev);

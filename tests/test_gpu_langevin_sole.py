@@ -40,7 +40,8 @@ def _means(kind, M, d):
 
 @pytest.mark.parametrize("kind", ["apart", "threshold", "overlapping", "twins", "offset", "weights"])
 @pytest.mark.parametrize("B,d,M,K,T", [(9, 150, 16, 8, 140), (40, 256, 5, 16, 60), (21, 601, 7, 1, 120), (300, 1000, 16, 16, 110),
-                                       (5, 1024, 3, 64, 130), (7, 1100, 16, 5, 120), (5, 2500, 16, 8, 100), (5, 4001, 4, 16, 110)])
+                                       (5, 1024, 3, 64, 130), (7, 1100, 16, 5, 120), (5, 2500, 16, 8, 100), (5, 4001, 4, 16, 110),
+                                       (3, 4093, 10, 16, 140)])
 def test_runs_equal_the_window_loop(kind, B, d, M, K, T):
     from paper_2501_05370_amd.sampler import LangevinSampler
     cfg = W.make_config("c5", B=B, d=d, M=M, K=K, T=T)
