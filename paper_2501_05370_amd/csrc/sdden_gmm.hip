@@ -310,7 +310,9 @@ __device__ __forceinline__ float readlane_f32(float v, int src_lane) {
 // loop cost the other steps 4 %.  us of a run with / without: 4096 chains, d = 64, M = 32 870 / 1050; 300 chains, d = 190,
 // M = 40 940 / 1660; 1 chain, d = 100, M = 20 510 / 770; 300 chains, d = 75, M = 12, two models 240 / 255; but 2000 chains,
 // d = 30, M = 20 475 / 456, 64 chains, d = 2, M = 8 172 / 164.  Taken where the share of the balls that hold a typical state
-// (radius^2 > d) times the pairs per lane reaches 6: these six have 16, 110, 29, 11, 3.4 and 0.
+// (radius^2 > d) times the pairs per lane reaches 6: these six have 16, 110, 29, 11, 3.4 and 0.  The same holds where the table lies
+// in the vector caches: overlapping components, d = 300, M = 4, 4096 chains 655 us with it, 628 without, apart 408 / 516.  Two models
+// follow the target's share.
 // PAIR (INDEP): two wavefronts a chain, one for each model; an instance of its own, because the branches around the two predictions
 // cost many chains 4 % (4096 chains, d = 10, M = 12, two models, 100 steps 568 us with them, 542 without).
 template <int E, int C, bool LDS, bool INDEP, bool FINE, bool ALONE, bool PAIR>
@@ -851,15 +853,15 @@ struct GmmDenoiser final : sdden {
 template <int E, bool LDS, bool FINE = !LDS>
 void launch_window_run(const RunArgs& p, bool alone, unsigned block, size_t shmem, hipStream_t st) {
   const dim3 grid(static_cast<unsigned>(p.B));
-  if (!LDS || alone) hipLaunchKernelGGL((gmm_window_run_kernel<E, LDS, FINE, true>), grid, dim3(block), shmem, st, p);
-  else hipLaunchKernelGGL((gmm_window_run_kernel<E, LDS, FINE, LDS ? false : true>), grid, dim3(block), shmem, st, p);
+  if (alone) hipLaunchKernelGGL((gmm_window_run_kernel<E, LDS, FINE, true>), grid, dim3(block), shmem, st, p);
+  else hipLaunchKernelGGL((gmm_window_run_kernel<E, LDS, FINE, false>), grid, dim3(block), shmem, st, p);
 }
 template <int E, bool LDS, bool FINE>
 hipError_t prepare_window_run() {
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gmm_window_run_kernel<E, LDS, FINE, true>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 256);
-  if (LDS && e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gmm_window_run_kernel<E, LDS, FINE, LDS ? false : true>),
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gmm_window_run_kernel<E, LDS, FINE, false>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 256);
   return e;
 }
@@ -871,11 +873,9 @@ void launch_run(const RunArgs& p, bool indep, unsigned grid, unsigned block, siz
   else if (indep) hipLaunchKernelGGL((gmm_run_kernel<E, C, LDS, true, FINE, ALONE, false>), dim3(grid), dim3(block), shmem, st, p);
   else hipLaunchKernelGGL((gmm_run_kernel<E, C, LDS, false, FINE, ALONE, false>), dim3(grid), dim3(block), shmem, st, p);
 }
-// A table in the vector caches has more than 34 pairs per lane: there an attempt costs next to nothing.
 template <int E, int C, bool LDS, bool FINE = !LDS>
 void launch_run(const RunArgs& p, bool indep, bool alone, unsigned grid, unsigned block, size_t shmem, hipStream_t st) {
-  if constexpr (!LDS) launch_run<E, C, LDS, FINE, true>(p, indep, grid, block, shmem, st);
-  else if (alone) launch_run<E, C, LDS, FINE, true>(p, indep, grid, block, shmem, st);
+  if (alone) launch_run<E, C, LDS, FINE, true>(p, indep, grid, block, shmem, st);
   else launch_run<E, C, LDS, FINE, false>(p, indep, grid, block, shmem, st);
 }
 

@@ -25,6 +25,8 @@ def _mixture(kind, M, d):
         lw[1] = -np.inf
     elif kind == "offset":
         mu = mu + 50.0
+    elif kind == "close":
+        mu = mu / 60.0
     return mu, sd, lw
 
 
@@ -63,6 +65,16 @@ def test_runs_equal_the_window_loop(kind, drafter, B, d, M, K, T):
     got, want = a.buf.counters.tolist(), b.buf.counters.tolist()
     assert got == want and got[0] == B * T
     assert np.max(np.abs(out - ref) / np.maximum(1.0, np.abs(ref).max(axis=1, keepdims=True))) < 1e-5
+
+
+# Tables out of LDS, components so close that no step is tried with one of them, for every row length and both chain kernels.
+@pytest.mark.parametrize("drafter,B,d,M,K,T", [("frozen", 1100, 64, 64, 4, 12), ("independent", 9, 64, 40, 4, 20), ("frozen", 3, 64, 48, 4, 20),
+                                               ("frozen", 1030, 100, 48, 3, 8), ("independent", 5, 100, 40, 3, 20), ("reused", 5, 100, 48, 5, 20),
+                                               ("frozen", 1030, 200, 33, 3, 8), ("independent", 5, 200, 20, 3, 20), ("reused_last", 5, 200, 48, 5, 20),
+                                               ("frozen", 5, 300, 4, 5, 30), ("independent", 1030, 300, 4, 3, 10), ("reused", 5, 600, 3, 4, 20),
+                                               ("independent", 5, 700, 8, 4, 20), ("frozen", 5, 1200, 2, 4, 20), ("independent", 4, 1200, 4, 4, 20)])
+def test_close_components_out_of_lds_equal_the_window_loop(drafter, B, d, M, K, T):
+    test_runs_equal_the_window_loop("close", drafter, B, d, M, K, T)
 
 
 # One workgroup per chain with 2, 4 or 8 wavefronts for the positions of a window: windows shorter and longer than a round, more
