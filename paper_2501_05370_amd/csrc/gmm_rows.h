@@ -220,7 +220,7 @@ __device__ __forceinline__ bool mean_of_one(const Model& g, const double2* tab, 
 // with / without: d = 1800 79 / 208, d = 1000 43 / 54; 1000 rows of d = 1000 81 / 157.  Row evaluations of up to 512
 // coordinates do without it: the compiler keeps their four loads together, and the registers cost more than the latency
 // where many wavefronts share a SIMD (32768 rows, 8 components: d = 200 60 / 58, d = 400 105 / 100).
-template <int E, int C, bool LDS, bool AHEAD, bool FINE>
+template <int E, int C, bool LDS, bool AHEAD, bool FINE, bool SHARES = (E * C == 1)>
 __device__ __forceinline__ void posterior_mean(const Model& g, const double2* tab, double* xs, const float (&x)[C][E], double ab,
                                                double sab, double base, int lane, float (&out)[C][E], Alone* was = nullptr, int k = 0) {
   const int lp = 6 - g.lm;
@@ -316,7 +316,8 @@ __device__ __forceinline__ void posterior_mean(const Model& g, const double2* ta
     }
   }
 
-  if constexpr (E == 1 && C == 1) {
+  if constexpr (SHARES) {
+    static_assert(E * C == 1, "a coordinate per lane");
     // Few pairs per lane: every component's share of a coordinate is in the logit phase's lanes already, and adding them up takes
     // log2(Mp) exchanges per pair instead of a loop over the live components; ahead with one pair, or from two live
     // components per pair on.  us of a run, with / without: 4096 chains, d = 3, M = 16, 100 steps 260 / 418; 4096 chains, d = 5,

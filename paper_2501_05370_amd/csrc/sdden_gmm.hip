@@ -10,6 +10,7 @@
 #include <algorithm>
 #include <cmath>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "gmm_rows.h"
@@ -313,9 +314,11 @@ __device__ __forceinline__ float readlane_f32(float v, int src_lane) {
 // (radius^2 > d) times the pairs per lane reaches 6: these six have 16, 110, 29, 11, 3.4 and 0.  The same holds where the table lies
 // in the vector caches: overlapping components, d = 300, M = 4, 4096 chains 655 us with it, 628 without, apart 408 / 516.  Two models
 // follow the target's share.
+// SHARES: the model may have its components' shares added up where they are (sdgmm::posterior_mean): runs that cannot are 1 to 3 %
+// faster without that code in the loop: 3000 chains, d = 60, M = 8, 100 steps 248 / 258, 2000 chains, d = 30, M = 20 287 / 294.
 // PAIR (INDEP): two wavefronts a chain, one for each model; an instance of its own, because the branches around the two predictions
 // cost many chains 4 % (4096 chains, d = 10, M = 12, two models, 100 steps 568 us with them, 542 without).
-template <int E, int C, bool LDS, bool INDEP, bool FINE, bool ALONE, bool PAIR>
+template <int E, int C, bool LDS, bool INDEP, bool FINE, bool ALONE, bool PAIR, bool SHARES>
 __global__ __launch_bounds__(256) void gmm_run_kernel(RunArgs p) {
   extern __shared__ __align__(16) unsigned char run_smem[];
   __shared__ unsigned long long sh_cnt[4];
@@ -388,7 +391,7 @@ __global__ __launch_bounds__(256) void gmm_run_kernel(RunArgs p) {
         if (PAIR && wave == 1) {}          // the other wavefront's
         else if (!ALONE || !sdgmm::mean_of_one<E, C, LDS, FINE>(p.t, tab_t, y, ab, sab, k, lane, alone_t, dq)) {
           if (ALONE) base_t = cst_t.at(p.t, k, lane);
-          sdgmm::posterior_mean<E, C, LDS, !LDS, FINE>(p.t, tab_t, xs, y, ab, sab, base_t, lane, dq, ALONE ? &alone_t : nullptr, k);
+          sdgmm::posterior_mean<E, C, LDS, !LDS, FINE, SHARES>(p.t, tab_t, xs, y, ab, sab, base_t, lane, dq, ALONE ? &alone_t : nullptr, k);
         }
         if (frozen && j == 0) {
 #pragma unroll
@@ -400,7 +403,7 @@ __global__ __launch_bounds__(256) void gmm_run_kernel(RunArgs p) {
           const double abq = sdgmm::readlane_f64(sb.q.x, at), sabq = sdgmm::readlane_f64(sb.q.y, at);
           if (!ALONE || !sdgmm::mean_of_one<E, C, LDS, FINE>(p.q, tab_q, y, abq, sabq, k, lane, alone_q, mp)) {
             if (ALONE) base_q = cst_q.at(p.q, k, lane);
-            sdgmm::posterior_mean<E, C, LDS, !LDS, FINE>(p.q, tab_q, xs, y, abq, sabq, base_q, lane, mp, ALONE ? &alone_q : nullptr, k);
+            sdgmm::posterior_mean<E, C, LDS, !LDS, FINE, SHARES>(p.q, tab_q, xs, y, abq, sabq, base_q, lane, mp, ALONE ? &alone_q : nullptr, k);
           }
         }
         if (PAIR) {                        // both go on with both: all that follows is the same on the two
@@ -507,7 +510,7 @@ __global__ __launch_bounds__(256) void gmm_run_kernel(RunArgs p) {
           const int at = n - sb.base;
           const double abn = sdgmm::readlane_f64(sb.t.x, at), sabn = sdgmm::readlane_f64(sb.t.y, at);
           if (!ALONE || !sdgmm::mean_of_one<E, C, LDS, FINE>(p.t, tab_t, dr, abn, sabn, n, lane, alone_t, d0))
-            sdgmm::posterior_mean<E, C, LDS, !LDS, FINE>(p.t, tab_t, xs, dr, abn, sabn, ALONE ? cst_t.at(p.t, n, lane) : next_t, lane, d0,
+            sdgmm::posterior_mean<E, C, LDS, !LDS, FINE, SHARES>(p.t, tab_t, xs, dr, abn, sabn, ALONE ? cst_t.at(p.t, n, lane) : next_t, lane, d0,
                                                          ALONE ? &alone_t : nullptr, n);
         }
       }
@@ -555,7 +558,7 @@ __global__ __launch_bounds__(256) void gmm_run_kernel(RunArgs p) {
 // Bound by a round's latency, about 2 us: 64 chains of the toy (d = 2, M = 8, K = 4, 3.8 of 4 accepted) 110 us a run, 161 with a
 // wavefront a chain; more in GmmDenoiser::run.
 // ---------------------------------------------------------------------------------------------
-template <int E, bool LDS, bool FINE, bool ALONE>
+template <int E, bool LDS, bool FINE, bool ALONE, bool SHARES>
 __global__ __launch_bounds__(512) void gmm_window_run_kernel(RunArgs p) {
   extern __shared__ __align__(16) unsigned char run_smem[];
   constexpr int kRow = 64 * E;
@@ -628,7 +631,7 @@ __global__ __launch_bounds__(512) void gmm_window_run_kernel(RunArgs p) {
 #pragma unroll
     for (int e = 0; e < E; ++e) xx[0][e] = x[e];
     if (!ALONE || !sdgmm::mean_of_one<E, 1, LDS, FINE>(p.t, tab, xx, ab, sab, k, lane, alone, oo))
-      sdgmm::posterior_mean<E, 1, LDS, !LDS, FINE>(p.t, tab, xs, xx, ab, sab, cst_k == k ? cst : sdgmm::lane_constant(p.t, k, lane), lane, oo,
+      sdgmm::posterior_mean<E, 1, LDS, !LDS, FINE, SHARES>(p.t, tab, xs, xx, ab, sab, cst_k == k ? cst : sdgmm::lane_constant(p.t, k, lane), lane, oo,
                                                    ALONE ? &alone : nullptr, k);
 #pragma unroll
     for (int e = 0; e < E; ++e) out[e] = oo[0][e];
@@ -850,33 +853,42 @@ struct GmmDenoiser final : sdden {
           float* out, int32_t* B_active, int64_t* counters, hipStream_t st) override;
 };
 
+// ALONE and SHARES as the run needs them.
+template <bool MAY_SHARE, class Launch>
+void choose_run(bool alone, bool shares, Launch launch) {
+  using std::true_type, std::false_type;
+  if constexpr (MAY_SHARE) {
+    if (shares) return alone ? launch(true_type{}, true_type{}) : launch(false_type{}, true_type{});
+  }
+  alone ? launch(true_type{}, false_type{}) : launch(false_type{}, false_type{});
+}
+
 template <int E, bool LDS, bool FINE = !LDS>
-void launch_window_run(const RunArgs& p, bool alone, unsigned block, size_t shmem, hipStream_t st) {
-  const dim3 grid(static_cast<unsigned>(p.B));
-  if (alone) hipLaunchKernelGGL((gmm_window_run_kernel<E, LDS, FINE, true>), grid, dim3(block), shmem, st, p);
-  else hipLaunchKernelGGL((gmm_window_run_kernel<E, LDS, FINE, false>), grid, dim3(block), shmem, st, p);
+void launch_window_run(const RunArgs& p, bool alone, bool shares, unsigned block, size_t shmem, hipStream_t st) {
+  choose_run<E == 1 && LDS>(alone, shares, [&](auto a, auto s) {
+    hipLaunchKernelGGL((gmm_window_run_kernel<E, LDS, FINE, a(), s()>), dim3(static_cast<unsigned>(p.B)), dim3(block), shmem, st, p);
+  });
 }
 template <int E, bool LDS, bool FINE>
 hipError_t prepare_window_run() {
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gmm_window_run_kernel<E, LDS, FINE, true>),
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gmm_window_run_kernel<E, LDS, FINE, true, false>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 256);
   if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gmm_window_run_kernel<E, LDS, FINE, false>),
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gmm_window_run_kernel<E, LDS, FINE, false, false>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 256);
   return e;
 }
 
-template <int E, int C, bool LDS, bool FINE, bool ALONE>
-void launch_run(const RunArgs& p, bool indep, unsigned grid, unsigned block, size_t shmem, hipStream_t st) {
-  if (indep && grid == static_cast<unsigned>(p.B) && block == 128)          // a workgroup of two wavefronts per chain
-    hipLaunchKernelGGL((gmm_run_kernel<E, C, LDS, true, FINE, ALONE, true>), dim3(grid), dim3(block), shmem, st, p);
-  else if (indep) hipLaunchKernelGGL((gmm_run_kernel<E, C, LDS, true, FINE, ALONE, false>), dim3(grid), dim3(block), shmem, st, p);
-  else hipLaunchKernelGGL((gmm_run_kernel<E, C, LDS, false, FINE, ALONE, false>), dim3(grid), dim3(block), shmem, st, p);
-}
 template <int E, int C, bool LDS, bool FINE = !LDS>
-void launch_run(const RunArgs& p, bool indep, bool alone, unsigned grid, unsigned block, size_t shmem, hipStream_t st) {
-  if (alone) launch_run<E, C, LDS, FINE, true>(p, indep, grid, block, shmem, st);
-  else launch_run<E, C, LDS, FINE, false>(p, indep, grid, block, shmem, st);
+void launch_run(const RunArgs& p, bool indep, bool alone, bool shares, unsigned grid, unsigned block, size_t shmem, hipStream_t st) {
+  choose_run<E * C == 1>(alone, shares, [&](auto a, auto s) {
+    if (indep && grid == static_cast<unsigned>(p.B) && block == 128)        // a workgroup of two wavefronts per chain
+      hipLaunchKernelGGL((gmm_run_kernel<E, C, LDS, true, FINE, a(), true, s()>), dim3(grid), dim3(block), shmem, st, p);
+    else if (indep)
+      hipLaunchKernelGGL((gmm_run_kernel<E, C, LDS, true, FINE, a(), false, s()>), dim3(grid), dim3(block), shmem, st, p);
+    else                                   // out of LDS one model has too many pairs per lane to share
+      hipLaunchKernelGGL((gmm_run_kernel<E, C, LDS, false, FINE, a(), false, LDS && s()>), dim3(grid), dim3(block), shmem, st, p);
+  });
 }
 
 int GmmDenoiser::run(sdden* draft, sd_ctx* ctx, int B, const float* y, const int32_t* n, const int64_t* chain_id,
@@ -927,24 +939,27 @@ int GmmDenoiser::run(sdden* draft, sd_ctx* ctx, int B, const float* y, const int
   int sh = row == 256 ? 0 : 6;             // log2 of the steps whose noise one pass draws
   while (row < 256 && (256 >> sh) < d) --sh;
   const size_t wshmem = (lds ? table : 0) + sizeof(double) * npad * W + sizeof(float) * (4 * W * row + 256 * (((2 * W + 1) >> sh) + 2));
+  // where a lane has one coordinate: one pair per lane, or enough components that more than two per pair can be live
+  auto may_share = [](const sdgmm::Model& m) { return m.nslots == 1 || m.M > 2 * m.nslots; };
+  const bool shares = may_share(g) || (q && may_share(q->g));
   if (B == 0) {}                           // no chains: the end kernel leaves the count
-  else if (W > 1 && lds && fine) launch_window_run<1, true, true>(p, often_alone, 64 * W, wshmem, st);
-  else if (W > 1 && lds && d <= 64) launch_window_run<1, true>(p, often_alone, 64 * W, wshmem, st);
-  else if (W > 1 && lds && d <= 128) launch_window_run<2, true>(p, often_alone, 64 * W, wshmem, st);
-  else if (W > 1 && lds) launch_window_run<4, true>(p, often_alone, 64 * W, wshmem, st);
-  else if (W > 1 && d <= 64) launch_window_run<1, false>(p, often_alone, 64 * W, wshmem, st);
-  else if (W > 1 && d <= 128) launch_window_run<2, false>(p, often_alone, 64 * W, wshmem, st);
-  else if (W > 1) launch_window_run<4, false>(p, often_alone, 64 * W, wshmem, st);
-  else if (lds && fine) launch_run<1, 1, true, true>(p, indep, often_alone, grid, block, shmem, st);
-  else if (lds && d <= 64) launch_run<1, 1, true>(p, indep, often_alone, grid, block, shmem, st);
-  else if (lds && d <= 128) launch_run<2, 1, true>(p, indep, often_alone, grid, block, shmem, st);
-  else if (lds) launch_run<4, 1, true>(p, indep, often_alone, grid, block, shmem, st);
-  else if (d <= 64) launch_run<1, 1, false>(p, indep, often_alone, grid, block, shmem, st);
-  else if (d <= 128) launch_run<2, 1, false>(p, indep, often_alone, grid, block, shmem, st);
-  else if (d <= 256) launch_run<4, 1, false>(p, indep, often_alone, grid, block, shmem, st);
-  else if (d <= 512) launch_run<4, 2, false>(p, indep, often_alone, grid, block, shmem, st);
-  else if (d <= 1024) launch_run<4, 4, false>(p, indep, often_alone, grid, block, shmem, st);
-  else launch_run<4, 8, false>(p, indep, often_alone, grid, block, shmem, st);
+  else if (W > 1 && lds && fine) launch_window_run<1, true, true>(p, often_alone, shares, 64 * W, wshmem, st);
+  else if (W > 1 && lds && d <= 64) launch_window_run<1, true>(p, often_alone, shares, 64 * W, wshmem, st);
+  else if (W > 1 && lds && d <= 128) launch_window_run<2, true>(p, often_alone, shares, 64 * W, wshmem, st);
+  else if (W > 1 && lds) launch_window_run<4, true>(p, often_alone, shares, 64 * W, wshmem, st);
+  else if (W > 1 && d <= 64) launch_window_run<1, false>(p, often_alone, shares, 64 * W, wshmem, st);
+  else if (W > 1 && d <= 128) launch_window_run<2, false>(p, often_alone, shares, 64 * W, wshmem, st);
+  else if (W > 1) launch_window_run<4, false>(p, often_alone, shares, 64 * W, wshmem, st);
+  else if (lds && fine) launch_run<1, 1, true, true>(p, indep, often_alone, shares, grid, block, shmem, st);
+  else if (lds && d <= 64) launch_run<1, 1, true>(p, indep, often_alone, shares, grid, block, shmem, st);
+  else if (lds && d <= 128) launch_run<2, 1, true>(p, indep, often_alone, shares, grid, block, shmem, st);
+  else if (lds) launch_run<4, 1, true>(p, indep, often_alone, shares, grid, block, shmem, st);
+  else if (d <= 64) launch_run<1, 1, false>(p, indep, often_alone, shares, grid, block, shmem, st);
+  else if (d <= 128) launch_run<2, 1, false>(p, indep, often_alone, shares, grid, block, shmem, st);
+  else if (d <= 256) launch_run<4, 1, false>(p, indep, often_alone, shares, grid, block, shmem, st);
+  else if (d <= 512) launch_run<4, 2, false>(p, indep, often_alone, shares, grid, block, shmem, st);
+  else if (d <= 1024) launch_run<4, 4, false>(p, indep, often_alone, shares, grid, block, shmem, st);
+  else launch_run<4, 8, false>(p, indep, often_alone, shares, grid, block, shmem, st);
   hipLaunchKernelGGL(run_end_kernel, dim3(1), dim3(1), 0, st, p.longest, p.counters, B_active);
   SD_HIP_TRY(err, hipGetLastError());
   return SD_OK;
