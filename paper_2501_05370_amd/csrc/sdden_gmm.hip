@@ -318,8 +318,12 @@ __device__ __forceinline__ float readlane_f32(float v, int src_lane) {
 // faster without that code in the loop: 3000 chains, d = 60, M = 8, 100 steps 248 / 258, 2000 chains, d = 30, M = 20 287 / 294.
 // PAIR (INDEP): two wavefronts a chain, one for each model; an instance of its own, because the branches around the two predictions
 // cost many chains 4 % (4096 chains, d = 10, M = 12, two models, 100 steps 568 us with them, 542 without).
-template <int E, int C, bool LDS, bool INDEP, bool FINE, bool ALONE, bool PAIR, bool SHARES>
-__global__ __launch_bounds__(256) void gmm_run_kernel(RunArgs p) {
+// DENSE (two models, ALONE, a coordinate per lane): held to the registers of four wavefronts per SIMD, for runs that fill more than
+// three: 4096 chains, 60 steps d = 64, M = 32 622 us with it, 730 without, M = 12 346 / 400; 1200 chains 245 / 233.
+enum Form { kPlain, kPair, kDense };
+template <int E, int C, bool LDS, bool INDEP, bool FINE, bool ALONE, Form FORM, bool SHARES>
+__global__ __launch_bounds__(256, FORM == kDense ? 4 : 1) void gmm_run_kernel(RunArgs p) {
+  constexpr bool PAIR = FORM == kPair;
   extern __shared__ __align__(16) unsigned char run_smem[];
   __shared__ unsigned long long sh_cnt[4];
   __shared__ int sh_longest;
@@ -883,11 +887,13 @@ template <int E, int C, bool LDS, bool FINE = !LDS>
 void launch_run(const RunArgs& p, bool indep, bool alone, bool shares, unsigned grid, unsigned block, size_t shmem, hipStream_t st) {
   choose_run<E * C == 1>(alone, shares, [&](auto a, auto s) {
     if (indep && grid == static_cast<unsigned>(p.B) && block == 128)        // a workgroup of two wavefronts per chain
-      hipLaunchKernelGGL((gmm_run_kernel<E, C, LDS, true, FINE, a(), true, s()>), dim3(grid), dim3(block), shmem, st, p);
+      hipLaunchKernelGGL((gmm_run_kernel<E, C, LDS, true, FINE, a(), kPair, s()>), dim3(grid), dim3(block), shmem, st, p);
+    else if (indep && p.B > 3 * 1024)      // a wavefront per chain, 1024 SIMDs
+      hipLaunchKernelGGL((gmm_run_kernel<E, C, LDS, true, FINE, a(), E * C == 1 && a() ? kDense : kPlain, s()>), dim3(grid), dim3(block), shmem, st, p);
     else if (indep)
-      hipLaunchKernelGGL((gmm_run_kernel<E, C, LDS, true, FINE, a(), false, s()>), dim3(grid), dim3(block), shmem, st, p);
+      hipLaunchKernelGGL((gmm_run_kernel<E, C, LDS, true, FINE, a(), kPlain, s()>), dim3(grid), dim3(block), shmem, st, p);
     else                                   // out of LDS one model has too many pairs per lane to share
-      hipLaunchKernelGGL((gmm_run_kernel<E, C, LDS, false, FINE, a(), false, LDS && s()>), dim3(grid), dim3(block), shmem, st, p);
+      hipLaunchKernelGGL((gmm_run_kernel<E, C, LDS, false, FINE, a(), kPlain, LDS && s()>), dim3(grid), dim3(block), shmem, st, p);
   });
 }
 

@@ -67,6 +67,14 @@ def test_runs_equal_the_window_loop(kind, drafter, B, d, M, K, T):
     assert np.max(np.abs(out - ref) / np.maximum(1.0, np.abs(ref).max(axis=1, keepdims=True))) < 1e-5
 
 
+# Two models where the form of the run changes: two wavefronts a chain up to 1024 chains, registers for four per SIMD from 3073 on; the
+# largest row, whose exchange between the two takes a workgroup over 64 KiB of LDS.
+@pytest.mark.parametrize("B,d,M,K,T", [(1024, 20, 3, 3, 20), (1025, 20, 3, 3, 20), (3072, 64, 12, 3, 12), (3073, 64, 12, 3, 12), (3080, 64, 40, 3, 8),
+                                       (3, 1874, 1, 4, 30), (5, 1872, 3, 4, 20), (4, 1030, 2, 4, 30)])
+def test_two_models_equal_the_window_loop(B, d, M, K, T):
+    test_runs_equal_the_window_loop("apart", "independent", B, d, M, K, T)
+
+
 # Tables out of LDS, components so close that no step is tried with one of them, for every row length and both chain kernels.
 @pytest.mark.parametrize("drafter,B,d,M,K,T", [("frozen", 1100, 64, 64, 4, 12), ("independent", 9, 64, 40, 4, 20), ("frozen", 3, 64, 48, 4, 20),
                                                ("frozen", 1030, 100, 48, 3, 8), ("independent", 5, 100, 40, 3, 20), ("reused", 5, 100, 48, 5, 20),
