@@ -308,12 +308,14 @@ __device__ __forceinline__ float readlane_f32(float v, int src_lane) {
 // FINE: reciprocal variances to fp64 rounding (sdgmm::needs_fine); the vector caches' form always has them.
 // ALONE: a step is first tried with the component its chain was last seen with alone, which takes no pass over the pairs, no
 // exchange of the row and no softmax; about 300 of 550 instructions at 32 pairs per lane, while the attempts and the wider
-// loop cost the other steps 4 %.  us of a run with / without: 4096 chains, d = 64, M = 32 870 / 1050; 300 chains, d = 190,
-// M = 40 940 / 1660; 1 chain, d = 100, M = 20 510 / 770; 300 chains, d = 75, M = 12, two models 240 / 255; but 2000 chains,
-// d = 30, M = 20 475 / 456, 64 chains, d = 2, M = 8 172 / 164.  Taken where the share of the balls that hold a typical state
-// (radius^2 > d) times the pairs per lane reaches 6: these six have 16, 110, 29, 11, 3.4 and 0.  The same holds where the table lies
-// in the vector caches: overlapping components, d = 300, M = 4, 4096 chains 655 us with it, 628 without, apart 408 / 516.  Two models
-// follow the target's share.
+// loop cost the other steps 4 to 10 %.  Taken where the share of the balls that hold a typical state (radius^2 > d) reaches 0.35 from 24
+// pairs per lane on, 0.45 below.  Runs of 100 or 200 steps, with / without it, over the share:
+//   28 to 52 pairs  0.16 1.04  0.23 1.08  0.39 0.97  0.40 0.97  0.49 0.81  0.56 0.69  0.62 0.74  0.75 0.59
+//   116 pairs       0.46 0.78  0.66 0.58  0.90 0.40
+//   4 to 20 pairs   0.12 1.09  0.22 1.05  0.41 1.00  0.46 0.92  0.49 0.90  0.60 0.79  0.70 0.79
+//   1 or 2 pairs    0.24 1.09  0.33 1.06  0.59 0.86  0.61 0.91
+//   two models      0.16 0.95  0.20 1.10  0.22 1.10  0.41 1.02 and 1.06  0.51 1.01  0.56 0.75  0.61 0.95  0.65 0.91  0.70 0.93 and 1.01
+// whether the table lies in LDS or not.  Two models follow the target's share.
 // SHARES: the model may have its components' shares added up where they are (sdgmm::posterior_mean): runs that cannot are 1 to 3 %
 // faster without that code in the loop: 3000 chains, d = 60, M = 8, 100 steps 248 / 258, 2000 chains, d = 30, M = 20 287 / 294.
 // PAIR (INDEP): two wavefronts a chain, one for each model; an instance of its own, because the branches around the two predictions
@@ -1074,7 +1076,7 @@ int sdden_gmm_create(int32_t M, int32_t d, const float* means, const float* stds
       delete g;
       return sdi::fail(E, SD_ERR_HIP, "sdden_gmm_create: %s", hipGetErrorString(e));
     }
-    g->often_alone = static_cast<double>(holds) * nslots >= 6.0 * static_cast<double>(T) * M;
+    g->often_alone = static_cast<double>(holds) >= (nslots >= 24 ? 0.35 : 0.45) * static_cast<double>(T) * M;
   } else {
     g->mu = g->dev_f; g->sd = g->dev_f + md; g->muT = g->dev_f + 2 * md; g->sdT = g->dev_f + 3 * md; g->ab = g->dev_f + 4 * md;
   }
