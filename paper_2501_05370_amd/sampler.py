@@ -197,16 +197,19 @@ class _SamplerBase:
 
 
 def _windows_are_faster(ctx: Context, den: Denoiser, B: int, carried: bool, batched_readbacks: bool) -> bool:
-    """Few chains of long predictions: one wavefront per chain predicts position after position, while a window's
-    separate calls predict all of its positions side by side.  The line lies where the positions a window is expected to
-    advance cost one wavefront more than the window costs the separate calls.  In us, fitted to 300 measured runs (64 to
-    1800 coordinates, 1 to 64 components, K = 16 to 64, T = 200 to 1000, 1 to 128 chains; none of them goes to the slower
-    side), with p the (component, coordinate) pairs per lane: a position 2.4 + 0.041 p, 4 more above 1024 coordinates; a
-    window 42 + 0.08 p + 0.4 K (its carried form 34 + 0.04 p + 0.4 K), a little more per row, 20 more with a readback each; its
-    advance about 8 sqrt(T / 200) (64 / d)^0.21, less near K.  One chain, T = 1000, K = 64, us a step in one launch / by
-    windows: d = 64, M = 32 2.3 / 3.7; d = 200, M = 48 10.5 / 5.6; d = 1000, M = 64 44 / 17."""
+    """Few chains of long predictions, more than 256 coordinates: there one wavefront per chain predicts position after position,
+    while a window's separate calls predict all of its positions side by side.  (Up to 256 the one launch does so too and is ahead
+    everywhere, whatever the components: one chain, d = 256, M = 64, T = 1000, K = 16 5.3 to 5.8 ms against 6.6 to 8.4, d = 128, K = 64
+    3.2 to 3.5 against 5.2 to 5.7.)  The line lies where the positions a window is expected to advance cost one wavefront
+    more than the window costs the separate calls.  In us, fitted to measured runs whose steps weigh all components (300 to 1800 coordinates, 1 to 64
+    components, K = 16 to 64, T = 200 to 1000, 1 to 128 chains), with p the (component, coordinate) pairs per lane: a position
+    2.4 + 0.041 p, 4 more above 1024 coordinates; a window 42 + 0.08 p + 0.4 K (its carried form 34 + 0.04 p + 0.4 K), a little
+    more per row, 20 more with a readback each; its advance about 8 sqrt(T / 200) (64 / d)^0.21, less near K.  One chain, T = 1000, K = 64,
+    ms in one launch / by windows with a readback each: d = 300, M = 48 22.5 / 8.8; d = 1000, M = 64 58 / 17.  How far the components lie apart
+    is not known here: one component holds most steps of far ones, and one launch is then ahead (d = 300 7.6 / 8.3; d = 1000, T = 200
+    3.7 / 6.7), where overlapping ones lose more the other way (T = 200 11.6 / 7.3, carried, T = 1000 64 / 13)."""
     M, K, d = getattr(den, "components", 0), ctx.K, ctx.d
-    if not 1 <= M <= 64 or B * K > 2048:
+    if not 1 <= M <= 64 or B * K > 2048 or d <= 256:
         return False
     pairs = -(-d // (64 >> (M - 1).bit_length()))
     position = 2.4 + 0.041 * pairs + (4 if d > 1024 else 0)

@@ -138,8 +138,8 @@ def test_a_context_that_changes_a_call(cls, name, calls):
 
 @pytest.mark.parametrize("cls", [DiffusionSampler, EfficientFrozenSampler])
 def test_few_chains_of_long_predictions_take_the_loop(cls, calls):
-    """One chain, long windows, thousands of pairs per wavefront: the separate calls; the sizes of the low-dimensional
-    study, many chains, or a denoiser that does not say how many components it has: one launch."""
+    """One chain, long windows, thousands of pairs per wavefront: the separate calls; up to 256 coordinates, many chains, or a
+    denoiser that does not say how many components it has: one launch."""
     def launches(components, **kw):
         calls.clear()
         s = _make(cls, **kw)
@@ -149,7 +149,9 @@ def test_few_chains_of_long_predictions_take_the_loop(cls, calls):
         s.run(torch.arange(kw.get("B", 2)))
         return "sdden_run" in calls
     assert not launches(64, B=1, d=1000, K=16)
-    assert not launches(48, B=4, d=200, K=64)
+    assert not launches(48, B=4, d=300, K=64)
+    assert launches(48, B=4, d=200, K=64)                # positions side by side in the one launch
+    assert launches(64, B=1, d=256, K=64)
     assert launches(64, B=200, d=1000, K=16)
     assert launches(32, B=1, d=64, K=64)
     assert launches(8, B=1, d=2, K=4)
