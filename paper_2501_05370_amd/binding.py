@@ -93,7 +93,6 @@ _SIGNATURES = {
 }
 
 _lib = None
-_raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
 
 
 def exported_symbols():
@@ -122,8 +121,9 @@ def load_library(path: Optional[str] = None):
 def _stream() -> int:
     """Handle of torch's current stream on the current device, read from torch's runtime directly: the Stream object that
     ``torch.cuda.current_stream()`` builds for every call costs 2.5 us, and calls on few chains are bound by the host.  Draft
-    and two low-rank predictions for 19 chains: 32 us a pass, 36 with it; accept calls on 8 chains 27 and 33."""
-    return _raw_stream(_current_device())
+    and two low-rank predictions for 19 chains: 32 us a pass, 36 with it; accept calls on 8 chains 27 and 33.  Looked up
+    at the call: a torch built without GPU support has neither function, and can still import this module."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _dev(t: Optional[torch.Tensor], dtype, name: str, allow_none: bool = False) -> Optional[int]:

@@ -3,6 +3,8 @@ rejects bad arguments before touching the device."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -88,3 +90,13 @@ def test_bench_refuses_more_than_one_gpu_and_needs_the_library():
         r = subprocess.run([sys.executable, os.path.join(root, "bench.py"), "--workload", "c1", "--no-cpu-baseline"],
                            capture_output=True, text=True, timeout=300, cwd=root)
         assert r.returncode != 0 and '"metric"' not in r.stdout
+
+
+def test_imports_with_a_torch_without_gpu_support():
+    """Such a torch lacks its CUDA runtime functions; names, signatures and argument checks are there all the same."""
+    code = ("import torch\n"
+            "for name in ('_cuda_getCurrentRawStream', '_cuda_getDevice'):\n"
+            "    delattr(torch._C, name)\n"
+            "from paper_2501_05370_amd import binding\n"
+            "assert 'sdden_eval' in binding.exported_symbols()\n")
+    subprocess.run([sys.executable, "-c", code], check=True, cwd=ROOT)
