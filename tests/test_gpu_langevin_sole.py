@@ -63,6 +63,39 @@ def test_runs_equal_the_window_loop(kind, B, d, M, K, T):
     assert [counters[i] for i in (0, 1, 2, 4)] == [got[i] for i in (0, 1, 2, 4)] and counters[0] == B * T
 
 
+# Distances carry powers of the standard deviation, in other units in the two kernels, and steps far below the slack's last bit
+# may follow each other for a whole run: means, steps and all at other scales, and steps of a hundredth of the usual length.
+@pytest.mark.parametrize("kind", ["apart", "threshold", "offset"])
+@pytest.mark.parametrize("std,length", [(0.25, 1.0), (4.0, 1.0), (1.0, 1e-2), (0.1, 1e-3)])
+@pytest.mark.parametrize("d,M,K,T", [(300, 16, 8, 200), (1000, 9, 16, 200), (1100, 6, 5, 200), (3000, 16, 16, 200)])
+def test_other_scales(kind, std, length, d, M, K, T):
+    from paper_2501_05370_amd.sampler import LangevinSampler
+    B = 5
+    cfg = W.make_config("c5", B=B, d=d, M=M, K=K, T=T)
+    mu, logw = _means(kind, M, d)
+    gamma = cfg.gamma * (std * length) ** 2
+    res = []
+    for one_launch in (True, False):
+        s = LangevinSampler(make_context(cfg.schedule, d, K, seed=4), (mu * std).contiguous(), logw, std, gamma, B)
+        b, n = s.buf, s.start(torch.arange(B, device="cuda"))
+        near = mu[torch.arange(B) % M] * torch.linspace(0.0, 1.0, B, device="cuda")[:, None]
+        b.y[:B] = (std * (b.y[:B] + near)).contiguous()              # from the origin to a component's mean
+        if one_launch and d <= 1024:
+            s.ctx.sd_langevin_run(B, b.y, b.n, b.chain_id, s.means, s.logw, std, M, gamma, T, b.y_out, b.n, b.counters)
+            res.append((b.y_out.clone(), b.counters.tolist()[:3]))
+            continue
+        if one_launch:
+            assert s._run_chains(B)
+            n = 0
+        while n > 0:
+            s.window(n)
+            s.advance(n)
+            n = int(b.B_active.item())
+        res.append((b.out.clone(), b.counters.tolist()[:3]))
+    assert torch.equal(res[0][0], res[1][0]) and bool(torch.isfinite(res[0][0]).all())
+    assert res[0][1] == res[1][1] and res[0][1][0] == B * T
+
+
 @pytest.mark.parametrize("d", [400, 1500])
 def test_one_component_and_a_state_that_is_no_number(d):
     """M = 1 has no other component at all; a chain whose state holds a NaN or an infinity ends as the loop's does."""
