@@ -55,6 +55,32 @@ def test_row_counts_at_tile_edges(d, r):
     g.sdden_set_active_count(None, 1)
 
 
+# Few rows add the slabs up inside the second product while a row's slabs hold 512 floats (d = 2048 at rank 64, 4096 at rank 32) and all
+# tiles' 16 MB (d = 2048: 64 rows of 16 x 16 tiles, from 97 on 128 of 32 x 32).
+@pytest.mark.parametrize("d,r,rows", [(2048, 50, (1, 64, 65, 96, 97, 128, 129)), (2064, 50, (1, 64)), (2048, 64, (33,)), (2048, 65, (33,)),
+                                      (4096, 20, (16, 32, 33)), (4112, 20, (16, 33))])
+def test_slabs_added_up_in_the_second_product(d, r, rows):
+    from paper_2501_05370_amd.binding import Denoiser
+    rng = np.random.default_rng(d + r)
+    T, R = 25, 600
+    p = W.lowrank_gaussian(rng, d, r)
+    sched = W.cosine_schedule(T)
+    g = Denoiser.sdden_lowrank_create(p.mu, p.U, p.s2, sched.alpha_bar_state)
+    g.sdden_reserve(R)
+    x = as_f32_f64(rng.standard_normal((R, d)))
+    k = rng.integers(0, T, size=R).astype(np.int32)
+    k[[0, 30, 63]] = [1, -1, T]
+    live = (k >= 0) & (k < T)
+    xg, kg = f32(x), dev(k, torch.int32)
+    whole = torch.full((R, d), 777.0, dtype=torch.float32, device="cuda")
+    g.sdden_eval(R, xg, kg, whole)                                   # too many rows for it
+    assert rel_err(host(whole)[live], LowRankDenoiser(p, sched.alpha_bar_state)(x[live], k[live])) < 2e-6
+    for n in rows:
+        out = torch.full((n, d), 777.0, dtype=torch.float32, device="cuda")
+        g.sdden_eval(n, xg[:n], kg[:n], out)
+        assert torch.equal(out, whole[:n]), n
+
+
 @pytest.mark.parametrize("r,R", [(1, 70), (2, 600), (4, 4096), (33, 4096)])
 def test_axis_aligned_basis_rounds_once_per_operation(r, R):
     """Columns of U along coordinate axes: the basis holds zeros and ones, both products are exact, and what is left are the
