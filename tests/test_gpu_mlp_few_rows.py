@@ -3,6 +3,8 @@ range (1024), widths at the edges of the column rule, masked rows and a device-s
 
 Tolerance 2e-2 of the row's scale, as for the other MLP tests: bf16 weights and activations, fp32 sums.  Against the
 kernels for many rows the results are the same bits: every kernel sums over k in one chain and in order."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -75,6 +77,34 @@ def test_every_tile_gives_the_same_bits():
         out = torch.zeros(rows, d, device="cuda")
         g.sdden_eval(rows, x[:rows], k[:rows], out)
         assert torch.equal(out, whole[:rows]), rows
+
+
+@pytest.mark.parametrize("d", [512, 1024, 1280])
+@pytest.mark.parametrize("R", [3, 16])
+def test_float_rows_found_by_the_first_product(R, d):
+    """The same without an image: up to 16 rows of up to 1024 coordinates the first product loads the floats, longer rows are packed."""
+    from paper_2501_05370_amd.binding import Denoiser
+    H, T = 256, 9
+    g = Denoiser.sdden_mlp_create(W.random_mlp(np.random.default_rng(1), d, H, 16), T, 1100)
+    gen = torch.Generator(device="cuda").manual_seed(2)
+    x = torch.randn(1100, d, device="cuda", generator=gen)
+    k = torch.randint(0, T, (1100,), device="cuda", generator=gen, dtype=torch.int32)
+    whole = torch.zeros(1100, d, device="cuda")
+    g.sdden_eval(1100, x, k, whole)                                  # the tiles for many rows
+    last = torch.full_like(k[:R], T)
+    last[-1:] = k[R - 1]
+    for krow, there, count in ((k[:R], range(R), None), (k[:R], range(min(R, 2)), 2), (torch.full_like(last, -1), (), None),
+                               (last, (R - 1,), None), (k[:R], (), 0)):
+        out = torch.full((R, d), 777.0, device="cuda")
+        xr = torch.full((R, d), math.nan, device="cuda")             # rows that are not there carry NaN
+        rows = torch.zeros(R, dtype=torch.bool, device="cuda")
+        rows[list(there)] = True
+        xr[rows] = x[:R][rows]
+        present = None if count is None else torch.tensor([count], dtype=torch.int32, device="cuda")
+        g.sdden_set_active_count(present, 1)
+        g.sdden_eval(R, xr, krow.contiguous(), out)
+        g.sdden_set_active_count(None, 1)
+        assert torch.equal(out[rows], whole[:R][rows]) and bool((out[~rows] == 777.0).all())
 
 
 @pytest.mark.parametrize("R", [16, 30, 100, 1000])
