@@ -123,14 +123,4 @@ __device__ __forceinline__ double halving_add(double lower, double upper) {
   }
 }
 
-// Sum over the wavefront, the same bits on every lane.
-__device__ __forceinline__ double wave_sum(double v) {
-  v += lane_xor<1>(v);
-  v += lane_xor<2>(v);
-  v += lane_xor<4>(v);
-  v += lane_xor<8>(v);
-  v = pair_sum_rows<16>(v);
-  return pair_sum_rows<32>(v);
-}
-
 }  // namespace sdlane

@@ -48,8 +48,6 @@ struct LangevinArgs {
   double gamma, inv_s2, inv_tau;
 };
 
-__device__ __forceinline__ double wave_sum(double v) { return sdlane::wave_sum(v); }
-
 // v of lane (lane ^ mask), mask a single bit known at compile time after unrolling
 __device__ __forceinline__ double dpp_xor(double v, int mask) {
   switch (mask) {
