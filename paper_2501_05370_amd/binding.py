@@ -121,7 +121,7 @@ def load_library(path: Optional[str] = None):
 def _stream() -> int:
     """Handle of torch's current stream on the current device, read from torch's runtime directly: the Stream object that
     ``torch.cuda.current_stream()`` builds for every call costs 2.5 us, and calls on few chains are bound by the host.  Draft
-    and two low-rank predictions for 19 chains: 32 us a pass, 36 with it; accept calls on 8 chains 27 and 33.  Looked up
+    and two low-rank predictions for 19 chains: 32 us a pass, 37.7 with it; accept calls on 8 chains 27 and 33.  Looked up
     at the call: a torch built without GPU support has neither function, and can still import this module."""
     return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 

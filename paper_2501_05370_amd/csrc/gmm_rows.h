@@ -139,7 +139,7 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v + other(v, std::integral_constant<int, 32>{});
 }
 
-// The component a chain was last seen with alone, where its state was then, and the squared radii (gmm_radius_kernel) of that
+// The component a chain was last seen with alone, where its state was at the last attempt, and the squared radii (gmm_radius_kernel) of that
 // component's balls at 64 steps, one per lane: in a ball nothing is loaded per step.
 struct Alone {
   int top = -1;
@@ -176,7 +176,9 @@ __device__ __forceinline__ bool mean_of_one(const Model& g, const double2* tab, 
   const int lp = 6 - g.lm, top = was.top;
   if (static_cast<unsigned>(k - was.base) >= 64u) was.load(g, k, lane);
   const float r2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(was.radius2), k - was.base));
-  if (!(r2 > 0.8f * was.rho2)) return false;       // far outside when last looked at: not worth the distance
+  // Far outside at the last attempt: not worth another one until the radius has come near that distance.  (Taking the distance anew
+  // from every evaluation makes more attempts that fail: two models, d = 100, M = 20, 300 chains, 200 steps 990 / 1016 us; no run gained.)
+  if (!(r2 > 0.8f * was.rho2)) return false;
   const double om = 1.0 - ab;
   double rho2 = 0.0;
   float2 t[C][E];

@@ -18,8 +18,8 @@
 // each other along k.  A direct load into LDS is then eight whole cache lines and a fragment read is conflict free
 // with no permutation; out of row-major operands a block is 16 half lines one row stride apart, which for these widths
 // (multiples of 512 bytes) meet on few cache channels (16 rows, split k: 57.6 us row-major, 40.3 in fragment order).
-// The weights' copy in this order is made when the denoiser is created; pack_rows_kernel writes the call's rows, and
-// each product's epilogue writes the next one's operand.
+// The weights' copy in this order is made when the denoiser is created; the call's rows the first product takes as they are
+// (their bf16 image, or few short fp32 ones) or from pack_rows_kernel, and each product's epilogue writes the next one's operand.
 //
 // Measured, the three products with pack_rows_kernel against the LDS tiles without their compaction and conversion:
 //   d = 12288, H = 4096    1 row 51 / 161 us   32 rows 54 / 169   64 rows 72 / 170   200 rows 136 / 158
@@ -37,7 +37,7 @@ using mlpgemm::u32x4;
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kPackThreads = 256;
-constexpr int kMaxRows = 1024;    // rows of a call: pack_rows_kernel ranks them four per thread
+constexpr int kMaxRows = 1024;    // rows of a call: pack_rows_kernel ranks them four per thread, the first product 16 per lane
 
 // Element offset of (row, k .. k + 7), k a multiple of 8, in fragment order.
 __host__ __device__ __forceinline__ size_t frag_offset(int row, int k, int K) {
@@ -54,8 +54,8 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(const uint16_t* __res
 }
 
 // The rows r < active rows with 0 <= krow[r] < T, in increasing order, as dense rows of F in fragment order, rounded to bf16:
-// for calls of more than 16 rows without a bf16 image (the others' first product loads the rows itself).  Every workgroup ranks all (at most kMaxRows) rows itself
-// -- one load per 256 rows -- and moves its 16 dense rows x `kchunk` columns; the first column of workgroups leaves
+// for calls without a bf16 image of more than 16 rows or, up to 16, of more than 1024 coordinates (the others' first product loads the
+// rows itself).  Every workgroup ranks all (at most kMaxRows) rows itself -- one load per 256 rows -- and moves its 16 dense rows x `kchunk` columns; the first column of workgroups leaves
 // rowidx and the count for the products.  One launch in place of a compaction and a conversion.
 __global__ __launch_bounds__(kPackThreads) void pack_rows_kernel(const float* __restrict__ X, const int32_t* __restrict__ krow, const int32_t* active,
                                                                  int rows_per_chain, int R, int T, int K, int kchunk,

@@ -210,9 +210,9 @@ __global__ __launch_bounds__(64 * kRowsPerBlock) void gmm_radius_kernel(sdgmm::M
 // Values: drafts, predictions and states are rounded to fp32 exactly where the separate calls store them; log-ratios
 // are fp64 sums of the same terms.
 // Measured against windows of separate calls: 4096 chains, d = 64, 32 components, 200 steps 0.87 ms against 4.76; 64 chains,
-// d = 2, 8 components, 100 steps 0.16 ms against 1.81; 300 chains, d = 75, 12 components, a draft model, 60 steps 0.25 ms
-// against 8.1.  The first is bound by fp64 issue, over half of it in the quarter of the steps in which many components are live,
-// the others by the latency of one wavefront's step (1.5 us): hence no branch per exchange level, no load and no
+// d = 2, 8 components, 100 steps 0.11 ms against 1.81 (gmm_window_run_kernel); 300 chains, d = 75, 12 components, a draft model, 60
+// steps 0.21 ms against 8.1 (two wavefronts a chain).  The first is bound by fp64 issue, over half of it in the quarter of the steps in
+// which many components are live, the others by the latency of one wavefront's step: hence no branch per exchange level, no load and no
 // generator pass per step.
 // ---------------------------------------------------------------------------------------------
 struct RunArgs {
