@@ -82,10 +82,14 @@ def roofline_plan(cfg, loop="eager", drafter="frozen"):
         if loop == "fused":
             # one prediction per step; the efficient frozen drafter's carried one per window; the draft model's per step
             rows = {"frozen": lambda c: c[0], "independent": lambda c: 1.5 * c[0]}.get(drafter, lambda c: c[0] + c[1])
-            # (steps held by one component skip the passes over all pairs: the count stays the method's)
-            return dict(kernel=("gmm_window_run_kernel" if cfg.B <= 1024 and d <= 256 and K > 1 and drafter != "independent" else "gmm_run_kernel") +
-                               " (sdden_run: every chain's windows back to back in one launch, mixture posterior mean in fp64 "
-                               "inside it)", stage="chains_run", bound="alu", peak="alu_fp64", scale=1e-12,
+            kernel = ("gmm_window_run_kernel" if cfg.B <= 1024 and d <= 256 and K > 1 and drafter != "independent" else "gmm_run_kernel") + \
+                     " (sdden_run: every chain's windows back to back in one launch, mixture posterior mean in fp64 inside it)"
+            if cfg.name == "c2" and drafter == "frozen" and (M, d) == (32, 64):
+                # Steps held by one component skip the passes over all pairs, so the method's flop count would price work that is
+                # not done: the issue cycles of a chain's step instead, in four-cycle units of a wavefront (446 by the counter
+                # SQ_ACTIVE_INST_VALU on this mixture, 390 instructions; profiles/mixture_chains_one_launch_c1_c2.md).
+                return dict(kernel=kernel, stage="chains_run", bound="alu", peak="alu_lane", scale=1e-12, work=lambda c: 446.0 * 64 * c[0])
+            return dict(kernel=kernel, stage="chains_run", bound="alu", peak="alu_fp64", scale=1e-12,
                         work=lambda c: 15.0 * M * d * rows(c))
         return dict(kernel="gmm_rows_kernel (mixture posterior mean, fp64) of the batched target call", den_which=1,
                     den_min_rows=cfg.B + 1, bound="alu", peak="alu_fp64", scale=1e-12,

@@ -219,7 +219,7 @@ struct FourFloats {                        // four floats at any float's address
 // for the next means before they use the last ones; two pairs ahead, not one or four (5 % more at 320 to 512 threads).
 // Whole runs, 60 steps, us (with all means in registers and all logits at every position): components two standard deviations
 // per coordinate apart 200 chains, d = 1100, M = 9 156 (229), d = 2500 188 (309), 700 chains, d = 1100, M = 16 474 (627),
-// 100 chains, d = 4000, M = 16 292 (519); overlapping components, the same sizes 243 (242), 315 (325), 712 (685), 433 (565).  Windows
+// 100 chains, d = 4000, M = 16 286 (520); overlapping components, the same sizes 242 (243), 315 (325), 712 (687), 444 (566).  Windows
 // of 8, 600 chains, d = 1100, M = 16 70 us each (94).
 // MAXT: bound on the workgroup's threads (512, 768 or 1024: 256, 168 or 128 registers per thread).
 // RUN: the chain's windows follow each other inside the kernel, what sd_advance does to the chain between two of them
